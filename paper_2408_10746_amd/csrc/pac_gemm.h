@@ -540,6 +540,8 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TL::WTM][TL::WTN], E
         for (int y = 0; y < TL::WTN; ++y) {
             const int col = col0 + (wn * TL::WTN + y) * 32 + i;
             const int row_base = row0 + (wm * TL::WTM + x) * 32 + 4 * g;
+            // eight blocks per wavefront: without this the compiler requests several blocks' operands at once and spills
+            if constexpr (TL::WTM * TL::WTN > 4) __builtin_amdgcn_sched_barrier(0);
             if constexpr (epi_is_batched<Epi>::value) {
                 epi.batch(row_base, col, acc[x][y], nrows, ncols);
             } else {

@@ -72,6 +72,20 @@ static size_t chain_lds(int L, int r, bool fwd)
 // Side of the square workgroup tiles of the contractions outside the chains: 64 up to r = 128, 128 above
 static int big_shapes(int r) { return r > 128; }
 
+// Which tiles a wide contraction runs on: 256 x 256 (pp_loop) or 128 x 256.  Estimated time = rounds over the 256 compute
+// units times a tile's time: its start and epilogue plus its K steps of 64.  Measured on 8192 x 8192 x 4096 and on single
+// tiles (us): K-contiguous 8 + 1.72 a step on the larger tile against 5 + 1.08, one workgroup per compute unit either way;
+// token contractions 9 + 1.87 against 6 + 2.3 for two of the smaller tiles at once.  So the larger tile takes the
+// contractions of many steps, and short ones only where it saves a round.
+static bool pp_pays(int64_t n256, int64_t n128, int steps)
+{
+    return n256 > 0 && cdiv(n256, 256) * (8 + 1.72 * steps) < cdiv(n128, 256) * (5 + 1.08 * steps);
+}
+static bool pp_pays_tokens(int64_t n256, int64_t n128, int steps)
+{
+    return n256 > 0 && cdiv(n256, 256) * (9 + 1.87 * steps) < cdiv(n128, 512) * (6 + 2.3 * steps);
+}
+
 int gram_path_kind(const Dims &D)
 {
     if (D.cache_dtype != 0 || (D.flags & 1)) return 0; // PAC_FLAG_PER_LAYER
@@ -145,6 +159,7 @@ void plan_gram_workspace(const Dims &D, WsLayout &W, int64_t &o)
     W.g_zpart = take((int64_t)W.max_tiles * D.C * 4);
     W.g_zpb = take((int64_t)D.B_max * cdiv(D.d, 256) * D.C * 4);
     W.g_Z = take(Lr * D.C * 4);
+    W.g_ZT = take(Lr * D.C * 4);
     W.g_dzsum = take(kMaxClasses * 4);
     W.g_cs = take(Lr * 4);
     W.g_Epart = take((int64_t)W.se * D.L * D.d * D.r * 4);
@@ -441,6 +456,7 @@ struct ProjArgs {
     RowMap map;
     int L, d, r, B;
     int nb_U, nb_Q, nb_C, row_tiles;
+    bool pp; // U and Q on 256 x 256 tiles (row_tiles, nb_U, nb_Q count those)
     const bf16_t *WdT, *Wu;
     const float *cusum; // [L+1][d]
     float *chat;        // [L][r]
@@ -664,11 +680,14 @@ template <int NT, int BK, bool QFULL> __global__ __launch_bounds__(NT > 4 ? 512 
         auto arow = [&](int m) { return cache + map.rowoff[m] + (int64_t)l * map.rowstride[m]; };
         auto brow = [&](int c) { return W + (int64_t)c * d; };
         EpiStoreF32 epi{a.U + (int64_t)l * a.map.M * a.r, a.r};
-        if constexpr (SH::BIG) gemm_nt<TU, true>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
-        else gemm_nt_deepA<TU, SH::kUStages>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
+        if constexpr (SH::BIG) {
+            if (BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, mt * PpTile::BM, ct * PpTile::BN, a.map.M, a.r);
+            else gemm_nt<TU, true>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
+        } else gemm_nt_deepA<TU, SH::kUStages>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
         return;
     }
-    const int tqm = (a.r + TQ::BM - 1) / TQ::BM, tqn = (a.r + TQ::BN - 1) / TQ::BN, tq2 = tqm * tqn, tc64 = (a.r + 63) / 64;
+    const int qbm = SH::BIG && a.pp ? PpTile::BM : TQ::BM;
+    const int tqm = (a.r + qbm - 1) / qbm, tqn = (a.r + TQ::BN - 1) / TQ::BN, tq2 = tqm * tqn, tc64 = (a.r + 63) / 64;
     if (b < a.nb_U + a.nb_Q) {
         if constexpr (SH::QSTACK) {
             // tile (ti, tj) of [L r] x [L r]; needed where some row layer is below some column layer
@@ -731,7 +750,8 @@ template <int NT, int BK, bool QFULL> __global__ __launch_bounds__(NT > 4 ? 512 
                 gn = a.QgN + ((int64_t)gi * pg + qb * (qb - 1) / 2 + jb) * a.r * a.r;
             }
             EpiQFull epi{a.QpN, a.QpT, a.r, oml, k, l, (int64_t)a.L * a.r, gn, gt};
-            gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
+            if (SH::BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, (idx / tqn) * PpTile::BM, (idx % tqn) * PpTile::BN, a.r, a.r);
+            else gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
         } else {
             EpiQ epi{a.QpN + (int64_t)p * a.r * a.r, a.QpT + (int64_t)p * a.r * a.r, a.r, oml};
             gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
@@ -1650,7 +1670,7 @@ struct TokRedArgs {
     int ntiles, B, C;
     const float *cspart, *HSpart, *dz;
     const int32_t *tile_samp, *samp_len;
-    float *cs, *Z, *dzsum;
+    float *cs, *Z, *ZT, *dzsum; // ZT: Z once more, [C][Lr] (wide shapes)
 };
 
 constexpr int kTokStages = 3;
@@ -1671,9 +1691,12 @@ template <int NT> struct TokRedShapes {
     static constexpr int kVecLds = 256 * (1 + kMaxClasses) * 4 + kMaxTiles * 4 + kMaxBatch * kMaxClasses * 4; // + tile and sample tables
     static constexpr int kTileLds = TE::LDS_BYTES > TG::LDS_BYTES ? TE::LDS_BYTES : TG::LDS_BYTES;
     static constexpr int kLds = kTileLds > kVecLds ? kTileLds : kVecLds;
+    static_assert(PpTile::LDS_BYTES >= kVecLds, "LDS budget of the token contractions");
 };
 
-template <int NT> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBlock) void k_gtokred(TokRedArgs a)
+// PP: on 256 x 256 tiles, 64 tokens per stage (an instantiation of its own: its registers and LDS leave room for one
+// workgroup per compute unit, the smaller tiles' for two)
+template <int NT, bool PP> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBlock) void k_gtokred(TokRedArgs a)
 {
     using TE = typename TokRedShapes<NT>::TE;
     using TG = typename TokRedShapes<NT>::TG;
@@ -1710,18 +1733,20 @@ template <int NT> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBloc
         const bf16_t *cache = a.cache;
         const bf16_t *dp = a.DP + (int64_t)l * a.r;
         const int d = a.d;
+        const int tps = (PP ? 64 : KT) / 16; // 16-token tiles per step
         auto atok = [&](int step, int grp, int r8) -> const bf16_t * {
-            const int tl = step * (KT / 16) + (grp >> 1), row = (grp & 1) * 8 + r8;
+            const int tl = step * tps + (grp >> 1), row = (grp & 1) * 8 + r8;
             if (tl >= ntl || row >= t_rows[tl]) return nullptr;
             return cache + t_aoff[tl] + (int64_t)row * d;
         };
         auto btok = [&](int step, int grp, int r8) -> const bf16_t * {
-            const int tl = step * (KT / 16) + (grp >> 1), row = (grp & 1) * 8 + r8;
+            const int tl = step * tps + (grp >> 1), row = (grp & 1) * 8 + r8;
             if (tl >= ntl || row >= t_rows[tl]) return nullptr;
             return dp + (int64_t)(t_m0[tl] + row) * Lr;
         };
         EpiStoreF32 epi{a.Epart + ((int64_t)split * a.L + l) * a.d * a.r, a.r};
-        gemm_tn<TE, true>(smem, atok, btok, a.zeros, epi, (ntl * 16 + KT - 1) / KT, it * TE::BM, ct * TE::BN, a.d, a.r, a.d, a.r);
+        if constexpr (PP) gemm_tn_pp(smem, atok, btok, a.zeros, epi, (ntl * 16 + 63) / 64, it * PpTile::BM, ct * PpTile::BN, a.d, a.r, a.d, a.r);
+        else gemm_tn<TE, true>(smem, atok, btok, a.zeros, epi, (ntl * 16 + KT - 1) / KT, it * TE::BM, ct * TE::BN, a.d, a.r, a.d, a.r);
         return;
     }
     if (b < a.nb_E + a.nb_G) {
@@ -1731,26 +1756,29 @@ template <int NT> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBloc
         idx /= a.sg;
         const int ti = idx / a.tgn, tj = idx % a.tgn;
         // needed only where some row layer is below some column layer
-        const int kmin = (ti * TG::BM) / a.r;
+        const int gbm = PP ? PpTile::BM : TG::BM, gkt = PP ? 64 : KT;
+        const int kmin = (ti * gbm) / a.r;
         const int lmax = min(Lr - 1, tj * TG::BN + TG::BN - 1) / a.r;
         if (kmin >= lmax) return;
         const int kbegin = split * a.rows_per_sg;
         const int kend = min(M, kbegin + a.rows_per_sg);
         const bf16_t *H = a.H, *DP = a.DP;
         auto atok = [&](int step, int grp, int r8) -> const bf16_t * {
-            const int k = kbegin + step * KT + grp * 8 + r8;
+            const int k = kbegin + step * gkt + grp * 8 + r8;
             return k < kend ? H + (int64_t)k * Lr : nullptr;
         };
         auto btok = [&](int step, int grp, int r8) -> const bf16_t * {
-            const int k = kbegin + step * KT + grp * 8 + r8;
+            const int k = kbegin + step * gkt + grp * 8 + r8;
             return k < kend ? DP + (int64_t)k * Lr : nullptr;
         };
         if (a.gg_direct) {
             EpiGramDirect epi{a.GGT, a.GGsc, Lr, a.r, a.params, a.PL};
-            gemm_tn<TG, true>(smem, atok, btok, a.zeros, epi, (kend - kbegin + KT - 1) / KT, ti * TG::BM, tj * TG::BN, Lr, Lr, Lr, Lr);
+            if constexpr (PP) gemm_tn_pp(smem, atok, btok, a.zeros, epi, (kend - kbegin + 63) / 64, ti * PpTile::BM, tj * PpTile::BN, Lr, Lr, Lr, Lr);
+            else gemm_tn<TG, true>(smem, atok, btok, a.zeros, epi, (kend - kbegin + KT - 1) / KT, ti * TG::BM, tj * TG::BN, Lr, Lr, Lr, Lr);
         } else {
             EpiStoreF32 epi{a.GGpart + (int64_t)split * Lr * Lr, Lr};
-            gemm_tn<TG, true>(smem, atok, btok, a.zeros, epi, (kend - kbegin + KT - 1) / KT, ti * TG::BM, tj * TG::BN, Lr, Lr, Lr, Lr);
+            if constexpr (PP) gemm_tn_pp(smem, atok, btok, a.zeros, epi, (kend - kbegin + 63) / 64, ti * PpTile::BM, tj * PpTile::BN, Lr, Lr, Lr, Lr);
+            else gemm_tn<TG, true>(smem, atok, btok, a.zeros, epi, (kend - kbegin + KT - 1) / KT, ti * TG::BM, tj * TG::BN, Lr, Lr, Lr, Lr);
         }
         return;
     }
@@ -1808,7 +1836,10 @@ template <int NT> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBloc
         for (int g2 = 0; g2 < 16; ++g2) tot += red[(g2 * 16 + ii) * (1 + kMaxClasses) + q];
         if (idx < Lr) {
             if (q == 0) a.cs[idx] = tot;
-            else a.Z[(int64_t)idx * C + q - 1] = tot;
+            else {
+                a.Z[(int64_t)idx * C + q - 1] = tot;
+                a.ZT[(int64_t)(q - 1) * Lr + idx] = tot;
+            }
         }
     }
     if (vb == 0 && t < C) {
@@ -1818,17 +1849,162 @@ template <int NT> __global__ __launch_bounds__(TokRedShapes<NT>::kThreadsPerBloc
     }
 }
 
+struct PostArgs {
+    int blk_off; // first block of this launch (parts may be launched separately for timing)
+    int L, d, r, C, B;
+    int nb_F, nb_W, nb_vec;
+    bool pp; // F and W on 256 x 256 tiles (nb_F, nb_W, slots count those)
+    const float *params;
+    int64_t PL;
+    const bf16_t *WuTs, *Wds, *GGT, *GGsc;
+    const float *E, *cusum, *cs, *Z, *ZT, *dzsum, *dz, *pb; // Z [Lr][C], ZT [C][Lr]
+    float *grads;
+    float *dlam_part;
+    int slots;
+};
+
+// The gradients that are no contractions (dc_up, dW_cls, dc_down, dc_cls) for the wide shapes (r > 128): a workgroup takes four neighbouring hidden indices j, its
+// four wavefronts the 512-column pieces of their rows of the two stacked copies in turn, every load 1 KB contiguous, the
+// column sums and Z (a copy with its classes apart: read as rows of C classes, 128 bytes from lane to lane, it was
+// fetched from L2 eight times over) once for four rows.  Bound by the two copies' bytes (134 MB LLaMA-7B-shaped).  As part of the tiles' launch, one
+// workgroup per compute unit beside their LDS, with a thread per (j, layer, part) whose 16-byte loads were 128 bytes
+// apart, it took 159 us there, as a launch of its own 114 us, with neighbouring lanes on neighbouring chunks 92 us.
+constexpr int kVecRows = 4; // = wavefronts of the workgroup
+static int post_vec_wide_lds(int Lr) { return kVecRows * (Lr / 32) * 4 + 4 * kVecRows * kMaxClasses * 4; }
+__device__ __forceinline__ void post_vec_wide(const PostArgs &a, int vb, char *smem) // 256 threads
+{
+    const int L = a.L, d = a.d, r = a.r, C = a.C, Lr = L * r;
+    const int64_t dr = (int64_t)d * r;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (vb < L) {
+        // a layer's dc_down^l = colsum(dpre_l) ; dc_cls = sum_s dz_s.  (All layers in one workgroup: 32 round trips to
+        // memory one after the other, 60 us.)
+        const int l = vb;
+        for (int nn = t; nn < r; nn += 256) a.grads[(int64_t)l * a.PL + dr + nn] = a.cs[l * r + nn];
+        if (l == 0 && t < C) a.grads[(int64_t)L * a.PL + (int64_t)d * C + t] = a.dzsum[t];
+        return;
+    }
+    const int j0 = (vb - L) * kVecRows; // d is a multiple of 32
+    const int ng = Lr / 32; // groups of 32 columns, none across a layer's boundary
+    float *part = reinterpret_cast<float *>(smem); // [row][group]: W_down^k[j] . cs_k over the group
+    float *wred = part + kVecRows * ng;            // [wavefront][row][class]
+    // what the end needs, requested first
+    const float oml = lane < L ? 1.f - a.params[(int64_t)lane * a.PL + a.PL - 1] : 0.f;
+    float base = 0.f; // (sum_s dz_s) W_cls^T [j], j this wavefront's row
+    {
+        const float *Wc = a.params + (int64_t)L * a.PL + (int64_t)(j0 + wave) * C;
+#pragma unroll
+        for (int c = 0; c < kMaxClasses; ++c)
+            if (c < C) base += a.dzsum[c] * Wc[c];
+    }
+    const bool pools = wave == 0 && lane < a.B; // pooled part of dW_cls: lane s of the first wavefront takes sample s
+    float pv[kVecRows];
+#pragma unroll
+    for (int q = 0; q < kVecRows; ++q) pv[q] = pools ? a.pb[(int64_t)lane * d + j0 + q] + a.cusum[(int64_t)L * d + j0 + q] : 0.f;
+    float wz[kVecRows][kMaxClasses];
+#pragma unroll
+    for (int q = 0; q < kVecRows; ++q)
+#pragma unroll
+        for (int c = 0; c < kMaxClasses; ++c) wz[q][c] = 0.f;
+    for (int c0 = wave * 512; c0 < Lr; c0 += 4 * 512) {
+        const int col = min(c0 + lane * 8, Lr - 8);
+        const bool live = c0 + lane * 8 < Lr;
+        u32x4 w[kVecRows], u[kVecRows];
+#pragma unroll
+        for (int q = 0; q < kVecRows; ++q) {
+            w[q] = *reinterpret_cast<const u32x4 *>(a.Wds + (int64_t)(j0 + q) * Lr + col);
+            u[q] = *reinterpret_cast<const u32x4 *>(a.WuTs + (int64_t)(j0 + q) * Lr + col);
+        }
+        const f32x4 cs0 = *reinterpret_cast<const f32x4 *>(a.cs + col), cs1 = *reinterpret_cast<const f32x4 *>(a.cs + col + 4);
+        float uf[kVecRows][8];
+#pragma unroll
+        for (int q = 0; q < kVecRows; ++q) {
+            Chunk<bf16_t> w8, u8;
+            __builtin_memcpy(&w8, &w[q], 16);
+            __builtin_memcpy(&u8, &u[q], 16);
+            float acc = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                acc += (e < 4 ? cs0[e & 3] : cs1[e & 3]) * to_f32(w8.e[e]);
+                uf[q][e] = live ? to_f32(u8.e[e]) : 0.f;
+            }
+            acc += __shfl_xor(acc, 1, 64);
+            acc += __shfl_xor(acc, 2, 64);
+            if (live && (lane & 3) == q) part[q * ng + (col >> 5)] = acc;
+        }
+#pragma unroll
+        for (int c = 0; c < kMaxClasses; ++c)
+            if (c < C) {
+                const f32x4 z0 = *reinterpret_cast<const f32x4 *>(a.ZT + (int64_t)c * Lr + col);
+                const f32x4 z1 = *reinterpret_cast<const f32x4 *>(a.ZT + (int64_t)c * Lr + col + 4);
+#pragma unroll
+                for (int q = 0; q < kVecRows; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) wz[q][c] += uf[q][e] * z0[e] + uf[q][4 + e] * z1[e];
+            }
+    }
+#pragma unroll
+    for (int c = 0; c < kMaxClasses; ++c)
+        if (c < C) {
+            const float z = pools ? a.dz[lane * C + c] : 0.f;
+#pragma unroll
+            for (int q = 0; q < kVecRows; ++q) wz[q][c] += pv[q] * z;
+        }
+#pragma unroll
+    for (int q = 0; q < kVecRows; ++q)
+#pragma unroll
+        for (int c = 0; c < kMaxClasses; ++c)
+            if (c < C) {
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) wz[q][c] += __shfl_xor(wz[q][c], o, 64);
+                if (lane == 0) wred[(wave * kVecRows + q) * kMaxClasses + c] = wz[q][c];
+            }
+    static_assert(kMaxBatch <= 64 && kVecRows == 4, "a lane per sample, a wavefront per row");
+    __syncthreads();
+    const int q = wave, j = j0 + q;
+    // dW_cls[j][c] = sum_s (pb[s][j] + cusum_L[j]) dz[s][c] + sum_k W_up^k[.][j] . Z_k[.][c]
+    if (lane < C) {
+        float tot = 0.f;
+        for (int w = 0; w < 4; ++w) tot += wred[(w * kVecRows + q) * kMaxClasses + lane];
+        a.grads[(int64_t)L * a.PL + (int64_t)j * C + lane] = tot;
+    }
+    // dc_up^k[j] = (sum_s dz_s) W_cls^T [j] + sum_{k'>k} (1-lambda_k') W_down^k'[j] . cs_k': lane k (L <= 64) forms its
+    // layer's term, then sums the later lanes'
+    float tk = 0.f;
+    if (lane < L)
+        for (int g = 0; g < r / 32; ++g) tk += part[q * ng + lane * (r / 32) + g];
+    tk *= oml;
+    float suf = tk; // inclusive suffix sum over the lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float up = __shfl_down(suf, o, 64);
+        suf += lane + o < 64 ? up : 0.f;
+    }
+    if (lane < L) a.grads[(int64_t)lane * a.PL + 2 * dr + r + j] = base + (suf - tk);
+}
+
 // ---------------------------------------------------------------------------
 // launch 6: ordered sums of the token-split partials: E, and the Gram matrix, kept as the two bf16
 // copies the last launch contracts: GG transposed, and GG with column layer l scaled by (1 - lambda_l)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_ggsum(int L, int r, int sg, const float *GGpart, const float *params,
+// (VEC: the wide shapes' vector part rides along, its workgroups first)
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_ggsum(PostArgs pa, int L, int r, int sg, const float *GGpart, const float *params,
                                                int64_t PL, bf16_t *GGT, bf16_t *GGsc, int nb_GG, int se,
                                                int64_t e_elems, const float *Epart, float *E)
 {
+    extern __shared__ __attribute__((aligned(1024))) char smem[]; // VEC: post_vec_wide_lds bytes
     __shared__ float tile[32][33];
     const int Lr = L * r;
-    const int b = blockIdx.x, t = threadIdx.x;
+    int b = blockIdx.x;
+    const int t = threadIdx.x;
+    if constexpr (VEC) {
+        if (b < pa.nb_vec) {
+            post_vec_wide(pa, b, smem);
+            return;
+        }
+        b -= pa.nb_vec;
+    }
     if (b >= nb_GG) {
         // E = ordered sum of its token-split partials, four elements per thread
         const int64_t o = ((int64_t)(b - nb_GG) * 256 + t) * 4;
@@ -1875,24 +2051,16 @@ __global__ __launch_bounds__(256) void k_ggsum(int L, int r, int sg, const float
 // ---------------------------------------------------------------------------
 // launch 7: the gradients
 // ---------------------------------------------------------------------------
-struct PostArgs {
-    int blk_off; // first block of this launch (parts may be launched separately for timing)
-    int L, d, r, C, B, se;
-    int nb_F, nb_W, nb_vec;
-    const float *params;
-    int64_t PL;
-    const bf16_t *WuTs, *Wds, *GGT, *GGsc;
-    const float *Epart, *cusum, *cs, *Z, *dzsum, *dz, *pb;
-    float *grads;
-    float *dlam_part;
-    int slots;
-};
+// Both epilogues: d and r are multiples of 32, so a block of 32 x 32 lies inside the result or outside.  Its 16 values per
+// lane sit at one lane offset plus a multiple of the row pitch that is the same for all lanes: kept in scalar registers
+// (with an address per value the 256 x 256 tiles' epilogue spilled 111 registers).
+__device__ __forceinline__ int epi_step(int v) { return 8 * (v >> 2) + (v & 3); } // row of value v behind row_base
+__device__ __forceinline__ float load_at(const float *p, uint32_t byte) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p) + byte); }
+__device__ __forceinline__ void store_at(float *p, uint32_t byte, float v) { *reinterpret_cast<float *>(reinterpret_cast<char *>(p) + byte) = v; }
 
 struct EpiF {
     static constexpr bool kBatched = true;
-    const float *Epart;
-    int se;
-    int64_t split_stride;
+    const float *E_l;
     const float *cusum_l, *cs_l, *Wd_l;
     float *gWd;
     int r;
@@ -1900,32 +2068,22 @@ struct EpiF {
     float dlam;
     __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols)
     {
-        const int cc = min(col, ncols - 1);
-        const float csv = cs_l[cc];
+        if ((row_base & ~31) >= nrows || col >= ncols) return;
+        const uint32_t at = 4u * ((uint32_t)row_base * r + col), rows = 4u * row_base;
+        const float csv = cs_l[col];
         float E[16], W[16], cu[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int rr = min(epi_row(row_base, v), nrows - 1);
-            const int64_t o = (int64_t)rr * r + cc;
-            E[v] = Epart[o];
-            W[v] = Wd_l[o];
-            cu[v] = cusum_l[rr];
-        }
-        for (int s = 1; s < se; ++s) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rr = min(epi_row(row_base, v), nrows - 1);
-                E[v] += Epart[(int64_t)s * split_stride + (int64_t)rr * r + cc];
-            }
+            const int64_t o = (int64_t)epi_step(v) * r;
+            E[v] = load_at(E_l + o, at);
+            W[v] = load_at(Wd_l + o, at);
+            cu[v] = load_at(cusum_l + epi_step(v), rows);
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int row = epi_row(row_base, v);
-            if (row < nrows && col < ncols) {
-                const float F = acc[v] + cu[v] * csv;
-                gWd[(int64_t)row * r + col] = lam * E[v] + (1.f - lam) * F;
-                dlam += (E[v] - F) * W[v];
-            }
+            const float F = acc[v] + cu[v] * csv;
+            store_at(gWd + (int64_t)epi_step(v) * r, at, lam * E[v] + (1.f - lam) * F);
+            dlam += (E[v] - F) * W[v];
         }
     }
 };
@@ -1937,23 +2095,22 @@ struct EpiW {
     int d, C;
     __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols) const
     {
-        const int cc = min(col, ncols - 1);
+        if ((row_base & ~31) >= nrows || col >= ncols) return;
         float out[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) out[v] = acc[v];
+#pragma unroll 1
         for (int c = 0; c < C; ++c) {
-            const float w = Wc[(int64_t)cc * C + c];
+            const float w = Wc[(int64_t)col * C + c];
             float z[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) z[v] = Z_l[(int64_t)min(epi_row(row_base, v), nrows - 1) * C + c];
+            for (int v = 0; v < 16; ++v) z[v] = load_at(Z_l + (int64_t)epi_step(v) * C + c, 4u * row_base * C);
 #pragma unroll
             for (int v = 0; v < 16; ++v) out[v] += z[v] * w;
         }
+        const uint32_t at = 4u * ((uint32_t)row_base * d + col);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = epi_row(row_base, v);
-            if (row < nrows && col < ncols) gWu[(int64_t)row * d + col] = out[v];
-        }
+        for (int v = 0; v < 16; ++v) store_at(gWu + (int64_t)epi_step(v) * d, at, out[v]);
     }
 };
 
@@ -1971,98 +2128,15 @@ template <int CC> __device__ __forceinline__ void zrows(const float *Z, const Ch
     }
 }
 
-template <int BK, bool BIG, bool XW = false> struct PostShapes {
-    // 64 x 64 with 64 KB of stages; or (r > 128) eight wavefronts, three stages, interleaved sub-steps:
-    // 128 rows of d x 256 columns of r for F, 256 rows of r x 128 columns of d for W
-    using TSmall = NtTile<2, 2, 1, 1, BK, BK == 64 ? 4 : 8>;
-    using TFF = typename std::conditional<BIG, NtTile<2, 4, 2, 2, BK, 3>, TSmall>::type;
-    using TFW = typename std::conditional<BIG, NtTile<4, 2, 2, 2, BK, 3>, TSmall>::type;
-    static constexpr int NH = XW ? 8 : BIG ? 4 : 2; // threads sharing one r-wide row in the vector part (XW: r > 256)
-    static constexpr int kThreadsPerBlock = BIG ? 512 : 256;
-    static constexpr int kVecLds = 128 * 4 + 128 * kMaxClasses * 4 + kMaxBatch * kMaxClasses * 4;
-    static constexpr int kLds = TFF::LDS_BYTES > TFW::LDS_BYTES ? TFF::LDS_BYTES : TFW::LDS_BYTES;
-    static_assert(kLds >= kVecLds, "LDS budget of the gradient kernel");
-};
-
-// BK = 64 when r is a multiple of 64, else 32: every K range below is a multiple of r
-template <int BK, bool BIG, bool XW> __global__ __launch_bounds__(BIG ? 512 : 256) void k_gpost(PostArgs a)
+constexpr int kPostVecLds = 128 * 4 + 128 * kMaxClasses * 4 + kMaxBatch * kMaxClasses * 4;
+// The rest of the gradients: block vb of nb_vec, four wavefronts; NH threads share one r-wide row; the column sums and Z are
+// staged in LDS where lds_bytes allow it.
+template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, int vb, char *smem, int lds_bytes)
 {
-    using TFF = typename PostShapes<BK, BIG, XW>::TFF;
-    using TFW = typename PostShapes<BK, BIG, XW>::TFW;
-    constexpr int kVecLds = PostShapes<BK, BIG, XW>::kVecLds;
-    constexpr int kLds = PostShapes<BK, BIG, XW>::kLds;
-    constexpr int NH = PostShapes<BK, BIG, XW>::NH;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
-    __shared__ float red[16];
     const int L = a.L, d = a.d, r = a.r, C = a.C;
     const int Lr = L * r;
     const int64_t dr = (int64_t)d * r;
-    const int b = (int)(gridDim.x - 1 - blockIdx.x) + a.blk_off, t = threadIdx.x; // reverse dispatch, as in k_gproj
-    if (b < a.nb_F) {
-        const int ti_d = (d + TFF::BM - 1) / TFF::BM, ti_r = (r + TFF::BN - 1) / TFF::BN;
-        // F_l = sum_{k<l} W_up^{kT} G_{kl}   ([d] x [l*r] times [l*r] x [r])
-        int l, slot, it, nt;
-        if (BIG && ti_d % 8 == 0) {
-            // A die takes ti_d / 8 tiles along d for every layer: the rows of the stacked W_up copy those tiles read are
-            // shared by all layers (each layer contracts a prefix of them), so they cross the fabric once per die
-            // instead of once per layer.  Within a die the layers run from the last (longest contraction) down.
-            const int per_die = ti_d / 8 * ti_r * L;
-            const int v = die_chunk_order(b, a.nb_F);
-            const int die = v / per_die, w = v % per_die;
-            l = w / (ti_d / 8 * ti_r);
-            const int q = w % (ti_d / 8 * ti_r);
-            it = die * (ti_d / 8) + q / ti_r;
-            nt = q % ti_r;
-            slot = it * ti_r + nt;
-        } else {
-            const int v = BIG ? die_group_order(b, a.nb_F, 8) : b;
-            l = v / (ti_d * ti_r);
-            slot = v % (ti_d * ti_r);
-            it = slot / ti_r;
-            nt = slot % ti_r;
-        }
-        const float *pl = a.params + (int64_t)l * a.PL;
-        const bf16_t *A = a.WuTs, *B = a.GGT + (int64_t)l * r * Lr;
-        auto arow = [&](int row) { return A + (int64_t)row * Lr; };
-        auto brow = [&](int c) { return B + (int64_t)c * Lr; };
-        EpiF epi{a.Epart + (int64_t)l * dr, a.se, (int64_t)L * dr, a.cusum + (int64_t)l * d, a.cs + (int64_t)l * r,
-                 pl, a.grads + (int64_t)l * a.PL, r, pl[a.PL - 1], 0.f};
-        gemm_nt<TFF, true>(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
-        const float tot = block_sum(epi.dlam, red);
-        if (t == 0) a.dlam_part[(int64_t)l * a.slots + slot] = tot; // summed in slot order by k_gfinish
-        return;
-    }
-    if (b < a.nb_F + a.nb_W) {
-        // dW_up^l = Z_l W_cls^T + sum_{k>l} (1-lambda_k) G_{lk} W_down^{kT}
-        const int ti_r = (r + TFW::BM - 1) / TFW::BM, ti_d = (d + TFW::BN - 1) / TFW::BN;
-        int l, at, jt;
-        if (BIG && ti_d % 8 == 0) {
-            // as for F: a die takes ti_d / 8 tiles along d (rows of the stacked W_down copy) for every layer
-            const int per_die = ti_d / 8 * ti_r * L;
-            const int v = die_chunk_order(b - a.nb_F, a.nb_W);
-            const int die = v / per_die, w = v % per_die;
-            l = L - 1 - w / (ti_d / 8 * ti_r); // the first layers have the longest contractions here
-            const int q = w % (ti_d / 8 * ti_r);
-            jt = die * (ti_d / 8) + q / ti_r;
-            at = q % ti_r;
-        } else {
-            int idx = BIG ? die_group_order(b - a.nb_F, a.nb_W, 8) : b - a.nb_F;
-            l = idx / (ti_d * ti_r);
-            idx %= ti_d * ti_r;
-            // (wide shapes: the row tiles of a column tile next to each other)
-            at = BIG ? idx % ti_r : idx / ti_d;
-            jt = BIG ? idx / ti_r : idx % ti_d;
-        }
-        const bf16_t *A = a.GGsc + (int64_t)l * r * Lr, *B = a.Wds;
-        auto arow = [&](int row) { return A + (int64_t)row * Lr; };
-        auto brow = [&](int c) { return B + (int64_t)c * Lr; };
-        EpiW epi{a.Z + (int64_t)l * r * C, a.params + (int64_t)L * a.PL,
-                 a.grads + (int64_t)l * a.PL + dr + r, d, C};
-        gemm_nt<TFW, true>(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
-        return;
-    }
-    if (BIG && t >= 256) return; // the remaining parts are written for four wavefronts
-    const int vb = b - a.nb_F - a.nb_W;
+    const int t = threadIdx.x;
     if (vb < a.nb_vec - 1) {
         // thread (jj, k, hf): hidden index j = vb * jpb + jj, layer k, part hf (of NH) of the r-wide rows
         float *tsh = reinterpret_cast<float *>(smem);          // [jpb][L]      (1-lambda_k) W_down^k[j] . cs_k
@@ -2080,15 +2154,16 @@ template <int BK, bool BIG, bool XW> __global__ __launch_bounds__(BIG ? 512 : 25
         constexpr int kMaxChunks = 8; // r / NH <= 64
         u32x4 wv[kMaxChunks], uv[kMaxChunks];
         {
-            const int64_t row = act ? (int64_t)j * Lr + (int64_t)k * r + hf * rh : 0;
+            // the NH threads of a row take its 16-byte chunks in turn: neighbouring lanes read neighbouring chunks
+            const int64_t row = act ? (int64_t)j * Lr + (int64_t)k * r + hf * 8 : 0;
 #pragma unroll
             for (int q = 0; q < kMaxChunks; ++q) {
-                const int qq = q * 8 < rh ? q * 8 : 0;
+                const int qq = q * 8 < rh ? q * 8 * NH : 0;
                 wv[q] = *reinterpret_cast<const u32x4 *>(a.Wds + row + qq);
                 uv[q] = *reinterpret_cast<const u32x4 *>(a.WuTs + row + qq);
             }
         }
-        const bool staged = (int64_t)Lr * (1 + C) * 4 + kVecLds <= kLds;
+        const bool staged = (int64_t)Lr * (1 + C) * 4 + kPostVecLds <= lds_bytes;
         for (int q = t; q < a.B * C; q += 256) sdz[q] = a.dz[q];
         if (staged) {
             stage_to_lds<256>(stage, a.cs, Lr);
@@ -2117,8 +2192,8 @@ template <int BK, bool BIG, bool XW> __global__ __launch_bounds__(BIG ? 512 : 25
         const float lamk = a.params[(int64_t)k * a.PL + a.PL - 1];
         __syncthreads();
         {
-            const float *csk = (staged ? stage : a.cs) + (int64_t)k * r + hf * rh;
-            const float *Zk = (staged ? stage + Lr : a.Z) + ((int64_t)k * r + hf * rh) * C;
+            const float *csk = (staged ? stage : a.cs) + (int64_t)k * r + hf * 8;
+            const float *Zk = (staged ? stage + Lr : a.Z) + ((int64_t)k * r + hf * 8) * C;
             float acc = 0.f;
             float wz[kMaxClasses];
 #pragma unroll
@@ -2131,24 +2206,24 @@ template <int BK, bool BIG, bool XW> __global__ __launch_bounds__(BIG ? 512 : 25
                         __builtin_memcpy(&w8, &wv[q], 16);
                         __builtin_memcpy(&u8, &uv[q], 16);
                         // 16-byte reads of the column sums (both sides are 16-byte aligned: rh % 8 == 0)
-                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(csk + q * 8);
-                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(csk + q * 8 + 4);
+                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(csk + q * 8 * NH);
+                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(csk + q * 8 * NH + 4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             acc += c0[e] * to_f32(w8.e[e]);
                             acc += c1[e] * to_f32(w8.e[4 + e]);
                         }
                         // Z of these 8 rows: 8 C consecutive floats, read as 2 C 16-byte pieces
-                        if (C == 3) zrows<3>(Zk + (int64_t)q * 8 * 3, u8, wz);
-                        else if (C == 4) zrows<4>(Zk + (int64_t)q * 8 * 4, u8, wz);
-                        else if (C == 2) zrows<2>(Zk + (int64_t)q * 8 * 2, u8, wz);
+                        if (C == 3) zrows<3>(Zk + (int64_t)q * 8 * NH * 3, u8, wz);
+                        else if (C == 4) zrows<4>(Zk + (int64_t)q * 8 * NH * 4, u8, wz);
+                        else if (C == 2) zrows<2>(Zk + (int64_t)q * 8 * NH * 2, u8, wz);
                         else {
 #pragma unroll
                             for (int e = 0; e < 8; ++e) {
                                 const float u = to_f32(u8.e[e]);
 #pragma unroll
                                 for (int c = 0; c < kMaxClasses; ++c)
-                                    if (c < C) wz[c] += u * Zk[(int64_t)(q * 8 + e) * C + c];
+                                    if (c < C) wz[c] += u * Zk[(int64_t)(q * 8 * NH + e) * C + c];
                             }
                         }
                     }
@@ -2196,6 +2271,103 @@ template <int BK, bool BIG, bool XW> __global__ __launch_bounds__(BIG ? 512 : 25
         a.grads[(int64_t)l * a.PL + dr + nn] = a.cs[idx];
     }
     if (t < C) a.grads[(int64_t)L * a.PL + (int64_t)d * C + t] = a.dzsum[t];
+}
+
+template <int BK, bool BIG> struct PostShapes {
+    // 64 x 64 with 64 KB of stages; or (r > 128) eight wavefronts, three stages, interleaved sub-steps:
+    // 128 rows of d x 256 columns of r for F, 256 rows of r x 128 columns of d for W
+    using TSmall = NtTile<2, 2, 1, 1, BK, BK == 64 ? 4 : 8>;
+    using TFF = typename std::conditional<BIG, NtTile<2, 4, 2, 2, BK, 3>, TSmall>::type;
+    using TFW = typename std::conditional<BIG, NtTile<4, 2, 2, 2, BK, 3>, TSmall>::type;
+    static constexpr int kThreadsPerBlock = BIG ? 512 : 256;
+    static constexpr int kLds = TFF::LDS_BYTES > TFW::LDS_BYTES ? TFF::LDS_BYTES : TFW::LDS_BYTES;
+    static_assert(kLds >= kPostVecLds, "LDS budget of the gradient kernel");
+};
+
+// BK = 64 when r is a multiple of 64, else 32: every K range below is a multiple of r
+template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k_gpost(PostArgs a)
+{
+    using TFF = typename PostShapes<BK, BIG>::TFF;
+    using TFW = typename PostShapes<BK, BIG>::TFW;
+    constexpr int kLds = PostShapes<BK, BIG>::kLds;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    __shared__ float red[16];
+    const int L = a.L, d = a.d, r = a.r, C = a.C;
+    const int Lr = L * r;
+    const int64_t dr = (int64_t)d * r;
+    const int b = (int)(gridDim.x - 1 - blockIdx.x) + a.blk_off, t = threadIdx.x; // reverse dispatch, as in k_gproj
+    if (b < a.nb_F) {
+        const int fbm = BIG && a.pp ? PpTile::BM : TFF::BM;
+        const int ti_d = (d + fbm - 1) / fbm, ti_r = (r + TFF::BN - 1) / TFF::BN;
+        // F_l = sum_{k<l} W_up^{kT} G_{kl}   ([d] x [l*r] times [l*r] x [r])
+        int l, slot, it, nt;
+        if (BIG && ti_d % 8 == 0) {
+            // A die takes ti_d / 8 tiles along d for every layer: the rows of the stacked W_up copy those tiles read are
+            // shared by all layers (each layer contracts a prefix of them), so they cross the fabric once per die
+            // instead of once per layer.  Within a die the layers run from the last (longest contraction) down.
+            const int per_die = ti_d / 8 * ti_r * L;
+            const int v = die_chunk_order(b, a.nb_F);
+            const int die = v / per_die, w = v % per_die;
+            l = w / (ti_d / 8 * ti_r);
+            const int q = w % (ti_d / 8 * ti_r);
+            it = die * (ti_d / 8) + q / ti_r;
+            nt = q % ti_r;
+            slot = it * ti_r + nt;
+        } else {
+            const int v = BIG ? die_group_order(b, a.nb_F, 8) : b;
+            l = v / (ti_d * ti_r);
+            slot = v % (ti_d * ti_r);
+            it = slot / ti_r;
+            nt = slot % ti_r;
+        }
+        const float *pl = a.params + (int64_t)l * a.PL;
+        const bf16_t *A = a.WuTs, *B = a.GGT + (int64_t)l * r * Lr;
+        auto arow = [&](int row) { return A + (int64_t)row * Lr; };
+        auto brow = [&](int c) { return B + (int64_t)c * Lr; };
+        EpiF epi{a.E + (int64_t)l * dr, a.cusum + (int64_t)l * d, a.cs + (int64_t)l * r,
+                 pl, a.grads + (int64_t)l * a.PL, r, pl[a.PL - 1], 0.f};
+        if (BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, l * r, it * PpTile::BM, nt * PpTile::BN, d, r);
+        else gemm_nt<TFF, true>(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
+        const float tot = block_sum(epi.dlam, red);
+        if (t == 0) a.dlam_part[(int64_t)l * a.slots + slot] = tot; // summed in slot order by k_gfinish
+        return;
+    }
+    if (b < a.nb_F + a.nb_W) {
+        // dW_up^l = Z_l W_cls^T + sum_{k>l} (1-lambda_k) G_{lk} W_down^{kT}
+        const int wbn = BIG && a.pp ? PpTile::BN : TFW::BN;
+        const int ti_r = (r + TFW::BM - 1) / TFW::BM, ti_d = (d + wbn - 1) / wbn;
+        int l, at, jt;
+        if (BIG && ti_d % 8 == 0) {
+            // as for F: a die takes ti_d / 8 tiles along d (rows of the stacked W_down copy) for every layer
+            const int per_die = ti_d / 8 * ti_r * L;
+            const int v = die_chunk_order(b - a.nb_F, a.nb_W);
+            const int die = v / per_die, w = v % per_die;
+            l = L - 1 - w / (ti_d / 8 * ti_r); // the first layers have the longest contractions here
+            const int q = w % (ti_d / 8 * ti_r);
+            jt = die * (ti_d / 8) + q / ti_r;
+            at = q % ti_r;
+        } else {
+            int idx = BIG ? die_group_order(b - a.nb_F, a.nb_W, 8) : b - a.nb_F;
+            l = idx / (ti_d * ti_r);
+            idx %= ti_d * ti_r;
+            // (wide shapes: the row tiles of a column tile next to each other)
+            at = BIG ? idx % ti_r : idx / ti_d;
+            jt = BIG ? idx / ti_r : idx % ti_d;
+        }
+        const bf16_t *A = a.GGsc + (int64_t)l * r * Lr, *B = a.Wds;
+        auto arow = [&](int row) { return A + (int64_t)row * Lr; };
+        auto brow = [&](int c) { return B + (int64_t)c * Lr; };
+        EpiW epi{a.Z + (int64_t)l * r * C, a.params + (int64_t)L * a.PL,
+                 a.grads + (int64_t)l * a.PL + dr + r, d, C};
+        if (BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, (l + 1) * r, Lr, at * PpTile::BM, jt * PpTile::BN, r, d);
+        else gemm_nt<TFW, true>(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
+        return;
+    }
+    if constexpr (!BIG) post_vec<2>(a, b - a.nb_F - a.nb_W, smem, kLds);
+    else if (t < 256) {
+        if (r > 256) post_vec<8>(a, b - a.nb_F - a.nb_W, smem, kLds);
+        else post_vec<4>(a, b - a.nb_F - a.nb_W, smem, kLds);
+    }
 }
 
 // last launch: the two scalar reductions whose inputs come from many workgroups, in a fixed order
@@ -2284,7 +2456,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     float *HSpart = (float *)(ws + W.g_HSpart), *cspart = (float *)(ws + W.g_cspart);
     float *logits = (float *)(ws + W.logits), *dz = (float *)(ws + W.dz);
     float *zpart = (float *)(ws + W.g_zpart), *zpb = (float *)(ws + W.g_zpb);
-    float *Z = (float *)(ws + W.g_Z), *dzsum = (float *)(ws + W.g_dzsum);
+    float *Z = (float *)(ws + W.g_Z), *ZT = (float *)(ws + W.g_ZT), *dzsum = (float *)(ws + W.g_dzsum);
     float *cs = (float *)(ws + W.g_cs);
     float *Epart = (float *)(ws + W.g_Epart), *GGpart = (float *)(ws + W.g_GGpart);
     bf16_t *GGT = (bf16_t *)(ws + W.g_GGT), *GGsc = (bf16_t *)(ws + W.g_GGsc);
@@ -2317,12 +2489,15 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         a.cache = cache; a.map = map; a.L = L; a.d = d; a.r = r; a.B = B;
         constexpr int kQRows = NT > 4 ? 128 : 64, kQCols = NT > 4 ? 256 : 64; // ProjShapes<NT, .>::TQ
         constexpr int kProjThreads = NT > 4 ? 512 : 256;
-        a.row_tiles = cdiv(M, 128); a.nb_U = a.row_tiles * L * (NT > 4 ? cdiv(r, 256) : 1);
+        a.pp = NT > 4 && d % 64 == 0 &&
+               pp_pays(((int64_t)cdiv(M, 256) * L + (int64_t)W.pairs * cdiv(r, 256)) * cdiv(r, 256),
+                       ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * cdiv(r, 256), d / 64);
+        a.row_tiles = cdiv(M, a.pp ? 256 : 128); a.nb_U = a.row_tiles * L * (NT > 4 ? cdiv(r, 256) : 1);
         a.nb_Q = W.pairs * cdiv(r, kQRows) * cdiv(r, kQCols);
         if (NT <= 4 && W.use_gram != 2) a.nb_Q = L > 1 ? cdiv(Lr, 128) * cdiv(Lr, 128) : 0; // ProjShapes::QSTACK
         if (NT > 4) { // blocks of 4 x 4 layer pairs, see k_gproj
             const int nlb = cdiv(L, 4);
-            a.nb_Q = L > 1 ? nlb * (nlb + 1) / 2 * 16 * cdiv(r, kQRows) * cdiv(r, kQCols) : 0;
+            a.nb_Q = L > 1 ? nlb * (nlb + 1) / 2 * 16 * cdiv(r, a.pp ? 256 : kQRows) * cdiv(r, kQCols) : 0;
         }
         a.nb_C = L * cdiv(r, 64);
         a.cusum = cusum; a.chat = chat; a.params = io.params; a.PL = D.PL;
@@ -2338,15 +2513,16 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         if (d % 64 == 0) {
             constexpr int lds = ProjShapes<NT, 64, true>::kLds > ProjShapes<NT, 64, false>::kLds ? ProjShapes<NT, 64, true>::kLds : ProjShapes<NT, 64, false>::kLds;
             if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, true>>(lds))); launch_proj(&k_gproj<NT, 64, true>, lds); }
-            else { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, false>>(lds))); launch_proj(&k_gproj<NT, 64, false>, lds); }
+            else if constexpr (NT <= 4) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, false>>(lds))); launch_proj(&k_gproj<NT, 64, false>, lds); }
         } else {
             constexpr int lds = ProjShapes<NT, 32, true>::kLds > ProjShapes<NT, 32, false>::kLds ? ProjShapes<NT, 32, true>::kLds : ProjShapes<NT, 32, false>::kLds;
             if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, true>>(lds))); launch_proj(&k_gproj<NT, 32, true>, lds); }
-            else { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, false>>(lds))); launch_proj(&k_gproj<NT, 32, false>, lds); }
+            else if constexpr (NT <= 4) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, false>>(lds))); launch_proj(&k_gproj<NT, 32, false>, lds); }
         }
     }
     PAC_HIP_TRY(hipGetLastError());
-    PAC_HIP_TRY((allow_lds_once<&k_gtokred<NT>>(TokRedShapes<NT>::kLds)));
+    PAC_HIP_TRY((allow_lds_once<&k_gtokred<NT, false>>(TokRedShapes<NT>::kLds)));
+    if constexpr (NT > 4) PAC_HIP_TRY((allow_lds_once<&k_gtokred<NT, true>>(PpTile::LDS_BYTES)));
     ChainArgs ca;
     ca.L = L; ca.r = r; ca.M = M; ca.tile_row0 = tile_row0; ca.tile_rows = tile_rows; ca.tile_samp = tile_samp;
     ca.params = io.params; ca.PL = D.PL; ca.d = d; ca.U = pre; ca.Gp = (bf16_t *)(ws + W.g_Gp); ca.chat = chat;
@@ -2457,18 +2633,25 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     }
     {
         TokRedArgs a;
+        bool pp;
         a.cache = cache; a.map = map; a.L = L; a.d = d; a.r = r;
-        a.e_tiles = cdiv(d, kETileCols);
         {
+            const int64_t ct = cdiv(Lr, 256) * (int64_t)W.sg / 2; // half of the Gram matrix's tiles are needed
+            pp = NT > 4 && pp_pays_tokens((int64_t)L * cdiv(d, 256) * cdiv(r, 256) * W.se + ct * cdiv(Lr, 256),
+                                     (int64_t)L * cdiv(d, 128) * cdiv(r, 256) * W.se + ct * cdiv(Lr, 128), cdiv(M, 64 * (W.se + W.sg) / 2));
+        }
+        a.e_tiles = cdiv(d, pp ? PpTile::BM : kETileCols);
+        {
+            const int tps = (pp ? 64 : TokRedShapes<NT>::KT) / 16;
             // W.se is fixed by the configuration (the partial buffers are sized for it)
             if (cdiv(ntiles, W.se) > kMaxSplitTiles) return hipErrorInvalidValue;
-            a.tiles_per_se = cdiv(cdiv(ntiles, W.se), TokRedShapes<NT>::KT / 16) * (TokRedShapes<NT>::KT / 16);
+            a.tiles_per_se = cdiv(cdiv(ntiles, W.se), tps) * tps;
             a.se = cdiv(ntiles, a.tiles_per_se);
         }
         a.tile_row0 = tile_row0; a.tile_rows = tile_rows; a.zeros = ws + W.g_zero;
         a.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
         a.sg = cdiv(M, a.rows_per_sg);
-        a.tg = cdiv(Lr, 128);
+        a.tg = cdiv(Lr, pp ? PpTile::BM : 128);
         a.tgn = cdiv(Lr, NT > 4 ? 256 : 128);
         a.nb_E = L * a.e_tiles * cdiv(r, NT > 4 ? 256 : 128) * a.se;
         a.reverse = NT <= 4 && L * a.e_tiles >= 128;
@@ -2477,42 +2660,57 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         // tokens not split: the Gram tiles write the two bf16 copies themselves, and E needs no sum either
         a.gg_direct = a.sg == 1; a.GGT = GGT; a.GGsc = GGsc; a.params = io.params; a.PL = D.PL;
         a.ntiles = ntiles; a.B = B; a.C = C; a.cspart = cspart; a.HSpart = HSpart; a.dz = dz;
-        a.tile_samp = tile_samp; a.samp_len = samp_len; a.cs = cs; a.Z = Z; a.dzsum = dzsum;
+        a.tile_samp = tile_samp; a.samp_len = samp_len; a.cs = cs; a.Z = Z; a.ZT = ZT; a.dzsum = dzsum;
         {
             const int counts[3] = {a.nb_E, a.nb_G, cdiv(Lr, 16)};
             const int classes[3] = {KC_G_TOKRED_E, KC_G_TOKRED_G, KC_G_TOKRED_VEC};
-            launch_parts(prof, st, split, k_gtokred<NT>, a, 3, counts, classes, KC_G_TOKRED, TokRedShapes<NT>::kThreadsPerBlock, TokRedShapes<NT>::kLds);
-        }
-        {
-            const int nb_GG = L > 1 && !a.gg_direct ? (Lr / 32) * (Lr / 32) : 0;
-            const int64_t e_elems = a.se > 1 ? (int64_t)L * d * r : 0;
-            float *E = (float *)(ws + W.g_E);
-            if (nb_GG + e_elems > 0)
-                PAC_LAUNCH(prof, st, KC_G_GGSUM, k_ggsum, dim3(nb_GG + cdiv(e_elems / 4, 256)), dim3(256), 0, st, L, r, a.sg,
-                           GGpart, io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
+            if constexpr (NT > 4) {
+                if (pp) launch_parts(prof, st, split, k_gtokred<NT, true>, a, 3, counts, classes, KC_G_TOKRED, 512, PpTile::LDS_BYTES);
+            }
+            if (!pp) launch_parts(prof, st, split, k_gtokred<NT, false>, a, 3, counts, classes, KC_G_TOKRED, TokRedShapes<NT>::kThreadsPerBlock, TokRedShapes<NT>::kLds);
         }
         const float *Esum = a.se > 1 ? (const float *)(ws + W.g_E) : Epart;
         PostArgs pa;
-        pa.L = L; pa.d = d; pa.r = r; pa.C = C; pa.B = B; pa.se = 1;
-        constexpr bool BIG = NT > 4, XW = NT > 8;
-        constexpr int NH = PostShapes<64, BIG, XW>::NH;
-        constexpr int kFRows = BIG ? 128 : 64, kFCols = BIG ? 256 : 64, kWRows = BIG ? 256 : 64, kWCols = BIG ? 128 : 64;
+        pa.L = L; pa.d = d; pa.r = r; pa.C = C; pa.B = B;
+        constexpr bool BIG = NT > 4;
+        // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
+        // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
+        // 4 to 7 us slower at 1.2 to 1.6 M).
+        const bool vec_wide = BIG && (int64_t)d * Lr >= (2 << 20);
+        const int NH = !BIG ? 2 : r > 256 ? 8 : 4; // threads per r-wide row in post_vec
+        constexpr int kFCols = BIG ? 256 : 64, kWRows = BIG ? 256 : 64;
+        pa.pp = BIG && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * cdiv(r, 256), (int64_t)2 * L * cdiv(d, 128) * cdiv(r, 256), (L - 1) * r / 128);
+        const int kFRows = pa.pp ? 256 : BIG ? 128 : 64, kWCols = pa.pp ? 256 : BIG ? 128 : 64;
         constexpr int kPostThreads = BIG ? 512 : 256;
         pa.nb_F = L * cdiv(d, kFRows) * cdiv(r, kFCols); pa.nb_W = L * cdiv(r, kWRows) * cdiv(d, kWCols);
-        pa.nb_vec = cdiv(d, (256 / NH) / L) + 1;
+        pa.nb_vec = vec_wide ? L + d / kVecRows : cdiv(d, (256 / NH) / L) + 1;
         pa.params = io.params; pa.PL = D.PL; pa.WuTs = WuTs; pa.Wds = Wds; pa.GGT = GGT; pa.GGsc = GGsc;
-        pa.Epart = Esum; pa.cusum = cusum; pa.cs = cs; pa.Z = Z; pa.dzsum = dzsum; pa.dz = dz; pa.pb = pb;
+        pa.E = Esum; pa.cusum = cusum; pa.cs = cs; pa.Z = Z; pa.ZT = ZT; pa.dzsum = dzsum; pa.dz = dz; pa.pb = pb;
         pa.grads = io.grads; pa.dlam_part = dlam_part;
         pa.slots = cdiv(d, kFRows) * cdiv(r, kFCols);
         {
-            const int counts[3] = {pa.nb_F, pa.nb_W, pa.nb_vec};
+            // post_vec_wide goes with the launch of the partial sums where there is one: it needs nothing of it
+            const int nb_GG = L > 1 && !a.gg_direct ? (Lr / 32) * (Lr / 32) : 0;
+            const int64_t e_elems = a.se > 1 ? (int64_t)L * d * r : 0;
+            const int nb_sum = nb_GG + cdiv(e_elems / 4, 256);
+            float *E = (float *)(ws + W.g_E);
+            if (!vec_wide) {
+                if (nb_sum > 0)
+                    PAC_LAUNCH(prof, st, KC_G_GGSUM, k_ggsum<false>, dim3(nb_sum), dim3(256), 0, st, pa, L, r, a.sg, GGpart,
+                               io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
+            } else {
+                PAC_LAUNCH(prof, st, nb_sum > 0 ? KC_G_GGSUM : split ? KC_G_POST_VEC : KC_G_POST, k_ggsum<true>,
+                           dim3(pa.nb_vec + nb_sum), dim3(256), post_vec_wide_lds(Lr), st, pa, L, r, a.sg, GGpart, io.params,
+                           D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
+            }
+            const int counts[3] = {pa.nb_F, pa.nb_W, vec_wide ? 0 : pa.nb_vec};
             const int classes[3] = {KC_G_POST_F, KC_G_POST_W, KC_G_POST_VEC};
-            PAC_HIP_TRY((allow_lds_once<&k_gpost<64, BIG, XW>>(PostShapes<64, BIG, XW>::kLds)));
-            PAC_HIP_TRY((allow_lds_once<&k_gpost<32, BIG, XW>>(PostShapes<32, BIG, XW>::kLds)));
+            PAC_HIP_TRY((allow_lds_once<&k_gpost<64, BIG>>(PostShapes<64, BIG>::kLds)));
+            PAC_HIP_TRY((allow_lds_once<&k_gpost<32, BIG>>(PostShapes<32, BIG>::kLds)));
             if (r % 64 == 0)
-                launch_parts(prof, st, split, k_gpost<64, BIG, XW>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<64, BIG, XW>::kLds);
+                launch_parts(prof, st, split, k_gpost<64, BIG>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<64, BIG>::kLds);
             else
-                launch_parts(prof, st, split, k_gpost<32, BIG, XW>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<32, BIG, XW>::kLds);
+                launch_parts(prof, st, split, k_gpost<32, BIG>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<32, BIG>::kLds);
         }
         if (io.defer) { // the optimizer launch that follows does the last two sums
             io.defer->used = true;
@@ -2533,9 +2731,8 @@ hipError_t launch_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMe
     case 2: return run_gram<2>(D, W, meta, io);
     case 3: return run_gram<3>(D, W, meta, io);
     case 4: return run_gram<4>(D, W, meta, io);
-    // above 128 the kernels take r as an argument: one instantiation up to 256, one above (gradient vector part)
-    case 5: case 6: case 7: case 8: return run_gram<8>(D, W, meta, io);
-    case 10: case 12: case 14: case 16: return run_gram<16>(D, W, meta, io);
+    // above 128 the kernels take r as an argument
+    case 5: case 6: case 7: case 8: case 10: case 12: case 14: case 16: return run_gram<8>(D, W, meta, io);
     }
     return hipErrorInvalidValue;
 }

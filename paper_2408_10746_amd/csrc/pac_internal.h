@@ -48,7 +48,7 @@ struct WsLayout {
     int64_t g_DP;                   // bf16 [Mmax][L*r]
     int64_t g_HSpart, g_cspart;     // f32 [max_tiles][L][r]
     int64_t g_zpart, g_zpb;         // f32 [max_tiles][C], [B_max][C]: shares of the logits
-    int64_t g_Z, g_dzsum, g_cs;
+    int64_t g_Z, g_ZT, g_dzsum, g_cs;
     int64_t g_Epart, g_GGpart;      // f32 [se][L][d*r], [sg][L*r][L*r]
     int64_t g_GGT, g_GGsc;          // bf16 [L*r][L*r]
     int64_t g_dlam_part;            // f32 [L][slots]

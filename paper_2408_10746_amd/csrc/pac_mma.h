@@ -35,13 +35,17 @@ template <int N> __device__ __forceinline__ void wait_vm()
 // transfers that run several stages ahead.  The code below counts them (wait_vm) instead; transfers
 // the compiler does not know of can only make its own waits stricter, never looser, because the
 // counter retires in issue order.
-__device__ __forceinline__ void dma16(const void *g, void *lds_wave_base)
+__device__ __forceinline__ void dma16_at(const void *g, uint32_t lds_wave_address)
 {
-    const uint32_t l = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_wave_base);
     // one wait state between the write of M0 and the transfer that reads it
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(l), "v"(g) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 : : "s"(__builtin_amdgcn_readfirstlane(lds_wave_address)), "v"(g) : "memory", "m0");
 }
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
+}
+__device__ __forceinline__ void dma16(const void *g, void *lds_wave_base) { dma16_at(g, lds_address(lds_wave_base)); }
 
 // ---------------------------------------------------------------------------
 // K-contiguous operands
@@ -382,6 +386,171 @@ __device__ __forceinline__ void gemm_nt_deepA(char *lds /* nt_deepA_lds<TL, SA>(
 template <class TL, int SA> constexpr int nt_deepA_lds() { return SA * TL::BM * TL::BK * 2 + (SA - 1) * TL::BN * TL::BK * 2; }
 
 // ---------------------------------------------------------------------------
+// 256 x 256 tiles, eight wavefronts in two groups that take turns at the matrix units
+//
+// What bounds a contraction here is how evenly the matrix units are fed: with one barrier per K step all wavefronts read
+// their fragments at the same time and then all multiply at the same time (gemm_nt above: 0.98 PFLOP/s on
+// 8192 x 8192 x 4096, 0.72 on 32 x (4096 x 256 x 4096)).  Here each SIMD holds one wavefront of each group, and a step of
+// 64 in K is four slots between workgroup barriers: read fragments (A rows of the first half, all of B) / 16 matrix
+// instructions / read the second half of A / 16 matrix instructions; group 1 runs one slot behind group 0, so one of the
+// two multiplies in every slot.  All transfers are issued between the matrix instructions, in their shadow.  Measured:
+// 1.24 PFLOP/s and 0.90 on those two shapes (the second moves 1.2 GB and is within 1.25 x of a plain copy of it).
+// Issued in the reading slots instead: 1.15 / 0.82; groups in step: 1.03 / 0.80; one wavefront-private pipeline with a
+// barrier per step: 1.21 / 0.81; the second half of A read during the first half's multiplications (two longer slots
+// per step): 1.06 / 0.83.
+//
+// LDS: two stages of 64 KB: A rows 0 .. 255, then B rows.  Wavefront (wm, wn) owns rows 128 wm .. + 127 in two halves
+// (h0 = its first 64 rows) and columns 64 wn .. + 63.  A stage is refilled in two pieces, S0 = both groups' h0 and B
+// (6 transfers per wavefront) and S1 = both h1 (2 transfers).  Slots of step t: group 0 reads h0 and B in 4t, multiplies
+// in 4t + 1, reads h1 in 4t + 2, multiplies in 4t + 3; group 1 one slot later.
+//   free:    h0 and B of stage t are read for the last time in slot 4t + 1 (group 1), h1 in 4t + 3; a wavefront's reads
+//            have arrived before the barrier that ends their slot.  S0(t + 2) is issued from slot 4t + 3 on, S1(t + 2)
+//            (into the stage of step t) from 4t + 5 on: after those reads.
+//   landed:  S0(t) is read from slot 4t on, S1(t) from 4t + 2 on.  Every wavefront waits for its own share before the
+//            barrier that ends the slot before.  Issue order per wavefront: S0(t + 1) [second multiplication of t - 1],
+//            S1(t + 1) [first multiplication of t], S0(t + 2), ...; at the end of its second multiplication of t group
+//            0 needs S0(t + 1), behind which S1(t + 1) and S0(t + 2) were issued: 8 may be outstanding; at the end of the
+//            first one S1(t), behind it S0(t + 1), S1(t + 1): 8.  Group 1 is half a step back: it waits at the end of its
+//            reading slots, for S1(t) with S0(t + 1) behind it (6) and for S0(t + 1) with S1(t + 1) behind it (2).
+// ---------------------------------------------------------------------------
+struct PpTile {
+    static constexpr int WM = 2, WN = 4, WTM = 4, WTN = 2, BK = 64;
+    static constexpr int BM = 256, BN = 256, NW = 8;
+    static constexpr int STAGE_BYTES = (BM + BN) * BK * 2, LDS_BYTES = 2 * STAGE_BYTES;
+};
+
+// workgroup barrier that leaves this wavefront's transfers in flight
+__device__ __forceinline__ void slot_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The slot sequence.  xfer(q, step): issue transfer q (0 .. 5 = S0, 6 and 7 = S1) of K step `step` (steps past the end
+// are issued too and never read); prepare(step): whatever xfer needs to know about that step, called in a reading slot
+// before its first transfer (between the calls for two steps only those two steps' transfers are issued: S1 of the step
+// prepared last, then, after the next call, S0 of the new one); fragA(stage, half, x, ks) / fragB(stage, y, ks): fragment reads.
+template <class Xfer, class Prep, class FragA, class FragB>
+__device__ __forceinline__ void pp_loop(char *lds, f32x16 (&acc)[4][2], int nsteps, int wm, const Xfer &xfer,
+                                        const Prep &prepare, const FragA &fragA, const FragB &fragB)
+{
+    prepare(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) xfer(q, 0);
+    prepare(1);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) xfer(q, 1);
+    wait_vm<8>(); // S0(0)
+    slot_barrier();
+    if (wm) {
+        wait_vm<6>(); // S1(0): read by group 0 from slot 2 on
+        slot_barrier();
+    }
+    bf16x8 a[2][4], b[2][4];
+    for (int st = 0; st < nsteps; ++st) {
+        const char *sb = lds + (st & 1) * PpTile::STAGE_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) a[x][ks] = fragA(sb, 0, x, ks);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) b[y][ks] = fragB(sb, y, ks);
+        }
+        if (wm) wait_vm<6>();
+        __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): the reads have arrived
+        slot_barrier();
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int ks = j >> 2, x = (j >> 1) & 1, y = j & 1;
+            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x][ks], b[y][ks], acc[x][y], 0, 0, 0);
+            if (j == 1 || j == 3) {
+                __builtin_amdgcn_sched_barrier(0);
+                xfer(6 + (j >> 1), st + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+        if (!wm) wait_vm<8>();
+        slot_barrier();
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) a[x][ks] = fragA(sb, 1, x, ks);
+        prepare(st + 2);
+        if (wm) wait_vm<2>();
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        slot_barrier();
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int ks = j >> 2, x = (j >> 1) & 1, y = j & 1;
+            acc[2 + x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x][ks], b[y][ks], acc[2 + x][y], 0, 0, 0);
+            if ((j & 1) && j < 12) {
+                __builtin_amdgcn_sched_barrier(0);
+                xfer(j >> 1, st + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+        if (!wm) wait_vm<8>();
+        slot_barrier();
+    }
+    if (!wm) slot_barrier(); // group 1's last slot
+    wait_vm<0>();            // the repeated transfers of the last steps must not outlive this use of the LDS
+    __syncthreads();
+}
+
+// stage row of transfer q of a wavefront (q 0, 1: h0 of A, 6, 7: h1 of A, 2 .. 5: B, in rows of 8)
+__device__ __forceinline__ int pp_row(int q, int wave)
+{
+    return q >= 2 && q < 6 ? 256 + (wave + 8 * (q - 2)) * 8 : (q & 1) * 128 + (q >= 6 ? 64 : 0) + wave * 8;
+}
+
+// As gemm_nt, on 256 x 256 tiles.  512 threads, LDS 1 KB aligned; (kend - kbegin) a multiple of 64.
+template <class ARow, class BRow, class Epi>
+__device__ __forceinline__ void gemm_nt_pp(char *lds /* PpTile::LDS_BYTES */, const ARow &arow, const BRow &brow, Epi &epi,
+                                           int kbegin, int kend, int row0, int col0, int nrows, int ncols)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+    const int nsteps = (kend - kbegin) / 64;
+    if (nsteps > 0) {
+        const uint32_t lds0 = lds_address(lds);
+        const bf16_t *gp[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int lr = pp_row(q, wave) + (lane >> 3);
+            const int lc = (lane & 7) ^ nt_swz<64>(lr);
+            gp[q] = (lr < 256 ? arow(min(row0 + lr, nrows - 1)) : brow(min(col0 + lr - 256, ncols - 1))) + lc * 8 + kbegin;
+        }
+        auto xfer = [&](int q, int step) {
+            dma16_at(gp[q] + min(step, nsteps - 1) * 64, lds0 + (step & 1) * PpTile::STAGE_BYTES + pp_row(q, wave) * 128);
+        };
+        const int i = lane & 31, g = lane >> 5;
+        int fo[4]; // byte offset of this lane's fragment inside a block of 32 rows
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) fo[ks] = i * 128 + (((2 * ks + g) ^ nt_swz<64>(i)) << 4);
+        const int ab = wm * 128 * 128, bb = (256 + wn * 64) * 128;
+        auto fragA = [&](const char *sb, int half, int x, int ks) {
+            return *reinterpret_cast<const bf16x8 *>(sb + ab + (2 * half + x) * 4096 + fo[ks]);
+        };
+        auto fragB = [&](const char *sb, int y, int ks) { return *reinterpret_cast<const bf16x8 *>(sb + bb + y * 4096 + fo[ks]); };
+        pp_loop(lds, acc, nsteps, wm, xfer, [](int) {}, fragA, fragB);
+    }
+    tile_epilogue<PpTile>(acc, epi, wm, wn, lane, row0, col0, nrows, ncols);
+}
+
+// ---------------------------------------------------------------------------
 // Contractions over the token index: C[i][n] = sum_t A[t][i] * B[t][n], both operands row-major
 // over tokens.  A stage holds KT token rows of BM columns of A and BN columns of B as 64-column
 // panels ([token][64] bf16, 128 bytes per row).  The transposing LDS load hands a lane 4 values
@@ -549,6 +718,67 @@ __device__ __forceinline__ void gemm_tn(char *lds /* TL::LDS_BYTES, 1 KB aligned
         __syncthreads();
     }
     tile_epilogue<TL>(acc, epi, wm, wn, lane, row0, col0, nrows, ncols);
+}
+
+// As gemm_tn, on 256 x 256 tiles with 64 tokens per stage (panels of 64 columns: A's four, then B's four).  A wavefront
+// transfers the tokens 8 wave .. 8 wave + 7 of every panel, so atok / btok are asked once per step and lane: group =
+// wavefront.  They are called one slot before the step's first transfer.
+template <class ATok, class BTok, class Epi>
+__device__ __forceinline__ void gemm_tn_pp(char *lds /* PpTile::LDS_BYTES, 1 KB aligned */, const ATok &atok, const BTok &btok,
+                                           const void *zeros, Epi &epi, int nsteps, int row0, int col0, int a_ncols,
+                                           int b_ncols, int nrows, int ncols)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+    if (nsteps > 0) {
+        constexpr int PANEL = 64 * 128;
+        const uint32_t lds0 = lds_address(lds);
+        const int r8 = lane >> 3;
+        const int lc = ((lane & 7) ^ (2 * (r8 & 3))) * 8; // token (8 wave + r8) % 4 = r8 % 4
+        // panel of transfer q: h0 of A = panels 0, 2; h1 = 1, 3; B = 4 .. 7
+        auto panel = [](int q) { return q < 2 ? 2 * q : q < 6 ? 2 + q : 2 * (q - 6) + 1; };
+        int colo[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            colo[q] = panel(q) < 4 ? min(row0 + 64 * panel(q) + lc, a_ncols - 8) : min(col0 + 64 * (panel(q) - 4) + lc, b_ncols - 8);
+        const bf16_t *pa = nullptr, *pb = nullptr; // this lane's token rows of the step prepared last, the one xfer is called for
+        auto prepare = [&](int step) {
+            const int s2 = min(step, nsteps - 1); // past the end: repeat the last step, never used
+            pa = atok(s2, wave, r8);
+            pb = btok(s2, wave, r8);
+        };
+        auto xfer = [&](int q, int step) {
+            const bf16_t *p = panel(q) < 4 ? pa : pb;
+            dma16_at(p ? p + colo[q] : reinterpret_cast<const bf16_t *>(zeros),
+                     lds0 + (step & 1) * PpTile::STAGE_BYTES + panel(q) * PANEL + wave * 1024);
+        };
+        // fragment addresses as in gemm_tn; a 32-column block is the left or right half of a panel
+        const int G = lane >> 4, v4 = (lane & 15) >> 2, w4 = lane & 3;
+        const int trow = 8 * (G >> 1) + v4;
+        int fo[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = h * 32 + 16 * (G & 1) + 4 * w4;
+            fo[h] = trow * 128 + (((c >> 3) ^ (2 * v4)) << 4) + ((c & 4) << 1);
+        }
+        auto fragA = [&](const char *sb, int half, int x, int ks) {
+            const char *p = sb + (2 * wm + half) * PANEL + fo[x] + ks * 2048;
+            return tr_read2(p, p + 512);
+        };
+        auto fragB = [&](const char *sb, int y, int ks) {
+            const char *p = sb + (4 + wn) * PANEL + fo[y] + ks * 2048;
+            return tr_read2(p, p + 512);
+        };
+        pp_loop(lds, acc, nsteps, wm, xfer, prepare, fragA, fragB);
+    }
+    tile_epilogue<PpTile>(acc, epi, wm, wn, lane, row0, col0, nrows, ncols);
 }
 
 } // namespace pac
