@@ -281,6 +281,124 @@ template <typename TC, int KU> __global__ __launch_bounds__(256) void k_fwd_down
     else fwd_down_tile<TC, false, KU>(a, smem);
 }
 
+// ---------------------------------------------------------------------------
+// fp32 contractions with a narrow output (columns of the adapter width) and a long K: 16 rows x 16 NB columns per
+// workgroup, K dealt over eight wavefronts that meet in LDS.
+//
+// What bounds them: on 64 x 64 tiles a 4096 x 96 output is 128 workgroups of which each walks K = 768 step by step, one
+// wavefront per SIMD on half of the compute units, and waits for memory at every step (31.6 us, 0.15 of the fp32 matrix
+// rate).  Here there is no step: a wavefront reads both operands straight into 16x16x4 matrix operands (four consecutive K
+// values per lane and 16-byte load, the same lane-to-K assignment on both sides), one unit of 16 in K ahead, and the only
+// barrier is the one before the eight partial sums are added.  T5-Base-shaped: down-projection 17.6 us (it also mixes two cache-sized operands), its reverse
+// 26.5 -> 15.7 us (the matrix instructions alone take 3.9 us).
+// ---------------------------------------------------------------------------
+constexpr int kRowWaves = 8;
+
+// x = lam * b + (1 - lam) * s (MIX == false: lam * b) of one token row
+template <bool MIX> struct RowX {
+    const float *b, *s;
+    float lam;
+    struct Raw { f32x4 b, s; };
+    __device__ Raw load(int k) const
+    {
+        Raw r;
+        r.b = *reinterpret_cast<const f32x4 *>(b + k);
+        if (MIX) r.s = *reinterpret_cast<const f32x4 *>(s + k);
+        return r;
+    }
+    __device__ f32x4 value(const Raw &r) const
+    {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = MIX ? lam * r.b[e] + (1.f - lam) * r.s[e] : lam * r.b[e];
+        return v;
+    }
+};
+struct RowPlain {
+    const float *p;
+    struct Raw { f32x4 v; };
+    __device__ Raw load(int k) const { return Raw{*reinterpret_cast<const f32x4 *>(p + k)}; }
+    __device__ f32x4 value(const Raw &r) const { return r.v; }
+};
+
+// a: this lane's row (lane % 16 of the tile, clamped by the caller) at k = 0; B rows of length K, K a multiple of 16;
+// epi(row, col, value) for rows < nrows and columns < ncols
+template <int NB, class ARow, class Epi>
+__device__ __forceinline__ void rows16_gemm(float *red /* kRowWaves * NB * 256 floats */, const ARow &a, const float *B, int K,
+                                            int row0, int col0, int nrows, int ncols, const Epi &epi)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+    const float *bp[NB];
+#pragma unroll
+    for (int y = 0; y < NB; ++y) bp[y] = B + (int64_t)min(col0 + 16 * y + (lane & 15), ncols - 1) * K + 4 * g;
+    f32x4 acc[NB];
+#pragma unroll
+    for (int y = 0; y < NB; ++y) acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int units = K / 16;
+    const int u0 = units * wave / kRowWaves, u1 = units * (wave + 1) / kRowWaves;
+    if (u0 < u1) {
+        typename ARow::Raw ra = a.load(u0 * 16 + 4 * g);
+        f32x4 rb[NB];
+#pragma unroll
+        for (int y = 0; y < NB; ++y) rb[y] = *reinterpret_cast<const f32x4 *>(bp[y] + u0 * 16);
+        for (int u = u0; u < u1; ++u) {
+            const int kn = min(u + 1, u1 - 1) * 16; // past the end: the last unit again, never used
+            const typename ARow::Raw na = a.load(kn + 4 * g);
+            f32x4 nb[NB];
+#pragma unroll
+            for (int y = 0; y < NB; ++y) nb[y] = *reinterpret_cast<const f32x4 *>(bp[y] + kn);
+            const f32x4 av = a.value(ra);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int y = 0; y < NB; ++y) acc[y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], rb[y][e], acc[y], 0, 0, 0);
+            ra = na;
+#pragma unroll
+            for (int y = 0; y < NB; ++y) rb[y] = nb[y];
+        }
+    }
+    // register v of a lane holds row 4 (lane / 16) + v, column lane % 16 of its block
+#pragma unroll
+    for (int y = 0; y < NB; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((wave * NB + y) * 4 + v) * 64 + lane] = acc[y][v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < NB * 256; e += 64 * kRowWaves) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kRowWaves; ++w) sum += red[w * NB * 256 + e];
+        const int ln = e & 63;
+        const int row = row0 + 4 * (ln >> 4) + ((e >> 6) & 3), col = col0 + 16 * (e >> 8) + (ln & 15);
+        if (row < nrows && col < ncols) epi(row, col, sum);
+    }
+}
+
+// Column blocks of 16 per workgroup: at most eight, and fewer where the row tiles alone would leave compute units idle
+// (512 rows: 32 tiles for 256 units).
+static int rows16_blocks(int M, int ncols)
+{
+    int chunks = cdiv(ncols, 128);
+    const int want = cdiv(256, cdiv(M, 16));
+    if (chunks < want) chunks = want;
+    return 2 * cdiv(cdiv(ncols, 32), chunks);
+}
+
+template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_fwd_down16(FwdDownArgs<float> a)
+{
+    __shared__ float red[kRowWaves * NB * 256];
+    const int row0 = blockIdx.x * 16, row = min(row0 + (int)(threadIdx.x & 15), a.map.M - 1);
+    const float *b = a.cache + a.map.rowoff[row] + (int64_t)a.layer * a.map.rowstride[row];
+    auto epi = [&](int rr, int col, float v) {
+        const float u = v + a.c_down[col];
+        a.pre[(int64_t)rr * a.r + col] = u;
+        a.h[(int64_t)rr * a.r + col] = gelu_f(u);
+    };
+    if (a.s_prev)
+        rows16_gemm<NB>(red, RowX<true>{b, a.s_prev + (int64_t)row * a.d, *a.lam}, a.WdT, a.d, row0, blockIdx.y * 16 * NB, a.map.M, a.r, epi);
+    else
+        rows16_gemm<NB>(red, RowX<false>{b, nullptr, *a.lam}, a.WdT, a.d, row0, blockIdx.y * 16 * NB, a.map.M, a.r, epi);
+}
+
 template <typename TC> struct FwdUpArgs {
     const TC *h;    // [M][r]
     const TC *WuT;  // [d][r]
@@ -323,42 +441,56 @@ template <typename TC, int KU> __global__ __launch_bounds__(256) void k_fwd_up(F
     gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.r, blockIdx.x * 64, blockIdx.y * 64, a.M, a.d);
 }
 
-// pooled[s][j] = mean_t ( b_L[t][j] + s_L[t][j] )
+// pooled[s][j] = mean_t ( b_L[t][j] + s_L[t][j] ).  64 columns per workgroup, tokens dealt over its 16 wavefronts: with one
+// thread per column over all tokens the launch took 45 us at 32 samples of 128 tokens (6.1 us now).
 template <typename TC>
-__global__ __launch_bounds__(256) void k_pool(const TC *__restrict__ cache, RowMap map, int last_layer, int d,
-                                              const float *__restrict__ s_last, const int32_t *samp_start,
-                                              const int32_t *samp_len, float *__restrict__ pooled)
+__global__ __launch_bounds__(1024) void k_pool(const TC *__restrict__ cache, RowMap map, int last_layer, int d,
+                                               const float *__restrict__ s_last, const int32_t *samp_start,
+                                               const int32_t *samp_len, float *__restrict__ pooled)
 {
-    const int s = blockIdx.x, j = blockIdx.y * 256 + threadIdx.x;
-    if (j >= d) return;
-    const int m0 = samp_start[s], len = samp_len[s];
+    __shared__ float red[16][64];
+    const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.y * 64 + lane;
+    const int m0 = samp_start[s], len = samp_len[s], jc = min(j, d - 1);
+    // a sample's rows of one layer are contiguous
+    const TC *b = cache + map.rowoff[m0] + (int64_t)last_layer * map.rowstride[m0] + jc;
+    const float *sl = s_last + (int64_t)m0 * d + jc;
     float acc = 0.f;
-    for (int t = 0; t < len; ++t) {
-        const int m = m0 + t;
-        const TC *b = cache + map.rowoff[m] + (int64_t)last_layer * map.rowstride[m];
-        acc += to_f32(b[j]) + s_last[(int64_t)m * d + j];
+#pragma unroll 4
+    for (int t = wave; t < len; t += 16) acc += to_f32(b[(int64_t)t * d]) + sl[(int64_t)t * d];
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && j < d) {
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) tot += red[w][lane];
+        pooled[(int64_t)s * d + j] = tot / (float)len;
     }
-    pooled[(int64_t)s * d + j] = acc / (float)len;
 }
 
-// logits, loss, dz = (softmax - onehot)/B.  One workgroup.
-__global__ __launch_bounds__(256) void k_head(const float *__restrict__ pooled, const float *__restrict__ Wcls,
-                                              const float *__restrict__ ccls, const int32_t *__restrict__ labels,
-                                              int B, int d, int C, float *__restrict__ logits_ws,
-                                              float *__restrict__ logits_out, float *__restrict__ dz,
+// z[s][c] = pooled_s . W_cls[:, c] + c_cls[c], one wavefront each
+__global__ __launch_bounds__(256) void k_head_z(const float *__restrict__ pooled, const float *__restrict__ Wcls,
+                                                const float *__restrict__ ccls, int B, int d, int C, float *__restrict__ z)
+{
+    const int pair = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (pair >= B * C) return;
+    const int s = pair / C, c = pair % C;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int j = lane; j < d; j += 64) acc += pooled[(int64_t)s * d + j] * Wcls[(int64_t)j * C + c];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    if (lane == 0) z[pair] = acc + ccls[c];
+}
+
+// loss and dz = (softmax - onehot) / B from the logits.  One workgroup (it also formed the logits once: 80 us at 32
+// samples, three classes and d = 768, 9.6 us as two launches).
+__global__ __launch_bounds__(256) void k_head(const float *__restrict__ logits_ws, const int32_t *__restrict__ labels,
+                                              int B, int C, float *__restrict__ logits_out, float *__restrict__ dz,
                                               float *__restrict__ loss_out)
 {
     __shared__ float z[kMaxBatch * kMaxClasses];
     __shared__ float red[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int pair = wave; pair < B * C; pair += 4) {
-        const int s = pair / C, c = pair % C;
-        float acc = 0.f;
-        for (int j = lane; j < d; j += 64) acc += pooled[(int64_t)s * d + j] * Wcls[(int64_t)j * C + c];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-        if (lane == 0) z[pair] = acc + ccls[c];
-    }
+    for (int i = threadIdx.x; i < B * C; i += 256) z[i] = logits_ws[i];
     __syncthreads();
     float my = 0.f;
     if ((int)threadIdx.x < B) {
@@ -372,7 +504,6 @@ __global__ __launch_bounds__(256) void k_head(const float *__restrict__ pooled, 
         my = (y >= 0 && y < C) ? lse - z[s * C + y] : NAN;
         for (int c = 0; c < C; ++c) {
             const float zz = z[s * C + c];
-            logits_ws[s * C + c] = zz;
             if (logits_out) logits_out[s * C + c] = zz;
             dz[s * C + c] = (expf(zz - lse) - (c == y ? 1.f : 0.f)) / (float)B;
         }
@@ -463,6 +594,17 @@ template <typename TC, int KU> __global__ __launch_bounds__(256) void k_bwd_dpre
     bl.src = a.Wu; bl.ld = a.d; bl.nrows = a.r;
     EpiDpre<TC> epi{a.pre, a.dpre, a.r};
     gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.d, blockIdx.x * 64, blockIdx.y * 64, a.M, a.r);
+}
+
+template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_bwd_dpre16(BwdDpreArgs<float> a)
+{
+    __shared__ float red[kRowWaves * NB * 256];
+    const int row0 = blockIdx.x * 16, row = min(row0 + (int)(threadIdx.x & 15), a.M - 1);
+    rows16_gemm<NB>(red, RowPlain{a.ds + (int64_t)row * a.d}, a.Wu, a.d, row0, blockIdx.y * 16 * NB, a.M, a.r,
+                    [&](int rr, int col, float v) {
+                        const int64_t o = (int64_t)rr * a.r + col;
+                        a.dpre[o] = v * gelu_grad_f(a.pre[o]);
+                    });
 }
 
 // Top layer: ds_L is the same vector for every token of a sample (dp_s / len_s), so
@@ -842,6 +984,14 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
                        WdT, Wu, WuT);
 
     const dim3 g_rows_r(cdiv(M, 64), cdiv(r, 64)), g_rows_d(cdiv(M, 64), cdiv(d, 64));
+    const int nb16 = rows16_blocks(M, r);
+    const dim3 g_rows16(cdiv(M, 16), cdiv(r, 16 * nb16));
+    auto with_blocks = [&](auto f) {
+        if (nb16 <= 2) f(std::integral_constant<int, 2>());
+        else if (nb16 <= 4) f(std::integral_constant<int, 4>());
+        else if (nb16 <= 6) f(std::integral_constant<int, 6>());
+        else f(std::integral_constant<int, 8>());
+    };
     // long K steps where the contraction length allows them
     const bool wide_d = d % Stage<TC, 4>::BK == 0, wide_r = r % Stage<TC, 4>::BK == 0;
     for (int l = 0; l < L; ++l) {
@@ -849,19 +999,25 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
         const float *s_prev = l == 0 ? nullptr : s_all + (int64_t)(l - 1) * Md;
         FwdDownArgs<TC> fa{cache, map, l, d, r, s_prev, WdT + (int64_t)l * dr, pl + dr, pl + PL - 1,
                            pre_all + (int64_t)l * Mr, h_all + (int64_t)l * Mr};
-        if (wide_d) PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down<TC, 4>), g_rows_r, dim3(256), 0, st, fa);
+        if constexpr (std::is_same<TC, float>::value) {
+            with_blocks([&](auto nb) {
+                PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, fa);
+            });
+        } else if (wide_d) PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down<TC, 4>), g_rows_r, dim3(256), 0, st, fa);
         else PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down<TC, 1>), g_rows_r, dim3(256), 0, st, fa);
         FwdUpArgs<TC> fu{h_all + (int64_t)l * Mr, WuT + (int64_t)l * dr, pl + 2 * dr + r, s_prev,
                          s_all + (int64_t)l * Md, M, d, r};
         if (wide_r) PAC_LAUNCH(prof, st, KC_FWD_UP, (k_fwd_up<TC, 4>), g_rows_d, dim3(256), 0, st, fu);
         else PAC_LAUNCH(prof, st, KC_FWD_UP, (k_fwd_up<TC, 1>), g_rows_d, dim3(256), 0, st, fu);
     }
-    PAC_LAUNCH(prof, st, KC_POOL, (k_pool<TC>), dim3(meta.B, cdiv(d, 256)), dim3(256), 0, st, cache, map, L - 1, d,
+    PAC_LAUNCH(prof, st, KC_POOL, (k_pool<TC>), dim3(meta.B, cdiv(d, 64)), dim3(1024), 0, st, cache, map, L - 1, d,
                        s_all + (int64_t)(L - 1) * Md, samp_start, samp_len, pooled);
     const float *Wcls = params + (int64_t)L * PL;
     const float *ccls = Wcls + (int64_t)d * D.C;
-    PAC_LAUNCH(prof, st, KC_HEAD, k_head, dim3(1), dim3(256), 0, st, pooled, Wcls, ccls, io.labels, meta.B, d, D.C, logits,
-                       io.logits_out, dz, io.loss_out);
+    PAC_LAUNCH(prof, st, KC_HEAD, k_head_z, dim3(cdiv((int64_t)meta.B * D.C, 4)), dim3(256), 0, st, pooled, Wcls, ccls, meta.B, d,
+                       D.C, logits);
+    PAC_LAUNCH(prof, st, KC_HEAD, k_head, dim3(1), dim3(256), 0, st, logits, io.labels, meta.B, D.C, io.logits_out, dz,
+                       io.loss_out);
     PAC_HIP_TRY(hipGetLastError());
     if (!io.grads) return hipSuccess;
 
@@ -887,7 +1043,11 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
                        pre_all + (int64_t)l * Mr, rowsamp, M, r, dpre);
         } else {
             BwdDpreArgs<TC> ba{ds, Wu + (int64_t)l * dr, pre_all + (int64_t)l * Mr, dpre, M, d, r};
-            if (wide_d) PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 4>), g_rows_r, dim3(256), 0, st, ba);
+            if constexpr (std::is_same<TC, float>::value) {
+                with_blocks([&](auto nb) {
+                    PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, ba);
+                });
+            } else if (wide_d) PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 4>), g_rows_r, dim3(256), 0, st, ba);
             else PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 1>), g_rows_r, dim3(256), 0, st, ba);
         }
         BwdWgradArgs<TC> wa{cache, map, l, d, r, s_prev, pl + PL - 1, h_all + (int64_t)l * Mr, ds, dpre, part, PL,
