@@ -88,14 +88,19 @@ __global__ __launch_bounds__(256) void k_dequant(const int8_t *__restrict__ code
 }
 
 // ---------------------------------------------------------------------------
-// linear layer on the stored form.  128 x 128 output tile per workgroup, four wavefronts of 2 x 2 accumulators of
-// 32 x 32 each; K in steps of 32 staged through two LDS buffers (x as it is, the codes converted to bf16, which holds
+// linear layer on the stored form.  64 WT x 64 WT output tile per workgroup, four wavefronts of WT x WT accumulators of
+// 32 x 32 each; K in steps of BK staged through two LDS buffers (x as it is, the codes converted to bf16, which holds
 // every code exactly).  A quantisation block's partial sum is kept apart (its first matrix instruction starts from
 // zero) and enters the total multiplied by 1 / c of that block and column: in the 32 x 32 accumulator layout all 16
 // values of a lane belong to one output column.
+// What bounds it: the vector units, which convert the codes and do one multiply-add per output value and block, and the
+// barrier of each step.  Hence the launch bound of two workgroups per compute unit: it holds the kernel to 256
+// registers, all of them vector registers, where the compiler otherwise kept one set of sums in accumulation registers
+// and moved each value out (and back) at every block end.  4096 x 4096 x 4096, 8 bits: blocks of 64 265 -> 209 us,
+// of 256 201 -> 170 us, of 32 317 -> 277 us (BK = 32), the constant of the next block requested a block early.
 // ---------------------------------------------------------------------------
-constexpr int kDqPitch = 32 * 2 + 16; // bytes per LDS row of a K step
-constexpr int kDqTile = 128;
+// bytes per LDS row of a K step: 20 (36) words, so that the 16-byte reads of 16 neighbouring rows meet every bank once
+template <int BK> constexpr int kDqPitch = BK * 2 + 16;
 
 struct DqArgs {
     const bf16_t *x;
@@ -117,37 +122,38 @@ __device__ __forceinline__ uint16_t dq_bf16_rne(float f)
     return (uint16_t)(u >> 16);
 }
 
-template <int BITS> __global__ __launch_bounds__(256) void k_dq_linear(DqArgs a)
+template <int BITS, int BK, int WT> __global__ __launch_bounds__(256, 2) void k_dq_linear(DqArgs a)
 {
-    __shared__ __attribute__((aligned(16))) char As[2][kDqTile * kDqPitch];
-    __shared__ __attribute__((aligned(16))) char Bs[2][kDqTile * kDqPitch];
+    constexpr int TILE = 64 * WT, PITCH = kDqPitch<BK>, PIECES = TILE * BK / 8 / 256, CPR = BK / 8;
+    __shared__ __attribute__((aligned(16))) char As[2][TILE * PITCH];
+    __shared__ __attribute__((aligned(16))) char Bs[2][TILE * PITCH];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int i = lane & 31, g = lane >> 5;
-    const int m0 = blockIdx.y * kDqTile, n0 = blockIdx.x * kDqTile;
-    const int K = a.K, nsteps = K / 32, bpr = K / a.block, steps_per_block = a.block / 32;
-    // this thread's share of a K step: 16 bytes of two x rows, 8 codes of two W rows (rows lrow and lrow + 64)
-    const int lrow = t >> 2, lch = t & 3;
-    const bf16_t *xp[2];
-    const int8_t *wp[2];
+    const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
+    const int K = a.K, nsteps = K / BK, bpr = K / a.block, steps_per_block = a.block / BK;
+    // this thread's share of a K step: 16 bytes of PIECES x rows, 8 codes of PIECES W rows (256 / CPR rows apart)
+    const int lrow = t / CPR, lch = t % CPR;
+    const bf16_t *xp[PIECES];
+    const int8_t *wp[PIECES];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int xm = min(m0 + lrow + 64 * h, a.M - 1), wr = min(n0 + lrow + 64 * h, a.N - 1);
+    for (int h = 0; h < PIECES; ++h) {
+        const int xm = min(m0 + lrow + 256 / CPR * h, a.M - 1), wr = min(n0 + lrow + 256 / CPR * h, a.N - 1);
         xp[h] = a.x + (int64_t)xm * K + lch * 8;
         wp[h] = a.codes + (BITS == 8 ? (int64_t)wr * K + lch * 8 : ((int64_t)wr * K + lch * 8) / 2);
     }
-    auto load = [&](int s, u32x4 (&av)[2], uint64_t (&bv)[2]) {
+    auto load = [&](int s, u32x4 (&av)[PIECES], uint64_t (&bv)[PIECES]) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            av[h] = *reinterpret_cast<const u32x4 *>(xp[h] + s * 32);
-            if (BITS == 8) bv[h] = *reinterpret_cast<const uint64_t *>(wp[h] + s * 32);
-            else bv[h] = *reinterpret_cast<const uint32_t *>(wp[h] + s * 16);
+        for (int h = 0; h < PIECES; ++h) {
+            av[h] = *reinterpret_cast<const u32x4 *>(xp[h] + s * BK);
+            if (BITS == 8) bv[h] = *reinterpret_cast<const uint64_t *>(wp[h] + s * BK);
+            else bv[h] = *reinterpret_cast<const uint32_t *>(wp[h] + s * (BK / 2));
         }
     };
-    auto store = [&](int buf, const u32x4 (&av)[2], const uint64_t (&bv)[2]) {
+    auto store = [&](int buf, const u32x4 (&av)[PIECES], const uint64_t (&bv)[PIECES]) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            *reinterpret_cast<u32x4 *>(As[buf] + (lrow + 64 * h) * kDqPitch + lch * 16) = av[h];
+        for (int h = 0; h < PIECES; ++h) {
+            *reinterpret_cast<u32x4 *>(As[buf] + (lrow + 256 / CPR * h) * PITCH + lch * 16) = av[h];
             // a code is an integer of at most 8 bits: its fp32 image has zero low mantissa bits, so the upper half of
             // that image IS its bf16 value (no rounding happens); two codes per 32-bit word
             u32x4 w;
@@ -165,33 +171,37 @@ template <int BITS> __global__ __launch_bounds__(256) void k_dq_linear(DqArgs a)
                 }
                 w[e2] = (__float_as_uint((float)q0) >> 16) | (__float_as_uint((float)q1) & 0xffff0000u);
             }
-            *reinterpret_cast<u32x4 *>(Bs[buf] + (lrow + 64 * h) * kDqPitch + lch * 16) = w;
+            *reinterpret_cast<u32x4 *>(Bs[buf] + (lrow + 256 / CPR * h) * PITCH + lch * 16) = w;
         }
     };
-    f32x16 tot[2][2], part[2][2];
+    f32x16 tot[WT][WT], part[WT][WT];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WT; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
+        for (int y = 0; y < WT; ++y)
 #pragma unroll
             for (int v = 0; v < 16; ++v) tot[x][y][v] = part[x][y][v] = 0.f;
-    const float *crow[2];
+    const float *crow[WT];
+    float cnext[WT]; // the coming block's constant, on its way since the block before began
 #pragma unroll
-    for (int y = 0; y < 2; ++y) crow[y] = a.consts + (int64_t)min(n0 + wn * 64 + y * 32 + i, a.N - 1) * bpr;
+    for (int y = 0; y < WT; ++y) {
+        crow[y] = a.consts + (int64_t)min(n0 + wn * (32 * WT) + y * 32 + i, a.N - 1) * bpr;
+        cnext[y] = crow[y][0];
+    }
     auto compute = [&](int buf, bool first) {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 fa[2], fb[2];
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            bf16x8 fa[WT], fb[WT];
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
-                fa[x] = *reinterpret_cast<const bf16x8 *>(As[buf] + (wm * 64 + x * 32 + i) * kDqPitch + ks * 32 + g * 16);
+            for (int x = 0; x < WT; ++x)
+                fa[x] = *reinterpret_cast<const bf16x8 *>(As[buf] + (wm * (32 * WT) + x * 32 + i) * PITCH + ks * 32 + g * 16);
 #pragma unroll
-            for (int y = 0; y < 2; ++y)
-                fb[y] = *reinterpret_cast<const bf16x8 *>(Bs[buf] + (wn * 64 + y * 32 + i) * kDqPitch + ks * 32 + g * 16);
+            for (int y = 0; y < WT; ++y)
+                fb[y] = *reinterpret_cast<const bf16x8 *>(Bs[buf] + (wn * (32 * WT) + y * 32 + i) * PITCH + ks * 32 + g * 16);
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
+            for (int x = 0; x < WT; ++x)
 #pragma unroll
-                for (int y = 0; y < 2; ++y) {
+                for (int y = 0; y < WT; ++y) {
                     f32x16 c0 = part[x][y];
                     if (ks == 0 && first) {
 #pragma unroll
@@ -201,25 +211,33 @@ template <int BITS> __global__ __launch_bounds__(256) void k_dq_linear(DqArgs a)
                 }
         }
     };
-    u32x4 av[2];
-    uint64_t bv[2];
+    u32x4 av[PIECES];
+    uint64_t bv[PIECES];
     load(0, av, bv);
     store(0, av, bv);
     __syncthreads();
-    int in_block = 0;
+    int in_block = 0, blk = 0;
+    float cnow[WT];
     for (int s = 0; s < nsteps; ++s) {
         const int buf = s & 1;
+        if (in_block == 0) {
+#pragma unroll
+            for (int y = 0; y < WT; ++y) {
+                cnow[y] = cnext[y];
+                cnext[y] = crow[y][min(blk + 1, bpr - 1)];
+            }
+        }
         if (s + 1 < nsteps) load(s + 1, av, bv);
         if (in_block == 0) compute(buf, true);
         else compute(buf, false);
         if (++in_block == steps_per_block) {
             in_block = 0;
-            const int blk = s / steps_per_block;
+            ++blk;
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                const float inv = __fdiv_rn(1.f, crow[y][blk]);
+            for (int y = 0; y < WT; ++y) {
+                const float inv = __fdiv_rn(1.f, cnow[y]);
 #pragma unroll
-                for (int x = 0; x < 2; ++x)
+                for (int x = 0; x < WT; ++x)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) tot[x][y][v] += part[x][y][v] * inv;
             }
@@ -228,14 +246,14 @@ template <int BITS> __global__ __launch_bounds__(256) void k_dq_linear(DqArgs a)
         __syncthreads();
     }
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-        const int n = n0 + wn * 64 + y * 32 + i;
+    for (int y = 0; y < WT; ++y) {
+        const int n = n0 + wn * (32 * WT) + y * 32 + i;
         if (n >= a.N) continue;
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < WT; ++x)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm * 64 + x * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                const int m = m0 + wm * (32 * WT) + x * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
                 if (m >= a.M) continue;
                 if (a.y) {
                     a.y[(int64_t)m * a.N + n] = tot[x][y][v];
@@ -259,6 +277,29 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
     return PAC_OK;
 }
 
+// More tiles of 128 x 128 than compute units: two share a unit and hide each other's waits.  Up to one per unit, tiles of
+// 64 x 64 (four times as many) are as fast or faster: K = 4096, blocks of 64, 256 tiles 72.5 against 74.5 us, 192 tiles
+// 57.4 / 73.4, 64 tiles 49 / 72, one tile row 37 / 73; beyond, 320 tiles 110.6 against 89.8 us, 1024 tiles 287 / 211.
+constexpr int kDqWideTiles = 257;
+
+template <int BITS, int BK, int WT> static void dq_launch_as(const DqArgs &a, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.N + 64 * WT - 1) / (64 * WT)), (unsigned)((a.M + 64 * WT - 1) / (64 * WT)));
+    hipLaunchKernelGGL((k_dq_linear<BITS, BK, WT>), grid, dim3(256), 0, st, a);
+}
+
+template <int WT> static void dq_launch(const DqArgs &a, int bits, hipStream_t st)
+{
+    // a K step never spans two blocks; blocks that are an odd multiple of 32 keep steps of 32
+    if (a.block % 64 == 0) {
+        if (bits == 8) dq_launch_as<8, 64, WT>(a, st);
+        else dq_launch_as<4, 64, WT>(a, st);
+    } else {
+        if (bits == 8) dq_launch_as<8, 32, WT>(a, st);
+        else dq_launch_as<4, 32, WT>(a, st);
+    }
+}
+
 hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, const float *consts, int N, int block,
                             int bits, float *y, void *cache, int cache_f32, int n_max, int layer, const BatchMeta *meta,
                             hipStream_t st)
@@ -267,9 +308,9 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     a.x = static_cast<const bf16_t *>(x); a.M = M; a.K = K; a.N = N; a.block = block; a.codes = codes; a.consts = consts;
     a.y = y; a.cache = cache; a.cache_f32 = cache_f32; a.n_max = n_max; a.layer = layer;
     if (meta) a.meta = *meta;
-    const dim3 grid((unsigned)((N + kDqTile - 1) / kDqTile), (unsigned)((M + kDqTile - 1) / kDqTile));
-    if (bits == 8) hipLaunchKernelGGL(k_dq_linear<8>, grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(k_dq_linear<4>, grid, dim3(256), 0, st, a);
+    const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
+    if (tiles128 >= kDqWideTiles) dq_launch<2>(a, bits, st);
+    else dq_launch<1>(a, bits, st);
     return hipGetLastError();
 }
 

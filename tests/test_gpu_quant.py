@@ -56,6 +56,18 @@ def test_quant_and_dequant_bit_exact(n, block, bits):
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(70, 128, 96, 64), (5, 64, 33, 32), (257, 768, 200, 128), (64, 1024, 64, 1024)])
 def test_linear_layer_against_oracle(M, K, N, block, bits):
+    check_linear_layer(M, K, N, block, bits)
+
+
+# 128 x 128 tiles: 272 of them, ragged at both edges, with blocks of one and three K steps of 32 and of one of 64; the
+# last has 256 and takes the small tiles, blocks of two K steps of 64
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block", [(2049, 64, 2001, 32), (2100, 192, 2033, 96), (2047, 192, 2100, 64), (2048, 256, 2048, 128)])
+def test_linear_layer_on_wide_and_narrow_tiles(M, K, N, block, bits):
+    check_linear_layer(M, K, N, block, bits)
+
+
+def check_linear_layer(M, K, N, block, bits):
     rng = np.random.default_rng(M + K + bits)
     W = weights(rng, N, K)
     x16 = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).to(torch.bfloat16)
