@@ -2082,7 +2082,8 @@ struct EpiF {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float F = acc[v] + cu[v] * csv;
-            store_at(gWd + (int64_t)epi_step(v) * r, at, lam * E[v] + (1.f - lam) * F);
+            // (the fused multiply-add written out: which of the two products it takes decides the last bit)
+            store_at(gWd + (int64_t)epi_step(v) * r, at, __builtin_fmaf(1.f - lam, F, lam * E[v]));
             dlam += (E[v] - F) * W[v];
         }
     }
@@ -2128,6 +2129,19 @@ template <int CC> __device__ __forceinline__ void zrows(const float *Z, const Ch
     }
 }
 
+// Lanes 2 i (hf 0) and 2 i + 1 (hf 1) hold chunk 2 q + hf of a row's first half (x) and of its second (y); afterwards lane
+// hf holds chunks 2 q (x) and 2 q + 1 (y) of half hf.  All 64 lanes take part.
+__device__ __forceinline__ void swap_halves(u32x4 &x, u32x4 &y, int hf)
+{
+    const u32x4 a = x, b = y; // (selected as values: a choice between the references puts the arrays behind them in memory)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t got = __builtin_amdgcn_mov_dpp((int)(hf ? a[e] : b[e]), 0xb1 /* lane ^ 1 */, 0xf, 0xf, true);
+        x[e] = hf ? got : a[e];
+        y[e] = hf ? b[e] : got;
+    }
+}
+
 constexpr int kPostVecLds = 128 * 4 + 128 * kMaxClasses * 4 + kMaxBatch * kMaxClasses * 4;
 // The rest of the gradients: block vb of nb_vec, four wavefronts; NH threads share one r-wide row; the column sums and Z are
 // staged in LDS where lds_bytes allow it.
@@ -2150,15 +2164,27 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
         const bool act = jj < jpb && j < d;
         const int rh = r / NH; // a multiple of 8
         const float *Wc = a.params + (int64_t)L * a.PL;
-        // this thread's two row segments, requested before anything else is waited for
+        // this thread's two row segments (chunks of 16 bytes), requested before anything else is waited for
         constexpr int kMaxChunks = 8; // r / NH <= 64
         u32x4 wv[kMaxChunks], uv[kMaxChunks];
-        {
-            // the NH threads of a row take its 16-byte chunks in turn: neighbouring lanes read neighbouring chunks
-            const int64_t row = act ? (int64_t)j * Lr + (int64_t)k * r + hf * 8 : 0;
+        if constexpr (NH == 2) {
+            // Neighbouring lanes request neighbouring chunks (r = 128, 24 layers, d = 1024: the launch 49.6 us; with every
+            // lane on its own half of the row 51.4), then exchange them: a lane sums its own half in order.  Slots
+            // q and q + 1 request chunk q + hf of the first and of the second half.
+#pragma unroll
+            for (int q = 0; q < kMaxChunks; q += 2) {
+                const int64_t at = act && q * 8 < rh ? (int64_t)j * Lr + (int64_t)k * r + (q + hf) * 8 : 0;
+                const int64_t at2 = act && q * 8 < rh ? at + rh : 0;
+                wv[q] = *reinterpret_cast<const u32x4 *>(a.Wds + at);
+                uv[q] = *reinterpret_cast<const u32x4 *>(a.WuTs + at);
+                wv[q + 1] = *reinterpret_cast<const u32x4 *>(a.Wds + at2);
+                uv[q + 1] = *reinterpret_cast<const u32x4 *>(a.WuTs + at2);
+            }
+        } else {
+            const int64_t row = act ? (int64_t)j * Lr + (int64_t)k * r + hf * rh : 0;
 #pragma unroll
             for (int q = 0; q < kMaxChunks; ++q) {
-                const int qq = q * 8 < rh ? q * 8 * NH : 0;
+                const int qq = q * 8 < rh ? q * 8 : 0;
                 wv[q] = *reinterpret_cast<const u32x4 *>(a.Wds + row + qq);
                 uv[q] = *reinterpret_cast<const u32x4 *>(a.WuTs + row + qq);
             }
@@ -2192,8 +2218,15 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
         const float lamk = a.params[(int64_t)k * a.PL + a.PL - 1];
         __syncthreads();
         {
-            const float *csk = (staged ? stage : a.cs) + (int64_t)k * r + hf * 8;
-            const float *Zk = (staged ? stage + Lr : a.Z) + ((int64_t)k * r + hf * 8) * C;
+            const float *csk = (staged ? stage : a.cs) + (int64_t)k * r + hf * rh;
+            const float *Zk = (staged ? stage + Lr : a.Z) + ((int64_t)k * r + hf * rh) * C;
+            if constexpr (NH == 2) {
+#pragma unroll
+                for (int q = 0; q < kMaxChunks; q += 2) {
+                    swap_halves(wv[q], wv[q + 1], hf);
+                    swap_halves(uv[q], uv[q + 1], hf);
+                }
+            }
             float acc = 0.f;
             float wz[kMaxClasses];
 #pragma unroll
@@ -2206,24 +2239,24 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
                         __builtin_memcpy(&w8, &wv[q], 16);
                         __builtin_memcpy(&u8, &uv[q], 16);
                         // 16-byte reads of the column sums (both sides are 16-byte aligned: rh % 8 == 0)
-                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(csk + q * 8 * NH);
-                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(csk + q * 8 * NH + 4);
+                        const f32x4 c0 = *reinterpret_cast<const f32x4 *>(csk + q * 8);
+                        const f32x4 c1 = *reinterpret_cast<const f32x4 *>(csk + q * 8 + 4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             acc += c0[e] * to_f32(w8.e[e]);
                             acc += c1[e] * to_f32(w8.e[4 + e]);
                         }
                         // Z of these 8 rows: 8 C consecutive floats, read as 2 C 16-byte pieces
-                        if (C == 3) zrows<3>(Zk + (int64_t)q * 8 * NH * 3, u8, wz);
-                        else if (C == 4) zrows<4>(Zk + (int64_t)q * 8 * NH * 4, u8, wz);
-                        else if (C == 2) zrows<2>(Zk + (int64_t)q * 8 * NH * 2, u8, wz);
+                        if (C == 3) zrows<3>(Zk + (int64_t)q * 8 * 3, u8, wz);
+                        else if (C == 4) zrows<4>(Zk + (int64_t)q * 8 * 4, u8, wz);
+                        else if (C == 2) zrows<2>(Zk + (int64_t)q * 8 * 2, u8, wz);
                         else {
 #pragma unroll
                             for (int e = 0; e < 8; ++e) {
                                 const float u = to_f32(u8.e[e]);
 #pragma unroll
                                 for (int c = 0; c < kMaxClasses; ++c)
-                                    if (c < C) wz[c] += u * Zk[(int64_t)(q * 8 * NH + e) * C + c];
+                                    if (c < C) wz[c] += u * Zk[(int64_t)(q * 8 + e) * C + c];
                             }
                         }
                     }

@@ -1,6 +1,9 @@
 """The branches of the launch rules that the parity cases' own shapes do not reach, at their edges."""
+import hashlib
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2408_10746_amd import inputs
 from paper_2408_10746_amd.inputs import Workload
@@ -40,3 +43,29 @@ def test_fp32_contractions(w):
     sess = make_session(w, lens=lens)
     sess.cache_fill(ids, acts, lens)
     check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
+
+
+# Every sum behind a gradient has a fixed order, and a launch rule or a faster load is no reason for other results: SHA-1 of
+# the gradients' bits.  The rows of the vector gradients: two threads each with 2, 6 and 8 chunks of 16 bytes, four with 5,
+# eight with 5.
+GRADIENT_BITS = [
+    (Workload("v1", L=3, d=96, n_max=40, B=3, r=32, C=3, N=3, cache_dtype="bf16", len_lo=9), "bf07fed9679412bf56da923467881f94334387db"),
+    (Workload("v2", L=5, d=160, n_max=50, B=4, r=96, C=4, N=4, cache_dtype="bf16", len_lo=17), "fcc7a8818c9045ccd5ce0796d3e563ec6c8a488b"),
+    (Workload("v3", L=4, d=128, n_max=33, B=6, r=128, C=5, N=6, cache_dtype="bf16", len_lo=30), "cfee8560e57df98e45a329d77ae95239dfc47066"),
+    (Workload("v4", L=6, d=192, n_max=70, B=3, r=160, C=2, N=3, cache_dtype="bf16", len_lo=20), "b65bb0db09c5898d574722af252de0d5bd5a0335"),
+    (Workload("v5", L=3, d=160, n_max=45, B=4, r=320, C=3, N=4, cache_dtype="bf16", len_lo=11), "ea5613cd8f4175923a991598be845cc257956889"),
+]
+
+
+def gradients(w):
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    sess = make_session(w, lens=lens)
+    sess.cache_fill(ids, inputs.batch_acts(w, ids), lens)
+    sess.set_params(inputs.random_params(w, up_scale=0.3))
+    sess.loss_grad(ids, torch.from_numpy(inputs.labels(w)[ids]).to(sess.dev))
+    return sess.grads.cpu().numpy()
+
+
+@pytest.mark.parametrize("w,sha1", GRADIENT_BITS, ids=[w.name for w, _ in GRADIENT_BITS])
+def test_gradients_keep_their_bits(w, sha1):
+    assert hashlib.sha1(gradients(w).tobytes()).hexdigest() == sha1
