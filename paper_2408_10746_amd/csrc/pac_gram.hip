@@ -2722,20 +2722,20 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         pa.grads = io.grads; pa.dlam_part = dlam_part;
         pa.slots = cdiv(d, kFRows) * cdiv(r, kFCols);
         {
-            // post_vec_wide goes with the launch of the partial sums where there is one: it needs nothing of it
             const int nb_GG = L > 1 && !a.gg_direct ? (Lr / 32) * (Lr / 32) : 0;
             const int64_t e_elems = a.se > 1 ? (int64_t)L * d * r : 0;
             const int nb_sum = nb_GG + cdiv(e_elems / 4, 256);
             float *E = (float *)(ws + W.g_E);
-            if (!vec_wide) {
-                if (nb_sum > 0)
-                    PAC_LAUNCH(prof, st, KC_G_GGSUM, k_ggsum<false>, dim3(nb_sum), dim3(256), 0, st, pa, L, r, a.sg, GGpart,
-                               io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
-            } else {
-                PAC_LAUNCH(prof, st, nb_sum > 0 ? KC_G_GGSUM : split ? KC_G_POST_VEC : KC_G_POST, k_ggsum<true>,
-                           dim3(pa.nb_vec + nb_sum), dim3(256), post_vec_wide_lds(Lr), st, pa, L, r, a.sg, GGpart, io.params,
-                           D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
-            }
+            // post_vec_wide goes with the launch of the partial sums where there is one (it needs nothing of it), and is a
+            // launch of its own, a part of KC_G_POST's work, where there is none or every part is asked for on its own
+            const bool rides = vec_wide && nb_sum > 0 && !split;
+            if (nb_sum > 0 && !rides)
+                PAC_LAUNCH(prof, st, KC_G_GGSUM, k_ggsum<false>, dim3(nb_sum), dim3(256), 0, st, pa, L, r, a.sg, GGpart,
+                           io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
+            if (vec_wide)
+                PAC_LAUNCH(prof, st, rides ? KC_G_GGSUM : split ? KC_G_POST_VEC : KC_G_POST, k_ggsum<true>,
+                           dim3(pa.nb_vec + (rides ? nb_sum : 0)), dim3(256), post_vec_wide_lds(Lr), st, pa, L, r, a.sg, GGpart,
+                           io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
             const int counts[3] = {pa.nb_F, pa.nb_W, vec_wide ? 0 : pa.nb_vec};
             const int classes[3] = {KC_G_POST_F, KC_G_POST_W, KC_G_POST_VEC};
             PAC_HIP_TRY((allow_lds_once<&k_gpost<64, BIG>>(PostShapes<64, BIG>::kLds)));

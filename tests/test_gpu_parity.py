@@ -590,6 +590,36 @@ def test_split_launches_match_fused_launches_bitwise(wname):
         assert torch.equal(a, b)
 
 
+# Gradients that are no contractions as whole rows (3 M elements of each stacked copy and more), with and without partial
+# sums over the tokens to share their launch
+ROWS = [(Workload("s1", L=3, d=2560, n_max=100, B=2, r=448, C=3, N=2, cache_dtype="bf16", len_lo=80), True),
+        (Workload("s2", L=6, d=2048, n_max=60, B=2, r=448, C=2, N=2, cache_dtype="bf16", len_lo=30), False)]
+
+
+@pytest.mark.parametrize("w,sums", ROWS, ids=[w.name for w, _ in ROWS])
+def test_split_launches_report_every_part(w, sums):
+    """With PAC_FLAG_SPLIT_LAUNCH each part of the gradients is one launch of its own class, and the results are the same."""
+    from paper_2408_10746_amd import binding as pb
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, params = inputs.batch_acts(w, ids), inputs.random_params(w, up_scale=0.5)
+    lab = torch.from_numpy(inputs.labels(w)[ids]).cuda()
+    got, launches = [], []
+    for flags in (0, 2):
+        sess = make_session(w, lens=lens, flags=flags)
+        sess.cache_fill(ids, acts, lens)
+        sess.set_params(params)
+        pb.pac_profile_begin(sess.ctx)
+        sess.loss_grad(ids, lab)
+        torch.cuda.synchronize()
+        launches.append({k: n for k, (_, n) in pb.pac_profile_end(sess.ctx).items() if k.startswith(("g_ggsum", "g_post"))})
+        got.append((sess.loss.clone(), sess.logits.clone(), sess.grads.clone()))
+    assert launches[0] == ({"g_ggsum": 1, "g_post": 1} if sums else {"g_post": 2})
+    parts = {"g_post.F": 1, "g_post.W": 1, "g_post.vec": 1}
+    assert launches[1] == (dict(parts, g_ggsum=1) if sums else parts)
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.timeout(1500)
 def test_llama7b_shape_full_batch():
     """d=4096, r=256, L=32, 256-token samples with outlier channels: the whole 16-sample batch (the launch shape
