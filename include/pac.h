@@ -144,6 +144,16 @@ int64_t pac_workspace_bytes(const pac_ctx *ctx);
  * layer by layer.  Decided by pac_create from the shape, cache dtype and flags.  -1 if ctx is NULL. */
 int32_t pac_step_path(const pac_ctx *ctx);
 
+/* Which tiles the launches of a step on such a batch take (same results up to rounding in each; host logic, for
+ * measurements and tests that have to know which form they ran):
+ *   out[0]  token rows per tile of the projection launch (paths 1, 2), of the layers' down-projections (path 0)
+ *   out[1]  columns of d per tile of the contractions over the tokens      out[2]  side of the gradient launch's tiles
+ *   out[3]  1: the gradients that are no contractions as whole rows        out[4], out[5]  token splits of the
+ *           weights' contraction and of the Gram matrix                    (out[1..5] are 0 on path 0)
+ * lens HOST, B entries in [1, n_max], or NULL = every sample has n_max tokens; B in [1, B_max].
+ * PAC_ERR_NULL, PAC_ERR_RANGE. */
+pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t out[6] /*HOST*/);
+
 /*
  * Store one backbone forward's per-layer activations (paper Sec. 4.2: during
  * the first epoch everything the adapters consume is cached).

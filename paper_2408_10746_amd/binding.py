@@ -25,7 +25,8 @@ PAC_FLAG_LAYER_CHAIN = 4
 
 EXPORTS = [
     "pac_create", "pac_destroy", "pac_status_str", "pac_param_count", "pac_param_offsets",
-    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_cache_fill", "pac_cache_lookup",
+    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_step_tiles", "pac_cache_fill",
+    "pac_cache_lookup",
     "pac_adapter_loss_grad", "pac_adapter_step", "pac_adapter_step_static",
     "pac_probe_hbm_read", "pac_probe_mfma_bf16", "pac_probe_mfma_flops", "pac_probe_hbm_update",
     "pac_profile_begin", "pac_profile_end", "pac_profile_class_name",
@@ -100,6 +101,8 @@ def lib():
         L.pac_workspace_bytes.argtypes = [vp]
         L.pac_step_path.restype = C.c_int32
         L.pac_step_path.argtypes = [vp]
+        L.pac_step_tiles.restype = C.c_int
+        L.pac_step_tiles.argtypes = [vp, vp, i32, C.POINTER(i32)]
         L.pac_cache_fill.restype = C.c_int
         L.pac_cache_fill.argtypes = [vp, vp, i64, vp, i32, vp, i32, vp, vp]
         L.pac_cache_lookup.restype = C.c_int
@@ -215,6 +218,14 @@ def pac_workspace_bytes(ctx) -> int:
 
 def pac_step_path(ctx) -> int:
     return int(lib().pac_step_path(ctx))
+
+
+def pac_step_tiles(ctx, lens, B: int) -> dict:
+    """lens: B lengths or None.  The tile choice of a step on such a batch, by name."""
+    la = _host_i32(lens)
+    out = (C.c_int32 * 6)()
+    _check(lib().pac_step_tiles(ctx, _hp(la), B, out), "pac_step_tiles")
+    return dict(zip(("proj", "tokens", "grads", "rows", "se", "sg"), (int(x) for x in out)))
 
 
 def pac_cache_fill(ctx, cache_ptr, cache_bytes, sample_ids, acts_ptr, acts_dtype, lens=None, stream=0) -> None:

@@ -193,6 +193,22 @@ int64_t pac_workspace_bytes(const pac_ctx *ctx) { return ctx ? ctx->W.total : -1
 
 int32_t pac_step_path(const pac_ctx *ctx) { return ctx ? ctx->W.use_gram : -1; }
 
+pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens, int32_t B, int32_t out[6])
+{
+    if (!ctx || !out) return PAC_ERR_NULL;
+    if (B < 1 || B > ctx->D.B_max) return PAC_ERR_RANGE;
+    int M = 0, ntiles = 0;
+    for (int32_t s = 0; s < B; ++s) {
+        const int32_t len = lens ? lens[s] : ctx->D.n_max;
+        if (len < 1 || len > ctx->D.n_max) return PAC_ERR_RANGE;
+        M += len;
+        ntiles += (len + kChainRows - 1) / kChainRows;
+    }
+    if (ctx->W.use_gram) gram_step_tiles(ctx->D, ctx->W, M, ntiles, out);
+    else layer_step_tiles(ctx->D, M, out);
+    return PAC_OK;
+}
+
 pac_status pac_cache_lookup(const pac_ctx *ctx, int64_t sample_id, int64_t *offset_elems, int32_t *len)
 {
     if (!ctx || !offset_elems || !len) return PAC_ERR_NULL;

@@ -42,7 +42,6 @@ namespace pac {
 static inline int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-constexpr int kChainRows = 16;   // token rows per chain workgroup
 constexpr int kChainPad = 8;     // bf16 elements of padding per LDS row
 constexpr int kMaxD = 4096;
 constexpr int kETileCols = 128; // columns of d one workgroup of the E contraction covers
@@ -71,20 +70,6 @@ static size_t chain_lds(int L, int r, bool fwd)
 
 // Side of the square workgroup tiles of the contractions outside the chains: 64 up to r = 128, 128 above
 static int big_shapes(int r) { return r > 128; }
-
-// Which tiles a wide contraction runs on: 256 x 256 (pp_loop) or 128 x 256.  Estimated time = rounds over the 256 compute
-// units times a tile's time: its start and epilogue plus its K steps of 64.  Measured on 8192 x 8192 x 4096 and on single
-// tiles (us): K-contiguous 8 + 1.72 a step on the larger tile against 5 + 1.08, one workgroup per compute unit either way;
-// token contractions 9 + 1.87 against 6 + 2.3 for two of the smaller tiles at once.  So the larger tile takes the
-// contractions of many steps, and short ones only where it saves a round.
-static bool pp_pays(int64_t n256, int64_t n128, int steps)
-{
-    return n256 > 0 && cdiv(n256, 256) * (8 + 1.72 * steps) < cdiv(n128, 256) * (5 + 1.08 * steps);
-}
-static bool pp_pays_tokens(int64_t n256, int64_t n128, int steps)
-{
-    return n256 > 0 && cdiv(n256, 256) * (9 + 1.87 * steps) < cdiv(n128, 512) * (6 + 2.3 * steps);
-}
 
 int gram_path_kind(const Dims &D)
 {
@@ -2458,6 +2443,65 @@ template <auto Kern> static hipError_t allow_lds_once(int lds)
     return result;
 }
 
+// Which tiles a wide contraction runs on: 256 x 256 (pp_loop) or 128 x 256.  Estimated time = rounds over the 256 compute
+// units times a tile's time: its start and epilogue plus its K steps of 64.  Measured on 8192 x 8192 x 4096 and on single
+// tiles (us): K-contiguous 8 + 1.72 a step on the larger tile against 5 + 1.08, one workgroup per compute unit either way;
+// token contractions 9 + 1.87 against 6 + 2.3 for two of the smaller tiles at once.  So the larger tile takes the
+// contractions of many steps, and short ones only where it saves a round.
+static bool pp_pays(int64_t n256, int64_t n128, int steps)
+{
+    return n256 > 0 && cdiv(n256, 256) * (8 + 1.72 * steps) < cdiv(n128, 256) * (5 + 1.08 * steps);
+}
+static bool pp_pays_tokens(int64_t n256, int64_t n128, int steps)
+{
+    return n256 > 0 && cdiv(n256, 256) * (9 + 1.87 * steps) < cdiv(n128, 512) * (6 + 2.3 * steps);
+}
+
+// Which form each launch of a step over M token rows (ntiles 16-row tiles) takes
+struct GramForms {
+    bool proj_pp, tok_pp, grad_pp; // 256 x 256 tiles
+    bool vec_wide;                 // the gradients that are no contractions as whole rows
+    int se, tiles_per_se;          // token splits of E, in 16-row tiles
+    int sg, rows_per_sg;           // token splits of the Gram matrix, in token rows
+};
+static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
+{
+    const int L = D.L, d = D.d, r = D.r;
+    const int64_t Lr = (int64_t)L * r, rt = cdiv(r, 256);
+    const bool big = big_shapes(r);
+    GramForms f;
+    f.proj_pp = big && d % 64 == 0 &&
+                pp_pays(((int64_t)cdiv(M, 256) * L + (int64_t)W.pairs * cdiv(r, 256)) * rt,
+                        ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * rt, d / 64);
+    const int64_t ct = cdiv(Lr, 256) * (int64_t)W.sg / 2; // half of the Gram matrix's tiles are needed
+    f.tok_pp = big && pp_pays_tokens((int64_t)L * cdiv(d, 256) * rt * W.se + ct * cdiv(Lr, 256),
+                                     (int64_t)L * cdiv(d, 128) * rt * W.se + ct * cdiv(Lr, 128), cdiv(M, 64 * (W.se + W.sg) / 2));
+    f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128);
+    // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
+    // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
+    // 4 to 7 us slower at 1.2 to 1.6 M).
+    f.vec_wide = big && d * Lr >= (2 << 20);
+    // W.se is fixed by the configuration (the partial buffers are sized for it)
+    const int kt = f.tok_pp ? 64 : big ? TokRedShapes<8>::KT : r == 96 ? TokRedShapes<3>::KT : kTokKT; // token rows of a step
+    const int tps = kt / 16;
+    f.tiles_per_se = cdiv(cdiv(ntiles, W.se), tps) * tps;
+    f.se = cdiv(ntiles, f.tiles_per_se);
+    f.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
+    f.sg = cdiv(M, f.rows_per_sg);
+    return f;
+}
+
+void gram_step_tiles(const Dims &D, const WsLayout &W, int M, int ntiles, int32_t out[6])
+{
+    const GramForms f = gram_forms(D, W, M, ntiles);
+    out[0] = f.proj_pp ? PpTile::BM : 128;
+    out[1] = f.tok_pp ? PpTile::BM : kETileCols;
+    out[2] = f.grad_pp ? PpTile::BM : big_shapes(D.r) ? 128 : 64;
+    out[3] = f.vec_wide;
+    out[4] = f.se;
+    out[5] = f.sg;
+}
+
 template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io)
 {
     hipStream_t st = io.stream;
@@ -2468,6 +2512,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     const bool split = (D.flags & 2) != 0;
     int ntiles = 0;
     for (int s = 0; s < B; ++s) ntiles += cdiv(meta.len[s], kChainRows);
+    const GramForms forms = gram_forms(D, W, M, ntiles);
 
     int64_t *rowoff = (int64_t *)(ws + W.rowoff);
     int32_t *rowstride = (int32_t *)(ws + W.rowstride);
@@ -2522,9 +2567,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         a.cache = cache; a.map = map; a.L = L; a.d = d; a.r = r; a.B = B;
         constexpr int kQRows = NT > 4 ? 128 : 64, kQCols = NT > 4 ? 256 : 64; // ProjShapes<NT, .>::TQ
         constexpr int kProjThreads = NT > 4 ? 512 : 256;
-        a.pp = NT > 4 && d % 64 == 0 &&
-               pp_pays(((int64_t)cdiv(M, 256) * L + (int64_t)W.pairs * cdiv(r, 256)) * cdiv(r, 256),
-                       ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * cdiv(r, 256), d / 64);
+        a.pp = forms.proj_pp;
         a.row_tiles = cdiv(M, a.pp ? 256 : 128); a.nb_U = a.row_tiles * L * (NT > 4 ? cdiv(r, 256) : 1);
         a.nb_Q = W.pairs * cdiv(r, kQRows) * cdiv(r, kQCols);
         if (NT <= 4 && W.use_gram != 2) a.nb_Q = L > 1 ? cdiv(Lr, 128) * cdiv(Lr, 128) : 0; // ProjShapes::QSTACK
@@ -2666,24 +2709,15 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     }
     {
         TokRedArgs a;
-        bool pp;
+        const bool pp = forms.tok_pp;
         a.cache = cache; a.map = map; a.L = L; a.d = d; a.r = r;
-        {
-            const int64_t ct = cdiv(Lr, 256) * (int64_t)W.sg / 2; // half of the Gram matrix's tiles are needed
-            pp = NT > 4 && pp_pays_tokens((int64_t)L * cdiv(d, 256) * cdiv(r, 256) * W.se + ct * cdiv(Lr, 256),
-                                     (int64_t)L * cdiv(d, 128) * cdiv(r, 256) * W.se + ct * cdiv(Lr, 128), cdiv(M, 64 * (W.se + W.sg) / 2));
-        }
         a.e_tiles = cdiv(d, pp ? PpTile::BM : kETileCols);
-        {
-            const int tps = (pp ? 64 : TokRedShapes<NT>::KT) / 16;
-            // W.se is fixed by the configuration (the partial buffers are sized for it)
-            if (cdiv(ntiles, W.se) > kMaxSplitTiles) return hipErrorInvalidValue;
-            a.tiles_per_se = cdiv(cdiv(ntiles, W.se), tps) * tps;
-            a.se = cdiv(ntiles, a.tiles_per_se);
-        }
+        if (cdiv(ntiles, W.se) > kMaxSplitTiles) return hipErrorInvalidValue;
+        a.tiles_per_se = forms.tiles_per_se;
+        a.se = forms.se;
         a.tile_row0 = tile_row0; a.tile_rows = tile_rows; a.zeros = ws + W.g_zero;
-        a.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
-        a.sg = cdiv(M, a.rows_per_sg);
+        a.rows_per_sg = forms.rows_per_sg;
+        a.sg = forms.sg;
         a.tg = cdiv(Lr, pp ? PpTile::BM : 128);
         a.tgn = cdiv(Lr, NT > 4 ? 256 : 128);
         a.nb_E = L * a.e_tiles * cdiv(r, NT > 4 ? 256 : 128) * a.se;
@@ -2706,13 +2740,10 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         PostArgs pa;
         pa.L = L; pa.d = d; pa.r = r; pa.C = C; pa.B = B;
         constexpr bool BIG = NT > 4;
-        // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
-        // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
-        // 4 to 7 us slower at 1.2 to 1.6 M).
-        const bool vec_wide = BIG && (int64_t)d * Lr >= (2 << 20);
+        const bool vec_wide = forms.vec_wide;
         const int NH = !BIG ? 2 : r > 256 ? 8 : 4; // threads per r-wide row in post_vec
         constexpr int kFCols = BIG ? 256 : 64, kWRows = BIG ? 256 : 64;
-        pa.pp = BIG && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * cdiv(r, 256), (int64_t)2 * L * cdiv(d, 128) * cdiv(r, 256), (L - 1) * r / 128);
+        pa.pp = forms.grad_pp;
         const int kFRows = pa.pp ? 256 : BIG ? 128 : 64, kWCols = pa.pp ? 256 : BIG ? 128 : 64;
         constexpr int kPostThreads = BIG ? 512 : 256;
         pa.nb_F = L * cdiv(d, kFRows) * cdiv(r, kFCols); pa.nb_W = L * cdiv(r, kWRows) * cdiv(d, kWCols);

@@ -56,6 +56,8 @@ struct WsLayout {
     int32_t g_dlam_slots;
 };
 
+constexpr int kChainRows = 16; // token rows per chain workgroup (Gram-matrix path)
+
 struct Dims {
     int32_t L, d, n_max, r, C, B_max;
     int64_t N;
@@ -137,6 +139,9 @@ hipError_t launch_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &m
 int gram_path_kind(const Dims &D); // a value of WsLayout::use_gram
 void plan_gram_workspace(const Dims &D, WsLayout &W, int64_t &offset);
 hipError_t launch_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io);
+// pac_step_tiles for a batch of M token rows in ntiles 16-row tiles
+void gram_step_tiles(const Dims &D, const WsLayout &W, int M, int ntiles, int32_t out[6]);
+void layer_step_tiles(const Dims &D, int M, int32_t out[6]);
 // mixed-precision linear layer on block-wise quantised weights (pac_quant.hip)
 // (returns a pac_status value)
 int check_dq_linear_args(const void *x, int32_t M, int32_t K, const int8_t *codes, const float *consts, int32_t N,

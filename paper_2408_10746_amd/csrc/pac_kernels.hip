@@ -1062,6 +1062,13 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
     return hipGetLastError();
 }
 
+void layer_step_tiles(const Dims &D, int M, int32_t out[6])
+{
+    (void)M;
+    for (int i = 0; i < 6; ++i) out[i] = 0;
+    out[0] = D.cache_dtype == 0 ? 64 : 16;
+}
+
 hipError_t launch_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io)
 {
     if (W.use_gram) return launch_gram_loss_grad(D, W, meta, io);

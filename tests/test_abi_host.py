@@ -96,6 +96,26 @@ def test_formulation_chosen_per_configuration():
     assert pb.lib().pac_step_path(None) == -1
 
 
+def step_tiles(L, d, n, r, B, lens=None, dtype=pb.PAC_BF16):
+    ctx = pb.pac_create(L, d, n, r, 3, B, 64, dtype)
+    try:
+        return pb.pac_step_tiles(ctx, lens, B)
+    finally:
+        pb.pac_destroy(ctx)
+
+
+def test_tiles_chosen_per_batch():
+    """Host logic: which tiles the launches of a step take."""
+    assert step_tiles(12, 768, 128, 96, 32) == dict(proj=128, tokens=128, grads=64, rows=0, se=4, sg=4)   # T5-Base-shaped
+    assert step_tiles(32, 4096, 256, 256, 16) == dict(proj=256, tokens=256, grads=256, rows=1, se=1, sg=1)  # LLaMA-7B-shaped
+    assert step_tiles(32, 4096, 1024, 512, 8, [640] * 8)["proj"] == 256                                     # long sequences
+    assert step_tiles(12, 768, 128, 96, 32, dtype=pb.PAC_F32) == dict(proj=16, tokens=0, grads=0, rows=0, se=0, sg=0)
+    with pytest.raises(pb.PacError) as e:
+        step_tiles(12, 768, 128, 96, 2, [128, 129])
+    assert e.value.status == pb.PAC_ERR_RANGE
+    assert pb.lib().pac_step_tiles(None, None, 1, (C.c_int32 * 6)()) == pb.PAC_ERR_NULL
+
+
 def test_argument_errors_are_caught_before_any_launch():
     """Fake (never dereferenced) device addresses: every call below must fail on the host."""
     ctx = pb.pac_create(2, 64, 16, 32, 3, 4, 8, pb.PAC_BF16)

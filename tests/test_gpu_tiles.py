@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2408_10746_amd import binding as pb
 from paper_2408_10746_amd import inputs
 from paper_2408_10746_amd.inputs import Workload
 
@@ -13,15 +14,29 @@ pytestmark = pytest.mark.gpu
 from tests.test_gpu_parity import TOL, check_against_oracle, make_session  # noqa: E402
 
 
+def tiles_of(w, lens):
+    ctx = pb.pac_create(w.L, w.d, w.n_max, w.r, w.C, w.B, w.N, pb.PAC_BF16 if w.cache_dtype == "bf16" else pb.PAC_F32)
+    try:
+        return pb.pac_step_tiles(ctx, lens[:w.B], w.B)
+    finally:
+        pb.pac_destroy(ctx)
+
+
 # 256 x 256 tiles (many layers: the smaller tiles would need a second round of the compute units), gradients that are no
-# contractions as whole rows.  Tails: p1 88 of 256 token rows and a last 64-token step of few valid tokens, d = 3.5 tiles;
-# p2 adapter rows of one and a quarter tiles, d = 3.25 tiles.
-@pytest.mark.parametrize("w", [
-    Workload("p1", L=20, d=896, n_max=230, B=3, r=256, C=4, N=3, cache_dtype="bf16", len_lo=170),
-    Workload("p2", L=16, d=832, n_max=301, B=2, r=320, C=5, N=2, cache_dtype="bf16", len_lo=299),
-], ids=lambda w: w.name)
-def test_wide_contractions_on_large_tiles(w):
+# contractions as whole rows.  Tails: p1 74 of 256 token rows and a last 64-token step of few valid tokens, d = 3.5 tiles;
+# p2 adapter rows of one and a quarter tiles, d = 3.25 tiles, the projection on the smaller tiles.
+LARGE_TILES = [
+    (Workload("p1", L=20, d=896, n_max=230, B=3, r=256, C=4, N=3, cache_dtype="bf16", len_lo=170),
+     dict(proj=256, tokens=256, grads=256, rows=1, se=2, sg=1)),
+    (Workload("p2", L=16, d=832, n_max=301, B=2, r=320, C=5, N=2, cache_dtype="bf16", len_lo=299),
+     dict(proj=128, tokens=256, grads=256, rows=1, se=2, sg=1)),
+]
+
+
+@pytest.mark.parametrize("w,tiles", LARGE_TILES, ids=[w.name for w, _ in LARGE_TILES])
+def test_wide_contractions_on_large_tiles(w, tiles):
     lens, ids = inputs.lengths(w), np.arange(w.B)
+    assert tiles_of(w, lens) == tiles
     acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
     sess = make_session(w, lens=lens)
     sess.cache_fill(ids, acts, lens)
