@@ -380,7 +380,23 @@ static int rows16_blocks(int M, int ncols)
     int chunks = cdiv(ncols, 128);
     const int want = cdiv(256, cdiv(M, 16));
     if (chunks < want) chunks = want;
-    return 2 * cdiv(cdiv(ncols, 32), chunks);
+    const int nb = 2 * cdiv(cdiv(ncols, 32), chunks);
+    return nb <= 2 ? 2 : nb <= 4 ? 4 : nb <= 6 ? 6 : 8;
+}
+
+// Where the 16-row tiles take a contraction and where the 64 x 64 ones do (k_fwd_down, k_bwd_dpre): a 16-row tile reads its
+// whole weight panel for 16 rows, four times the bytes per row, so they pay where the 64 x 64 grid leaves compute units
+// idle and lose where it fills them.  Rounds over the 256 compute units, one workgroup each: a round of 16-row tiles costs
+// 2 + NB, of 64 x 64 tiles 9.5 on top of 9.5 (11 where K comes in short steps), in units of 3.6 us at K = 2048.  Both sides
+// measured at 320 shapes, d = 256 .. 4096, r = 32 .. 512, 256 .. 32768 rows; the rule is off by more than 5 % at two.  Two
+// layers of the reverse at d = 2048, 16-row against 64 x 64: 4096 rows, r = 128 124 / 155 us; 8192 rows, r = 128 198 / 179,
+// r = 96 160 / 172, r = 32 92 / 167; 4096 rows, r = 512 363 / 239; d = 2080, 8192 rows, r = 128 199 / 230.
+static bool rows16_pays(int M, int ncols, bool long_steps)
+{
+    const int nb = rows16_blocks(M, ncols);
+    const int rounds16 = cdiv((int64_t)cdiv(M, 16) * cdiv(ncols, 16 * nb), 256);
+    const int rounds64 = cdiv((int64_t)cdiv(M, 64) * cdiv(ncols, 64), 256);
+    return 2 * rounds16 * (2 + nb) < 19 * (1 + rounds64) + (long_steps ? 0 : 3);
 }
 
 template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_fwd_down16(FwdDownArgs<float> a)
@@ -987,22 +1003,24 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
     const int nb16 = rows16_blocks(M, r);
     const dim3 g_rows16(cdiv(M, 16), cdiv(r, 16 * nb16));
     auto with_blocks = [&](auto f) {
-        if (nb16 <= 2) f(std::integral_constant<int, 2>());
-        else if (nb16 <= 4) f(std::integral_constant<int, 4>());
-        else if (nb16 <= 6) f(std::integral_constant<int, 6>());
+        if (nb16 == 2) f(std::integral_constant<int, 2>());
+        else if (nb16 == 4) f(std::integral_constant<int, 4>());
+        else if (nb16 == 6) f(std::integral_constant<int, 6>());
         else f(std::integral_constant<int, 8>());
     };
     // long K steps where the contraction length allows them
     const bool wide_d = d % Stage<TC, 4>::BK == 0, wide_r = r % Stage<TC, 4>::BK == 0;
+    const bool rows16 = std::is_same<TC, float>::value && rows16_pays(M, r, wide_d);
     for (int l = 0; l < L; ++l) {
         const float *pl = params + (int64_t)l * PL;
         const float *s_prev = l == 0 ? nullptr : s_all + (int64_t)(l - 1) * Md;
         FwdDownArgs<TC> fa{cache, map, l, d, r, s_prev, WdT + (int64_t)l * dr, pl + dr, pl + PL - 1,
                            pre_all + (int64_t)l * Mr, h_all + (int64_t)l * Mr};
-        if constexpr (std::is_same<TC, float>::value) {
-            with_blocks([&](auto nb) {
-                PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, fa);
-            });
+        if (rows16) {
+            if constexpr (std::is_same<TC, float>::value)
+                with_blocks([&](auto nb) {
+                    PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, fa);
+                });
         } else if (wide_d) PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down<TC, 4>), g_rows_r, dim3(256), 0, st, fa);
         else PAC_LAUNCH(prof, st, KC_FWD_DOWN, (k_fwd_down<TC, 1>), g_rows_r, dim3(256), 0, st, fa);
         FwdUpArgs<TC> fu{h_all + (int64_t)l * Mr, WuT + (int64_t)l * dr, pl + 2 * dr + r, s_prev,
@@ -1043,10 +1061,11 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
                        pre_all + (int64_t)l * Mr, rowsamp, M, r, dpre);
         } else {
             BwdDpreArgs<TC> ba{ds, Wu + (int64_t)l * dr, pre_all + (int64_t)l * Mr, dpre, M, d, r};
-            if constexpr (std::is_same<TC, float>::value) {
-                with_blocks([&](auto nb) {
-                    PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, ba);
-                });
+            if (rows16) {
+                if constexpr (std::is_same<TC, float>::value)
+                    with_blocks([&](auto nb) {
+                        PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, ba);
+                    });
             } else if (wide_d) PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 4>), g_rows_r, dim3(256), 0, st, ba);
             else PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 1>), g_rows_r, dim3(256), 0, st, ba);
         }
@@ -1064,9 +1083,8 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
 
 void layer_step_tiles(const Dims &D, int M, int32_t out[6])
 {
-    (void)M;
     for (int i = 0; i < 6; ++i) out[i] = 0;
-    out[0] = D.cache_dtype == 0 ? 64 : 16;
+    out[0] = D.cache_dtype != 0 && rows16_pays(M, D.r, D.d % Stage<float, 4>::BK == 0) ? 16 : 64;
 }
 
 hipError_t launch_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io)

@@ -110,6 +110,12 @@ def test_tiles_chosen_per_batch():
     assert step_tiles(32, 4096, 256, 256, 16) == dict(proj=256, tokens=256, grads=256, rows=1, se=1, sg=1)  # LLaMA-7B-shaped
     assert step_tiles(32, 4096, 1024, 512, 8, [640] * 8)["proj"] == 256                                     # long sequences
     assert step_tiles(12, 768, 128, 96, 32, dtype=pb.PAC_F32) == dict(proj=16, tokens=0, grads=0, rows=0, se=0, sg=0)
+    # fp32 contractions: 16-row tiles where 64 x 64 ones leave compute units idle, the latter where they fill the chip
+    fp32 = {(768, 96, 4096): 16, (768, 96, 8192): 16, (2048, 32, 16384): 16, (1024, 128, 4096): 16, (4096, 512, 1024): 16,
+            (1024, 128, 8192): 64, (1024, 256, 4096): 64, (4096, 256, 8192): 64, (2048, 512, 2048): 64, (4096, 512, 8192): 64,
+            (2048, 32, 32768): 64, (2080, 128, 8192): 16, (2080, 512, 2048): 16, (2080, 512, 4096): 64}
+    for (d, r, rows), tile in fp32.items():
+        assert step_tiles(3, d, rows // 32, r, 32, dtype=pb.PAC_F32)["proj"] == tile, (d, r, rows)
     with pytest.raises(pb.PacError) as e:
         step_tiles(12, 768, 128, 96, 2, [128, 129])
     assert e.value.status == pb.PAC_ERR_RANGE

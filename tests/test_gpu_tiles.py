@@ -44,16 +44,20 @@ def test_wide_contractions_on_large_tiles(w, tiles):
 
 
 # fp32: 16-row tiles with 8, 6 (the second column chunk part empty), 4 and 6 column blocks per workgroup; K of 2 .. 10
-# units over eight wavefronts, a last row tile of a few rows
-@pytest.mark.parametrize("w", [
-    Workload("f1", L=2, d=96, n_max=130, B=32, r=128, C=3, N=32, cache_dtype="f32", len_lo=128),
-    Workload("f2", L=2, d=160, n_max=68, B=32, r=160, C=2, N=32, cache_dtype="f32", len_lo=62),
-    Workload("f3", L=3, d=64, n_max=68, B=32, r=128, C=2, N=32, cache_dtype="f32", len_lo=62),
-    Workload("f4", L=2, d=32, n_max=130, B=32, r=96, C=5, N=32, cache_dtype="f32", len_lo=128),
-    Workload("f5", L=2, d=288, n_max=9, B=3, r=64, C=2, N=3, cache_dtype="f32", len_lo=1),
-], ids=lambda w: w.name)
-def test_fp32_contractions(w):
+# units over eight wavefronts, a last row tile of a few rows.  64 x 64 tiles where they fill the chip: K in long steps (f6)
+# and in short ones (f7).
+@pytest.mark.parametrize("w,rows", [
+    (Workload("f1", L=2, d=96, n_max=130, B=32, r=128, C=3, N=32, cache_dtype="f32", len_lo=128), 16),
+    (Workload("f2", L=2, d=160, n_max=68, B=32, r=160, C=2, N=32, cache_dtype="f32", len_lo=62), 16),
+    (Workload("f3", L=3, d=64, n_max=68, B=32, r=128, C=2, N=32, cache_dtype="f32", len_lo=62), 16),
+    (Workload("f4", L=2, d=32, n_max=130, B=32, r=96, C=5, N=32, cache_dtype="f32", len_lo=128), 16),
+    (Workload("f5", L=2, d=288, n_max=9, B=3, r=64, C=2, N=3, cache_dtype="f32", len_lo=1), 16),
+    (Workload("f6", L=2, d=64, n_max=75, B=32, r=512, C=2, N=32, cache_dtype="f32", len_lo=70), 64),
+    (Workload("f7", L=2, d=96, n_max=140, B=32, r=512, C=3, N=32, cache_dtype="f32", len_lo=135), 64),
+], ids=lambda w: getattr(w, "name", None))
+def test_fp32_contractions(w, rows):
     lens, ids = inputs.lengths(w), np.arange(w.B)
+    assert tiles_of(w, lens)["proj"] == rows
     acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
     sess = make_session(w, lens=lens)
     sess.cache_fill(ids, acts, lens)
