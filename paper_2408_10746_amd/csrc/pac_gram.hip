@@ -441,7 +441,6 @@ struct ProjArgs {
     RowMap map;
     int L, d, r, B;
     int nb_U, nb_Q, nb_C, row_tiles;
-    bool pp; // U and Q on 256 x 256 tiles (row_tiles, nb_U, nb_Q count those)
     const bf16_t *WdT, *Wu;
     const float *cusum; // [L+1][d]
     float *chat;        // [L][r]
@@ -622,25 +621,32 @@ using T64K = Tile<2, 2, 1, 1, 4>; // 128-token K step for the token contractions
 
 // Stage counts are kept small on purpose: more workgroups per compute unit hide the memory latency
 // better than deeper rings in fewer workgroups (measured both ways).
-template <int NT, int BK, bool QFULL = false> struct ProjShapes {
+// PP: U and Q on 256 x 256 tiles (pp_loop), counted so in row_tiles, nb_U and nb_Q; an instantiation of its own
+template <int NT, int BK, bool QFULL, bool PP> struct ProjShapes {
     static constexpr bool BIG = NT > 4;
+    static_assert(!PP || (BIG && BK == 64), "pp_loop takes 64 of K a step");
     static constexpr bool QSTACK = !BIG && !QFULL; // Q as one contraction over the stacked projections
     // r > 128: 128 x 256 tiles (all of r), eight wavefronts, three stages, interleaved sub-steps; one workgroup per CU
-    using TBig = NtTile<2, 4, 2, 2, BK, 3>;
+    using TBig = typename std::conditional<PP, PpTile, NtTile<2, 4, 2, 2, BK, 3>>::type;
     using TU = typename std::conditional<BIG, TBig, NtTile<4, 1, 1, (BIG ? 1 : NT), BK, 2>>::type; // 128 token rows x r
     using TQ = typename std::conditional<BIG, TBig, typename std::conditional<QSTACK, NtTile<2, 2, 2, 2, BK, 2>, NtTile<2, 2, 1, 1, BK, 3>>::type>::type; // 128 x 128 of the stacked product, 64 x 64 of a pair, or 128 x 256
     static constexpr int kThreadsPerBlock = BIG ? 512 : 256;
     using TC = Tile<2, 2, 1, 1, BK / 32>;   // the one-row chat contraction (staged through registers)
     static constexpr int kUStages = 3; // the small shapes' U tile: three stages of cache rows, two of the projection
-    static constexpr int kULds = BIG ? TU::LDS_BYTES : nt_deepA_lds<TU, kUStages>();
+    template <class T> static constexpr int u_lds()
+    {
+        if constexpr (BIG) return T::LDS_BYTES;
+        else return nt_deepA_lds<T, kUStages>();
+    }
+    static constexpr int kULds = u_lds<TU>();
     static constexpr int kA = kULds > TQ::LDS_BYTES ? kULds : TQ::LDS_BYTES;
     static constexpr int kB = tile_lds_bytes<bf16_t, TC>() > 8 * 256 * 4 ? tile_lds_bytes<bf16_t, TC>() : 8 * 256 * 4;
     static constexpr int kLds = kA > kB ? kA : kB;
 };
 
-template <int NT, int BK, bool QFULL> __global__ __launch_bounds__(NT > 4 ? 512 : 256) void k_gproj(ProjArgs a)
+template <int NT, int BK, bool QFULL, bool PP> __global__ __launch_bounds__(NT > 4 ? 512 : 256) void k_gproj(ProjArgs a)
 {
-    using SH = ProjShapes<NT, BK, QFULL>;
+    using SH = ProjShapes<NT, BK, QFULL, PP>;
     using TU = typename SH::TU;
     using TQ = typename SH::TQ;
     constexpr int KU = BK / 32;
@@ -665,14 +671,12 @@ template <int NT, int BK, bool QFULL> __global__ __launch_bounds__(NT > 4 ? 512 
         auto arow = [&](int m) { return cache + map.rowoff[m] + (int64_t)l * map.rowstride[m]; };
         auto brow = [&](int c) { return W + (int64_t)c * d; };
         EpiStoreF32 epi{a.U + (int64_t)l * a.map.M * a.r, a.r};
-        if constexpr (SH::BIG) {
-            if (BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, mt * PpTile::BM, ct * PpTile::BN, a.map.M, a.r);
-            else gemm_nt<TU, true>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
-        } else gemm_nt_deepA<TU, SH::kUStages>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
+        if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
+        else if constexpr (SH::BIG) gemm_nt<TU, true>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
+        else gemm_nt_deepA<TU, SH::kUStages>(smem, arow, brow, epi, 0, a.d, mt * TU::BM, ct * TU::BN, a.map.M, a.r);
         return;
     }
-    const int qbm = SH::BIG && a.pp ? PpTile::BM : TQ::BM;
-    const int tqm = (a.r + qbm - 1) / qbm, tqn = (a.r + TQ::BN - 1) / TQ::BN, tq2 = tqm * tqn, tc64 = (a.r + 63) / 64;
+    const int tqm = (a.r + TQ::BM - 1) / TQ::BM, tqn = (a.r + TQ::BN - 1) / TQ::BN, tq2 = tqm * tqn, tc64 = (a.r + 63) / 64;
     if (b < a.nb_U + a.nb_Q) {
         if constexpr (SH::QSTACK) {
             // tile (ti, tj) of [L r] x [L r]; needed where some row layer is below some column layer
@@ -735,7 +739,7 @@ template <int NT, int BK, bool QFULL> __global__ __launch_bounds__(NT > 4 ? 512 
                 gn = a.QgN + ((int64_t)gi * pg + qb * (qb - 1) / 2 + jb) * a.r * a.r;
             }
             EpiQFull epi{a.QpN, a.QpT, a.r, oml, k, l, (int64_t)a.L * a.r, gn, gt};
-            if (SH::BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, (idx / tqn) * PpTile::BM, (idx % tqn) * PpTile::BN, a.r, a.r);
+            if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
             else gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
         } else {
             EpiQ epi{a.QpN + (int64_t)p * a.r * a.r, a.QpT + (int64_t)p * a.r * a.r, a.r, oml};
@@ -1838,7 +1842,6 @@ struct PostArgs {
     int blk_off; // first block of this launch (parts may be launched separately for timing)
     int L, d, r, C, B;
     int nb_F, nb_W, nb_vec;
-    bool pp; // F and W on 256 x 256 tiles (nb_F, nb_W, slots count those)
     const float *params;
     int64_t PL;
     const bf16_t *WuTs, *Wds, *GGT, *GGsc;
@@ -2291,23 +2294,25 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
     if (t < C) a.grads[(int64_t)L * a.PL + (int64_t)d * C + t] = a.dzsum[t];
 }
 
-template <int BK, bool BIG> struct PostShapes {
+// PP: F and W on 256 x 256 tiles (pp_loop), counted so in nb_F, nb_W and slots; an instantiation of its own
+template <int BK, bool BIG, bool PP> struct PostShapes {
+    static_assert(!PP || (BIG && BK == 64), "pp_loop takes 64 of K a step");
     // 64 x 64 with 64 KB of stages; or (r > 128) eight wavefronts, three stages, interleaved sub-steps:
     // 128 rows of d x 256 columns of r for F, 256 rows of r x 128 columns of d for W
     using TSmall = NtTile<2, 2, 1, 1, BK, BK == 64 ? 4 : 8>;
-    using TFF = typename std::conditional<BIG, NtTile<2, 4, 2, 2, BK, 3>, TSmall>::type;
-    using TFW = typename std::conditional<BIG, NtTile<4, 2, 2, 2, BK, 3>, TSmall>::type;
+    using TFF = typename std::conditional<PP, PpTile, typename std::conditional<BIG, NtTile<2, 4, 2, 2, BK, 3>, TSmall>::type>::type;
+    using TFW = typename std::conditional<PP, PpTile, typename std::conditional<BIG, NtTile<4, 2, 2, 2, BK, 3>, TSmall>::type>::type;
     static constexpr int kThreadsPerBlock = BIG ? 512 : 256;
     static constexpr int kLds = TFF::LDS_BYTES > TFW::LDS_BYTES ? TFF::LDS_BYTES : TFW::LDS_BYTES;
     static_assert(kLds >= kPostVecLds, "LDS budget of the gradient kernel");
 };
 
 // BK = 64 when r is a multiple of 64, else 32: every K range below is a multiple of r
-template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k_gpost(PostArgs a)
+template <int BK, bool BIG, bool PP> __global__ __launch_bounds__(BIG ? 512 : 256) void k_gpost(PostArgs a)
 {
-    using TFF = typename PostShapes<BK, BIG>::TFF;
-    using TFW = typename PostShapes<BK, BIG>::TFW;
-    constexpr int kLds = PostShapes<BK, BIG>::kLds;
+    using TFF = typename PostShapes<BK, BIG, PP>::TFF;
+    using TFW = typename PostShapes<BK, BIG, PP>::TFW;
+    constexpr int kLds = PostShapes<BK, BIG, PP>::kLds;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     __shared__ float red[16];
     const int L = a.L, d = a.d, r = a.r, C = a.C;
@@ -2315,8 +2320,7 @@ template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k
     const int64_t dr = (int64_t)d * r;
     const int b = (int)(gridDim.x - 1 - blockIdx.x) + a.blk_off, t = threadIdx.x; // reverse dispatch, as in k_gproj
     if (b < a.nb_F) {
-        const int fbm = BIG && a.pp ? PpTile::BM : TFF::BM;
-        const int ti_d = (d + fbm - 1) / fbm, ti_r = (r + TFF::BN - 1) / TFF::BN;
+        const int ti_d = (d + TFF::BM - 1) / TFF::BM, ti_r = (r + TFF::BN - 1) / TFF::BN;
         // F_l = sum_{k<l} W_up^{kT} G_{kl}   ([d] x [l*r] times [l*r] x [r])
         int l, slot, it, nt;
         if (BIG && ti_d % 8 == 0) {
@@ -2344,7 +2348,7 @@ template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k
         auto brow = [&](int c) { return B + (int64_t)c * Lr; };
         EpiF epi{a.E + (int64_t)l * dr, a.cusum + (int64_t)l * d, a.cs + (int64_t)l * r,
                  pl, a.grads + (int64_t)l * a.PL, r, pl[a.PL - 1], 0.f};
-        if (BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, 0, l * r, it * PpTile::BM, nt * PpTile::BN, d, r);
+        if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
         else gemm_nt<TFF, true>(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
         const float tot = block_sum(epi.dlam, red);
         if (t == 0) a.dlam_part[(int64_t)l * a.slots + slot] = tot; // summed in slot order by k_gfinish
@@ -2352,8 +2356,7 @@ template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k
     }
     if (b < a.nb_F + a.nb_W) {
         // dW_up^l = Z_l W_cls^T + sum_{k>l} (1-lambda_k) G_{lk} W_down^{kT}
-        const int wbn = BIG && a.pp ? PpTile::BN : TFW::BN;
-        const int ti_r = (r + TFW::BM - 1) / TFW::BM, ti_d = (d + wbn - 1) / wbn;
+        const int ti_r = (r + TFW::BM - 1) / TFW::BM, ti_d = (d + TFW::BN - 1) / TFW::BN;
         int l, at, jt;
         if (BIG && ti_d % 8 == 0) {
             // as for F: a die takes ti_d / 8 tiles along d (rows of the stacked W_down copy) for every layer
@@ -2377,7 +2380,7 @@ template <int BK, bool BIG> __global__ __launch_bounds__(BIG ? 512 : 256) void k
         auto brow = [&](int c) { return B + (int64_t)c * Lr; };
         EpiW epi{a.Z + (int64_t)l * r * C, a.params + (int64_t)L * a.PL,
                  a.grads + (int64_t)l * a.PL + dr + r, d, C};
-        if (BIG && BK == 64 && a.pp) gemm_nt_pp(smem, arow, brow, epi, (l + 1) * r, Lr, at * PpTile::BM, jt * PpTile::BN, r, d);
+        if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
         else gemm_nt<TFW, true>(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
         return;
     }
@@ -2567,13 +2570,13 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         a.cache = cache; a.map = map; a.L = L; a.d = d; a.r = r; a.B = B;
         constexpr int kQRows = NT > 4 ? 128 : 64, kQCols = NT > 4 ? 256 : 64; // ProjShapes<NT, .>::TQ
         constexpr int kProjThreads = NT > 4 ? 512 : 256;
-        a.pp = forms.proj_pp;
-        a.row_tiles = cdiv(M, a.pp ? 256 : 128); a.nb_U = a.row_tiles * L * (NT > 4 ? cdiv(r, 256) : 1);
+        const bool pp = forms.proj_pp;
+        a.row_tiles = cdiv(M, pp ? 256 : 128); a.nb_U = a.row_tiles * L * (NT > 4 ? cdiv(r, 256) : 1);
         a.nb_Q = W.pairs * cdiv(r, kQRows) * cdiv(r, kQCols);
         if (NT <= 4 && W.use_gram != 2) a.nb_Q = L > 1 ? cdiv(Lr, 128) * cdiv(Lr, 128) : 0; // ProjShapes::QSTACK
         if (NT > 4) { // blocks of 4 x 4 layer pairs, see k_gproj
             const int nlb = cdiv(L, 4);
-            a.nb_Q = L > 1 ? nlb * (nlb + 1) / 2 * 16 * cdiv(r, a.pp ? 256 : kQRows) * cdiv(r, kQCols) : 0;
+            a.nb_Q = L > 1 ? nlb * (nlb + 1) / 2 * 16 * cdiv(r, pp ? 256 : kQRows) * cdiv(r, kQCols) : 0;
         }
         a.nb_C = L * cdiv(r, 64);
         a.cusum = cusum; a.chat = chat; a.params = io.params; a.PL = D.PL;
@@ -2586,14 +2589,28 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
             launch_parts(prof, st, split, kern, a, 4, counts, classes, KC_G_PROJ, kProjThreads, lds);
         };
         const bool q_full = W.use_gram == 2;
-        if (d % 64 == 0) {
-            constexpr int lds = ProjShapes<NT, 64, true>::kLds > ProjShapes<NT, 64, false>::kLds ? ProjShapes<NT, 64, true>::kLds : ProjShapes<NT, 64, false>::kLds;
-            if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, true>>(lds))); launch_proj(&k_gproj<NT, 64, true>, lds); }
-            else if constexpr (NT <= 4) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, false>>(lds))); launch_proj(&k_gproj<NT, 64, false>, lds); }
+        if constexpr (NT > 4) {
+            if (pp) {
+                constexpr int lds = ProjShapes<NT, 64, true, true>::kLds;
+                PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, true, true>>(lds)));
+                launch_proj(&k_gproj<NT, 64, true, true>, lds);
+            } else if (d % 64 == 0) {
+                constexpr int lds = ProjShapes<NT, 64, true, false>::kLds;
+                PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, true, false>>(lds)));
+                launch_proj(&k_gproj<NT, 64, true, false>, lds);
+            } else {
+                constexpr int lds = ProjShapes<NT, 32, true, false>::kLds;
+                PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, true, false>>(lds)));
+                launch_proj(&k_gproj<NT, 32, true, false>, lds);
+            }
+        } else if (d % 64 == 0) {
+            constexpr int lds = ProjShapes<NT, 64, true, false>::kLds > ProjShapes<NT, 64, false, false>::kLds ? ProjShapes<NT, 64, true, false>::kLds : ProjShapes<NT, 64, false, false>::kLds;
+            if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, true, false>>(lds))); launch_proj(&k_gproj<NT, 64, true, false>, lds); }
+            else { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 64, false, false>>(lds))); launch_proj(&k_gproj<NT, 64, false, false>, lds); }
         } else {
-            constexpr int lds = ProjShapes<NT, 32, true>::kLds > ProjShapes<NT, 32, false>::kLds ? ProjShapes<NT, 32, true>::kLds : ProjShapes<NT, 32, false>::kLds;
-            if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, true>>(lds))); launch_proj(&k_gproj<NT, 32, true>, lds); }
-            else if constexpr (NT <= 4) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, false>>(lds))); launch_proj(&k_gproj<NT, 32, false>, lds); }
+            constexpr int lds = ProjShapes<NT, 32, true, false>::kLds > ProjShapes<NT, 32, false, false>::kLds ? ProjShapes<NT, 32, true, false>::kLds : ProjShapes<NT, 32, false, false>::kLds;
+            if (q_full) { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, true, false>>(lds))); launch_proj(&k_gproj<NT, 32, true, false>, lds); }
+            else { PAC_HIP_TRY((allow_lds_once<&k_gproj<NT, 32, false, false>>(lds))); launch_proj(&k_gproj<NT, 32, false, false>, lds); }
         }
     }
     PAC_HIP_TRY(hipGetLastError());
@@ -2743,8 +2760,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         const bool vec_wide = forms.vec_wide;
         const int NH = !BIG ? 2 : r > 256 ? 8 : 4; // threads per r-wide row in post_vec
         constexpr int kFCols = BIG ? 256 : 64, kWRows = BIG ? 256 : 64;
-        pa.pp = forms.grad_pp;
-        const int kFRows = pa.pp ? 256 : BIG ? 128 : 64, kWCols = pa.pp ? 256 : BIG ? 128 : 64;
+        const int kFRows = forms.grad_pp ? 256 : BIG ? 128 : 64, kWCols = kFRows;
         constexpr int kPostThreads = BIG ? 512 : 256;
         pa.nb_F = L * cdiv(d, kFRows) * cdiv(r, kFCols); pa.nb_W = L * cdiv(r, kWRows) * cdiv(d, kWCols);
         pa.nb_vec = vec_wide ? L + d / kVecRows : cdiv(d, (256 / NH) / L) + 1;
@@ -2769,12 +2785,25 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
                            io.params, D.PL, GGT, GGsc, nb_GG, a.se, e_elems, Epart, E);
             const int counts[3] = {pa.nb_F, pa.nb_W, vec_wide ? 0 : pa.nb_vec};
             const int classes[3] = {KC_G_POST_F, KC_G_POST_W, KC_G_POST_VEC};
-            PAC_HIP_TRY((allow_lds_once<&k_gpost<64, BIG>>(PostShapes<64, BIG>::kLds)));
-            PAC_HIP_TRY((allow_lds_once<&k_gpost<32, BIG>>(PostShapes<32, BIG>::kLds)));
-            if (r % 64 == 0)
-                launch_parts(prof, st, split, k_gpost<64, BIG>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<64, BIG>::kLds);
-            else
-                launch_parts(prof, st, split, k_gpost<32, BIG>, pa, 3, counts, classes, KC_G_POST, kPostThreads, PostShapes<32, BIG>::kLds);
+            auto launch_post = [&](auto kern, int lds) {
+                launch_parts(prof, st, split, kern, pa, 3, counts, classes, KC_G_POST, kPostThreads, lds);
+            };
+            if constexpr (BIG) {
+                if (forms.grad_pp) {
+                    constexpr int lds = PostShapes<64, true, true>::kLds;
+                    PAC_HIP_TRY((allow_lds_once<&k_gpost<64, true, true>>(lds)));
+                    launch_post(&k_gpost<64, true, true>, lds);
+                }
+            }
+            if (!forms.grad_pp && r % 64 == 0) {
+                constexpr int lds = PostShapes<64, BIG, false>::kLds;
+                PAC_HIP_TRY((allow_lds_once<&k_gpost<64, BIG, false>>(lds)));
+                launch_post(&k_gpost<64, BIG, false>, lds);
+            } else if (!forms.grad_pp) {
+                constexpr int lds = PostShapes<32, BIG, false>::kLds;
+                PAC_HIP_TRY((allow_lds_once<&k_gpost<32, BIG, false>>(lds)));
+                launch_post(&k_gpost<32, BIG, false>, lds);
+            }
         }
         if (io.defer) { // the optimizer launch that follows does the last two sums
             io.defer->used = true;
