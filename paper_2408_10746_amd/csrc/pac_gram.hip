@@ -447,7 +447,7 @@ struct ProjArgs {
     const float *params;
     int64_t PL;
     float *U;          // [L][M][r]
-    bf16_t *QpN, *QpT; // [pairs][r][r] in fragment-major order (EpiQ), or (q_full) [L*r][L*r] each (EpiQFull)
+    bf16_t *QpN, *QpT; // [pairs][r][r] in fragment-major order (EpiQStacked), or (q_full) [L*r][L*r] each (EpiQFull)
     bf16_t *QgN, *QgT; // q_full: the pairs inside a group of chain_group layers once more, fragment-major
     int chain_group;
     const int32_t *samp_start, *samp_len;
@@ -521,17 +521,6 @@ __device__ __forceinline__ int64_t frag_index(int n, int kk, int r)
 {
     return ((int64_t)((n >> 4) * (r >> 5) + (kk >> 5)) * 64 + (n & 15) + 16 * ((kk & 31) >> 3)) * 8 + (kk & 7);
 }
-
-struct EpiQ {
-    bf16_t *qn, *qt;
-    int r;
-    float one_minus_lam; // of the later layer of the pair: the backward chain uses (1-lambda_l) Q_{kl}
-    __device__ void operator()(int row, int col, float v) const
-    {
-        qn[frag_index(row, col, r)] = static_cast<bf16_t>(one_minus_lam * v); // backward: B[n=row][kk=col]
-        qt[frag_index(col, row, r)] = static_cast<bf16_t>(v);                 // forward:  B[n=col][kk=row]
-    }
-};
 
 // All products Q_{kl} of the single-launch chains from ONE contraction over the stacked projections: row (k, j) of the
 // stacked up-projections against column (l, n) of the stacked down-projections; only k < l is kept.
@@ -695,7 +684,7 @@ template <int NT, int BK, bool QFULL, bool PP> __global__ __launch_bounds__(NT >
             gemm_nt<TQ>(smem, arow, brow, epi, 0, a.d, ti * TQ::BM, tj * TQ::BN, Lr, Lr);
             return;
         }
-        int idx, k, l, p;
+        int idx, k, l;
         if constexpr (SH::BIG) {
             // Blocks of 4 x 4 layer pairs (k in 4 kb.., l in 4 lb.., kb <= lb), one block per die at a time: its tiles
             // read 4 + 4 projection matrices between them instead of two each (numbered pair by pair and round-robin,
@@ -712,10 +701,9 @@ template <int NT, int BK, bool QFULL, bool PP> __global__ __launch_bounds__(NT >
             k = 4 * kb + (pr & 3);
             l = 4 * lb + (pr >> 2);
             if (k >= l || l >= a.L) return;
-            p = pair_index(k, l);
         } else {
             idx = b - a.nb_U;
-            p = idx / tq2;
+            const int p = idx / tq2;
             idx -= p * tq2;
             // pair p = (k, l), k < l
             l = 1;
@@ -727,24 +715,19 @@ template <int NT, int BK, bool QFULL, bool PP> __global__ __launch_bounds__(NT >
         auto arow = [&](int row) { return Wu + (int64_t)row * d; };
         auto brow = [&](int c) { return Wd + (int64_t)c * d; };
         const float oml = 1.f - a.params[(int64_t)l * a.PL + a.PL - 1];
-        if constexpr (QFULL) {
-            // slot of an in-group pair: the forward chain reaches it at step (l - l0, k - l0) of its group, the
-            // backward chain at step (l1 - 1 - k, l1 - 1 - l); slot of step (q, j) = q (q - 1) / 2 + j
-            const int g = a.chain_group, gi = l / g;
-            bf16_t *gn = nullptr, *gt = nullptr;
-            if (k / g == gi) {
-                const int l0 = gi * g, l1 = min(l0 + g, a.L), pg = g * (g - 1) / 2;
-                const int qf = l - l0, jf = k - l0, qb = l1 - 1 - k, jb = l1 - 1 - l;
-                gt = a.QgT + ((int64_t)gi * pg + qf * (qf - 1) / 2 + jf) * a.r * a.r;
-                gn = a.QgN + ((int64_t)gi * pg + qb * (qb - 1) / 2 + jb) * a.r * a.r;
-            }
-            EpiQFull epi{a.QpN, a.QpT, a.r, oml, k, l, (int64_t)a.L * a.r, gn, gt};
-            if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
-            else gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
-        } else {
-            EpiQ epi{a.QpN + (int64_t)p * a.r * a.r, a.QpT + (int64_t)p * a.r * a.r, a.r, oml};
-            gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
+        // slot of an in-group pair: the forward chain reaches it at step (l - l0, k - l0) of its group, the
+        // backward chain at step (l1 - 1 - k, l1 - 1 - l); slot of step (q, j) = q (q - 1) / 2 + j
+        const int g = a.chain_group, gi = l / g;
+        bf16_t *gn = nullptr, *gt = nullptr;
+        if (k / g == gi) {
+            const int l0 = gi * g, l1 = min(l0 + g, a.L), pg = g * (g - 1) / 2;
+            const int qf = l - l0, jf = k - l0, qb = l1 - 1 - k, jb = l1 - 1 - l;
+            gt = a.QgT + ((int64_t)gi * pg + qf * (qf - 1) / 2 + jf) * a.r * a.r;
+            gn = a.QgN + ((int64_t)gi * pg + qb * (qb - 1) / 2 + jb) * a.r * a.r;
         }
+        EpiQFull epi{a.QpN, a.QpT, a.r, oml, k, l, (int64_t)a.L * a.r, gn, gt};
+        if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
+        else gemm_nt<TQ, true>(smem, arow, brow, epi, 0, a.d, (idx / tqn) * TQ::BM, (idx % tqn) * TQ::BN, a.r, a.r);
         return;
     }
     if (b < a.nb_U + a.nb_Q + a.nb_C) {
@@ -2516,6 +2499,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     int ntiles = 0;
     for (int s = 0; s < B; ++s) ntiles += cdiv(meta.len[s], kChainRows);
     const GramForms forms = gram_forms(D, W, M, ntiles);
+    if (NT > 4 && W.use_gram != 2) return hipErrorInvalidValue; // the wide shapes have the layer-by-layer chains only
 
     int64_t *rowoff = (int64_t *)(ws + W.rowoff);
     int32_t *rowstride = (int32_t *)(ws + W.rowstride);
