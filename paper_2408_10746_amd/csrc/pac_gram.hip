@@ -2429,14 +2429,16 @@ template <auto Kern> static hipError_t allow_lds_once(int lds)
     return result;
 }
 
-// Which tiles a wide contraction runs on: 256 x 256 (pp_loop) or 128 x 256.  Estimated time = rounds over the 256 compute
-// units times a tile's time: its start and epilogue plus its K steps of 64.  Measured on 8192 x 8192 x 4096 and on single
-// tiles (us): K-contiguous 8 + 1.72 a step on the larger tile against 5 + 1.08, one workgroup per compute unit either way;
-// token contractions 9 + 1.87 against 6 + 2.3 for two of the smaller tiles at once.  So the larger tile takes the
-// contractions of many steps, and short ones only where it saves a round.
-static bool pp_pays(int64_t n256, int64_t n128, int steps)
+// Which tiles a wide K-contiguous contraction runs on: 256 x 256 (pp_loop) or 128 x 256, one workgroup per compute unit
+// either way.  Estimated time = (tiles per unit + 0.7 of a tile for the last round) x a tile's time, its start and epilogue
+// plus its K steps of 64 (us): 14 + 1.7 a step on the larger tile, 8 + 1.08 on the smaller.  Both sides of both launches
+// measured at 150 shapes, L = 2 .. 48, d = 128 .. 4096, r = 160 .. 512, 64 .. 8192 token rows: the larger tile where this
+// picks it gains up to 25 % of the launch, and it never picks it where it is more than 3 % slower.  (Whole rounds times a
+// start of 8 and 5 us, taken from single tiles of a plain product, picked it for short contractions and small grids: the
+// projection of 3 layers of 512 x 512 at 6144 rows 46 us against 30, the gradients of 20 of 896 x 256 147 against 119.)
+static bool pp_pays(int64_t n256, int64_t n128, double steps)
 {
-    return n256 > 0 && cdiv(n256, 256) * (8 + 1.72 * steps) < cdiv(n128, 256) * (5 + 1.08 * steps);
+    return n256 > 0 && (n256 / 256. + 0.7) * (14 + 1.7 * steps) < (n128 / 256. + 0.7) * (8 + 1.08 * steps);
 }
 static bool pp_pays_tokens(int64_t n256, int64_t n128, int steps)
 {
@@ -2462,7 +2464,7 @@ static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
     const int64_t ct = cdiv(Lr, 256) * (int64_t)W.sg / 2; // half of the Gram matrix's tiles are needed
     f.tok_pp = big && pp_pays_tokens((int64_t)L * cdiv(d, 256) * rt * W.se + ct * cdiv(Lr, 256),
                                      (int64_t)L * cdiv(d, 128) * rt * W.se + ct * cdiv(Lr, 128), cdiv(M, 64 * (W.se + W.sg) / 2));
-    f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128);
+    f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128.);
     // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
     // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
     // 4 to 7 us slower at 1.2 to 1.6 M).

@@ -110,6 +110,16 @@ def test_tiles_chosen_per_batch():
     assert step_tiles(32, 4096, 256, 256, 16) == dict(proj=256, tokens=256, grads=256, rows=1, se=1, sg=1)  # LLaMA-7B-shaped
     assert step_tiles(32, 4096, 1024, 512, 8, [640] * 8)["proj"] == 256                                     # long sequences
     assert step_tiles(12, 768, 128, 96, 32, dtype=pb.PAC_F32) == dict(proj=16, tokens=0, grads=0, rows=0, se=0, sg=0)
+    # wide K-contiguous contractions: 256 x 256 tiles where there are many long ones, not for short or few ones
+    assert step_tiles(3, 512, 768, 512, 8)["proj"] == 128       # (46 us against 30)
+    assert step_tiles(11, 448, 224, 320, 1)["proj"] == 128      # (65 / 46)
+    assert step_tiles(3, 1280, 648, 512, 8)["proj"] == 128      # (58 / 45)
+    assert step_tiles(48, 256, 768, 160, 8)["proj"] == 256      # (150 / 179)
+    assert step_tiles(17, 2560, 892, 448, 4)["proj"] == 256     # (368 / 414)
+    assert step_tiles(20, 896, 197, 256, 3)["grads"] == 128     # (147 / 119)
+    assert step_tiles(8, 1632, 178, 448, 8)["grads"] == 128     # (119 / 98)
+    assert step_tiles(31, 672, 50, 512, 2)["grads"] == 256      # (492 / 561)
+    assert step_tiles(22, 2080, 50, 256, 8)["grads"] == 256     # (222 / 251)
     # fp32 contractions: 16-row tiles where 64 x 64 ones leave compute units idle, the latter where they fill the chip
     fp32 = {(768, 96, 4096): 16, (768, 96, 8192): 16, (2048, 32, 16384): 16, (1024, 128, 4096): 16, (4096, 512, 1024): 16,
             (1024, 128, 8192): 64, (1024, 256, 4096): 64, (4096, 256, 8192): 64, (2048, 512, 2048): 64, (4096, 512, 8192): 64,
