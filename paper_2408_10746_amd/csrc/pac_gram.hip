@@ -2440,9 +2440,35 @@ static bool pp_pays(int64_t n256, int64_t n128, double steps)
 {
     return n256 > 0 && (n256 / 256. + 0.7) * (14 + 1.7 * steps) < (n128 / 256. + 0.7) * (8 + 1.08 * steps);
 }
-static bool pp_pays_tokens(int64_t n256, int64_t n128, int steps)
+
+// Tiles of rows x 256 that hold some pair of a row layer below a column layer of the stacked Gram matrix
+static int64_t gram_tiles(int L, int r, int rows)
 {
-    return n256 > 0 && cdiv(n256, 256) * (9 + 1.87 * steps) < cdiv(n128, 512) * (6 + 2.3 * steps);
+    const int64_t Lr = (int64_t)L * r;
+    int64_t n = 0;
+    for (int64_t c0 = 0; c0 < Lr; c0 += 256) {
+        const int64_t last = (c0 + 255 < Lr ? c0 + 255 : Lr - 1) / r; // the tile's last column layer
+        n += cdiv(last * r, rows);
+    }
+    return n;
+}
+
+// The same choice for the contractions over the tokens, where two of the smaller tiles share a compute unit: the weights'
+// nE tiles of sE steps and the Gram matrix's nG of sG, in one launch.  Estimated time = their work over the places for
+// them + a share of the longest tile (us): 9 + 1.7 a step in 256 places + 0.8 against 4 + 2.6 in 512 + 0.5.  Measured and
+// checked as above: up to 30 % of the launch gained, 6 % lost at most but for one shape (16 layers of 2048 x 224, 6144
+// rows: 272 us against 225, where the two kinds of large tiles do not overlap).  (Rounds with the mean number of steps
+// picked the large tiles for many short splits and for one long Gram tile: 24 layers of 512 x 160 at 1024 rows 54 us
+// against 43, 4 of 256 x 512 at 6424 rows 133 against 118.)
+struct TokTiles {
+    int64_t nE, nG;
+};
+static bool pp_pays_tokens(const TokTiles &t256, const TokTiles &t128, double sE, double sG)
+{
+    const double longest = sE > sG ? sE : sG;
+    const double large = (t256.nE * (9 + 1.7 * sE) + t256.nG * (9 + 1.7 * sG)) / 256 + 0.8 * (9 + 1.7 * longest);
+    const double small = (t128.nE * (4 + 2.6 * sE) + t128.nG * (4 + 2.6 * sG)) / 512 + 0.5 * (4 + 2.6 * longest);
+    return large < small;
 }
 
 // Which form each launch of a step over M token rows (ntiles 16-row tiles) takes
@@ -2461,21 +2487,21 @@ static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
     f.proj_pp = big && d % 64 == 0 &&
                 pp_pays(((int64_t)cdiv(M, 256) * L + (int64_t)W.pairs * cdiv(r, 256)) * rt,
                         ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * rt, d / 64);
-    const int64_t ct = cdiv(Lr, 256) * (int64_t)W.sg / 2; // half of the Gram matrix's tiles are needed
-    f.tok_pp = big && pp_pays_tokens((int64_t)L * cdiv(d, 256) * rt * W.se + ct * cdiv(Lr, 256),
-                                     (int64_t)L * cdiv(d, 128) * rt * W.se + ct * cdiv(Lr, 128), cdiv(M, 64 * (W.se + W.sg) / 2));
     f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128.);
     // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
     // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
     // 4 to 7 us slower at 1.2 to 1.6 M).
     f.vec_wide = big && d * Lr >= (2 << 20);
+    f.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
+    f.sg = cdiv(M, f.rows_per_sg);
+    f.tok_pp = big && pp_pays_tokens({(int64_t)L * cdiv(d, 256) * rt * W.se, gram_tiles(L, r, 256) * f.sg},
+                                     {(int64_t)L * cdiv(d, 128) * rt * W.se, gram_tiles(L, r, 128) * f.sg},
+                                     ntiles / 4. / W.se, M / 64. / f.sg);
     // W.se is fixed by the configuration (the partial buffers are sized for it)
     const int kt = f.tok_pp ? 64 : big ? TokRedShapes<8>::KT : r == 96 ? TokRedShapes<3>::KT : kTokKT; // token rows of a step
     const int tps = kt / 16;
     f.tiles_per_se = cdiv(cdiv(ntiles, W.se), tps) * tps;
     f.se = cdiv(ntiles, f.tiles_per_se);
-    f.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
-    f.sg = cdiv(M, f.rows_per_sg);
     return f;
 }
 

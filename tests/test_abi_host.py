@@ -120,6 +120,14 @@ def test_tiles_chosen_per_batch():
     assert step_tiles(8, 1632, 178, 448, 8)["grads"] == 128     # (119 / 98)
     assert step_tiles(31, 672, 50, 512, 2)["grads"] == 256      # (492 / 561)
     assert step_tiles(22, 2080, 50, 256, 8)["grads"] == 256     # (222 / 251)
+    # contractions over the tokens: the large tiles where both kinds of tile walk over many tokens
+    assert step_tiles(24, 512, 128, 160, 8)["tokens"] == 128    # (54 / 43)
+    assert step_tiles(16, 832, 300, 320, 2)["tokens"] == 128    # (71 / 51)
+    assert step_tiles(4, 256, 803, 512, 8)["tokens"] == 128     # (133 / 118)
+    assert step_tiles(27, 768, 327, 320, 16)["tokens"] == 256   # (503 / 658)
+    assert step_tiles(12, 1024, 256, 256, 16)["tokens"] == 256  # (92 / 111)
+    t = step_tiles(4, 2048, 768, 256, 8)
+    assert t["tokens"] == 256 and t["se"] == 3 and t["sg"] == 4  # (54 / 70)
     # fp32 contractions: 16-row tiles where 64 x 64 ones leave compute units idle, the latter where they fill the chip
     fp32 = {(768, 96, 4096): 16, (768, 96, 8192): 16, (2048, 32, 16384): 16, (1024, 128, 4096): 16, (4096, 512, 1024): 16,
             (1024, 128, 8192): 64, (1024, 256, 4096): 64, (4096, 256, 8192): 64, (2048, 512, 2048): 64, (4096, 512, 8192): 64,

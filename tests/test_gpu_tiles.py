@@ -30,6 +30,9 @@ LARGE_TILES = [
     # all three
     (Workload("p2", L=48, d=1216, n_max=300, B=3, r=192, C=2, N=3, cache_dtype="bf16", len_lo=250), dict(proj=256, tokens=256, grads=256, rows=1, sg=1)),
     (Workload("p3", L=24, d=1216, n_max=300, B=3, r=448, C=5, N=3, cache_dtype="bf16", len_lo=250), dict(proj=256, tokens=256, grads=256, rows=1, sg=1)),
+    # the contractions over the tokens alone, both results split over them
+    (Workload("p4", L=12, d=1216, n_max=500, B=8, r=160, C=3, N=8, cache_dtype="bf16", len_lo=400), dict(tokens=256, grads=128, se=2, sg=2)),
+    (Workload("p5", L=4, d=1952, n_max=1000, B=6, r=256, C=3, N=6, cache_dtype="bf16", len_lo=960), dict(proj=128, tokens=256, grads=128)),
 ]
 
 
