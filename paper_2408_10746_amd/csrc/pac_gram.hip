@@ -2488,10 +2488,11 @@ static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
                 pp_pays(((int64_t)cdiv(M, 256) * L + (int64_t)W.pairs * cdiv(r, 256)) * rt,
                         ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * rt, d / 64);
     f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128.);
-    // Vector part of the wide shapes: from 2 M elements in each of the two stacked copies on as whole rows
-    // (post_vec_wide: 159 -> 41 us at 33 M, 26 us less at 4.2 M), below as a part of the launch of the tiles (rows
-    // 4 to 7 us slower at 1.2 to 1.6 M).
-    f.vec_wide = big && d * Lr >= (2 << 20);
+    // Vector part of the wide shapes: from 3 M elements in each of the two stacked copies on as whole rows, below as a part
+    // of the launch of the tiles.  Both forms of both launches, 370 shapes: the rows gain 41 us of 631 at 33 M elements,
+    // 5 to 20 us at 4 to 10 M, 3 to 5 at 3 M (worst 3 to 5 us lost at few layers), lose 5 to 10 us at 2 M and below, where
+    // the part fills compute units that the tiles leave idle (8 layers of 1024 x 256: sums and gradients 51 us, rows 62).
+    f.vec_wide = big && d * Lr >= (3 << 20);
     f.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
     f.sg = cdiv(M, f.rows_per_sg);
     f.tok_pp = big && pp_pays_tokens({(int64_t)L * cdiv(d, 256) * rt * W.se, gram_tiles(L, r, 256) * f.sg},

@@ -128,6 +128,11 @@ def test_tiles_chosen_per_batch():
     assert step_tiles(12, 1024, 256, 256, 16)["tokens"] == 256  # (92 / 111)
     t = step_tiles(4, 2048, 768, 256, 8)
     assert t["tokens"] == 256 and t["se"] == 3 and t["sg"] == 4  # (54 / 70)
+    # vector gradients as whole rows
+    assert step_tiles(8, 1024, 768, 256, 8)["rows"] == 0        # 2 M elements of a stacked copy: 62 us against 51
+    assert step_tiles(4, 2048, 768, 256, 8)["rows"] == 0        # 2 M: 43 / 35
+    assert step_tiles(8, 1024, 256, 384, 8)["rows"] == 1        # 3 M: 73 / 78
+    assert step_tiles(16, 1024, 256, 192, 16)["rows"] == 1      # 3 M: 77 / 81
     # fp32 contractions: 16-row tiles where 64 x 64 ones leave compute units idle, the latter where they fill the chip
     fp32 = {(768, 96, 4096): 16, (768, 96, 8192): 16, (2048, 32, 16384): 16, (1024, 128, 4096): 16, (4096, 512, 1024): 16,
             (1024, 128, 8192): 64, (1024, 256, 4096): 64, (4096, 256, 8192): 64, (2048, 512, 2048): 64, (4096, 512, 8192): 64,

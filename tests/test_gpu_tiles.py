@@ -33,6 +33,8 @@ LARGE_TILES = [
     # the contractions over the tokens alone, both results split over them
     (Workload("p4", L=12, d=1216, n_max=500, B=8, r=160, C=3, N=8, cache_dtype="bf16", len_lo=400), dict(tokens=256, grads=128, se=2, sg=2)),
     (Workload("p5", L=4, d=1952, n_max=1000, B=6, r=256, C=3, N=6, cache_dtype="bf16", len_lo=960), dict(proj=128, tokens=256, grads=128)),
+    # vector gradients as whole rows in the launch of the token splits' sums
+    (Workload("p6", L=3, d=2560, n_max=100, B=2, r=448, C=3, N=2, cache_dtype="bf16", len_lo=80), dict(proj=128, tokens=128, grads=128, rows=1, se=2, sg=2)),
 ]
 
 
