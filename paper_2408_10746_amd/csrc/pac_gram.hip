@@ -2290,6 +2290,11 @@ template <int BK, bool BIG, bool PP> struct PostShapes {
     static_assert(kLds >= kPostVecLds, "LDS budget of the gradient kernel");
 };
 
+// Tells the compiler that no load of its own is under way.  The tiles' code comes behind the vector part in the laid-out
+// control flow, and without this its loops waited in every K step for the registers of that part's loads, which no path
+// here has issued, and so for the transfers in flight.
+__device__ __forceinline__ void settle_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); } // vmcnt(0)
+
 // BK = 64 when r is a multiple of 64, else 32: every K range below is a multiple of r
 template <int BK, bool BIG, bool PP> __global__ __launch_bounds__(BIG ? 512 : 256) void k_gpost(PostArgs a)
 {
@@ -2331,6 +2336,7 @@ template <int BK, bool BIG, bool PP> __global__ __launch_bounds__(BIG ? 512 : 25
         auto brow = [&](int c) { return B + (int64_t)c * Lr; };
         EpiF epi{a.E + (int64_t)l * dr, a.cusum + (int64_t)l * d, a.cs + (int64_t)l * r,
                  pl, a.grads + (int64_t)l * a.PL, r, pl[a.PL - 1], 0.f};
+        if constexpr (BIG) settle_loads();
         if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
         else gemm_nt<TFF, true>(smem, arow, brow, epi, 0, l * r, it * TFF::BM, nt * TFF::BN, d, r);
         const float tot = block_sum(epi.dlam, red);
@@ -2363,6 +2369,7 @@ template <int BK, bool BIG, bool PP> __global__ __launch_bounds__(BIG ? 512 : 25
         auto brow = [&](int c) { return B + (int64_t)c * Lr; };
         EpiW epi{a.Z + (int64_t)l * r * C, a.params + (int64_t)L * a.PL,
                  a.grads + (int64_t)l * a.PL + dr + r, d, C};
+        if constexpr (BIG) settle_loads();
         if constexpr (PP) gemm_nt_pp(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
         else gemm_nt<TFW, true>(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
         return;
