@@ -2437,15 +2437,15 @@ template <auto Kern> static hipError_t allow_lds_once(int lds)
 }
 
 // Which tiles a wide K-contiguous contraction runs on: 256 x 256 (pp_loop) or 128 x 256, one workgroup per compute unit
-// either way.  Estimated time = (tiles per unit + 0.7 of a tile for the last round) x a tile's time, its start and epilogue
-// plus its K steps of 64 (us): 14 + 1.7 a step on the larger tile, 8 + 1.08 on the smaller.  Both sides of both launches
-// measured at 150 shapes, L = 2 .. 48, d = 128 .. 4096, r = 160 .. 512, 64 .. 8192 token rows: the larger tile where this
-// picks it gains up to 25 % of the launch, and it never picks it where it is more than 3 % slower.  (Whole rounds times a
-// start of 8 and 5 us, taken from single tiles of a plain product, picked it for short contractions and small grids: the
-// projection of 3 layers of 512 x 512 at 6144 rows 46 us against 30, the gradients of 20 of 896 x 256 147 against 119.)
+// either way.  Estimated time = (tiles per unit + 0.8 of a tile for the last round) x a tile's time, its start and epilogue
+// plus its K steps of 64 (us): 15 + 1.65 a step on the larger tile, 8 + 1.08 on the smaller.  Both forms of both launches
+// measured at 370 shapes, L = 2 .. 48, d = 128 .. 4096, r = 160 .. 512, 64 .. 8192 token rows: where this picks the larger
+// tile the launch is up to 1.2 x as fast and 4 % slower at most.  (Whole rounds times a start of 8 and 5 us, taken from
+// single tiles of a plain product, picked it for short contractions and small grids: the projection of 3 layers of
+// 512 x 512 at 6144 rows 46 us against 30, the gradients of 20 of 896 x 256 147 against 119.)
 static bool pp_pays(int64_t n256, int64_t n128, double steps)
 {
-    return n256 > 0 && (n256 / 256. + 0.7) * (14 + 1.7 * steps) < (n128 / 256. + 0.7) * (8 + 1.08 * steps);
+    return n256 > 0 && (n256 / 256. + 0.8) * (15 + 1.65 * steps) < (n128 / 256. + 0.8) * (8 + 1.08 * steps);
 }
 
 // Tiles of rows x 256 that hold some pair of a row layer below a column layer of the stacked Gram matrix
