@@ -2448,33 +2448,47 @@ static bool pp_pays(int64_t n256, int64_t n128, double steps)
     return n256 > 0 && (n256 / 256. + 0.8) * (15 + 1.65 * steps) < (n128 / 256. + 0.8) * (8 + 1.08 * steps);
 }
 
-// Tiles of rows x 256 that hold some pair of a row layer below a column layer of the stacked Gram matrix
-static int64_t gram_tiles(int L, int r, int rows)
+// The tiles of a launch of the contractions over the tokens: the weights' nE (dispatched first) and those nG of the Gram
+// matrix's rows x 256 tiles that hold a pair of a row layer below a column layer (the rest of the grid is empty); fullest:
+// how many of both the fullest of the eight dies gets, blocks being dealt to them round-robin.
+struct TokTiles {
+    int64_t nE, nG, fullest;
+};
+static TokTiles tok_tiles(int L, int r, int64_t nE, int sg, int rows)
 {
-    const int64_t Lr = (int64_t)L * r;
-    int64_t n = 0;
-    for (int64_t c0 = 0; c0 < Lr; c0 += 256) {
-        const int64_t last = (c0 + 255 < Lr ? c0 + 255 : Lr - 1) / r; // the tile's last column layer
-        n += cdiv(last * r, rows);
+    const int64_t Lr = (int64_t)L * r, tg = cdiv(Lr, rows), tgn = cdiv(Lr, 256);
+    int64_t die[8];
+    auto below = [](int64_t n, int x) { return (n + 7 - x) / 8; }; // blocks of die x among the first n
+    for (int x = 0; x < 8; ++x) die[x] = below(nE, x);
+    TokTiles t{nE, 0, 0};
+    for (int64_t ti = 0; ti < tg; ++ti) {
+        const int64_t k1 = ti * rows / r + 1; // the first column layer a tile of this row needs
+        if (k1 >= L) break;
+        const int64_t tj0 = k1 * r > 255 ? cdiv(k1 * r - 255, 256) : 0;
+        const int64_t b0 = nE + (ti * tgn + tj0) * sg, b1 = nE + (ti + 1) * tgn * sg;
+        t.nG += b1 - b0;
+        for (int x = 0; x < 8; ++x) die[x] += below(b1, x) - below(b0, x);
     }
-    return n;
+    for (int x = 0; x < 8; ++x) t.fullest = die[x] > t.fullest ? die[x] : t.fullest;
+    return t;
 }
 
-// The same choice for the contractions over the tokens, where two of the smaller tiles share a compute unit: the weights'
-// nE tiles of sE steps and the Gram matrix's nG of sG, in one launch.  Estimated time = their work over the places for
-// them + a share of the longest tile (us): 9 + 1.7 a step in 256 places + 0.8 against 4 + 2.6 in 512 + 0.5.  Measured and
-// checked as above: up to 30 % of the launch gained, 6 % lost at most but for one shape (16 layers of 2048 x 224, 6144
-// rows: 272 us against 225, where the two kinds of large tiles do not overlap).  (Rounds with the mean number of steps
-// picked the large tiles for many short splits and for one long Gram tile: 24 layers of 512 x 160 at 1024 rows 54 us
-// against 43, 4 of 256 x 512 at 6424 rows 133 against 118.)
-struct TokTiles {
-    int64_t nE, nG;
-};
+// The same choice for the contractions over the tokens: sE, sG steps of 64 tokens per tile.  Two of the smaller tiles share
+// a compute unit, and from one unit's view a weights' tile runs beside another or beside a Gram tile, each at half speed;
+// of the larger ones there is room for 32 on a die, but from 29 on some wait for a second round (the empty tiles between
+// them need a place too).  Times in us, both forms measured at 499 shapes (as above, more of many tokens): picked at 193 of
+// them, where the launch is 1.15 x as fast on average, 1.5 x at most, and 9 % (5 us) slower at worst.  (Rounds with the mean
+// number of steps picked the larger tiles for many short splits and for one long Gram tile: 24 layers of 512 x 160 at 1024
+// rows 54 us against 43, 4 of 256 x 512 at 6424 rows 133 against 118.)
 static bool pp_pays_tokens(const TokTiles &t256, const TokTiles &t128, double sE, double sG)
 {
-    const double longest = sE > sG ? sE : sG;
-    const double large = (t256.nE * (9 + 1.7 * sE) + t256.nG * (9 + 1.7 * sG)) / 256 + 0.8 * (9 + 1.7 * longest);
-    const double small = (t128.nE * (4 + 2.6 * sE) + t128.nG * (4 + 2.6 * sG)) / 512 + 0.5 * (4 + 2.6 * longest);
+    auto mean = [](const TokTiles &t, double tE, double tG) { return (t.nE * tE + t.nG * tG) / (t.nE + t.nG); };
+    const double lE = 12 + 1.4 * sE, lG = 12 + 1.4 * sG, l1 = lE > lG ? lE : lG;
+    const double lmany = mean(t256, lE, lG) * (t256.fullest <= 56 ? 2 : t256.fullest / 28. + 0.4);
+    const double large = t256.fullest <= 28 || l1 > lmany ? l1 : lmany;
+    const double eE = 2 + 1.3 * sE, eG = 2 + 1.3 * sG, e1 = eE + (eE > eG ? eE : eG);
+    const double emany = 2 * mean(t128, eE, eG) * (t128.fullest / 64. + 0.4);
+    const double small = t128.fullest <= 64 || e1 > emany ? e1 : emany;
     return large < small;
 }
 
@@ -2502,9 +2516,8 @@ static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
     f.vec_wide = big && d * Lr >= (3 << 20);
     f.rows_per_sg = cdiv(cdiv(M, W.sg), 128) * 128;
     f.sg = cdiv(M, f.rows_per_sg);
-    f.tok_pp = big && pp_pays_tokens({(int64_t)L * cdiv(d, 256) * rt * W.se, gram_tiles(L, r, 256) * f.sg},
-                                     {(int64_t)L * cdiv(d, 128) * rt * W.se, gram_tiles(L, r, 128) * f.sg},
-                                     ntiles / 4. / W.se, M / 64. / f.sg);
+    f.tok_pp = big && pp_pays_tokens(tok_tiles(L, r, (int64_t)L * cdiv(d, 256) * rt * W.se, f.sg, 256),
+                                     tok_tiles(L, r, (int64_t)L * cdiv(d, 128) * rt * W.se, f.sg, 128), ntiles / 4. / W.se, M / 64. / f.sg);
     // W.se is fixed by the configuration (the partial buffers are sized for it)
     const int kt = f.tok_pp ? 64 : big ? TokRedShapes<8>::KT : r == 96 ? TokRedShapes<3>::KT : kTokKT; // token rows of a step
     const int tps = kt / 16;

@@ -124,6 +124,11 @@ def test_tiles_chosen_per_batch():
     assert step_tiles(24, 512, 128, 160, 8)["tokens"] == 128    # (54 / 43)
     assert step_tiles(16, 832, 300, 320, 2)["tokens"] == 128    # (71 / 51)
     assert step_tiles(4, 256, 803, 512, 8)["tokens"] == 128     # (133 / 118)
+    assert step_tiles(16, 2048, 768, 224, 8)["tokens"] == 128   # (272 / 225)
+    assert step_tiles(24, 1280, 768, 160, 8)["tokens"] == 128   # (279 / 213)
+    assert step_tiles(18, 640, 189, 160, 16)["tokens"] == 128   # (101 / 77)
+    assert step_tiles(4, 1024, 768, 192, 8)["tokens"] == 256    # (36 / 44)
+    assert step_tiles(16, 2048, 768, 256, 8)["tokens"] == 256
     assert step_tiles(27, 768, 327, 320, 16)["tokens"] == 256   # (503 / 658)
     assert step_tiles(12, 1024, 256, 256, 16)["tokens"] == 256  # (92 / 111)
     t = step_tiles(4, 2048, 768, 256, 8)
