@@ -280,7 +280,10 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
 // More tiles of 128 x 128 than compute units: two share a unit and hide each other's waits.  Up to one per unit, tiles of
 // 64 x 64 (four times as many) are as fast or faster: K = 4096, blocks of 64, 256 tiles 72.5 against 74.5 us, 192 tiles
 // 57.4 / 73.4, 64 tiles 49 / 72, one tile row 37 / 73; beyond, 320 tiles 110.6 against 89.8 us, 1024 tiles 287 / 211.
-constexpr int kDqWideTiles = 257;
+// Blocks that are an odd multiple of 32 keep K steps of 32, where a wide tile has less to hide its barriers behind: K = 1920,
+// blocks of 32, 288 tiles 54.4 against 67.7 us, 320 tiles 57.6 / 69.5, 352 tiles 69.6 / 70.0, 448 tiles 84.5 / 70.8.
+// Up to 64 rows leave half of a wide tile and more empty: 16 x 33000, K = 1920, blocks of 64, 29.9 against 44.6 us.
+static bool dq_wide(int64_t tiles128, int M, int block) { return M > 64 && tiles128 > (block % 64 == 0 ? 256 : 320); }
 
 template <int BITS, int BK, int WT> static void dq_launch_as(const DqArgs &a, hipStream_t st)
 {
@@ -309,7 +312,7 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     a.y = y; a.cache = cache; a.cache_f32 = cache_f32; a.n_max = n_max; a.layer = layer;
     if (meta) a.meta = *meta;
     const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
-    if (tiles128 >= kDqWideTiles) dq_launch<2>(a, bits, st);
+    if (dq_wide(tiles128, M, block)) dq_launch<2>(a, bits, st);
     else dq_launch<1>(a, bits, st);
     return hipGetLastError();
 }

@@ -59,11 +59,19 @@ def test_linear_layer_against_oracle(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# 128 x 128 tiles: 272 of them, ragged at both edges, with blocks of one and three K steps of 32 and of one of 64; the
-# last has 256 and takes the small tiles, blocks of two K steps of 64
+# outputs of 272 tiles of 128 x 128, ragged at both edges: blocks of one and three K steps of 32 (on the small tiles) and of
+# one of 64 (on the large ones); the last has 256 and takes the small tiles, blocks of two K steps of 64
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2049, 64, 2001, 32), (2100, 192, 2033, 96), (2047, 192, 2100, 64), (2048, 256, 2048, 128)])
 def test_linear_layer_on_wide_and_narrow_tiles(M, K, N, block, bits):
+    check_linear_layer(M, K, N, block, bits)
+
+
+# where the line lies elsewhere: K steps of 32 take the large tiles from 321 on (342 and 361 here, then 304), up to 64 rows
+# never do
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block", [(2401, 64, 2200, 32), (2310, 192, 2311, 96), (2400, 96, 2001, 32), (40, 128, 33000, 64)])
+def test_linear_layer_tiles_by_block_and_rows(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
