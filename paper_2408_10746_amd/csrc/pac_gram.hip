@@ -1837,9 +1837,10 @@ struct PostArgs {
 // The gradients that are no contractions (dc_up, dW_cls, dc_down, dc_cls) for the wide shapes (r > 128): a workgroup takes four neighbouring hidden indices j, its
 // four wavefronts the 512-column pieces of their rows of the two stacked copies in turn, every load 1 KB contiguous, the
 // column sums and Z (a copy with its classes apart: read as rows of C classes, 128 bytes from lane to lane, it was
-// fetched from L2 eight times over) once for four rows.  Bound by the two copies' bytes (134 MB LLaMA-7B-shaped).  As part of the tiles' launch, one
-// workgroup per compute unit beside their LDS, with a thread per (j, layer, part) whose 16-byte loads were 128 bytes
-// apart, it took 159 us there, as a launch of its own 114 us, with neighbouring lanes on neighbouring chunks 92 us.
+// fetched from L2 eight times over) once for four rows.  Bound by the two copies' bytes (134 MB LLaMA-7B-shaped).  There
+// it takes 57 us as a launch of its own, the form with a thread per (j, layer, part), whose 16-byte loads are 128 bytes
+// apart, 107 us; with that form inside the tiles' launch, one workgroup per compute unit beside their LDS, the gradients
+// took 630 us, with this one in front of it 554.
 constexpr int kVecRows = 4; // = wavefronts of the workgroup
 static int post_vec_wide_lds(int Lr) { return kVecRows * (Lr / 32) * 4 + 4 * kVecRows * kMaxClasses * 4; }
 __device__ __forceinline__ void post_vec_wide(const PostArgs &a, int vb, char *smem) // 256 threads
@@ -2116,8 +2117,12 @@ __device__ __forceinline__ void swap_halves(u32x4 &x, u32x4 &y, int hf)
 constexpr int kPostVecLds = 128 * 4 + 128 * kMaxClasses * 4 + kMaxBatch * kMaxClasses * 4;
 // The rest of the gradients: block vb of nb_vec, four wavefronts; NH threads share one r-wide row; the column sums and Z are
 // staged in LDS where lds_bytes allow it.
-template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, int vb, char *smem, int lds_bytes)
+// PAIRS: two threads a row request neighbouring chunks of it and exchange them afterwards, so that each still sums its own
+// half in order (24 layers of 1024 x 128: the launch 52.2 us, with every lane on its own half 55.0; 6 of 1024 x 128 15.4 /
+// 18.2).  Not for rows of one or two lines, nor for more classes than zrows has forms for: nothing gained there.
+template <int NH, bool PAIRS = false> __device__ __forceinline__ void post_vec(const PostArgs &a, int vb, char *smem, int lds_bytes)
 {
+    static_assert(!PAIRS || NH == 2, "an exchange between two lanes");
     const int L = a.L, d = a.d, r = a.r, C = a.C;
     const int Lr = L * r;
     const int64_t dr = (int64_t)d * r;
@@ -2138,14 +2143,13 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
         // this thread's two row segments (chunks of 16 bytes), requested before anything else is waited for
         constexpr int kMaxChunks = 8; // r / NH <= 64
         u32x4 wv[kMaxChunks], uv[kMaxChunks];
-        if constexpr (NH == 2) {
-            // Neighbouring lanes request neighbouring chunks (r = 128, 24 layers, d = 1024: the launch 49.6 us; with every
-            // lane on its own half of the row 51.4), then exchange them: a lane sums its own half in order.  Slots
-            // q and q + 1 request chunk q + hf of the first and of the second half.
+        if constexpr (PAIRS) {
+            // slots q and q + 1: chunk q + hf of the first and of the second half
 #pragma unroll
             for (int q = 0; q < kMaxChunks; q += 2) {
-                const int64_t at = act && q * 8 < rh ? (int64_t)j * Lr + (int64_t)k * r + (q + hf) * 8 : 0;
-                const int64_t at2 = act && q * 8 < rh ? at + rh : 0;
+                const bool live = act && q * 8 < rh;
+                const int64_t at = live ? (int64_t)j * Lr + (int64_t)k * r + (q + hf) * 8 : 0;
+                const int64_t at2 = live ? at + rh : 0;
                 wv[q] = *reinterpret_cast<const u32x4 *>(a.Wds + at);
                 uv[q] = *reinterpret_cast<const u32x4 *>(a.WuTs + at);
                 wv[q + 1] = *reinterpret_cast<const u32x4 *>(a.Wds + at2);
@@ -2177,7 +2181,7 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
                 }
 #pragma unroll
             for (int c = 0; c < kMaxClasses; ++c)
-                if (c < C) base += dzs_r[c] * wc_r[c];
+                if (c < C) base = __builtin_fmaf(dzs_r[c], wc_r[c], base); // (written out: see EpiF)
         }
         float pbv[2]; // pooled last-layer means of the samples s = k + (NH q + hf) L this thread covers first
 #pragma unroll
@@ -2191,12 +2195,13 @@ template <int NH> __device__ __forceinline__ void post_vec(const PostArgs &a, in
         {
             const float *csk = (staged ? stage : a.cs) + (int64_t)k * r + hf * rh;
             const float *Zk = (staged ? stage + Lr : a.Z) + ((int64_t)k * r + hf * rh) * C;
-            if constexpr (NH == 2) {
+            if constexpr (PAIRS) {
 #pragma unroll
-                for (int q = 0; q < kMaxChunks; q += 2) {
-                    swap_halves(wv[q], wv[q + 1], hf);
-                    swap_halves(uv[q], uv[q + 1], hf);
-                }
+                for (int q = 0; q < kMaxChunks; q += 2)
+                    if (q * 8 < rh) {
+                        swap_halves(wv[q], wv[q + 1], hf);
+                        swap_halves(uv[q], uv[q + 1], hf);
+                    }
             }
             float acc = 0.f;
             float wz[kMaxClasses];
@@ -2374,8 +2379,10 @@ template <int BK, bool BIG, bool PP> __global__ __launch_bounds__(BIG ? 512 : 25
         else gemm_nt<TFW, true>(smem, arow, brow, epi, (l + 1) * r, Lr, at * TFW::BM, jt * TFW::BN, r, d);
         return;
     }
-    if constexpr (!BIG) post_vec<2>(a, b - a.nb_F - a.nb_W, smem, kLds);
-    else if (t < 256) {
+    if constexpr (!BIG) {
+        if (r > 64 && C <= 4) post_vec<2, true>(a, b - a.nb_F - a.nb_W, smem, kLds);
+        else post_vec<2>(a, b - a.nb_F - a.nb_W, smem, kLds);
+    } else if (t < 256) {
         if (r > 256) post_vec<8>(a, b - a.nb_F - a.nb_W, smem, kLds);
         else post_vec<4>(a, b - a.nb_F - a.nb_W, smem, kLds);
     }
@@ -2510,7 +2517,7 @@ static GramForms gram_forms(const Dims &D, const WsLayout &W, int M, int ntiles)
                         ((int64_t)cdiv(M, 128) * L + (int64_t)W.pairs * cdiv(r, 128)) * rt, d / 64);
     f.grad_pp = big && r % 64 == 0 && pp_pays((int64_t)2 * L * cdiv(d, 256) * rt, (int64_t)2 * L * cdiv(d, 128) * rt, (L - 1) * r / 128.);
     // Vector part of the wide shapes: from 3 M elements in each of the two stacked copies on as whole rows, below as a part
-    // of the launch of the tiles.  Both forms of both launches, 370 shapes: the rows gain 41 us of 631 at 33 M elements,
+    // of the launch of the tiles.  Both forms of both launches, 370 shapes: the rows gain 76 us of 630 at 33 M elements,
     // 5 to 20 us at 4 to 10 M, 3 to 5 at 3 M (worst 3 to 5 us lost at few layers), lose 5 to 10 us at 2 M and below, where
     // the part fills compute units that the tiles leave idle (8 layers of 1024 x 256: sums and gradients 51 us, rows 62).
     f.vec_wide = big && d * Lr >= (3 << 20);
