@@ -311,10 +311,14 @@ struct EpiBias {
     {
         const float b = bias[min(col, ncols - 1)];
         if (col >= ncols) return;
+        float u[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) u[v] = acc[v] + b;
+        settle(u);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = epi_row(row_base, v);
-            if (row < nrows) out[(int64_t)row * ld + col] = acc[v] + b;
+            if (row < nrows) out[(int64_t)row * ld + col] = u[v];
         }
     }
 };
@@ -415,16 +419,23 @@ template <int EPI> struct EpiLin {
             x[v] = EPI == 1 ? a.res[o] : EPI == 3 ? a.aux[o] : 0.f;
         }
         if (col >= ncols) return;
+        float u[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            u[v] = EPI <= 2 ? acc[v] + bias : acc[v];
+            if (EPI == 1) u[v] += x[v];
+            if (EPI == 3) u[v] *= lgelu_grad(x[v]);
+            if (EPI == 2) x[v] = lgelu(u[v]);
+        }
+        settle(u);
+        if (EPI == 2) settle(x);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = epi_row(row_base, v);
             if (row < nrows) {
                 const int64_t o = (int64_t)row * a.N + col;
-                if (EPI == 0) a.out[o] = acc[v] + bias;
-                if (EPI == 1) a.out[o] = acc[v] + bias + x[v];
-                if (EPI == 2) { const float u = acc[v] + bias; a.out[o] = u; a.out2[o] = lgelu(u); }
-                if (EPI == 3) a.out[o] = acc[v] * lgelu_grad(x[v]);
-                if (EPI == 4) a.out[o] = acc[v];
+                a.out[o] = u[v];
+                if (EPI == 2) a.out2[o] = x[v];
             }
         }
     }
@@ -440,16 +451,23 @@ template <int EPI> struct EpiLin {
             x[v] = EPI == 1 ? a.res[o] : EPI == 3 ? a.aux[o] : 0.f;
         }
         if (col >= ncols) return;
+        float u[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            u[v] = EPI <= 2 ? acc[v] + bias : acc[v];
+            if (EPI == 1) u[v] += x[v];
+            if (EPI == 3) u[v] *= lgelu_grad(x[v]);
+            if (EPI == 2) x[v] = lgelu(u[v]);
+        }
+        settle(u);
+        if (EPI == 2) settle(x);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = row_base + v;
             if (row < nrows) {
                 const int64_t o = (int64_t)row * a.N + col;
-                if (EPI == 0) a.out[o] = acc[v] + bias;
-                if (EPI == 1) a.out[o] = acc[v] + bias + x[v];
-                if (EPI == 2) { const float u = acc[v] + bias; a.out[o] = u; a.out2[o] = lgelu(u); }
-                if (EPI == 3) a.out[o] = acc[v] * lgelu_grad(x[v]);
-                if (EPI == 4) a.out[o] = acc[v];
+                a.out[o] = u[v];
+                if (EPI == 2) a.out2[o] = x[v];
             }
         }
     }
@@ -626,6 +644,18 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
             for (int v = 0; v < 4; ++v)
                 *reinterpret_cast<f32x2 *>(pp + (4 * g4 + v) * PW + 32 * pq + 2 * i) = f32x2{acc[2 * pq][v], acc[2 * pq + 1][v]};
     };
+    // what the pair-wise sums below read, under way during the contraction: T * w / 2 = 256 WB pairs of columns
+    auto p_row = [&](int u) { return (t + 256 * u) / (w / 2); };
+    auto p_col = [&](int u) { return 2 * ((t + 256 * u) % (w / 2)); };
+    float xr[2 * WB], bo[2 * WB], b2[2 * WB];
+#pragma unroll
+    for (int u = 0; u < WB; ++u)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            xr[2 * u + e] = a.X[(int64_t)min(m0 + p_row(u), M - 1) * w + p_col(u) + e];
+            bo[2 * u + e] = a.bo[p_col(u) + e];
+            b2[2 * u + e] = a.b2[p_col(u) + e];
+        }
     // ---- t = o W_o + b_o + x ----
     zero();
     c0.mul(bufA, PW, wave * (w / 4), 0, acc, i, g4);
@@ -633,10 +663,10 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
     c1.load(a.W1, f, 0, wave * w, 1, i, g4);
     to_part();
     __syncthreads();
-    for (int idx = t; idx < T * (w / 2); idx += 256) {
-        const int row = idx / (w / 2), col = 2 * (idx % (w / 2)), m = m0 + row, mc = min(m, M - 1);
-        const f32x2 xr = *reinterpret_cast<const f32x2 *>(a.X + (int64_t)mc * w + col);
-        f32x2 v = {a.bo[col] + xr[0], a.bo[col + 1] + xr[1]};
+#pragma unroll
+    for (int u = 0; u < WB; ++u) {
+        const int row = p_row(u), col = p_col(u);
+        f32x2 v = {bo[2 * u] + xr[2 * u], bo[2 * u + 1] + xr[2 * u + 1]};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const f32x2 pv = *reinterpret_cast<const f32x2 *>(part + ((size_t)q * T + row) * PW + col);
@@ -644,16 +674,18 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
             v[1] += pv[1];
         }
         *reinterpret_cast<f32x2 *>(bufT + row * PW + col) = v;
-        if (m < M) *reinterpret_cast<f32x2 *>(a.T + (int64_t)m * w + col) = v;
+        if (m0 + row < M) *reinterpret_cast<f32x2 *>(a.T + (int64_t)(m0 + row) * w + col) = v;
     }
     __syncthreads();
     // ---- LayerNorm 2: sixteen threads per row ----
     {
         const int row = t >> 4, sub = t & 15, m = m0 + row;
-        float x[NB], sum = 0.f;
+        float x[NB], g2[NB], h2[NB], sum = 0.f;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             x[q] = bufT[row * PW + sub + 16 * q];
+            g2[q] = a.g2[sub + 16 * q];
+            h2[q] = a.h2[sub + 16 * q];
             sum += x[q];
         }
 #pragma unroll
@@ -667,11 +699,13 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
         const float rstd = 1.f / sqrtf(ss / (float)w + 1e-5f);
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
-            const int c = sub + 16 * q;
-            const float y = (x[q] - mu) * rstd * a.g2[c] + a.h2[c];
-            bufA[row * PW + c] = y;
-            if (m < M) a.TN[(int64_t)m * w + c] = y;
+            x[q] = (x[q] - mu) * rstd * g2[q] + h2[q];
+            bufA[row * PW + sub + 16 * q] = x[q];
         }
+        settle(x);
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (m < M) a.TN[(int64_t)m * w + sub + 16 * q] = x[q];
         if (sub == 0 && m < M) {
             a.st2[2 * (int64_t)m] = mu;
             a.st2[2 * (int64_t)m + 1] = rstd;
@@ -679,6 +713,9 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
     }
     __syncthreads();
     // ---- f1 = tn W_1 + b_1, g = GELU(f1): this wavefront's w columns ----
+    float b1[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) b1[q] = a.b1[wave * w + 32 * (q >> 1) + 2 * i + (q & 1)];
     zero();
     c0.mul(bufA, PW, 0, 0, acc, i, g4);
     c0.load(a.W1, f, 0, wave * w, 2, i, g4);
@@ -691,11 +728,10 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
 #pragma unroll
     for (int pq = 0; pq < WB; ++pq) {
         const int col = wave * w + 32 * pq + 2 * i;
-        const f32x2 bb = *reinterpret_cast<const f32x2 *>(a.b1 + col);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 4 * g4 + v, m = m0 + row;
-            const f32x2 u = {acc[2 * pq][v] + bb[0], acc[2 * pq + 1][v] + bb[1]};
+            const f32x2 u = {acc[2 * pq][v] + b1[2 * pq], acc[2 * pq + 1][v] + b1[2 * pq + 1]};
             const f32x2 gl = {lgelu(u[0]), lgelu(u[1])};
             *reinterpret_cast<f32x2 *>(bufG + row * PF + col) = gl;
             if (m < M) {
@@ -715,10 +751,11 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_fwd(MlpArgs a)
     c1.mul(bufG, PF, wave * w, 3, acc, i, g4);
     to_part();
     __syncthreads();
-    for (int idx = t; idx < T * (w / 2); idx += 256) {
-        const int row = idx / (w / 2), col = 2 * (idx % (w / 2)), m = m0 + row;
+#pragma unroll
+    for (int u = 0; u < WB; ++u) {
+        const int row = p_row(u), col = p_col(u), m = m0 + row;
         const f32x2 tr = *reinterpret_cast<const f32x2 *>(bufT + row * PW + col);
-        f32x2 v = {a.b2[col] + tr[0], a.b2[col + 1] + tr[1]};
+        f32x2 v = {b2[2 * u] + tr[0], b2[2 * u + 1] + tr[1]};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const f32x2 pv = *reinterpret_cast<const f32x2 *>(part + ((size_t)q * T + row) * PW + col);
@@ -781,6 +818,15 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_bwd(MlpBwdArgs a
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             f1v[pq][v] = *reinterpret_cast<const f32x2 *>(a.F1 + (int64_t)min(m0 + 4 * g4 + v, M - 1) * f + wave * w + 32 * pq + 2 * i);
+    // and what the reverse of the LayerNorm reads (sixteen threads per row)
+    const int lrow = min(m0 + (t >> 4), M - 1);
+    const float mu = a.st2[2 * (int64_t)lrow], rstd = a.st2[2 * (int64_t)lrow + 1];
+    float tin[NB], g2[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        tin[q] = a.T[(int64_t)lrow * w + (t & 15) + 16 * q];
+        g2[q] = a.g2[(t & 15) + 16 * q];
+    }
     __syncthreads();
     f32x4 acc[NB];
     auto zero = [&]() {
@@ -832,16 +878,15 @@ template <int WB> __global__ __launch_bounds__(256) void k_lmlp_bwd(MlpBwdArgs a
     __syncthreads();
     // ---- reverse of LayerNorm 2: sixteen threads per row; dy xh and dy of every row go to `part` for the block sums ----
     {
-        const int row = t >> 4, sub = t & 15, m = m0 + row, mc = min(m, M - 1);
+        const int row = t >> 4, sub = t & 15, m = m0 + row;
         const bool rowok = m < M;
-        const float mu = a.st2[2 * (int64_t)mc], rstd = a.st2[2 * (int64_t)mc + 1];
         float xh[NB], dxh[NB], s1 = 0.f, s2 = 0.f;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int c = sub + 16 * q;
             const float dy = rowok ? bufA[row * PW + c] : 0.f;
-            xh[q] = rowok ? (a.T[(int64_t)mc * w + c] - mu) * rstd : 0.f;
-            dxh[q] = dy * a.g2[c];
+            xh[q] = rowok ? (tin[q] - mu) * rstd : 0.f;
+            dxh[q] = dy * g2[q];
             part[(size_t)row * PW + c] = dy * xh[q];
             part[((size_t)T + row) * PW + c] = dy;
             s1 += dxh[q];
@@ -905,14 +950,29 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_fwd(QkvArgs a)
     {
         const int row = t >> 4, sub = t & 15, m = m0 + row, mc = min(m, M - 1);
         const float lam = *a.lam;
-        float x[NB], sum = 0.f;
+        float x[NB], prev[NB], g1[NB], h1[NB], sum = 0.f;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
-            const int64_t o = (int64_t)mc * w + sub + 16 * q;
-            x[q] = lam * a.U[o] + (1.f - lam) * (a.Aprev ? a.Aprev[o] : 0.f);
-            if (m < M) a.X[o] = x[q];
+            x[q] = a.U[(int64_t)mc * w + sub + 16 * q];
+            g1[q] = a.g1[sub + 16 * q];
+            h1[q] = a.h1[sub + 16 * q];
+            prev[q] = 0.f;
+        }
+        if (a.Aprev) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q) prev[q] = a.Aprev[(int64_t)mc * w + sub + 16 * q];
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            x[q] = lam * x[q] + (1.f - lam) * prev[q];
             sum += x[q];
         }
+        settle(x);
+        settle(g1);
+        settle(h1);
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (m < M) a.X[(int64_t)m * w + sub + 16 * q] = x[q];
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) sum += __shfl_xor(sum, o, 64);
         const float mu = sum / (float)w;
@@ -925,7 +985,7 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_fwd(QkvArgs a)
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int c = sub + 16 * q;
-            const float y = (x[q] - mu) * rstd * a.g1[c] + a.h1[c];
+            const float y = (x[q] - mu) * rstd * g1[q] + h1[q];
             bufA[row * PW + c] = y;
             if (m < M) a.XN[(int64_t)m * w + c] = y;
         }
@@ -936,6 +996,9 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_fwd(QkvArgs a)
     }
     __syncthreads();
     if (wave >= 3) return;
+    float bb[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) bb[q] = a.bqkv[wave * w + 32 * (q >> 1) + 2 * i + (q & 1)];
     f32x4 acc[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -945,14 +1008,14 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_fwd(QkvArgs a)
     c1.load(a.Wqkv, 3 * w, 0, wave * w, 3, i, g4);
     c0.mul(bufA, PW, 0, 2, acc, i, g4);
     c1.mul(bufA, PW, 0, 3, acc, i, g4);
+    settle(bb);
 #pragma unroll
     for (int pq = 0; pq < WB; ++pq) {
         const int col = wave * w + 32 * pq + 2 * i;
-        const f32x2 bb = *reinterpret_cast<const f32x2 *>(a.bqkv + col);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int m = m0 + 4 * g4 + v;
-            if (m < M) *reinterpret_cast<f32x2 *>(a.QKV + (int64_t)m * 3 * w + col) = f32x2{acc[2 * pq][v] + bb[0], acc[2 * pq + 1][v] + bb[1]};
+            if (m < M) *reinterpret_cast<f32x2 *>(a.QKV + (int64_t)m * 3 * w + col) = f32x2{acc[2 * pq][v] + bb[2 * pq], acc[2 * pq + 1][v] + bb[2 * pq + 1]};
         }
     }
 }
@@ -1011,12 +1074,27 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_bwd(QkvBwdArgs a
         const float lam = *a.lam;
         const float mu = a.st1[2 * (int64_t)mc], rstd = a.st1[2 * (int64_t)mc + 1];
         float xh[NB], dxh[NB], s1 = 0.f, s2 = 0.f;
+        // everything this part reads, requested at once
+        float xin[NB], gin[NB], dt[NB], uin[NB], prev[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int64_t o = (int64_t)mc * w + sub + 16 * q;
+            xin[q] = a.X[o];
+            gin[q] = a.g1[sub + 16 * q];
+            dt[q] = a.DT[o];
+            uin[q] = a.U[o];
+            prev[q] = 0.f;
+        }
+        if (a.Aprev) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q) prev[q] = a.Aprev[(int64_t)mc * w + sub + 16 * q];
+        }
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int c = sub + 16 * q;
             const float dy = rowok ? bufA[row * PW + c] : 0.f;
-            xh[q] = rowok ? (a.X[(int64_t)mc * w + c] - mu) * rstd : 0.f;
-            dxh[q] = dy * a.g1[c];
+            xh[q] = rowok ? (xin[q] - mu) * rstd : 0.f;
+            dxh[q] = dy * gin[q];
             part[(size_t)row * PW + c] = dy * xh[q];
             part[((size_t)T + row) * PW + c] = dy;
             s1 += dxh[q];
@@ -1031,13 +1109,15 @@ template <int WB> __global__ __launch_bounds__(256) void k_lqkv_bwd(QkvBwdArgs a
         float dlam = 0.f;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
+            dt[q] += rstd * (dxh[q] - m1 - xh[q] * m2);
+            if (rowok) dlam += dt[q] * (uin[q] - prev[q]);
+        }
+        settle(dt);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
             const int64_t o = (int64_t)mc * w + sub + 16 * q;
-            const float dx = a.DT[o] + rstd * (dxh[q] - m1 - xh[q] * m2);
-            if (rowok) {
-                a.DX[o] = dx;
-                dlam += dx * (a.U[o] - (a.Aprev ? a.Aprev[o] : 0.f));
-                if (a.DAprev) a.DAprev[o] = (1.f - lam) * dx;
-            }
+            if (rowok) a.DX[o] = dt[q];
+            if (rowok && a.DAprev) a.DAprev[o] = (1.f - lam) * dt[q];
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) dlam += __shfl_xor(dlam, o, 64);
