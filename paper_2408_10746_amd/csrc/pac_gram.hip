@@ -46,8 +46,8 @@ constexpr int kChainPad = 8;     // bf16 elements of padding per LDS row
 constexpr int kMaxD = 4096;
 constexpr int kETileCols = 128; // columns of d one workgroup of the E contraction covers
 constexpr int kMaxSplitTiles = 512; // 16-token tiles one workgroup of the E contraction walks over at most
+constexpr int kMaxChainGroups = 16; // groups of layers of the layer-by-layer chains (gram_path_kind's limits and g = min(8, 1024 / r))
 constexpr int kMaxTiles = 8192;     // 16-token tiles of a batch (LDS table of the column-sum reduction)
-constexpr int kSeqTile = 128;       // side of the workgroup tile of a per-layer chain contraction
 
 // Slots of the chain kernels' LDS ring of per-token inputs.  Two suffice: the helper wavefront keeps the
 // tiles of the next two steps in registers and writes the tile of step s+1 while the contracting
@@ -126,12 +126,12 @@ void plan_gram_workspace(const Dims &D, WsLayout &W, int64_t &o)
     W.g_QpN = take(q_bytes);
     W.g_QpT = take(q_bytes);
     W.chain_group = 1;
+    W.chain_split = 0;
     W.g_P = W.g_ghat = W.g_QgN = W.g_QgT = 0;
     if (W.use_gram == 2) {
         // layers per group of the layer-by-layer chains: about 1024 columns per wide contraction
         const int g = 1024 / D.r;
         W.chain_group = g < 1 ? 1 : (g > 8 ? 8 : g);
-        W.g_P = take(D.Mmax * (int64_t)W.chain_group * D.r * 4);
         W.g_ghat = take((int64_t)D.B_max * Lr * 4);
         const int64_t in_group = (int64_t)cdiv(D.L, W.chain_group) * (W.chain_group * (W.chain_group - 1) / 2);
         W.g_QgN = take((in_group + 1) * D.r * D.r * 2);
@@ -152,6 +152,12 @@ void plan_gram_workspace(const Dims &D, WsLayout &W, int64_t &o)
     W.g_E = take((int64_t)D.L * D.d * D.r * 4);
     W.g_GGT = take(Lr * Lr * 2);
     W.g_GGsc = take(Lr * Lr * 2);
+    if (W.use_gram == 2) {
+        // The running sums of all groups (fp32 [groups][Mmax][g*r]) take the space of the contractions over the tokens, which are
+        // written after both chains; where that is too small they are kept for one group at a time.
+        W.chain_split = o - W.g_Epart >= D.Mmax * cdiv(D.L, W.chain_group) * W.chain_group * D.r * 4 && cdiv(D.L, W.chain_group) <= kMaxChainGroups;
+        W.g_P = W.chain_split ? W.g_Epart : take(D.Mmax * (int64_t)W.chain_group * D.r * 4);
+    }
     W.g_dlam_slots = cdiv(D.d, 64) * cdiv(D.r, 64);
     W.g_dlam_part = take((int64_t)D.L * W.g_dlam_slots * 4);
     W.g_samp_tile0 = take((kMaxBatch + 1) * 4);
@@ -1200,44 +1206,85 @@ template <bool FWD, int NT, int CMAX = kMaxClasses> __global__ __launch_bounds__
 // rows (l, .) of QT, both K-contiguous; the backward chain takes columns (l+1)*r.. of DP and rows (l, .)
 // of QN [(l,n)][(k,j)] = (1-lambda_k) Q_{lk}[n][j].
 //
-// The layers are taken in groups of g.  What the layers before a group contribute to all g layers of
-// the group is one wide contraction (K = all earlier layers, N = g*r: enough 128 x 128 tiles to fill
-// the chip without splitting K).  Inside the group each layer contracts over the group's earlier layers
-// and then adds the wide contraction's result and applies the nonlinearity, so that no partial sums
-// travel through memory more than once: up to r = 256 one launch walks all layers of the group per
-// 16-token tile (k_gseq_group), above that each layer is a short tiled contraction of its own
-// (k_gseq_layer).  The per-tile column sums the later launches need are taken from the finished bf16
-// arrays in one pass per direction.
+// The layers are taken in groups of g, and what earlier (later) groups contribute to a group comes from contractions over
+// ranges of groups: a range is cut in two, its first part walks its layers, then ONE contraction adds what that part
+// contributes to all of the second part (K = the first, N = the second), then the second part walks its own; both parts
+// are cut the same way.  The running sums wait in fp32 in P.  Where to cut is planned per call (seq_plan) from the tiles'
+// measured times: grids that leave the last round of tiles nearly full, and long K for the large tiles.  (One contraction
+// per group over everything before it does the same operations on g r = 1024 columns at a time, 328 tiles of 128 x 128 for
+// 5120 token rows: 32 layers of r = 512, both directions, 4.23 ms against 2.7 ms.)  Inside the group each layer contracts over
+// the group's earlier layers and then adds P and applies the nonlinearity: up to r = 256 one launch walks all layers of the
+// group per 16-token tile (k_gseq_group), above that each layer is a short tiled contraction of its own (k_gseq_layer).
+// The per-tile column sums the later launches need are taken from the finished bf16 arrays in one pass per direction.
 // ---------------------------------------------------------------------------
 struct SeqBigArgs {
     const bf16_t *A;  // H or DP [M][L*r]
     const bf16_t *Bq; // QT or QN [L*r][L*r]
-    float *P;         // [M][ldp]
+    float *P;         // [groups][M][ldp], the first group contributed to (rows of one group next to each other: rows of all
+                      // groups, a power of two apart, put a group's columns on an eighth of the memory channels)
     int L, r, M, ldp;
-    int brow0, ncols;  // rows (group's first layer) * r .. + ncols of Bq
-    int kbegin, kend;  // columns of A contracted
-    int ctiles;
+    int brow0, ncols; // rows of Bq
+    int kbegin, kend; // columns of A contracted
+    int rtiles, ctiles;
+    int add;          // P already holds what other ranges contributed
 };
 
+// Tiles of a wide chain contraction: 128 x 128 with four wavefronts, 128 x 256 with eight (both three stages, interleaved
+// sub-steps), 256 x 256 (pp_loop); one workgroup per compute unit each
+enum SeqForm { kSeq128 = 0, kSeq256 = 1, kSeqPp = 2 };
+template <int FORM, int BK> struct SeqBigTile {
+    using T = typename std::conditional<FORM == kSeqPp, PpTile,
+              typename std::conditional<FORM == kSeq256, NtTile<2, 4, 2, 2, BK, 3>, NtTile<2, 2, 2, 2, BK, 3>>::type>::type;
+};
 template <int BK> struct SeqShapes {
-    using TB = NtTile<2, 2, 2, 2, BK, 3>; // kSeqTile x kSeqTile, three stages, interleaved sub-steps: there is one such workgroup per compute unit
     using TS = NtTile<2, 2, 1, 1, BK, 3>; // 64 x 64 for the short contractions inside a group
-    static_assert(TB::BM == kSeqTile && TB::BN == kSeqTile, "tile side of the wide chain contraction");
 };
 
-template <int BK> __global__ __launch_bounds__(256) void k_gseq_big(SeqBigArgs a)
+struct EpiSeqBig {
+    static constexpr bool kBatched = true;
+    float *P;
+    int M, ldp;
+    bool add;
+    __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols) const
+    {
+        if (col >= ncols) return;
+        const int grp = col / ldp; // one for all 32 columns of a block: ldp is a multiple of 32
+        float *p = P + (int64_t)grp * M * ldp + (col - grp * ldp);
+        float out[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) out[v] = acc[v];
+        if (add) {
+            float old[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) old[v] = p[(int64_t)min(epi_row(row_base, v), nrows - 1) * ldp];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) out[v] += old[v];
+            settle(out);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int m = epi_row(row_base, v);
+            if (m < nrows) p[(int64_t)m * ldp] = out[v];
+        }
+    }
+};
+
+template <int FORM, int BK> __global__ __launch_bounds__(64 * (SeqBigTile<FORM, BK>::T::NW)) void k_gseq_big(SeqBigArgs a)
 {
-    using TL = typename SeqShapes<BK>::TB;
+    using TL = typename SeqBigTile<FORM, BK>::T;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    // a die's range of tiles: whole rows of column tiles, so that a row tile of A is fetched by one die only
+    // A die's range of tiles walks strips of four row tiles column by column: the 32 tiles a die works on at a time are
+    // 4 x 8 and share 12 operand panels in its L2 (one row of 32 tiles: 33).
     const int v = die_chunk_order(blockIdx.x, gridDim.x);
-    const int ct = v % a.ctiles, rt = v / a.ctiles;
+    const int strip = v / (4 * a.ctiles), in = v - strip * 4 * a.ctiles, rows = min(4, a.rtiles - 4 * strip);
+    const int ct = in / rows, rt = 4 * strip + in % rows;
     const int64_t Lr = (int64_t)a.L * a.r;
     const bf16_t *A = a.A, *Bq = a.Bq + (int64_t)a.brow0 * Lr;
     auto arow = [&](int m) { return A + (int64_t)m * Lr; };
     auto brow = [&](int n) { return Bq + (int64_t)n * Lr; };
-    EpiStoreF32 epi{a.P, a.ldp};
-    gemm_nt<TL, true>(smem, arow, brow, epi, a.kbegin, a.kend, rt * kSeqTile, ct * kSeqTile, a.M, a.ncols);
+    EpiSeqBig epi{a.P, a.M, a.ldp, a.add != 0};
+    if constexpr (FORM == kSeqPp) gemm_nt_pp(smem, arow, brow, epi, a.kbegin, a.kend, rt * TL::BM, ct * TL::BN, a.M, a.ncols);
+    else gemm_nt<TL, true>(smem, arow, brow, epi, a.kbegin, a.kend, rt * TL::BM, ct * TL::BN, a.M, a.ncols);
 }
 
 struct SeqLayerArgs {
@@ -2455,6 +2502,40 @@ static bool pp_pays(int64_t n256, int64_t n128, double steps)
     return n256 > 0 && (n256 / 256. + 0.8) * (15 + 1.65 * steps) < (n128 / 256. + 0.8) * (8 + 1.08 * steps);
 }
 
+// The wide contractions of the chains.  Estimated time of one over M rows, N columns and K (us): rounds of tiles x (start,
+// epilogue and the fp32 sums' way through memory + a step of 64 in K, dearer the fuller the chip); fitted on all three
+// tiles at 22 launches, 512 to 8192 rows, K and N 768 to 8192 (4096 each: 176 us on 128 x 128 tiles, 141 on 128 x 256, 113
+// on 256 x 256; 1024 each at 2048 rows: 17.0, 21.0, 30.1; 5120 rows, 2048 each: 74, 73, 63).
+struct SeqPick {
+    SeqForm form;
+    double us;
+};
+static SeqPick seq_pick(int M, int K, int N, bool k64)
+{
+    static const struct { int bm, bn; double start, step, fill; } kTiles[3] = {{128, 128, 8, 0.37, 0.24}, {128, 256, 8, 0.65, 0.33}, {256, 256, 13, 0.82, 0.68}};
+    SeqPick best{kSeq128, 0};
+    for (int f = 0; f < (k64 ? 3 : 2); ++f) { // pp_loop takes 64 of K a step
+        const int64_t tiles = (int64_t)cdiv(M, kTiles[f].bm) * cdiv(N, kTiles[f].bn);
+        const double us = cdiv(tiles, 256) * (kTiles[f].start + K / 64. * (kTiles[f].step + kTiles[f].fill * (tiles < 256 ? tiles / 256. : 1)));
+        if (f == 0 || us < best.us) best = SeqPick{(SeqForm)f, us};
+    }
+    return best;
+}
+
+// cut[n]: how many groups the first part of a range of n groups has, the least estimated time of all contractions inside it
+static void seq_plan(int M, int gr, int ngroups, bool k64, int (&cut)[kMaxChainGroups + 1])
+{
+    double best[kMaxChainGroups + 1] = {};
+    for (int n = 2; n <= ngroups; ++n)
+        for (int m = 1; m < n; ++m) {
+            const double us = best[m] + best[n - m] + seq_pick(M, m * gr, (n - m) * gr, k64).us;
+            if (m == 1 || us < best[n]) {
+                best[n] = us;
+                cut[n] = m;
+            }
+        }
+}
+
 // The tiles of a launch of the contractions over the tokens: the weights' nE (dispatched first) and those nG of the Gram
 // matrix's rows x 256 tiles that hold a pair of a row layer below a column layer (the rest of the grid is empty); fullest:
 // how many of both the fullest of the eight dies gets, blocks being dealt to them round-robin.
@@ -2691,33 +2772,50 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
     } else {
         // groups of W.chain_group layers: one wide contraction per group, then the group's own layers
         const bool k64 = r % 64 == 0;
-        const int big_lds = k64 ? SeqShapes<64>::TB::LDS_BYTES : SeqShapes<32>::TB::LDS_BYTES;
         const int small_lds = k64 ? SeqShapes<64>::TS::LDS_BYTES : SeqShapes<32>::TS::LDS_BYTES;
-        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<64>>(SeqShapes<64>::TB::LDS_BYTES)));
-        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<32>>(SeqShapes<32>::TB::LDS_BYTES)));
+        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeq128, 64>>(SeqBigTile<kSeq128, 64>::T::LDS_BYTES)));
+        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeq128, 32>>(SeqBigTile<kSeq128, 32>::T::LDS_BYTES)));
+        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeq256, 64>>(SeqBigTile<kSeq256, 64>::T::LDS_BYTES)));
+        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeq256, 32>>(SeqBigTile<kSeq256, 32>::T::LDS_BYTES)));
+        PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeqPp, 64>>(SeqBigTile<kSeqPp, 64>::T::LDS_BYTES)));
         PAC_HIP_TRY((allow_lds_once<&k_gseq_group<true>>(160 * 1024)));
         PAC_HIP_TRY((allow_lds_once<&k_gseq_group<false>>(160 * 1024)));
         float *P = (float *)(ws + W.g_P), *ghat = (float *)(ws + W.g_ghat);
-        const int g = W.chain_group, ldp = g * r;
-        const int rt128 = cdiv(M, kSeqTile), rt64 = cdiv(M, 64), ct64 = cdiv(r, 64);
-        auto chain_group = [&](bool fwd, int l0) {
-            const int l1 = l0 + g < L ? l0 + g : L;
-            const int cls = fwd ? KC_G_CHAIN_FWD : KC_G_CHAIN_BWD;
+        const int g = W.chain_group, ngroups = cdiv(L, g), ldp = g * r;
+        auto Pgroup = [&](int q) { return P + (W.chain_split ? (int64_t)q * M * ldp : 0); };
+        const int rt64 = cdiv(M, 64), ct64 = cdiv(r, 64);
+        // what groups [s0, s1) contribute to groups [d0, d1)
+        auto chain_big = [&](bool fwd, int s0, int s1, int d0, int d1, bool add) {
+            auto col = [&](int q) { return (q * g < L ? q * g : L) * r; };
             SeqBigArgs ba;
-            ba.A = fwd ? H : DP; ba.Bq = fwd ? QpT : QpN; ba.P = P; ba.L = L; ba.r = r; ba.M = M; ba.ldp = ldp;
-            ba.brow0 = l0 * r; ba.ncols = (l1 - l0) * r;
-            ba.kbegin = fwd ? 0 : l1 * r; ba.kend = fwd ? l0 * r : Lr;
-            ba.ctiles = cdiv(ba.ncols, kSeqTile);
-            const bool have_big = ba.kend > ba.kbegin;
-            if (have_big) {
-                if (k64) PAC_LAUNCH(prof, st, cls, k_gseq_big<64>, dim3(rt128 * ba.ctiles), dim3(256), big_lds, st, ba);
-                else PAC_LAUNCH(prof, st, cls, k_gseq_big<32>, dim3(rt128 * ba.ctiles), dim3(256), big_lds, st, ba);
-            }
+            ba.A = fwd ? H : DP; ba.Bq = fwd ? QpT : QpN; ba.P = Pgroup(d0); ba.L = L; ba.r = r; ba.M = M; ba.ldp = ldp;
+            ba.brow0 = col(d0); ba.ncols = col(d1) - col(d0);
+            ba.kbegin = col(s0); ba.kend = col(s1);
+            ba.add = add;
+            const SeqForm form = seq_pick(M, ba.kend - ba.kbegin, ba.ncols, k64).form;
+            auto launch = [&](auto kern, auto tile) {
+                using T = decltype(tile);
+                ba.rtiles = cdiv(M, T::BM);
+                ba.ctiles = cdiv(ba.ncols, T::BN);
+                PAC_LAUNCH(prof, st, fwd ? KC_G_CHAIN_FWD : KC_G_CHAIN_BWD, kern, dim3(ba.rtiles * ba.ctiles), dim3(64 * T::NW),
+                           T::LDS_BYTES, st, ba);
+            };
+            if (form == kSeqPp) launch(&k_gseq_big<kSeqPp, 64>, SeqBigTile<kSeqPp, 64>::T());
+            else if (form == kSeq256 && k64) launch(&k_gseq_big<kSeq256, 64>, SeqBigTile<kSeq256, 64>::T());
+            else if (form == kSeq256) launch(&k_gseq_big<kSeq256, 32>, SeqBigTile<kSeq256, 32>::T());
+            else if (k64) launch(&k_gseq_big<kSeq128, 64>, SeqBigTile<kSeq128, 64>::T());
+            else launch(&k_gseq_big<kSeq128, 32>, SeqBigTile<kSeq128, 32>::T());
+        };
+        // the layers of group q, P holding what the groups before (backward: after) it contribute
+        auto chain_group = [&](bool fwd, int q) {
+            const int l0 = q * g, l1 = l0 + g < L ? l0 + g : L;
+            const int cls = fwd ? KC_G_CHAIN_FWD : KC_G_CHAIN_BWD;
+            const float *Pg = (fwd ? l0 > 0 : l1 < L) ? Pgroup(q) : nullptr;
             if (r <= kGroupMaxR) {
                 // one launch for the group's layers (wider adapters: one launch per layer, below)
                 SeqGroupArgs ga;
                 SeqLayerArgs &la = ga.la;
-                la.A = ba.A; la.Bq = ba.Bq; la.P = have_big ? P : nullptr; la.ldp = ldp; la.pcol0 = 0;
+                la.A = fwd ? H : DP; la.Bq = fwd ? QpT : QpN; la.P = Pg; la.ldp = ldp; la.pcol0 = 0;
                 la.l = l0; la.L = L; la.r = r; la.M = M; la.d = d;
                 la.kbegin = 0; la.kend = 0; la.ctiles = 0;
                 la.U = pre; la.Gp = ca.Gp; la.chat = chat; la.params = io.params; la.PL = D.PL;
@@ -2730,10 +2828,10 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
                 else PAC_LAUNCH(prof, st, cls, (k_gseq_group<false>), grid, block, lds, st, ga);
                 return;
             }
-            for (int q = 0; q < l1 - l0; ++q) {
-                const int l = fwd ? l0 + q : l1 - 1 - q;
+            for (int i = 0; i < l1 - l0; ++i) {
+                const int l = fwd ? l0 + i : l1 - 1 - i;
                 SeqLayerArgs la;
-                la.A = ba.A; la.Bq = ba.Bq; la.P = have_big ? P : nullptr; la.ldp = ldp; la.pcol0 = (l - l0) * r;
+                la.A = fwd ? H : DP; la.Bq = fwd ? QpT : QpN; la.P = Pg; la.ldp = ldp; la.pcol0 = (l - l0) * r;
                 la.l = l; la.L = L; la.r = r; la.M = M; la.d = d;
                 la.kbegin = fwd ? l0 * r : (l + 1) * r; la.kend = fwd ? l * r : l1 * r; la.ctiles = ct64;
                 la.U = pre; la.Gp = ca.Gp; la.chat = chat; la.params = io.params; la.PL = D.PL;
@@ -2748,8 +2846,31 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
                 }
             }
         };
-        const int ngroups = cdiv(L, g);
-        for (int q = 0; q < ngroups; ++q) chain_group(true, q * g);
+        int cut[kMaxChainGroups + 1];
+        if (W.chain_split) seq_plan(M, g * r, ngroups, k64, cut);
+        auto chain = [&](auto &self, bool fwd, int q0, int q1) -> void {
+            if (q1 - q0 == 1) return chain_group(fwd, q0);
+            if (!W.chain_split) { // no room for every group's sums: group by group
+                for (int i = q0; i < q1; ++i) {
+                    const int q = fwd ? i : q1 - 1 - i;
+                    if (i > q0) chain_big(fwd, fwd ? q0 : q + 1, fwd ? q : q1, q, q + 1, false);
+                    chain_group(fwd, q);
+                }
+                return;
+            }
+            // a group's first share comes from the range that starts with the chain's first group: stored, not added
+            const int mid = fwd ? q0 + cut[q1 - q0] : q1 - cut[q1 - q0];
+            if (fwd) {
+                self(self, fwd, q0, mid);
+                chain_big(fwd, q0, mid, mid, q1, q0 > 0);
+                self(self, fwd, mid, q1);
+            } else {
+                self(self, fwd, mid, q1);
+                chain_big(fwd, mid, q1, q0, mid, q1 < ngroups);
+                self(self, fwd, q0, mid);
+            }
+        };
+        chain(chain, true, 0, ngroups);
         PAC_LAUNCH(prof, st, KC_G_CHAIN_FWD, k_gseq_colsum, dim3(ntiles, cdiv(Lr, 256)), dim3(256), 0, st, H, Lr, tile_row0,
                    tile_rows, HSpart);
         PAC_LAUNCH(prof, st, KC_G_HEAD, k_gseq_zpart, dim3(ntiles), dim3(256), 0, st, HSpart, V, Lr, C, zpart);
@@ -2760,7 +2881,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
             return hipGetLastError();
         }
         PAC_LAUNCH(prof, st, KC_G_CHAIN_BWD, k_gseq_ghat, dim3(cdiv(Lr, 256), B), dim3(256), 0, st, dz, V, samp_len, Lr, C, ghat);
-        for (int q = ngroups - 1; q >= 0; --q) chain_group(false, q * g);
+        chain(chain, false, 0, ngroups);
         PAC_LAUNCH(prof, st, KC_G_CHAIN_BWD, k_gseq_colsum, dim3(ntiles, cdiv(Lr, 256)), dim3(256), 0, st, DP, Lr, tile_row0,
                    tile_rows, cspart);
     }

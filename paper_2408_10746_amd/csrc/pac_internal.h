@@ -38,7 +38,8 @@ struct WsLayout {
     int32_t pairs;      // L (L - 1) / 2 layer pairs k < l
     int32_t se, sg;     // token splits of the E and Gram contractions
     int32_t chain_group; // layers per group of the layer-by-layer chains
-    int64_t g_P;        // f32 [Mmax][chain_group * r]: what the layers outside a group contribute to the group's layers
+    int32_t chain_split; // their contributions to each other as planned ranges (else group by group)
+    int64_t g_P;        // f32 [groups][M][chain_group * r] (else one group's): what other groups contribute to a group's layers
     int64_t g_ghat;     // f32 [B_max][L*r]
     int64_t g_tile_row0, g_tile_rows, g_tile_samp;
     int64_t g_WuTs, g_Wds;          // bf16 [d][L*r] stacked projection copies
