@@ -251,13 +251,20 @@ template <typename TC> struct EpiFwdDown {
     __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols) const
     {
         const float cd = c_down[min(col, ncols - 1)];
+        float u[16], g[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            u[v] = acc[v] + cd;
+            g[v] = gelu_f(u[v]);
+        }
+        settle(u);
+        settle(g);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = epi_row(row_base, v);
             if (row < nrows && col < ncols) {
-                const float u = acc[v] + cd;
-                pre[(int64_t)row * r + col] = u;
-                h[(int64_t)row * r + col] = to_tc(gelu_f(u), TC());
+                pre[(int64_t)row * r + col] = u[v];
+                h[(int64_t)row * r + col] = to_tc(g[v], TC());
             }
         }
     }
@@ -322,7 +329,7 @@ struct RowPlain {
 };
 
 // a: this lane's row (lane % 16 of the tile, clamped by the caller) at k = 0; B rows of length K, K a multiple of 16;
-// epi(row, col, value) for rows < nrows and columns < ncols
+// per element epi.put(row, col, epi.value(sum, epi.fetch(row, col))) for rows < nrows and columns < ncols
 template <int NB, class ARow, class Epi>
 __device__ __forceinline__ void rows16_gemm(float *red /* kRowWaves * NB * 256 floats */, const ARow &a, const float *B, int K,
                                             int row0, int col0, int nrows, int ncols, const Epi &epi)
@@ -334,6 +341,12 @@ __device__ __forceinline__ void rows16_gemm(float *red /* kRowWaves * NB * 256 f
     f32x4 acc[NB];
 #pragma unroll
     for (int y = 0; y < NB; ++y) acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int NE = NB / 2; // of the NB * 256 sums, per thread
+    auto e_row = [&](int q) { const int e = threadIdx.x + q * 64 * kRowWaves; return row0 + 4 * ((e & 63) >> 4) + ((e >> 6) & 3); };
+    auto e_col = [&](int q) { const int e = threadIdx.x + q * 64 * kRowWaves; return col0 + 16 * (e >> 8) + (e & 15); };
+    float in[NE]; // what the epilogue reads, under way during the contraction
+#pragma unroll
+    for (int q = 0; q < NE; ++q) in[q] = epi.fetch(min(e_row(q), nrows - 1), min(e_col(q), ncols - 1));
     const int units = K / 16;
     const int u0 = units * wave / kRowWaves, u1 = units * (wave + 1) / kRowWaves;
     if (u0 < u1) {
@@ -363,13 +376,18 @@ __device__ __forceinline__ void rows16_gemm(float *red /* kRowWaves * NB * 256 f
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[((wave * NB + y) * 4 + v) * 64 + lane] = acc[y][v];
     __syncthreads();
-    for (int e = threadIdx.x; e < NB * 256; e += 64 * kRowWaves) {
-        float sum = 0.f;
+    float sum[NE];
 #pragma unroll
-        for (int w = 0; w < kRowWaves; ++w) sum += red[w * NB * 256 + e];
-        const int ln = e & 63;
-        const int row = row0 + 4 * (ln >> 4) + ((e >> 6) & 3), col = col0 + 16 * (e >> 8) + (ln & 15);
-        if (row < nrows && col < ncols) epi(row, col, sum);
+    for (int q = 0; q < NE; ++q) {
+        sum[q] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kRowWaves; ++w) sum[q] += red[w * NB * 256 + threadIdx.x + q * 64 * kRowWaves];
+        sum[q] = epi.value(sum[q], in[q]);
+    }
+    settle(sum);
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        if (e_row(q) < nrows && e_col(q) < ncols) epi.put(e_row(q), e_col(q), sum[q]);
     }
 }
 
@@ -399,16 +417,22 @@ static bool rows16_pays(int M, int ncols, bool long_steps)
     return 2 * rounds16 * (2 + nb) < 19 * (1 + rounds64) + (long_steps ? 0 : 3);
 }
 
+struct EpiDown16 {
+    const FwdDownArgs<float> &a;
+    __device__ float fetch(int, int col) const { return a.c_down[col]; }
+    __device__ float value(float sum, float c) const { return sum + c; }
+    __device__ void put(int row, int col, float u) const
+    {
+        a.pre[(int64_t)row * a.r + col] = u;
+        a.h[(int64_t)row * a.r + col] = gelu_f(u);
+    }
+};
 template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_fwd_down16(FwdDownArgs<float> a)
 {
     __shared__ float red[kRowWaves * NB * 256];
     const int row0 = blockIdx.x * 16, row = min(row0 + (int)(threadIdx.x & 15), a.map.M - 1);
     const float *b = a.cache + a.map.rowoff[row] + (int64_t)a.layer * a.map.rowstride[row];
-    auto epi = [&](int rr, int col, float v) {
-        const float u = v + a.c_down[col];
-        a.pre[(int64_t)rr * a.r + col] = u;
-        a.h[(int64_t)rr * a.r + col] = gelu_f(u);
-    };
+    const EpiDown16 epi{a};
     if (a.s_prev)
         rows16_gemm<NB>(red, RowX<true>{b, a.s_prev + (int64_t)row * a.d, *a.lam}, a.WdT, a.d, row0, blockIdx.y * 16 * NB, a.map.M, a.r, epi);
     else
@@ -434,14 +458,20 @@ struct EpiFwdUp {
     {
         const int cc = min(col, ncols - 1);
         const float cu = c_up[cc];
-        float sp[16];
+        float s[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-            sp[v] = s_prev ? s_prev[(int64_t)min(epi_row(row_base, v), nrows - 1) * d + cc] : 0.f;
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        if (s_prev) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = s_prev[(int64_t)min(epi_row(row_base, v), nrows - 1) * d + cc];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = s[v] + acc[v] + cu;
+        settle(s);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = epi_row(row_base, v);
-            if (row < nrows && col < ncols) s_out[(int64_t)row * d + col] = sp[v] + acc[v] + cu;
+            if (row < nrows && col < ncols) s_out[(int64_t)row * d + col] = s[v];
         }
     }
 };
@@ -529,18 +559,17 @@ __global__ __launch_bounds__(256) void k_head(const float *__restrict__ logits_w
 }
 
 // dW_cls, dc_cls, and ds_L[m][j] = (dz_s W_cls^T)[j] / len_s for every token row
-__global__ __launch_bounds__(256) void k_head_bwd(const float *__restrict__ pooled, const float *__restrict__ Wcls,
-                                                  const float *__restrict__ dz, int B, int M, int d, int C,
-                                                  const int32_t *__restrict__ rowsamp,
-                                                  const int32_t *__restrict__ samp_len, float *__restrict__ gWcls,
-                                                  float *__restrict__ gccls, float *__restrict__ ds,
-                                                  int rows_per_block)
+__device__ __forceinline__ void head_bwd(const float *__restrict__ pooled, const float *__restrict__ Wcls,
+                                         const float *__restrict__ dz, int B, int M, int d, int C,
+                                         const int32_t *__restrict__ rowsamp,
+                                         const int32_t *__restrict__ samp_len, float *__restrict__ gWcls,
+                                         float *__restrict__ gccls, float *__restrict__ ds,
+                                         int rows_per_block, int bx, int by, float *sdz /* kMaxBatch * kMaxClasses */)
 {
-    __shared__ float sdz[kMaxBatch * kMaxClasses];
     for (int i = threadIdx.x; i < B * C; i += 256) sdz[i] = dz[i];
     __syncthreads();
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < C) {
+    const int j = bx * 256 + threadIdx.x;
+    if (bx == 0 && by == 0 && (int)threadIdx.x < C) {
         float acc = 0.f;
         for (int s = 0; s < B; ++s) acc += sdz[s * C + threadIdx.x];
         gccls[threadIdx.x] = acc;
@@ -548,14 +577,14 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *__restrict__ pool
     if (j >= d) return;
     float w[kMaxClasses];
     for (int c = 0; c < C; ++c) w[c] = Wcls[(int64_t)j * C + c];
-    if (blockIdx.y == 0) {
+    if (by == 0) {
         for (int c = 0; c < C; ++c) {
             float acc = 0.f;
             for (int s = 0; s < B; ++s) acc += pooled[(int64_t)s * d + j] * sdz[s * C + c];
             gWcls[(int64_t)j * C + c] = acc;
         }
     }
-    const int m0 = blockIdx.y * rows_per_block;
+    const int m0 = by * rows_per_block;
     const int m1 = min(M, m0 + rows_per_block);
     int cur = -1;
     float val = 0.f;
@@ -594,44 +623,104 @@ template <typename TC> struct EpiDpre {
 #pragma unroll
         for (int v = 0; v < 16; ++v) pv[v] = pre[(int64_t)min(epi_row(row_base, v), nrows - 1) * r + cc];
 #pragma unroll
+        for (int v = 0; v < 16; ++v) pv[v] = acc[v] * gelu_grad_f(pv[v]);
+        settle(pv);
+#pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = epi_row(row_base, v);
-            if (row < nrows && col < ncols) dpre[(int64_t)row * r + col] = to_tc(acc[v] * gelu_grad_f(pv[v]), TC());
+            if (row < nrows && col < ncols) dpre[(int64_t)row * r + col] = to_tc(pv[v], TC());
         }
     }
 };
 
-template <typename TC, int KU> __global__ __launch_bounds__(256) void k_bwd_dpre(BwdDpreArgs<TC> a)
+// grads of one layer = ordered sum of the split partials; dlambda = ordered sum of the dx partials.  It rides on the launch
+// of the next layer's dpre (which needs nothing of it): nr workgroups behind that launch's own.
+struct ReduceArgs {
+    const float *part;
+    int splits;
+    int64_t PL;
+    const float *dlam_part;
+    int nslots;
+    float *g_layer;
+};
+template <int NT> __device__ __forceinline__ void reduce_layer(const ReduceArgs &a, int blk, float *red /* 256 floats of LDS */)
+{
+    const int t = threadIdx.x;
+    const int64_t i = (int64_t)blk * NT + t;
+    if (i < a.PL - 1) {
+        float acc = 0.f;
+#pragma unroll 4
+        for (int s = 0; s < a.splits; ++s) acc += a.part[(int64_t)s * a.PL + i];
+        a.g_layer[i] = acc;
+    }
+    if ((int64_t)blk == (a.PL - 1) / NT) {
+        // the gate: the workgroup that owns it sums the dx partials, each of 256 threads a strided share in
+        // slot order, the 256 shares combined in a fixed tree
+        if (t < 256) {
+            float acc = 0.f;
+            for (int s0 = t; s0 < a.nslots; s0 += 256 * 8) {
+                float p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) p[u] = a.dlam_part[min(s0 + 256 * u, a.nslots - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (s0 + 256 * u < a.nslots) acc += p[u];
+            }
+            red[t] = acc;
+        }
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (t < w) red[t] += red[t + w];
+            __syncthreads();
+        }
+        if (t == 0) a.g_layer[a.PL - 1] = red[0];
+    }
+}
+__global__ __launch_bounds__(256) void k_reduce_layer(ReduceArgs a)
+{
+    __shared__ float red[256];
+    reduce_layer<256>(a, blockIdx.x, red);
+}
+
+// nd workgroups of 64 x 64 tiles (row tiles fastest), the rest reduce the layer above
+template <typename TC, int KU> __global__ __launch_bounds__(256) void k_bwd_dpre(BwdDpreArgs<TC> a, ReduceArgs ra, int nd)
 {
     __shared__ __attribute__((aligned(16))) char smem[tile_lds_bytes<TC, T64U<KU>>()];
+    static_assert(tile_lds_bytes<TC, T64U<KU>>() >= 256 * 4, "scratch of the reduction");
+    if ((int)blockIdx.x >= nd) return reduce_layer<256>(ra, blockIdx.x - nd, reinterpret_cast<float *>(smem));
+    const int mt = (a.M + 63) / 64;
     LoadRowsF32<TC, 64, KU> al;
     al.src = a.ds; al.ld = a.d; al.nrows = a.M;
     LoadRowsTC<TC, 64, KU> bl;
     bl.src = a.Wu; bl.ld = a.d; bl.nrows = a.r;
     EpiDpre<TC> epi{a.pre, a.dpre, a.r};
-    gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.d, blockIdx.x * 64, blockIdx.y * 64, a.M, a.r);
+    gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.d, blockIdx.x % mt * 64, blockIdx.x / mt * 64, a.M, a.r);
 }
 
-template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_bwd_dpre16(BwdDpreArgs<float> a)
+struct EpiDpre16 {
+    const BwdDpreArgs<float> &a;
+    __device__ float fetch(int row, int col) const { return a.pre[(int64_t)row * a.r + col]; }
+    __device__ float value(float sum, float pre) const { return sum * gelu_grad_f(pre); }
+    __device__ void put(int row, int col, float v) const { a.dpre[(int64_t)row * a.r + col] = v; }
+};
+template <int NB> __global__ __launch_bounds__(64 * kRowWaves) void k_bwd_dpre16(BwdDpreArgs<float> a, ReduceArgs ra, int nd)
 {
     __shared__ float red[kRowWaves * NB * 256];
-    const int row0 = blockIdx.x * 16, row = min(row0 + (int)(threadIdx.x & 15), a.M - 1);
-    rows16_gemm<NB>(red, RowPlain{a.ds + (int64_t)row * a.d}, a.Wu, a.d, row0, blockIdx.y * 16 * NB, a.M, a.r,
-                    [&](int rr, int col, float v) {
-                        const int64_t o = (int64_t)rr * a.r + col;
-                        a.dpre[o] = v * gelu_grad_f(a.pre[o]);
-                    });
+    if ((int)blockIdx.x >= nd) return reduce_layer<64 * kRowWaves>(ra, blockIdx.x - nd, red);
+    const int mt = (a.M + 15) / 16;
+    const int row0 = blockIdx.x % mt * 16, row = min(row0 + (int)(threadIdx.x & 15), a.M - 1);
+    rows16_gemm<NB>(red, RowPlain{a.ds + (int64_t)row * a.d}, a.Wu, a.d, row0, blockIdx.x / mt * 16 * NB, a.M, a.r, EpiDpre16{a});
 }
 
 // Top layer: ds_L is the same vector for every token of a sample (dp_s / len_s), so
 // dh_L = ds_L W_up^{LT} is computed once per sample in fp32 instead of through the matrix cores
 // (rounding that vector to bf16 would put the same error on every token of the sample).
-__global__ __launch_bounds__(256) void k_dh_top(const float *__restrict__ dz, const float *__restrict__ Wcls,
-                                                const float *__restrict__ Wu /* [r][d] fp32 */,
-                                                const int32_t *__restrict__ samp_len, int B, int d, int r, int C,
-                                                float *__restrict__ dh /* [B][r] */)
+__device__ __forceinline__ void dh_top(const float *__restrict__ dz, const float *__restrict__ Wcls,
+                                       const float *__restrict__ Wu /* [r][d] fp32 */,
+                                       const int32_t *__restrict__ samp_len, int B, int d, int r, int C,
+                                       float *__restrict__ dh /* [B][r] */, int blk)
 {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row = blk * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= B * r) return;
     const int s = row / r, k = row % r;
     float acc = 0.f;
@@ -645,6 +734,26 @@ __global__ __launch_bounds__(256) void k_dh_top(const float *__restrict__ dz, co
     if (lane == 0) dh[row] = acc / (float)samp_len[s];
 }
 
+// What needs dz and nothing else: nt workgroups of dh_top (long chains of loads: dispatched first), then head_bwd
+struct HeadBwdArgs {
+    const float *pooled, *Wcls, *dz;
+    int B, M, d, r, C;
+    const int32_t *rowsamp, *samp_len;
+    float *gWcls, *gccls, *ds;
+    int rows_per_block;
+    const float *Wu_top;
+    float *dh;
+    int nt;
+};
+__global__ __launch_bounds__(256) void k_head_bwd(HeadBwdArgs a)
+{
+    __shared__ float sdz[kMaxBatch * kMaxClasses];
+    if ((int)blockIdx.x < a.nt) return dh_top(a.dz, a.Wcls, a.Wu_top, a.samp_len, a.B, a.d, a.r, a.C, a.dh, blockIdx.x);
+    const int b = blockIdx.x - a.nt, nx = (a.d + 255) / 256;
+    head_bwd(a.pooled, a.Wcls, a.dz, a.B, a.M, a.d, a.C, a.rowsamp, a.samp_len, a.gWcls, a.gccls, a.ds, a.rows_per_block,
+             b % nx, b / nx, sdz);
+}
+
 template <typename TC>
 __global__ __launch_bounds__(256) void k_dpre_top(const float *__restrict__ dh, const float *__restrict__ pre,
                                                   const int32_t *__restrict__ rowsamp, int M, int r,
@@ -656,9 +765,8 @@ __global__ __launch_bounds__(256) void k_dpre_top(const float *__restrict__ dh, 
     dpre[idx] = to_tc(dh[rowsamp[m] * r + k] * gelu_grad_f(pre[idx]), TC());
 }
 
-// Token reductions.  blockIdx.z = 0: dW_up[r][d] = h^T ds, dc_up = colsum(ds);
-//                    blockIdx.z = 1: dW_down[d][r] = x^T dpre, dc_down = colsum(dpre).
-// blockIdx.y = split over token rows; results go to part[split] in the layer-block layout.
+// Token reductions, split over token rows: dW_up[r][d] = h^T ds, dc_up = colsum(ds) (the first tiles * splits workgroups) and
+// dW_down[d][r] = x^T dpre, dc_down = colsum(dpre).  Results go to part[split] in the layer-block layout.
 template <typename TC> struct BwdWgradArgs {
     const TC *cache;
     RowMap map;
@@ -671,6 +779,7 @@ template <typename TC> struct BwdWgradArgs {
     float *part;     // [splits][PL]
     int64_t PL;
     int rows_per_split; // multiple of the K step
+    int tiles, splits;  // workgroups: tile fastest, then split, then which of the two
 };
 
 struct EpiStore {
@@ -697,18 +806,18 @@ __device__ __forceinline__ void write_colsums(BL &bl, float *red /* 256 * CE flo
     }
 }
 
-template <typename TC> __global__ __launch_bounds__(256) void k_bwd_wgrad(BwdWgradArgs<TC> a)
+template <typename TC> __device__ __forceinline__ void bwd_wgrad_tile(const BwdWgradArgs<TC> &a, int blk, char *smem)
 {
-    __shared__ __attribute__((aligned(16))) char smem[tile_lds_bytes<TC, T64K>()];
     static_assert(tile_lds_bytes<TC, T64K>() >= 256 * 8 * 4, "column-sum scratch must fit");
     const int M = a.map.M;
-    const int kbegin = blockIdx.y * a.rows_per_split;
+    const int tile = blk % a.tiles, split = blk / a.tiles % a.splits;
+    const int kbegin = split * a.rows_per_split;
     const int kend = min(M, kbegin + a.rows_per_split);
-    float *part = a.part + (int64_t)blockIdx.y * a.PL;
+    float *part = a.part + (int64_t)split * a.PL;
     const int64_t dr = (int64_t)a.d * a.r;
-    if (blockIdx.z == 0) {
+    if (blk < a.tiles * a.splits) {
         const int tj = a.d / 64 + (a.d % 64 ? 1 : 0);
-        const int ti = blockIdx.x / tj, tjx = blockIdx.x % tj;
+        const int ti = tile / tj, tjx = tile % tj;
         LoadCols<TC, 64, 4, TC, false> al;
         al.src = a.h; al.ld = a.r; al.ncols = a.r; al.kend = kend;
         LoadCols<TC, 64, 4, float, true> bl;
@@ -718,7 +827,7 @@ template <typename TC> __global__ __launch_bounds__(256) void k_bwd_wgrad(BwdWgr
         if (ti == 0) write_colsums<TC>(bl, reinterpret_cast<float *>(smem), part + 2 * dr + a.r, a.d, tjx * 64);
     } else {
         const int tj = a.r / 64 + (a.r % 64 ? 1 : 0);
-        const int ti = blockIdx.x / tj, tjx = blockIdx.x % tj;
+        const int ti = tile / tj, tjx = tile % tj;
         LoadCols<TC, 64, 4, TC, true> bl;
         bl.src = a.dpre; bl.ld = a.r; bl.ncols = a.r; bl.kend = kend;
         EpiStore epi{part, a.r};
@@ -737,7 +846,7 @@ template <typename TC> __global__ __launch_bounds__(256) void k_bwd_wgrad(BwdWgr
     }
 }
 
-// dx = dpre W_down^T ; dlambda partial ; ds <- ds + (1 - lambda) dx   (in place)
+// dx = dpre W_down^T ; dlambda partial ; ds_out = ds + (1 - lambda) dx
 template <typename TC> struct BwdDxArgs {
     const TC *dpre; // [M][r]
     const TC *Wd;   // [d][r]
@@ -746,8 +855,10 @@ template <typename TC> struct BwdDxArgs {
     int layer, d, r;
     const float *s_prev; // or null
     const float *lam;
-    float *ds;        // [M][d] in/out
+    const float *ds;  // [M][d]
+    float *ds_out;    // [M][d], another array: the token reductions read ds in the same launch
     float *dlam_part; // one per workgroup
+    int mt;           // row tiles
 };
 
 template <typename TC> struct EpiDx {
@@ -757,7 +868,8 @@ template <typename TC> struct EpiDx {
     int layer, d;
     const float *s_prev;
     float lam;
-    float *ds;
+    const float *ds;
+    float *ds_out;
     float dlam;
     __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols)
     {
@@ -784,58 +896,36 @@ template <typename TC> struct EpiDx {
             const int row = epi_row(row_base, v);
             if (row < nrows && col < ncols) {
                 dlam += (b[v] - s[v]) * acc[v];
-                ds[(int64_t)row * d + col] = dsv[v] + (1.f - lam) * acc[v];
+                ds_out[(int64_t)row * d + col] = dsv[v] + (1.f - lam) * acc[v];
             }
         }
     }
 };
 
-template <typename TC, int KU> __global__ __launch_bounds__(256) void k_bwd_dx(BwdDxArgs<TC> a)
+template <typename TC, int KU> __device__ __forceinline__ void bwd_dx_tile(const BwdDxArgs<TC> &a, int blk, char *smem, float *red)
 {
-    __shared__ __attribute__((aligned(16))) char smem[tile_lds_bytes<TC, T64U<KU>>()];
-    __shared__ float red[4];
+    const int mt = blk % a.mt, ct = blk / a.mt;
     LoadRowsTC<TC, 64, KU> al;
     al.src = a.dpre; al.ld = a.r; al.nrows = a.map.M;
     LoadRowsTC<TC, 64, KU> bl;
     bl.src = a.Wd; bl.ld = a.r; bl.nrows = a.d;
-    EpiDx<TC> epi{a.cache, a.map, a.layer, a.d, a.s_prev, *a.lam, a.ds, 0.f};
-    gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.r, blockIdx.x * 64, blockIdx.y * 64, a.map.M, a.d);
+    EpiDx<TC> epi{a.cache, a.map, a.layer, a.d, a.s_prev, *a.lam, a.ds, a.ds_out, 0.f};
+    gemm_tile<TC, T64U<KU>>(smem, al, bl, epi, 0, a.r, mt * 64, ct * 64, a.map.M, a.d);
     const float tot = block_sum(epi.dlam, red);
-    if (threadIdx.x == 0) a.dlam_part[blockIdx.y * gridDim.x + blockIdx.x] = tot;
+    if (threadIdx.x == 0) a.dlam_part[blk] = tot;
 }
 
-// grads of one layer = ordered sum of the split partials; dlambda = ordered sum of the dx partials
-__global__ __launch_bounds__(256) void k_reduce_layer(const float *__restrict__ part, int splits, int64_t PL,
-                                                      const float *__restrict__ dlam_part, int nslots,
-                                                      float *__restrict__ g_layer)
+// What a layer's backward does once dpre is known: the token reductions (nw workgroups) and dx, neither of which needs the
+// other's results, in one launch.  Alone either leaves the chip partly idle (512 rows, d = 256: 12.5 and 5.5 us one behind
+// the other; 4096 rows, d = 768, r = 96: 26.0 and 16.6).
+template <typename TC, int KU> __global__ __launch_bounds__(256) void k_bwd_layer(BwdWgradArgs<TC> wa, BwdDxArgs<TC> xa, int nw, int blk_off)
 {
-    __shared__ float red[256];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < PL - 1) {
-        float acc = 0.f;
-        for (int s = 0; s < splits; ++s) acc += part[(int64_t)s * PL + i];
-        g_layer[i] = acc;
-    }
-    if ((int64_t)blockIdx.x == (PL - 1) / 256) {
-        // the gate: the workgroup that owns it sums the dx partials, each thread a strided share in
-        // slot order, the 256 shares combined in a fixed tree
-        float acc = 0.f;
-        for (int s0 = threadIdx.x; s0 < nslots; s0 += 256 * 8) {
-            float p[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) p[u] = dlam_part[min(s0 + 256 * u, nslots - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (s0 + 256 * u < nslots) acc += p[u];
-        }
-        red[threadIdx.x] = acc;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) g_layer[PL - 1] = red[0];
-    }
+    constexpr int kW = tile_lds_bytes<TC, T64K>(), kX = tile_lds_bytes<TC, T64U<KU>>();
+    __shared__ __attribute__((aligned(16))) char smem[kW > kX ? kW : kX];
+    __shared__ float red[4];
+    const int b = blockIdx.x + blk_off;
+    if (b < nw) bwd_wgrad_tile<TC>(wa, b, smem);
+    else bwd_dx_tile<TC, KU>(xa, b - nw, smem, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1041,43 +1131,57 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
 
     float *grads = io.grads;
     const int rows_per_block = 64;
-    PAC_LAUNCH(prof, st, KC_HEAD_BWD, k_head_bwd, dim3(cdiv(d, 256), cdiv(M, rows_per_block)), dim3(256), 0, st, pooled, Wcls, dz,
-                       meta.B, M, d, D.C, rowsamp, samp_len, grads + (int64_t)L * PL,
-                       grads + (int64_t)L * PL + (int64_t)d * D.C, ds, rows_per_block);
+    float *dh = dlam_part; // B*r floats; the first launch of the layers' backward overwrites it afterwards
+    HeadBwdArgs ha{pooled, Wcls, dz, meta.B, M, d, r, D.C, rowsamp, samp_len, grads + (int64_t)L * PL,
+                   grads + (int64_t)L * PL + (int64_t)d * D.C, ds, rows_per_block, params + (int64_t)(L - 1) * PL + dr + r, dh,
+                   cdiv((int64_t)meta.B * r, 4)};
+    PAC_LAUNCH(prof, st, KC_HEAD_BWD, k_head_bwd, dim3(ha.nt + cdiv(d, 256) * cdiv(M, rows_per_block)), dim3(256), 0, st, ha);
 
     const int kstep = Stage<TC, 4>::BK;
     int splits = W.splits;
     int rows_per_split = cdiv(cdiv(M, splits), kstep) * kstep;
     splits = cdiv(M, rows_per_split);
-    const int wg_tiles = cdiv(r, 64) * cdiv(d, 64);
+    const int wg_tiles = cdiv(r, 64) * cdiv(d, 64), nw = wg_tiles * splits * 2, nx = (int)(g_rows_d.x * g_rows_d.y);
+    const bool split = (D.flags & 2) != 0; // PAC_FLAG_SPLIT_LAUNCH
+    // ds of the layer at hand and of the one below take turns in two arrays; the top layer's side state has been pooled
+    float *ds_cur = ds, *ds_next = s_all + (int64_t)(L - 1) * Md;
     for (int l = L - 1; l >= 0; --l) {
         const float *pl = params + (int64_t)l * PL;
         const float *s_prev = l == 0 ? nullptr : s_all + (int64_t)(l - 1) * Md;
         if (l == L - 1) {
-            float *dh_top = dlam_part; // B*r floats; the dx kernel overwrites it afterwards
-            PAC_LAUNCH(prof, st, KC_BWD_DPRE, k_dh_top, dim3(cdiv((int64_t)meta.B * r, 4)), dim3(256), 0, st, dz, Wcls,
-                       pl + dr + r, samp_len, meta.B, d, r, D.C, dh_top);
-            PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_dpre_top<TC>), dim3(cdiv(Mr, 256)), dim3(256), 0, st, dh_top,
+            PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_dpre_top<TC>), dim3(cdiv(Mr, 256)), dim3(256), 0, st, dh,
                        pre_all + (int64_t)l * Mr, rowsamp, M, r, dpre);
         } else {
-            BwdDpreArgs<TC> ba{ds, Wu + (int64_t)l * dr, pre_all + (int64_t)l * Mr, dpre, M, d, r};
+            // with it the sums over what the layer above left
+            const ReduceArgs ra{part, splits, PL, dlam_part, nx, grads + (int64_t)(l + 1) * PL};
+            BwdDpreArgs<TC> ba{ds_cur, Wu + (int64_t)l * dr, pre_all + (int64_t)l * Mr, dpre, M, d, r};
+            const int nd16 = (int)(g_rows16.x * g_rows16.y), nd64 = (int)(g_rows_r.x * g_rows_r.y);
+            auto reducers = [&](int threads) { return split ? 0 : cdiv(PL, threads); };
+            if (split) PAC_LAUNCH(prof, st, KC_REDUCE, k_reduce_layer, dim3(cdiv(PL, 256)), dim3(256), 0, st, ra);
             if (rows16) {
                 if constexpr (std::is_same<TC, float>::value)
                     with_blocks([&](auto nb) {
-                        PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre16<decltype(nb)::value>), g_rows16, dim3(64 * kRowWaves), 0, st, ba);
+                        PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre16<decltype(nb)::value>), dim3(nd16 + reducers(64 * kRowWaves)),
+                                   dim3(64 * kRowWaves), 0, st, ba, ra, nd16);
                     });
-            } else if (wide_d) PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 4>), g_rows_r, dim3(256), 0, st, ba);
-            else PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 1>), g_rows_r, dim3(256), 0, st, ba);
+            } else if (wide_d) PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 4>), dim3(nd64 + reducers(256)), dim3(256), 0, st, ba, ra, nd64);
+            else PAC_LAUNCH(prof, st, KC_BWD_DPRE, (k_bwd_dpre<TC, 1>), dim3(nd64 + reducers(256)), dim3(256), 0, st, ba, ra, nd64);
         }
-        BwdWgradArgs<TC> wa{cache, map, l, d, r, s_prev, pl + PL - 1, h_all + (int64_t)l * Mr, ds, dpre, part, PL,
-                            rows_per_split};
-        PAC_LAUNCH(prof, st, KC_BWD_WGRAD, (k_bwd_wgrad<TC>), dim3(wg_tiles, splits, 2), dim3(256), 0, st, wa);
-        BwdDxArgs<TC> xa{dpre, Wd + (int64_t)l * dr, cache, map, l, d, r, s_prev, pl + PL - 1, ds, dlam_part};
-        if (wide_r) PAC_LAUNCH(prof, st, KC_BWD_DX, (k_bwd_dx<TC, 4>), g_rows_d, dim3(256), 0, st, xa);
-        else PAC_LAUNCH(prof, st, KC_BWD_DX, (k_bwd_dx<TC, 1>), g_rows_d, dim3(256), 0, st, xa);
-        PAC_LAUNCH(prof, st, KC_REDUCE, k_reduce_layer, dim3(cdiv(PL, 256)), dim3(256), 0, st, part, splits, PL, dlam_part,
-                           (int)(g_rows_d.x * g_rows_d.y), grads + (int64_t)l * PL);
+        BwdWgradArgs<TC> wa{cache, map, l, d, r, s_prev, pl + PL - 1, h_all + (int64_t)l * Mr, ds_cur, dpre, part, PL,
+                            rows_per_split, wg_tiles, splits};
+        BwdDxArgs<TC> xa{dpre, Wd + (int64_t)l * dr, cache, map, l, d, r, s_prev, pl + PL - 1, ds_cur, ds_next, dlam_part, (int)g_rows_d.x};
+        auto launch_layer = [&](int cls, int off, int n) {
+            if (wide_r) PAC_LAUNCH(prof, st, cls, (k_bwd_layer<TC, 4>), dim3(n), dim3(256), 0, st, wa, xa, nw, off);
+            else PAC_LAUNCH(prof, st, cls, (k_bwd_layer<TC, 1>), dim3(n), dim3(256), 0, st, wa, xa, nw, off);
+        };
+        if (split) {
+            launch_layer(KC_BWD_WGRAD, 0, nw);
+            launch_layer(KC_BWD_DX, nw, nx);
+        } else launch_layer(KC_BWD_WGRAD, 0, nw + nx);
+        std::swap(ds_cur, ds_next);
     }
+    PAC_LAUNCH(prof, st, KC_REDUCE, k_reduce_layer, dim3(cdiv(PL, 256)), dim3(256), 0, st,
+               (ReduceArgs{part, splits, PL, dlam_part, nx, grads}));
     return hipGetLastError();
 }
 

@@ -78,6 +78,9 @@ def test_chains_over_groups_of_layers(w):
     (Workload("f5", L=2, d=288, n_max=9, B=3, r=64, C=2, N=3, cache_dtype="f32", len_lo=1), 16),
     (Workload("f6", L=2, d=64, n_max=75, B=32, r=512, C=2, N=32, cache_dtype="f32", len_lo=70), 64),
     (Workload("f7", L=2, d=96, n_max=140, B=32, r=512, C=3, N=32, cache_dtype="f32", len_lo=135), 64),
+    # one layer (no dpre launch for its sums to ride on) and five (the two arrays of the side gradient take turns)
+    (Workload("f8", L=1, d=64, n_max=40, B=3, r=32, C=2, N=3, cache_dtype="f32", len_lo=7), 16),
+    (Workload("f9", L=5, d=96, n_max=70, B=7, r=64, C=3, N=7, cache_dtype="f32", len_lo=7), 16),
 ], ids=lambda w: getattr(w, "name", None))
 def test_fp32_contractions(w, rows):
     lens, ids = inputs.lengths(w), np.arange(w.B)
