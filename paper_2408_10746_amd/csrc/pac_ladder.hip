@@ -1290,8 +1290,15 @@ template <bool MIX> __global__ __launch_bounds__(256) void k_lln_bwd(LnBwdArgs a
 }
 
 // ---------------------------------------------------------------------------
-// Attention of one sample and head per workgroup; a thread owns a query row (forward, reverse phase 1)
-// or a key row (reverse phase 2).  K and V (and Q, dO in the reverse pass) of the head sit in LDS.
+// Attention of one sample and head per workgroup (and a share of its rows: blockIdx.y), in fp32 on the matrix units; a
+// wavefront owns 16 query rows (forward, reverse phase 1) or 16 key rows (reverse phase 2) at a time.  K and V (and Q, dO
+// in the reverse pass) of the head sit in LDS.
+//
+// With a row per group of lanes and vector arithmetic these kernels were bound by their LDS reads, two to four rows of 4 DH
+// bytes per pair of query and key: 12.2 us forward and 26 us back a layer at 32 samples of 128 tokens and 12 heads of 8.
+// Here a block of 16 x 16 pairs reads its rows once.  The scores are formed so that a lane's four values are what the next
+// product wants of its second operand: with the own rows along the lanes (n = lane % 16) and the other rows along the
+// registers (m = 4 (lane / 16) + v), instruction v of the product over the other rows contracts those with m % 4 = v.
 // ---------------------------------------------------------------------------
 struct AttnArgs {
     const float *QKV; // [M][3w]
@@ -1302,171 +1309,236 @@ struct AttnArgs {
     float *dQKV;     // reverse: [M][3w]
     int w, nh, n_max;
     float scale;
-    int tpr;    // lanes per row: a power of two, 1 .. 8
     int nchunk; // workgroups per sample and head (blockIdx.y): each takes a contiguous share of the rows
 };
 // Probabilities are formed as 2^(score - max) with the scores scaled by log2(e) beforehand (folded into the query's
-// scale): the hardware's exponential is base 2, so a natural exponential costs a multiply and range fix-ups per call,
-// and these kernels are bound by their vector arithmetic.  Results below the normal range flush to zero.
+// scale): the hardware's exponential is base 2, so a natural exponential costs a multiply and range fix-ups per call.
+// Results below the normal range flush to zero.
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ float lexp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// A row is shared by `tpr` neighbouring lanes (a power of two, chosen so that the sample's rows fill the
-// workgroup); each takes every tpr-th key (query) and the partial results are combined with lane exchanges.
-__device__ __forceinline__ float grp_sum(float v, int tpr)
-{
-    for (int o = 1; o < tpr; o <<= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float grp_max(float v, int tpr)
-{
-    for (int o = 1; o < tpr; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
+
+template <int DH> struct Attn {
+    static constexpr int P = DH + (DH >= 32 ? 4 : 0); // pitch of a row in LDS: 16 rows' reads spread over all banks
+    static constexpr int CPL = DH / 4;                // columns per lane of a contraction over the head's columns
+    static constexpr int NB = (DH + 15) / 16;         // blocks of 16 output columns
+    typedef float vec __attribute__((ext_vector_type(CPL == 1 ? 1 : CPL == 2 ? 2 : 4)));
+    static constexpr int VE = CPL < 4 ? CPL : 4;
+    static __host__ __device__ int rows(int n_max) { return (n_max + 15) & ~15; }
+    // rows 0 .. n - 1 of a head's DH columns, 16 bytes a lane, and zeros up to a whole block of 16 rows: the products then
+    // address whole blocks from one pointer (clamped rows cost more vector instructions than the products)
+    static __device__ __forceinline__ void stage(float *dst, const float *src, int64_t ld, int n)
+    {
+        for (int idx = threadIdx.x; idx < ((n + 15) & ~15) * (DH / 4); idx += 256) {
+            const int j = idx / (DH / 4), c = 4 * (idx % (DH / 4));
+            f32x4 v = *reinterpret_cast<const f32x4 *>(src + min(j, n - 1) * ld + c);
+            if (j >= n) v = f32x4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4 *>(dst + j * P + c) = v;
+        }
+    }
+    // this lane's CPL columns of a row
+    static __device__ __forceinline__ void row(const float *lds, int r, int g4, float (&x)[CPL])
+    {
+#pragma unroll
+        for (int u = 0; u < CPL; u += VE) {
+            const vec v = *reinterpret_cast<const vec *>(lds + r * P + g4 * CPL + u);
+#pragma unroll
+            for (int e = 0; e < VE; ++e) x[u + e] = v[e];
+        }
+    }
+    // 16 x 16 products over the head's columns: rows r0 .. + 15 of lds against the lanes' own rows
+    static __device__ __forceinline__ f32x4 dots(const float *lds, int r0, const float (&own)[CPL], int i, int g4)
+    {
+        float x[CPL];
+        row(lds + r0 * P, i, g4, x);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < CPL; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u], own[u], acc, 0, 0, 0);
+        return acc;
+    }
+    // acc[c][own] += sum over rows r0 .. + 15 of lds[row][c] p[row][own], p as dots() lays it out (zero past the last row)
+    static __device__ __forceinline__ void add(f32x4 (&acc)[NB], const float *lds, int r0, const f32x4 &p, int i, int g4)
+    {
+        const float *base = lds + 4 * g4 * P + (DH < 16 ? min(i, DH - 1) : i) + r0 * P;
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(base[v * P + 16 * q], p[v], acc[q], 0, 0, 0);
+    }
+    // rows r0 + 4 g4 + v from n on: x
+    static __device__ __forceinline__ void past(f32x4 &p, int r0, int n, float x, int g4)
+    {
+        if (r0 + 16 <= n) return;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (r0 + 4 * g4 + v >= n) p[v] = x;
+    }
+    // columns 16 q + 4 g4 .. + 3 of the lane's own row
+    static __device__ __forceinline__ void put(float *dst, const f32x4 (&acc)[NB], float mul, int g4)
+    {
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (16 * q + 4 * g4 < DH) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[q][e] * mul;
+                *reinterpret_cast<f32x4 *>(dst + 16 * q + 4 * g4) = v;
+            }
+    }
+    // whole tiles of 16 rows per workgroup: rows [lo, hi) of n
+    static __device__ __forceinline__ void share(int n, int nchunk, int &lo, int &hi)
+    {
+        const int rpc = ((n + nchunk - 1) / nchunk + 15) & ~15;
+        lo = blockIdx.y * rpc;
+        hi = min(n, lo + rpc);
+    }
+};
 
 template <int DH> __global__ __launch_bounds__(256) void k_lattn_fwd(AttnArgs a)
 {
+    using T = Attn<DH>;
     extern __shared__ __attribute__((aligned(16))) float lsm[];
     const int s = blockIdx.x / a.nh, h = blockIdx.x % a.nh;
     const int m0 = a.samp_start[s], n = a.samp_len[s];
-    const int w3 = 3 * a.w;
-    float *ks = lsm, *vs = lsm + (int64_t)a.n_max * DH;
-    for (int idx = threadIdx.x; idx < n * DH; idx += 256) {
-        const int j = idx / DH, c = idx % DH;
-        const float *row = a.QKV + (int64_t)(m0 + j) * w3 + h * DH + c;
-        ks[idx] = row[a.w];
-        vs[idx] = row[2 * a.w];
-    }
+    const int64_t w3 = 3 * a.w;
+    const float *qkv = a.QKV + (int64_t)m0 * w3 + h * DH;
+    float *ks = lsm, *vs = lsm + T::rows(a.n_max) * T::P;
+    int r_lo, r_hi;
+    T::share(n, a.nchunk, r_lo, r_hi);
+    if (r_lo >= n) return;
+    T::stage(ks, qkv + a.w, w3, n);
+    T::stage(vs, qkv + 2 * a.w, w3, n);
     __syncthreads();
-    const int tpr = a.tpr, part = threadIdx.x % tpr, rpp = 256 / tpr;
-    const int rpc = (n + a.nchunk - 1) / a.nchunk, r_lo = blockIdx.y * rpc, r_hi = min(n, r_lo + rpc);
-    // (every lane of a group runs the same number of rounds: the exchanges below need all of them)
-    for (int i0 = r_lo; i0 < r_hi; i0 += rpp) {
-        const int i = i0 + (int)threadIdx.x / tpr;
-        const bool live = i < r_hi;
-        const int ic = live ? i : n - 1;
-        float q[DH];
-        const float *qp = a.QKV + (int64_t)(m0 + ic) * w3 + h * DH;
+    const int lane = threadIdx.x & 63, i = lane & 15, g4 = lane >> 4;
+    for (int i0 = r_lo + 16 * (threadIdx.x >> 6); i0 < r_hi; i0 += 64) {
+        const int ic = min(i0 + i, n - 1);
+        float q[T::CPL];
 #pragma unroll
-        for (int c = 0; c < DH; ++c) q[c] = qp[c] * (a.scale * kLog2e); // scores in units of ln 2: one exp2 instruction each
-        // running maximum, sum and weighted values over this lane's keys
-        float mx = -INFINITY, l = 0.f, acc[DH];
+        for (int u = 0; u < T::CPL; ++u) q[u] = qkv[ic * w3 + g4 * T::CPL + u] * (a.scale * kLog2e); // scores in units of ln 2
+        // running maximum (the same in the four lanes of a row), this lane's share of the sum, weighted values
+        float mx = -INFINITY, l = 0.f;
+        f32x4 acc[T::NB];
 #pragma unroll
-        for (int c = 0; c < DH; ++c) acc[c] = 0.f;
-        // four keys per round: one rescaling of the running sums per round instead of one per key
-        for (int j0 = part; j0 < n; j0 += 4 * tpr) {
-            float sc[4];
+        for (int c = 0; c < T::NB; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // 64 keys a round: one rescaling of the running sums
+        auto round = [&](int j0, auto blocks) {
+            constexpr int KB = decltype(blocks)::value;
+            f32x4 sc[KB];
+            float mn = mx;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u * tpr;
-                const float *kr = ks + min(j, n - 1) * DH;
-                float t = 0.f;
-#pragma unroll
-                for (int c = 0; c < DH; ++c) t += q[c] * kr[c];
-                sc[u] = j < n ? t : -INFINITY;
+            for (int b = 0; b < KB; ++b) {
+                sc[b] = T::dots(ks, j0 + 16 * b, q, i, g4);
+                T::past(sc[b], j0 + 16 * b, n, -INFINITY, g4);
+                mn = fmaxf(mn, fmaxf(fmaxf(sc[b][0], sc[b][1]), fmaxf(sc[b][2], sc[b][3])));
             }
-            const float mn = fmaxf(fmaxf(mx, fmaxf(sc[0], sc[1])), fmaxf(sc[2], sc[3])); // sc[0] is always a key: finite
+            mn = fmaxf(mn, __shfl_xor(mn, 16, 64));
+            mn = fmaxf(mn, __shfl_xor(mn, 32, 64)); // finite: a round's first key is a key
             const float corr = lexp2(mx - mn);
             l *= corr;
 #pragma unroll
-            for (int c = 0; c < DH; ++c) acc[c] *= corr;
+            for (int c = 0; c < T::NB; ++c)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float p = lexp2(sc[u] - mn); // 0 for the slots past the last key
-                const float *vr = vs + min(j0 + u * tpr, n - 1) * DH;
-                l += p;
+                for (int v = 0; v < 4; ++v) acc[c][v] *= corr;
 #pragma unroll
-                for (int c = 0; c < DH; ++c) acc[c] += p * vr[c];
+            for (int b = 0; b < KB; ++b) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    sc[b][v] = lexp2(sc[b][v] - mn); // 0 for the slots past the last key
+                    l += sc[b][v];
+                }
+                T::add(acc, vs, j0 + 16 * b, sc[b], i, g4);
             }
             mx = mn;
+        };
+        int j0 = 0;
+        for (; j0 + 48 < n; j0 += 64) round(j0, std::integral_constant<int, 4>());
+        for (; j0 < n; j0 += 16) round(j0, std::integral_constant<int, 1>());
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (i0 + i < r_hi) {
+            T::put(a.O + (int64_t)(m0 + ic) * a.w + h * DH, acc, 1.f / l, g4);
+            if (g4 == 0) a.LSE[(int64_t)(m0 + ic) * a.nh + h] = mx * kLn2 + logf(l); // natural logarithm
         }
-        const float mall = grp_max(mx, tpr);
-        const float corr = mx == -INFINITY ? 0.f : lexp2(mx - mall);
-        l = grp_sum(l * corr, tpr);
-        const float inv = 1.f / l;
-        float *op = a.O + (int64_t)(m0 + ic) * a.w + h * DH;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) {
-            const float v = grp_sum(acc[c] * corr, tpr) * inv;
-            if (live && part == 0) op[c] = v;
-        }
-        if (live && part == 0) a.LSE[(int64_t)(m0 + i) * a.nh + h] = mall * kLn2 + logf(l); // natural logarithm
     }
 }
 
 template <int DH> __global__ __launch_bounds__(256) void k_lattn_bwd(AttnArgs a)
 {
+    using T = Attn<DH>;
     extern __shared__ __attribute__((aligned(16))) float lsm[];
     const int s = blockIdx.x / a.nh, h = blockIdx.x % a.nh;
     const int m0 = a.samp_start[s], n = a.samp_len[s];
-    const int w3 = 3 * a.w;
-    const int64_t nd = (int64_t)a.n_max * DH;
-    float *qs = lsm, *ks = lsm + nd, *vs = lsm + 2 * nd, *dos = lsm + 3 * nd, *lse = lsm + 4 * nd, *Dr = lse + a.n_max;
-    for (int idx = threadIdx.x; idx < n * DH; idx += 256) {
-        const int j = idx / DH, c = idx % DH;
-        const float *row = a.QKV + (int64_t)(m0 + j) * w3 + h * DH + c;
-        qs[idx] = row[0];
-        ks[idx] = row[a.w];
-        vs[idx] = row[2 * a.w];
-        dos[idx] = a.dO[(int64_t)(m0 + j) * a.w + h * DH + c];
-    }
-    for (int i = threadIdx.x; i < n; i += 256) {
-        lse[i] = a.LSE[(int64_t)(m0 + i) * a.nh + h] * kLog2e;
-        const float *op = a.O + (int64_t)(m0 + i) * a.w + h * DH;
-        const float *dp = a.dO + (int64_t)(m0 + i) * a.w + h * DH;
+    const int64_t w3 = 3 * a.w, nd = T::rows(a.n_max) * T::P;
+    const float *qkv = a.QKV + (int64_t)m0 * w3 + h * DH, *go = a.dO + (int64_t)m0 * a.w + h * DH;
+    float *qs = lsm, *ks = lsm + nd, *vs = lsm + 2 * nd, *dos = lsm + 3 * nd, *lse = lsm + 4 * nd, *Dr = lse + T::rows(a.n_max);
+    int r_lo, r_hi;
+    T::share(n, a.nchunk, r_lo, r_hi);
+    if (r_lo >= n) return;
+    T::stage(qs, qkv, w3, n);
+    T::stage(ks, qkv + a.w, w3, n);
+    T::stage(vs, qkv + 2 * a.w, w3, n);
+    T::stage(dos, go, a.w, n);
+    for (int r = threadIdx.x; r < T::rows(n); r += 256) {
+        const int rc = min(r, n - 1);
+        const float *op = a.O + (int64_t)(m0 + rc) * a.w + h * DH, *dp = go + (int64_t)rc * a.w;
+        const float le = a.LSE[(int64_t)(m0 + rc) * a.nh + h] * kLog2e;
         float D = 0.f;
 #pragma unroll
-        for (int c = 0; c < DH; ++c) D += op[c] * dp[c];
-        Dr[i] = D;
+        for (int c = 0; c < DH; c += 4) {
+            const f32x4 o4 = *reinterpret_cast<const f32x4 *>(op + c), d4 = *reinterpret_cast<const f32x4 *>(dp + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) D += o4[e] * d4[e];
+        }
+        lse[r] = r < n ? le : INFINITY; // no probability past the last query
+        Dr[r] = r < n ? D : 0.f;
     }
     __syncthreads();
-    const int tpr = a.tpr, part = threadIdx.x % tpr, rpp = 256 / tpr;
-    const int rpc = (n + a.nchunk - 1) / a.nchunk, r_lo = blockIdx.y * rpc, r_hi = min(n, r_lo + rpc);
-    // phase 1, query row i: dq_i = scale * sum_j P_ij (dO_i . v_j - D_i) k_j
-    for (int i0 = r_lo; i0 < r_hi; i0 += rpp) {
-        const int i = i0 + (int)threadIdx.x / tpr;
-        const bool live = i < r_hi;
-        const int ic = live ? i : n - 1;
-        float q[DH], go[DH], dq[DH];
-#pragma unroll
-        for (int c = 0; c < DH; ++c) { q[c] = qs[ic * DH + c] * (a.scale * kLog2e); go[c] = dos[ic * DH + c]; dq[c] = 0.f; }
-        const float li = lse[ic], Di = Dr[ic];
-        for (int j = part; j < n; j += tpr) {
-            float sc = 0.f, dpv = 0.f;
-#pragma unroll
-            for (int c = 0; c < DH; ++c) { sc += q[c] * ks[j * DH + c]; dpv += go[c] * vs[j * DH + c]; }
-            const float ds = lexp2(sc - li) * (dpv - Di);
-#pragma unroll
-            for (int c = 0; c < DH; ++c) dq[c] += ds * ks[j * DH + c];
-        }
+    const int lane = threadIdx.x & 63, i = lane & 15, g4 = lane >> 4;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = r_lo + 16 * (threadIdx.x >> 6); i0 < r_hi; i0 += 64) {
+        const int ic = min(i0 + i, n - 1);
         float *out = a.dQKV + (int64_t)(m0 + ic) * w3 + h * DH;
+        float x[T::CPL], y[T::CPL];
+        f32x4 acc[T::NB], acc2[T::NB];
+        // phase 1, query row: dq_i = scale * sum_j P_ij (dO_i . v_j - D_i) k_j
+        T::row(qs, ic, g4, x);
+        T::row(dos, ic, g4, y);
 #pragma unroll
-        for (int c = 0; c < DH; ++c) {
-            const float v = grp_sum(dq[c], tpr) * a.scale;
-            if (live && part == 0) out[c] = v;
+        for (int u = 0; u < T::CPL; ++u) x[u] *= a.scale * kLog2e;
+#pragma unroll
+        for (int c = 0; c < T::NB; ++c) acc[c] = zero;
+        const float li = lse[ic], Di = Dr[ic];
+#pragma unroll 2
+        for (int j0 = 0; j0 < n; j0 += 16) {
+            f32x4 ds = T::dots(ks, j0, x, i, g4);
+            const f32x4 dp = T::dots(vs, j0, y, i, g4);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ds[v] = lexp2(ds[v] - li) * (dp[v] - Di);
+            T::past(ds, j0, n, 0.f, g4);
+            T::add(acc, ks, j0, ds, i, g4);
         }
-    }
-    // phase 2, key row j: dv_j = sum_i P_ij dO_i ; dk_j = scale * sum_i P_ij (dO_i . v_j - D_i) q_i
-    for (int j0 = r_lo; j0 < r_hi; j0 += rpp) {
-        const int j = j0 + (int)threadIdx.x / tpr;
-        const bool live = j < r_hi;
-        const int jc = live ? j : n - 1;
-        float k[DH], v[DH], dk[DH], dv[DH];
+        if (i0 + i < r_hi) T::put(out, acc, a.scale, g4);
+        // phase 2, key row: dv_j = sum_i P_ij dO_i ; dk_j = scale * sum_i P_ij (dO_i . v_j - D_i) q_i
+        T::row(ks, ic, g4, x);
+        T::row(vs, ic, g4, y);
 #pragma unroll
-        for (int c = 0; c < DH; ++c) { k[c] = ks[jc * DH + c] * (a.scale * kLog2e); v[c] = vs[jc * DH + c]; dk[c] = 0.f; dv[c] = 0.f; }
-        for (int i = part; i < n; i += tpr) {
-            float sc = 0.f, dpv = 0.f;
+        for (int u = 0; u < T::CPL; ++u) x[u] *= a.scale * kLog2e;
 #pragma unroll
-            for (int c = 0; c < DH; ++c) { sc += qs[i * DH + c] * k[c]; dpv += dos[i * DH + c] * v[c]; }
-            const float p = lexp2(sc - lse[i]);
-            const float ds = p * (dpv - Dr[i]);
+        for (int c = 0; c < T::NB; ++c) acc[c] = acc2[c] = zero;
+#pragma unroll 2
+        for (int j0 = 0; j0 < n; j0 += 16) {
+            f32x4 p = T::dots(qs, j0, x, i, g4), ds = T::dots(dos, j0, y, i, g4);
+            const f32x4 lr = *reinterpret_cast<const f32x4 *>(lse + j0 + 4 * g4), dr = *reinterpret_cast<const f32x4 *>(Dr + j0 + 4 * g4);
 #pragma unroll
-            for (int c = 0; c < DH; ++c) { dv[c] += p * dos[i * DH + c]; dk[c] += ds * qs[i * DH + c]; }
+            for (int v = 0; v < 4; ++v) {
+                p[v] = lexp2(p[v] - lr[v]);
+                ds[v] = p[v] * (ds[v] - dr[v]);
+            }
+            T::add(acc, qs, j0, ds, i, g4);
+            T::add(acc2, dos, j0, p, i, g4);
         }
-        float *out = a.dQKV + (int64_t)(m0 + jc) * w3 + h * DH;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) {
-            const float gk = grp_sum(dk[c], tpr) * a.scale, gv = grp_sum(dv[c], tpr);
-            if (live && part == 0) { out[a.w + c] = gk; out[2 * a.w + c] = gv; }
+        if (i0 + i < r_hi) {
+            T::put(out + a.w, acc, a.scale, g4);
+            T::put(out + 2 * a.w, acc2, 1.f, g4);
         }
     }
 }
@@ -1867,11 +1939,11 @@ template <auto Kern> hipError_t lds_once(int bytes)
 template <int DH> hipError_t launch_attn(bool bwd, const AttnArgs &a, int B, hipStream_t st, Profiler *prof)
 {
     if (!bwd) {
-        const int lds = 2 * a.n_max * DH * 4;
+        const int lds = 2 * Attn<DH>::rows(a.n_max) * Attn<DH>::P * 4;
         LAD_TRY((lds_once<&k_lattn_fwd<DH>>(lds)));
         LAD_LAUNCH(prof, st, KC_L_ATTN, (k_lattn_fwd<DH>), dim3(B * a.nh, a.nchunk), dim3(256), lds, st, a);
     } else {
-        const int lds = (4 * a.n_max * DH + 2 * a.n_max) * 4;
+        const int lds = (4 * Attn<DH>::P + 2) * Attn<DH>::rows(a.n_max) * 4;
         LAD_TRY((lds_once<&k_lattn_bwd<DH>>(lds)));
         LAD_LAUNCH(prof, st, KC_L_ATTN, (k_lattn_bwd<DH>), dim3(B * a.nh, a.nchunk), dim3(256), lds, st, a);
     }
@@ -1935,15 +2007,10 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
         }
     }
     const float scale = 1.f / sqrtf((float)a.dh);
-    int nlong = 1; // longest sample of the batch: lanes per attention row so that its rows fill a workgroup
+    int nlong = 1; // longest sample of the batch
     for (int i = 0; i < B; ++i) nlong = meta.len[i] > nlong ? meta.len[i] : nlong;
-    // several workgroups per sample and head (about 64 rows each: measured against 32 and 128 at 128-token samples),
-    // the rows of one shared by up to 8 lanes
-    int nchunk = nlong / 64;
-    nchunk = nchunk < 1 ? 1 : (nchunk > 8 ? 8 : nchunk);
-    const int rows_per_wg = (nlong + nchunk - 1) / nchunk;
-    int tpr = 1;
-    while (tpr < 8 && 2 * tpr * rows_per_wg <= 256) tpr *= 2;
+    int nchunk = cdivi(nlong, 64); // workgroups per sample and head: 64 rows each, one tile of 16 per wavefront
+    nchunk = nchunk > 8 ? 8 : nchunk;
     for (int l = 0; l < L; ++l) {
         const float *pl = params + (int64_t)l * a.PLb;
         if (w <= 128) { // gate, LayerNorm 1 and the q, k, v projection in one launch
@@ -1965,7 +2032,7 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
                       nullptr, nullptr, lay(a.QKV, l, 3 * w), nullptr);
         }
         AttnArgs at{lay(a.QKV, l, 3 * w), samp_start, samp_len, lay(a.O, l, w), lay(a.LSE, l, a.nh), nullptr, nullptr, w,
-                    a.nh, (int)(Mm / a.Bmax), scale, tpr, nchunk};
+                    a.nh, (int)(Mm / a.Bmax), scale, nchunk};
         LAD_TRY(attn(a.dh, false, at, B, st, prof));
         if (w <= 128) { // the rest of the layer in one launch
             MlpArgs ma{lay(a.O, l, w), lay(a.X, l, w), pl + a.fo[F_WO], pl + a.fo[F_BO], pl + a.fo[F_G2], pl + a.fo[F_H2],
@@ -2034,7 +2101,7 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
         lin<true, 4>(prof, st, KC_L_LIN, DT, w, pl + a.fo[F_WO], w, M, w, w, nullptr, nullptr, nullptr, F(a.DO_), nullptr);
         }
         AttnArgs at{lay(a.QKV, l, 3 * w), samp_start, samp_len, lay(a.O, l, w), lay(a.LSE, l, a.nh), F(a.DO_), DQKV, w,
-                    a.nh, (int)(Mm / a.Bmax), scale, tpr, nchunk};
+                    a.nh, (int)(Mm / a.Bmax), scale, nchunk};
         LAD_TRY(attn(a.dh, true, at, B, st, prof));
         if (w <= 128) { // dxn, the reverse of LayerNorm 1 and of the gate in one launch
             const float *wt = F(a.WT) + (int64_t)l * (2 * w * f + 4 * w * w) + (int64_t)2 * w * f + (int64_t)w * w;
