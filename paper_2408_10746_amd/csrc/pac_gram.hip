@@ -1647,20 +1647,24 @@ __global__ __launch_bounds__(256) void k_gseq_ghat(const float *dz, const float 
 }
 
 // zpart[tile][c] = sum_kk (column sums of h over the tile)[kk] V[kk][c]
-__global__ __launch_bounds__(256) void k_gseq_zpart(const float *HSpart, const float *V, int Lr, int C, float *zpart)
+// CMAX classes at most, each loaded without a branch (the last one again past C) so that the loads of several rounds are
+// under way together: one round trip to memory per round took 41 us at 320 tiles of 16384 columns, two classes (20 us now)
+template <int CMAX> __global__ __launch_bounds__(256) void k_gseq_zpart(const float *HSpart, const float *V, int Lr, int C, float *zpart)
 {
     __shared__ float red[16];
     const int tile = blockIdx.x, t = threadIdx.x;
-    float acc[kMaxClasses];
+    float acc[CMAX];
 #pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c) acc[c] = 0.f;
+    for (int c = 0; c < CMAX; ++c) acc[c] = 0.f;
+#pragma unroll (CMAX <= 4 ? 8 : 2)
     for (int kk = t; kk < Lr; kk += 256) {
         const float hs = HSpart[(int64_t)tile * Lr + kk];
 #pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c)
-            if (c < C) acc[c] += hs * V[(int64_t)kk * C + c];
+        for (int c = 0; c < CMAX; ++c) acc[c] += hs * V[(int64_t)kk * C + min(c, C - 1)];
     }
-    for (int c = 0; c < C; ++c) {
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+        if (c >= C) break;
         const float tot = block_sum(acc[c], red);
         if (t == 0) zpart[(int64_t)tile * C + c] = tot;
     }
@@ -2873,7 +2877,8 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
         chain(chain, true, 0, ngroups);
         PAC_LAUNCH(prof, st, KC_G_CHAIN_FWD, k_gseq_colsum, dim3(ntiles, cdiv(Lr, 256)), dim3(256), 0, st, H, Lr, tile_row0,
                    tile_rows, HSpart);
-        PAC_LAUNCH(prof, st, KC_G_HEAD, k_gseq_zpart, dim3(ntiles), dim3(256), 0, st, HSpart, V, Lr, C, zpart);
+        if (C <= 4) PAC_LAUNCH(prof, st, KC_G_HEAD, k_gseq_zpart<4>, dim3(ntiles), dim3(256), 0, st, HSpart, V, Lr, C, zpart);
+        else PAC_LAUNCH(prof, st, KC_G_HEAD, k_gseq_zpart<kMaxClasses>, dim3(ntiles), dim3(256), 0, st, HSpart, V, Lr, C, zpart);
         PAC_LAUNCH(prof, st, KC_G_HEAD, k_glogits, dim3(B), dim3(64), 0, st, ca);
         if (!io.grads) {
             PAC_LAUNCH(prof, st, KC_G_FINISH, k_gfinish, dim3(1), dim3(64), 0, st, loss_part, B, io.loss_out, nullptr, 0, L,
