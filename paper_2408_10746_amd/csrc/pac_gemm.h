@@ -496,18 +496,21 @@ __device__ __forceinline__ void mma_tile(const float *As, const float *Bs, f32x1
 {
     using S = Stage<float, KU>;
     const int i = lane & 31, g = lane >> 5;
+    // a lane reads four consecutive K values of its row for four instructions (both operands use the same assignment)
 #pragma unroll
-    for (int q = 0; q < S::BK / 2; ++q) {
-        float a[WTM], b[WTN];
+    for (int q = 0; q < S::BK / 8; ++q) {
+        f32x4 a[WTM], b[WTN];
 #pragma unroll
-        for (int x = 0; x < WTM; ++x) a[x] = As[(arow0 + x * 32 + i) * S::LDP + q * 2 + g];
+        for (int x = 0; x < WTM; ++x) a[x] = *reinterpret_cast<const f32x4 *>(As + (arow0 + x * 32 + i) * S::LDP + q * 8 + g * 4);
 #pragma unroll
-        for (int y = 0; y < WTN; ++y) b[y] = Bs[(brow0 + y * 32 + i) * S::LDP + q * 2 + g];
+        for (int y = 0; y < WTN; ++y) b[y] = *reinterpret_cast<const f32x4 *>(Bs + (brow0 + y * 32 + i) * S::LDP + q * 8 + g * 4);
 #pragma unroll
-        for (int x = 0; x < WTM; ++x)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int y = 0; y < WTN; ++y)
-                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+            for (int x = 0; x < WTM; ++x)
+#pragma unroll
+                for (int y = 0; y < WTN; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x][e], b[y][e], acc[x][y], 0, 0, 0);
     }
 }
 
