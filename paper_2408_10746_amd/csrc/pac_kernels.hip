@@ -10,6 +10,7 @@
 // ordered (no floating-point atomics), so a step is bit-reproducible.
 #include "pac_gemm.h"
 #include "pac_internal.h"
+#include "../../include/pac.h"
 
 namespace pac {
 
@@ -34,12 +35,13 @@ using T64K = Tile<2, 2, 1, 1, 4>; // same tile, 256 bytes of K per step (token r
 static inline int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-static int choose_splits(const Dims &D)
+// Token splits of a layer's weight gradients: about `workgroups` of them, at least min_rows token rows each
+static int choose_splits(const Dims &D, int workgroups, int min_rows)
 {
     // tiles of both weight-gradient contractions of one layer
     int64_t tiles = 2 * (int64_t)cdiv(D.r, 64) * cdiv(D.d, 64);
-    int s = (int)((1024 + tiles - 1) / tiles);
-    int max_by_rows = (int)((D.Mmax + 255) / 256); // at least 256 token rows per split
+    int s = cdiv(workgroups, tiles);
+    int max_by_rows = cdiv(D.Mmax, min_rows);
     if (s > max_by_rows) s = max_by_rows;
     if (s > 32) s = 32;
     if (s < 1) s = 1;
@@ -72,14 +74,23 @@ void plan_workspace(const Dims &D, WsLayout &W)
     W.pooled = take((int64_t)D.B_max * D.d * 4);
     W.logits = take((int64_t)D.B_max * D.C * 4);
     W.dz = take((int64_t)D.B_max * D.C * 4);
-    W.splits = choose_splits(D);
-    W.part = gram ? 0 : take((int64_t)W.splits * D.PL * 4);
     W.dlam_slots = cdiv(D.Mmax, 64) * cdiv(D.d, 64);
     if (W.dlam_slots < D.B_max * D.r) W.dlam_slots = D.B_max * D.r; // also holds the top layer's dh [B][r]
     W.dlam_part = gram ? 0 : take((int64_t)W.dlam_slots * 4);
     W.grads = take(D.P * 4);
     W.use_gram = 0;
     if (gram) plan_gram_workspace(D, W, o);
+    // Four steps of 64 token rows a split, and shorter splits where those are fewer than the compute units (512 rows,
+    // d = 256, r = 32: two splits of eight tiles, 12.4 us a layer, against 6.4 us with eight), unless only they would take the
+    // workspace past what pac_adapter_step_static has.
+    W.splits = choose_splits(D, 1024, 256);
+    W.part = 0;
+    if (!gram) {
+        const int more = choose_splits(D, 256, 64);
+        auto end = [&](int splits) { return align256(o + splits * D.PL * 4); };
+        if (more > W.splits && (end(more) <= PAC_STATIC_WORKSPACE_BYTES || end(W.splits) > PAC_STATIC_WORKSPACE_BYTES)) W.splits = more;
+        W.part = take((int64_t)W.splits * D.PL * 4);
+    }
     W.total = o;
 }
 
