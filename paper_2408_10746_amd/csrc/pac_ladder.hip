@@ -1680,13 +1680,15 @@ __global__ __launch_bounds__(256) void k_lhead_a(HeadArgs a)
 // thread per hidden column j (blockIdx.x) and a chunk of kUpChunk rows of W_up (blockIdx.y): dW_up[c][j] for the
 // chunk; the first chunk's blocks also write dp[s][j], dc_up[j], dW_cls[j][.]; block (0, 0) the loss and dc_cls
 constexpr int kUpChunk = 8;
-__global__ __launch_bounds__(256) void k_lhead_b(HeadArgs a)
+// CM classes at most, dz in rows of CM padded with zeros: a branch per class and an LDS round trip per class and sample
+// took 28 us for the launch at 32 samples and three classes (11 us now)
+template <int CM> __global__ __launch_bounds__(256) void k_lhead_b(HeadArgs a)
 {
-    __shared__ float dzs[kMaxBatch * kMaxClasses];
+    __shared__ __attribute__((aligned(16))) float dzs[kMaxBatch * CM];
     __shared__ float ab[kMaxBatch * kUpChunk];
     const bool first = blockIdx.y == 0;
     const int cbase = blockIdx.y * kUpChunk;
-    for (int q = threadIdx.x; q < a.B * a.C; q += 256) dzs[q] = a.dz[q];
+    for (int q = threadIdx.x; q < a.B * CM; q += 256) dzs[q] = q % CM < a.C ? a.dz[q / CM * a.C + q % CM] : 0.f;
     for (int q = threadIdx.x; q < a.B * kUpChunk; q += 256) {
         const int sidx = q / kUpChunk, c = cbase + q % kUpChunk;
         ab[q] = c < a.w ? a.abar[(int64_t)sidx * a.w + c] : 0.f;
@@ -1700,33 +1702,43 @@ __global__ __launch_bounds__(256) void k_lhead_b(HeadArgs a)
     if (!a.grads) return;
     if (first && blockIdx.x == 0 && (int)threadIdx.x < a.C) {
         float acc = 0.f;
-        for (int s = 0; s < a.B; ++s) acc += dzs[s * a.C + threadIdx.x];
+        for (int s = 0; s < a.B; ++s) acc += dzs[s * CM + threadIdx.x];
         a.grads[a.occls + threadIdx.x] = acc;
     }
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= a.d) return;
     const float *Wcls = a.params + a.oWcls + (int64_t)j * a.C;
-    float wc[kMaxClasses], dwc[kMaxClasses];
+    float wc[CM], dwc[CM];
 #pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c) { wc[c] = c < a.C ? Wcls[c] : 0.f; dwc[c] = 0.f; }
+    for (int c = 0; c < CM; ++c) { wc[c] = c < a.C ? Wcls[min(c, a.C - 1)] : 0.f; dwc[c] = 0.f; }
     float dcup = 0.f, up[kUpChunk];
 #pragma unroll
     for (int c = 0; c < kUpChunk; ++c) up[c] = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < a.B; ++s) {
-        float dp = 0.f;
+    // four samples at a time: their loads and LDS reads first, the stores of dp last
+    for (int s0 = 0; s0 < a.B; s0 += 4) {
+        float dp[4], pl[4];
 #pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c)
-            if (c < a.C) dp += dzs[s * a.C + c] * wc[c];
+        for (int u = 0; u < 4; ++u) {
+            const int s = min(s0 + u, a.B - 1);
+            pl[u] = first ? a.pooled[(int64_t)s * a.d + j] : 0.f;
+            dp[u] = 0.f;
 #pragma unroll
-        for (int c = 0; c < kUpChunk; ++c) up[c] += ab[s * kUpChunk + c] * dp;
+            for (int c = 0; c < CM; ++c) dp[u] += dzs[s * CM + c] * wc[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = s0 + u;
+            if (s >= a.B) break;
+#pragma unroll
+            for (int c = 0; c < kUpChunk; ++c) up[c] += ab[s * kUpChunk + c] * dp[u];
+#pragma unroll
+            for (int c = 0; c < CM; ++c) dwc[c] += pl[u] * dzs[s * CM + c];
+            dcup += dp[u];
+        }
         if (first) {
-            const float pl = a.pooled[(int64_t)s * a.d + j];
 #pragma unroll
-            for (int c = 0; c < kMaxClasses; ++c)
-                if (c < a.C) dwc[c] += pl * dzs[s * a.C + c];
-            a.dp[(int64_t)s * a.d + j] = dp;
-            dcup += dp;
+            for (int u = 0; u < 4; ++u)
+                if (s0 + u < a.B) a.dp[(int64_t)(s0 + u) * a.d + j] = dp[u];
         }
     }
 #pragma unroll
@@ -1735,7 +1747,7 @@ __global__ __launch_bounds__(256) void k_lhead_b(HeadArgs a)
     if (first) {
         a.grads[a.ocup + j] = dcup;
 #pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c)
+        for (int c = 0; c < CM; ++c)
             if (c < a.C) a.grads[a.oWcls + (int64_t)j * a.C + c] = dwc[c];
     }
 }
@@ -2065,7 +2077,9 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
     LAD_LAUNCH(prof, st, KC_L_HEAD, (k_lpool<SRC>), dim3(B, cdivi(d, 256) + 1), dim3(256), 0, st, h);
     LAD_LAUNCH(prof, st, KC_L_HEAD, k_lpooled, dim3(B, cdivi(d, 256)), dim3(256), 0, st, h);
     LAD_LAUNCH(prof, st, KC_L_HEAD, k_lhead_a, dim3(B), dim3(256), 0, st, h);
-    LAD_LAUNCH(prof, st, KC_L_HEAD, k_lhead_b, dim3(cdivi(d, 256), grads ? cdivi(w, kUpChunk) : 1), dim3(256), 0, st, h);
+    const dim3 grid_b(cdivi(d, 256), grads ? cdivi(w, kUpChunk) : 1);
+    if (h.C <= 4) LAD_LAUNCH(prof, st, KC_L_HEAD, k_lhead_b<4>, grid_b, dim3(256), 0, st, h);
+    else LAD_LAUNCH(prof, st, KC_L_HEAD, k_lhead_b<kMaxClasses>, grid_b, dim3(256), 0, st, h);
     if (!grads) return hipGetLastError();
     LAD_LAUNCH(prof, st, KC_L_HEAD, k_lhead_c, dim3(B, cdivi(w, 16)), dim3(256), 0, st, h);
 

@@ -184,3 +184,13 @@ def test_unsupported_and_argument_errors():
     ctx = pb.pac_create(2, 64, 16, 512, 3, 4, 4, pb.PAC_BF16)
     assert pb.pac_ladder_param_count(ctx) == -1             # wider than the row kernels cover
     pb.pac_destroy(ctx)
+
+
+# Attention in blocks of 16 rows and rounds of 64 keys: every head width, samples of one row, of whole blocks and rounds and of
+# one row more or less; five samples (the head takes four at a time) and six classes.
+@pytest.mark.parametrize("r,heads,n_max", [(32, 8, 200), (64, 8, 129), (96, 6, 145), (64, 2, 113), (128, 2, 80)],
+                         ids=lambda v: str(v))
+def test_attention_blocks(r, heads, n_max):
+    w = Workload("attn", L=2, d=64, n_max=n_max, B=5, r=r, C=6, N=5, cache_dtype="f32", len_lo=1)
+    lens = np.array([1, 16, 65, n_max - 1, n_max], dtype=np.int32)
+    run_case(w, heads, lens, seed=5, what=f"w {r}, {heads} heads, {n_max} tokens")
