@@ -1647,8 +1647,10 @@ __global__ __launch_bounds__(256) void k_gseq_ghat(const float *dz, const float 
 }
 
 // zpart[tile][c] = sum_kk (column sums of h over the tile)[kk] V[kk][c]
-// CMAX classes at most, each loaded without a branch (the last one again past C) so that the loads of several rounds are
-// under way together: one round trip to memory per round took 41 us at 320 tiles of 16384 columns, two classes (20 us now)
+// CMAX classes at most.  Up to four are loaded without a branch (the last one again past C) so that the loads of several rounds
+// are under way together: one round trip to memory per round took 41 us at 320 tiles of 16384 columns, two classes (19 us now).
+// Above four a round's own loads are enough, and loads of classes that are not there cost more than they hide (64 tiles of
+// 8192 columns, nine classes: 50.5 us with sixteen loads, 39.9 with the branch; 128 of 2304, five: 14.8 and 9.6).
 template <int CMAX> __global__ __launch_bounds__(256) void k_gseq_zpart(const float *HSpart, const float *V, int Lr, int C, float *zpart)
 {
     __shared__ float red[16];
@@ -1656,11 +1658,12 @@ template <int CMAX> __global__ __launch_bounds__(256) void k_gseq_zpart(const fl
     float acc[CMAX];
 #pragma unroll
     for (int c = 0; c < CMAX; ++c) acc[c] = 0.f;
-#pragma unroll (CMAX <= 4 ? 8 : 2)
+#pragma unroll (CMAX <= 4 ? 8 : 1)
     for (int kk = t; kk < Lr; kk += 256) {
         const float hs = HSpart[(int64_t)tile * Lr + kk];
 #pragma unroll
-        for (int c = 0; c < CMAX; ++c) acc[c] += hs * V[(int64_t)kk * C + min(c, C - 1)];
+        for (int c = 0; c < CMAX; ++c)
+            if (CMAX <= 4 || c < C) acc[c] += hs * V[(int64_t)kk * C + min(c, C - 1)];
     }
 #pragma unroll
     for (int c = 0; c < CMAX; ++c) {

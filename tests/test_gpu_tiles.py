@@ -67,6 +67,18 @@ def test_chains_over_groups_of_layers(w):
     check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["bf16"], what=w.name)
 
 
+# The logit shares of the layer-by-layer chains: loads without a branch up to four classes, per class above.
+@pytest.mark.parametrize("C", [1, 4, 5, 16])
+def test_chain_class_counts(C):
+    w = Workload(f"k{C}", L=9, d=64, n_max=37, B=3, r=160, C=C, N=3, cache_dtype="bf16", len_lo=5)
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+    sess = make_session(w, lens=lens)
+    assert pb.pac_step_path(sess.ctx) == 2
+    sess.cache_fill(ids, acts, lens)
+    check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["bf16"], what=w.name)
+
+
 # fp32: 16-row tiles with 8, 6 (the second column chunk part empty), 4 and 6 column blocks per workgroup; K of 2 .. 10
 # units over eight wavefronts, a last row tile of a few rows.  64 x 64 tiles where they fill the chip: K in long steps (f6)
 # and in short ones (f7).
