@@ -1242,14 +1242,17 @@ template <int BK> struct SeqShapes {
 
 struct EpiSeqBig {
     static constexpr bool kBatched = true;
-    float *P;
+    float *P; // sums of the group of the tile's first column,
+    int gcol; // which starts at this column
     int M, ldp;
     bool add;
     __device__ void batch(int row_base, int col, const f32x16 &acc, int nrows, int ncols) const
     {
         if (col >= ncols) return;
-        const int grp = col / ldp; // one for all 32 columns of a block: ldp is a multiple of 32
-        float *p = P + (int64_t)grp * M * ldp + (col - grp * ldp);
+        // No tile is wider than a group (ldp >= 256), so its columns belong to one group or to two.  (Dividing by ldp in each
+        // block, with one wavefront per SIMD: 0.5 us of a launch of 12, 4096 rows and 320 or 960 columns.)
+        const int c = col - gcol;
+        float *p = P + c + (c >= ldp ? (int64_t)(M - 1) * ldp : 0);
         float out[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) out[v] = acc[v];
@@ -1275,14 +1278,16 @@ template <int FORM, int BK> __global__ __launch_bounds__(64 * (SeqBigTile<FORM, 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // A die's range of tiles walks strips of four row tiles column by column: the 32 tiles a die works on at a time are
     // 4 x 8 and share 12 operand panels in its L2 (one row of 32 tiles: 33).
-    const int v = die_chunk_order(blockIdx.x, gridDim.x);
-    const int strip = v / (4 * a.ctiles), in = v - strip * 4 * a.ctiles, rows = min(4, a.rtiles - 4 * strip);
-    const int ct = in / rows, rt = 4 * strip + in % rows;
+    const uint32_t v = die_chunk_order(blockIdx.x, gridDim.x), strip = v / (4u * a.ctiles), in = v - strip * 4u * a.ctiles;
+    const uint32_t rows = a.rtiles - 4 * strip; // at least one
+    const int ct = rows >= 4 ? in / 4 : in / rows, rt = 4 * strip + (rows >= 4 ? in % 4 : in % rows);
+    int grp = 0; // of the tile's first column
+    while (ct * TL::BN >= (grp + 1) * a.ldp) ++grp;
     const int64_t Lr = (int64_t)a.L * a.r;
     const bf16_t *A = a.A, *Bq = a.Bq + (int64_t)a.brow0 * Lr;
     auto arow = [&](int m) { return A + (int64_t)m * Lr; };
     auto brow = [&](int n) { return Bq + (int64_t)n * Lr; };
-    EpiSeqBig epi{a.P, a.M, a.ldp, a.add != 0};
+    EpiSeqBig epi{a.P + (int64_t)grp * a.M * a.ldp, grp * a.ldp, a.M, a.ldp, a.add != 0};
     if constexpr (FORM == kSeqPp) gemm_nt_pp(smem, arow, brow, epi, a.kbegin, a.kend, rt * TL::BM, ct * TL::BN, a.M, a.ncols);
     else gemm_nt<TL, true>(smem, arow, brow, epi, a.kbegin, a.kend, rt * TL::BM, ct * TL::BN, a.M, a.ncols);
 }
