@@ -1264,10 +1264,16 @@ struct EpiSeqBig {
             for (int v = 0; v < 16; ++v) out[v] += old[v];
             settle(out);
         }
+        p += (int64_t)row_base * ldp;
+        // a masked store is a branch each, taken to the end of the kernel and back: only where the block has rows past the end
+        // (the first active lane holds the block's first row)
+        if (__builtin_amdgcn_readfirstlane(row_base) + 31 < nrows) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int m = epi_row(row_base, v);
-            if (m < nrows) p[(int64_t)m * ldp] = out[v];
+            for (int v = 0; v < 16; ++v) p[epi_row(0, v) * ldp] = out[v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (epi_row(row_base, v) < nrows) p[epi_row(0, v) * ldp] = out[v];
         }
     }
 };
