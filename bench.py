@@ -23,13 +23,15 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
 MFMA_BF16_PEAK_TFLOPS = 2500.0
-CACHE_PASS_CLASSES = ("g_proj", "g_tokred", "fwd_down", "bwd_wgrad")
+CACHE_PASS_CLASSES = ("g_proj", "g_tokred", "fwd_down", "bwd_layer", "bwd_wgrad")
 
 
-def kernel_models(w, M):
+def kernel_models(w, M, split):
     """Algorithmic work of one step's launches of each kernel class: (HBM bytes, flops).
     (The per-layer classes launch once per layer; the layer-by-layer chains of the wide-adapter
-    path launch several kernels per layer; every other class is one launch per step.)
+    path launch several kernels per layer; every other class is one launch per step.  In the per-layer
+    backward bwd_layer is the token reductions and dx in one launch, and the sums of every layer but the
+    last ride on the launch of the next one's dpre; with `split` launches each is a class of its own.)
 
     Bytes are what the method must move for that piece of the step (cache slab of the layer,
     saved pre-activations, parameters/gradients), not what a particular kernel happens to
@@ -42,11 +44,12 @@ def kernel_models(w, M):
     return {
         "fwd_down": (L * (slab + pre), 2.0 * M * d * r * L),
         "fwd_up": (0, 2.0 * M * d * r * L),
-        "bwd_dpre": (L * pre, 2.0 * M * d * r * L),
+        "bwd_dpre": (L * pre + (0 if split else (L - 1) * PL * 4), 2.0 * M * d * r * L),
+        "bwd_layer": (L * (slab + PL * 4), 6.0 * M * d * r * L),
         "bwd_wgrad": (L * (slab + PL * 4), 4.0 * M * d * r * L),
         "bwd_dx": (L * slab, 2.0 * M * d * r * L),
         "adamw": (w.P * 28, 12.0 * w.P),
-        "reduce": (L * PL * 4, 0.0),
+        "reduce": ((L if split else 1) * PL * 4, 0.0),
         "shadows": (w.P * 4, 0.0),
         "pool": (slab, 0.0),
         "head": (B * d * 4, 2.0 * B * d * C),
@@ -207,7 +210,7 @@ def run_workload(name, N, steps, warmup, flags, keep_cpu_samples=0, want_peaks=F
         sess.step(plan[k], labs[k], keep_grads=False)
     prof = pb.pac_profile_end(sess.ctx)
     M = float(np.mean([lens_all[ids].sum() for ids in plan[warmup:warmup + prof_steps]]))
-    models = kernel_models(w, M)
+    models = kernel_models(w, M, bool(flags & pb.PAC_FLAG_SPLIT_LAUNCH))
     slice_bytes = w.L * M * w.d * (2 if w.cache_dtype == "bf16" else 4)
     measured = measure_peaks(torch, pb, sess, slice_bytes) if want_peaks else None
 

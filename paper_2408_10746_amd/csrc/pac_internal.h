@@ -72,9 +72,10 @@ struct Dims {
 // Kernel classes for per-kernel timing.
 enum KClass {
     KC_CACHE_FILL = 0, KC_SETUP, KC_SHADOWS, KC_FWD_DOWN, KC_FWD_UP, KC_POOL, KC_HEAD, KC_HEAD_BWD,
-    KC_BWD_DPRE, KC_BWD_WGRAD, KC_BWD_DX, KC_REDUCE, KC_ADAMW,
+    KC_BWD_DPRE, KC_BWD_LAYER, KC_REDUCE, KC_ADAMW,
     KC_G_PREP, KC_G_PROJ, KC_G_CHAIN_FWD, KC_G_HEAD, KC_G_CHAIN_BWD, KC_G_TOKRED, KC_G_GGSUM, KC_G_POST, KC_G_FINISH,
     // parts of the fused launches, seen only with PAC_FLAG_SPLIT_LAUNCH
+    KC_BWD_WGRAD, KC_BWD_DX,
     KC_G_PREP_SETUP, KC_G_PREP_COPY, KC_G_PREP_CHAT, KC_G_PREP_V, KC_G_PROJ_U, KC_G_PROJ_Q, KC_G_PROJ_PB,
     KC_G_TOKRED_E, KC_G_TOKRED_G, KC_G_TOKRED_VEC, KC_G_POST_F, KC_G_POST_W, KC_G_POST_VEC,
     // the ladder architecture (pac_ladder.hip)

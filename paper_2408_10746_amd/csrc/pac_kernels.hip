@@ -755,12 +755,14 @@ struct HeadBwdArgs {
     const float *Wu_top;
     float *dh;
     int nt;
+    int blk_off; // first block of this launch
 };
 __global__ __launch_bounds__(256) void k_head_bwd(HeadBwdArgs a)
 {
     __shared__ float sdz[kMaxBatch * kMaxClasses];
-    if ((int)blockIdx.x < a.nt) return dh_top(a.dz, a.Wcls, a.Wu_top, a.samp_len, a.B, a.d, a.r, a.C, a.dh, blockIdx.x);
-    const int b = blockIdx.x - a.nt, nx = (a.d + 255) / 256;
+    const int blk = blockIdx.x + a.blk_off;
+    if (blk < a.nt) return dh_top(a.dz, a.Wcls, a.Wu_top, a.samp_len, a.B, a.d, a.r, a.C, a.dh, blk);
+    const int b = blk - a.nt, nx = (a.d + 255) / 256;
     head_bwd(a.pooled, a.Wcls, a.dz, a.B, a.M, a.d, a.C, a.rowsamp, a.samp_len, a.gWcls, a.gccls, a.ds, a.rows_per_block,
              b % nx, b / nx, sdz);
 }
@@ -1142,18 +1144,23 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
 
     float *grads = io.grads;
     const int rows_per_block = 64;
-    float *dh = dlam_part; // B*r floats; the first launch of the layers' backward overwrites it afterwards
+    const bool split = (D.flags & 2) != 0; // PAC_FLAG_SPLIT_LAUNCH
+    float *dh = dlam_part; // B*r floats; read by the top layer's k_dpre_top, overwritten by the k_bwd_layer after it
     HeadBwdArgs ha{pooled, Wcls, dz, meta.B, M, d, r, D.C, rowsamp, samp_len, grads + (int64_t)L * PL,
                    grads + (int64_t)L * PL + (int64_t)d * D.C, ds, rows_per_block, params + (int64_t)(L - 1) * PL + dr + r, dh,
-                   cdiv((int64_t)meta.B * r, 4)};
-    PAC_LAUNCH(prof, st, KC_HEAD_BWD, k_head_bwd, dim3(ha.nt + cdiv(d, 256) * cdiv(M, rows_per_block)), dim3(256), 0, st, ha);
+                   cdiv((int64_t)meta.B * r, 4), 0};
+    const int nh = cdiv(d, 256) * cdiv(M, rows_per_block);
+    if (split) {
+        PAC_LAUNCH(prof, st, KC_BWD_DPRE, k_head_bwd, dim3(ha.nt), dim3(256), 0, st, ha);
+        ha.blk_off = ha.nt;
+    }
+    PAC_LAUNCH(prof, st, KC_HEAD_BWD, k_head_bwd, dim3(ha.nt - ha.blk_off + nh), dim3(256), 0, st, ha);
 
     const int kstep = Stage<TC, 4>::BK;
     int splits = W.splits;
     int rows_per_split = cdiv(cdiv(M, splits), kstep) * kstep;
     splits = cdiv(M, rows_per_split);
     const int wg_tiles = cdiv(r, 64) * cdiv(d, 64), nw = wg_tiles * splits * 2, nx = (int)(g_rows_d.x * g_rows_d.y);
-    const bool split = (D.flags & 2) != 0; // PAC_FLAG_SPLIT_LAUNCH
     // ds of the layer at hand and of the one below take turns in two arrays; the top layer's side state has been pooled
     float *ds_cur = ds, *ds_next = s_all + (int64_t)(L - 1) * Md;
     for (int l = L - 1; l >= 0; --l) {
@@ -1188,7 +1195,7 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
         if (split) {
             launch_layer(KC_BWD_WGRAD, 0, nw);
             launch_layer(KC_BWD_DX, nw, nx);
-        } else launch_layer(KC_BWD_WGRAD, 0, nw + nx);
+        } else launch_layer(KC_BWD_LAYER, 0, nw + nx);
         std::swap(ds_cur, ds_next);
     }
     PAC_LAUNCH(prof, st, KC_REDUCE, k_reduce_layer, dim3(cdiv(PL, 256)), dim3(256), 0, st,

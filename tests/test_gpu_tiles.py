@@ -115,6 +115,34 @@ GRADIENT_BITS = [
 ]
 
 
+# Per-layer path: with PAC_FLAG_SPLIT_LAUNCH every part of the joined launches is a launch of its own class, with the same
+# bits.  fp32 on 16-row tiles with one layer and with five, on 64 x 64 tiles; bf16 by flag.
+@pytest.mark.parametrize("w,flags", [
+    (Workload("l1", L=1, d=64, n_max=40, B=3, r=32, C=2, N=3, cache_dtype="f32", len_lo=7), 0),
+    (Workload("l5", L=5, d=96, n_max=70, B=7, r=64, C=3, N=7, cache_dtype="f32", len_lo=7), 0),
+    (Workload("l3", L=3, d=64, n_max=75, B=32, r=512, C=2, N=32, cache_dtype="f32", len_lo=70), 0),
+    (Workload("b3", L=3, d=96, n_max=50, B=5, r=64, C=3, N=5, cache_dtype="bf16", len_lo=9), pb.PAC_FLAG_PER_LAYER),
+], ids=lambda v: getattr(v, "name", None))
+def test_per_layer_split_launches(w, flags):
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, lab = inputs.batch_acts(w, ids), torch.from_numpy(inputs.labels(w)[ids]).cuda()
+    got, launches = [], []
+    for split in (0, pb.PAC_FLAG_SPLIT_LAUNCH):
+        sess = make_session(w, lens=lens, flags=flags | split)
+        assert pb.pac_step_path(sess.ctx) == 0
+        sess.cache_fill(ids, acts, lens)
+        sess.set_params(inputs.random_params(w, up_scale=0.5))
+        pb.pac_profile_begin(sess.ctx)
+        sess.loss_grad(ids, lab)
+        torch.cuda.synchronize()
+        launches.append({k: n for k, (_, n) in pb.pac_profile_end(sess.ctx).items() if k.startswith(("head_bwd", "bwd_", "reduce"))})
+        got.append((sess.loss.clone(), sess.logits.clone(), sess.grads.clone()))
+    assert launches[0] == {"head_bwd": 1, "bwd_dpre": w.L, "bwd_layer": w.L, "reduce": 1}
+    assert launches[1] == {"head_bwd": 1, "bwd_dpre": w.L + 1, "bwd_wgrad": w.L, "bwd_dx": w.L, "reduce": w.L}
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a, b)
+
+
 def gradients(w):
     lens, ids = inputs.lengths(w), np.arange(w.B)
     sess = make_session(w, lens=lens)
