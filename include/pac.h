@@ -96,8 +96,8 @@ typedef struct {
 /* Measurement aid: launch every part of the fused multi-part launches on its own, so that
  * pac_profile_end reports one class per part (slower; results unchanged). */
 #define PAC_FLAG_SPLIT_LAUNCH 2
-/* On the Gram-matrix path, run the two chains over the layers layer by layer (groups of layers: one
- * wide contraction per group, one short one per layer; the form used where a 16-token tile's history
+/* On the Gram-matrix path, run the two chains over the layers layer by layer (groups of layers: wide
+ * contractions between ranges of groups, a short one per layer inside them; the form used where a 16-token tile's history
  * of all layers does not fit a compute unit's LDS, e.g. r > 128) even where the single-launch chains
  * apply (same results up to rounding). */
 #define PAC_FLAG_LAYER_CHAIN 4
@@ -153,6 +153,14 @@ int32_t pac_step_path(const pac_ctx *ctx);
  * lens HOST, B entries in [1, n_max], or NULL = every sample has n_max tokens; B in [1, B_max].
  * PAC_ERR_NULL, PAC_ERR_RANGE. */
 pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t out[6] /*HOST*/);
+
+/* How the layer-by-layer chains (path 2) of a step on such a batch are cut into contractions between groups of layers (the
+ * same results up to rounding however they are; for measurements and tests, as above):
+ *   out[0]  groups of layers                     out[1]  layers of a group (the last may hold fewer)
+ *   out[2]  1: ranges of groups, cut where the tiles' times say; 0: one contraction per group over everything before it
+ *   out[3]  groups before the first cut          out[4], out[5]  rows and columns of that contraction's tiles
+ * out[3..5] are 0 where there is one group, all are 0 on paths 0 and 1.  Arguments and errors as in pac_step_tiles. */
+pac_status pac_chain_plan(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t out[6] /*HOST*/);
 
 /*
  * Store one backbone forward's per-layer activations (paper Sec. 4.2: during

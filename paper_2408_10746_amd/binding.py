@@ -25,7 +25,7 @@ PAC_FLAG_LAYER_CHAIN = 4
 
 EXPORTS = [
     "pac_create", "pac_destroy", "pac_status_str", "pac_param_count", "pac_param_offsets",
-    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_step_tiles", "pac_cache_fill",
+    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_step_tiles", "pac_chain_plan", "pac_cache_fill",
     "pac_cache_lookup",
     "pac_adapter_loss_grad", "pac_adapter_step", "pac_adapter_step_static",
     "pac_probe_hbm_read", "pac_probe_mfma_bf16", "pac_probe_mfma_flops", "pac_probe_hbm_update",
@@ -103,6 +103,8 @@ def lib():
         L.pac_step_path.argtypes = [vp]
         L.pac_step_tiles.restype = C.c_int
         L.pac_step_tiles.argtypes = [vp, vp, i32, C.POINTER(i32)]
+        L.pac_chain_plan.restype = C.c_int
+        L.pac_chain_plan.argtypes = [vp, vp, i32, C.POINTER(i32)]
         L.pac_cache_fill.restype = C.c_int
         L.pac_cache_fill.argtypes = [vp, vp, i64, vp, i32, vp, i32, vp, vp]
         L.pac_cache_lookup.restype = C.c_int
@@ -226,6 +228,14 @@ def pac_step_tiles(ctx, lens, B: int) -> dict:
     out = (C.c_int32 * 6)()
     _check(lib().pac_step_tiles(ctx, _hp(la), B, out), "pac_step_tiles")
     return dict(zip(("proj", "tokens", "grads", "rows", "se", "sg"), (int(x) for x in out)))
+
+
+def pac_chain_plan(ctx, lens, B: int) -> dict:
+    """How the layer-by-layer chains of a step on B samples of the given lengths (None: all n_max) are cut (host logic)."""
+    la = _host_i32(lens)
+    out = (C.c_int32 * 6)()
+    _check(lib().pac_chain_plan(ctx, _hp(la), B, out), "pac_chain_plan")
+    return dict(zip(("groups", "layers", "ranges", "first", "rows", "cols"), (int(x) for x in out)))
 
 
 def pac_cache_fill(ctx, cache_ptr, cache_bytes, sample_ids, acts_ptr, acts_dtype, lens=None, stream=0) -> None:

@@ -194,17 +194,35 @@ int64_t pac_workspace_bytes(const pac_ctx *ctx) { return ctx ? ctx->W.total : -1
 
 int32_t pac_step_path(const pac_ctx *ctx) { return ctx ? ctx->W.use_gram : -1; }
 
-pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens, int32_t B, int32_t out[6])
+// Token rows and 16-row tiles of a batch that need not have been filled
+static pac_status batch_rows(const pac_ctx *ctx, const int32_t *lens, int32_t B, int &M, int &ntiles)
 {
-    if (!ctx || !out) return PAC_ERR_NULL;
     if (B < 1 || B > ctx->D.B_max) return PAC_ERR_RANGE;
-    int M = 0, ntiles = 0;
+    M = ntiles = 0;
     for (int32_t s = 0; s < B; ++s) {
         const int32_t len = lens ? lens[s] : ctx->D.n_max;
         if (len < 1 || len > ctx->D.n_max) return PAC_ERR_RANGE;
         M += len;
         ntiles += (len + kChainRows - 1) / kChainRows;
     }
+    return PAC_OK;
+}
+
+pac_status pac_chain_plan(const pac_ctx *ctx, const int32_t *lens, int32_t B, int32_t out[6])
+{
+    if (!ctx || !out) return PAC_ERR_NULL;
+    int M, ntiles;
+    const pac_status s = batch_rows(ctx, lens, B, M, ntiles);
+    if (s == PAC_OK) gram_chain_plan(ctx->D, ctx->W, M, out);
+    return s;
+}
+
+pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens, int32_t B, int32_t out[6])
+{
+    if (!ctx || !out) return PAC_ERR_NULL;
+    int M, ntiles;
+    const pac_status s = batch_rows(ctx, lens, B, M, ntiles);
+    if (s != PAC_OK) return s;
     if (ctx->W.use_gram) gram_step_tiles(ctx->D, ctx->W, M, ntiles, out);
     else layer_step_tiles(ctx->D, M, out);
     return PAC_OK;

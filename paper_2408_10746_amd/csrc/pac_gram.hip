@@ -2524,17 +2524,18 @@ static bool pp_pays(int64_t n256, int64_t n128, double steps)
 // epilogue and the fp32 sums' way through memory + a step of 64 in K, dearer the fuller the chip); fitted on all three
 // tiles at 22 launches, 512 to 8192 rows, K and N 768 to 8192 (4096 each: 176 us on 128 x 128 tiles, 141 on 128 x 256, 113
 // on 256 x 256; 1024 each at 2048 rows: 17.0, 21.0, 30.1; 5120 rows, 2048 each: 74, 73, 63).
+static const struct { int bm, bn; double start, step, fill; } kSeqTimes[3] = {{128, 128, 8, 0.37, 0.24}, {128, 256, 8, 0.65, 0.33}, {256, 256, 13, 0.82, 0.68}};
 struct SeqPick {
     SeqForm form;
     double us;
 };
 static SeqPick seq_pick(int M, int K, int N, bool k64)
 {
-    static const struct { int bm, bn; double start, step, fill; } kTiles[3] = {{128, 128, 8, 0.37, 0.24}, {128, 256, 8, 0.65, 0.33}, {256, 256, 13, 0.82, 0.68}};
     SeqPick best{kSeq128, 0};
     for (int f = 0; f < (k64 ? 3 : 2); ++f) { // pp_loop takes 64 of K a step
-        const int64_t tiles = (int64_t)cdiv(M, kTiles[f].bm) * cdiv(N, kTiles[f].bn);
-        const double us = cdiv(tiles, 256) * (kTiles[f].start + K / 64. * (kTiles[f].step + kTiles[f].fill * (tiles < 256 ? tiles / 256. : 1)));
+        const auto &t = kSeqTimes[f];
+        const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn);
+        const double us = cdiv(tiles, 256) * (t.start + K / 64. * (t.step + t.fill * (tiles < 256 ? tiles / 256. : 1)));
         if (f == 0 || us < best.us) best = SeqPick{(SeqForm)f, us};
     }
     return best;
@@ -2552,6 +2553,24 @@ static void seq_plan(int M, int gr, int ngroups, bool k64, int (&cut)[kMaxChainG
                 cut[n] = m;
             }
         }
+}
+
+void gram_chain_plan(const Dims &D, const WsLayout &W, int M, int32_t out[6])
+{
+    for (int i = 0; i < 6; ++i) out[i] = 0;
+    if (W.use_gram != 2) return;
+    const int g = W.chain_group, ngroups = cdiv(D.L, g);
+    const bool k64 = D.r % 64 == 0;
+    out[0] = ngroups;
+    out[1] = g;
+    out[2] = W.chain_split;
+    if (ngroups == 1) return;
+    int cut[kMaxChainGroups + 1];
+    if (W.chain_split) seq_plan(M, g * D.r, ngroups, k64, cut);
+    out[3] = W.chain_split ? cut[ngroups] : ngroups - 1;
+    const SeqForm form = seq_pick(M, out[3] * g * D.r, (D.L - out[3] * g) * D.r, k64).form;
+    out[4] = kSeqTimes[form].bm;
+    out[5] = kSeqTimes[form].bn;
 }
 
 // The tiles of a launch of the contractions over the tokens: the weights' nE (dispatched first) and those nG of the Gram
@@ -2788,7 +2807,7 @@ template <int NT> static hipError_t run_gram(const Dims &D, const WsLayout &W, c
             return hipErrorInvalidValue;
         }
     } else {
-        // groups of W.chain_group layers: one wide contraction per group, then the group's own layers
+        // groups of W.chain_group layers: contractions between ranges of groups, and each group's own layers
         const bool k64 = r % 64 == 0;
         const int small_lds = k64 ? SeqShapes<64>::TS::LDS_BYTES : SeqShapes<32>::TS::LDS_BYTES;
         PAC_HIP_TRY((allow_lds_once<&k_gseq_big<kSeq128, 64>>(SeqBigTile<kSeq128, 64>::T::LDS_BYTES)));

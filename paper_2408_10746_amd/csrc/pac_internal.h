@@ -144,6 +144,7 @@ hipError_t launch_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMe
 // pac_step_tiles for a batch of M token rows in ntiles 16-row tiles
 void gram_step_tiles(const Dims &D, const WsLayout &W, int M, int ntiles, int32_t out[6]);
 void layer_step_tiles(const Dims &D, int M, int32_t out[6]);
+void gram_chain_plan(const Dims &D, const WsLayout &W, int M, int32_t out[6]); // pac_chain_plan for a batch of M token rows
 // mixed-precision linear layer on block-wise quantised weights (pac_quant.hip)
 // (returns a pac_status value)
 int check_dq_linear_args(const void *x, int32_t M, int32_t K, const int8_t *codes, const float *consts, int32_t N,

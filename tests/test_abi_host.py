@@ -150,6 +150,26 @@ def test_tiles_chosen_per_batch():
     assert pb.lib().pac_step_tiles(None, None, 1, (C.c_int32 * 6)()) == pb.PAC_ERR_NULL
 
 
+def test_chain_plan_per_batch():
+    """Host logic: how the layer-by-layer chains are cut, and the tiles of the widest contraction."""
+    def plan(L, d, n, r, B, lens=None, **kw):
+        ctx = pb.pac_create(L, d, n, r, 3, B, 64, pb.PAC_BF16, **kw)
+        try:
+            return tuple(pb.pac_chain_plan(ctx, lens, B).values())
+        finally:
+            pb.pac_destroy(ctx)
+    assert plan(32, 4096, 256, 256, 16) == (8, 4, 1, 4, 256, 256)              # LLaMA-7B-shaped: halves
+    assert plan(32, 4096, 1024, 512, 8, [640] * 8) == (16, 2, 1, 13, 256, 256)  # long sequences
+    assert plan(14, 32, 4200, 160, 2) == (3, 6, 0, 2, 128, 128)                # many tokens on few weights: no room for ranges
+    assert plan(4, 512, 64, 224, 8) == (1, 4, 1, 0, 0, 0)                      # one group
+    assert plan(12, 768, 128, 96, 32) == (0, 0, 0, 0, 0, 0)                    # single-launch chains
+    assert plan(12, 768, 128, 96, 32, flags=pb.PAC_FLAG_LAYER_CHAIN)[:3] == (2, 8, 1)
+    with pytest.raises(pb.PacError) as e:
+        plan(32, 4096, 256, 256, 2, [256, 0])
+    assert e.value.status == pb.PAC_ERR_RANGE
+    assert pb.lib().pac_chain_plan(None, None, 1, (C.c_int32 * 6)()) == pb.PAC_ERR_NULL
+
+
 def test_argument_errors_are_caught_before_any_launch():
     """Fake (never dereferenced) device addresses: every call below must fail on the host."""
     ctx = pb.pac_create(2, 64, 16, 32, 3, 4, 8, pb.PAC_BF16)

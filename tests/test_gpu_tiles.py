@@ -51,18 +51,21 @@ def test_wide_contractions_on_large_tiles(w, tiles):
 
 # The layer-by-layer chains over several groups of layers: 256 x 256 tiles (c1), K steps of 32 and a last group of two layers
 # (c2), many tokens on few weights, where the groups' sums do not fit beside each other (c3), five groups of which the last
-# holds one layer, on a few rows (c4), a group that is not a power of two wide (c5).
-@pytest.mark.parametrize("w", [
-    Workload("c1", L=8, d=32, n_max=180, B=30, r=512, C=2, N=30, cache_dtype="bf16", len_lo=160),
-    Workload("c2", L=14, d=96, n_max=90, B=5, r=160, C=3, N=5, cache_dtype="bf16", len_lo=3),
-    Workload("c3", L=14, d=32, n_max=4200, B=2, r=160, C=2, N=2, cache_dtype="bf16", len_lo=3900),
-    Workload("c4", L=9, d=64, n_max=23, B=1, r=384, C=4, N=1, cache_dtype="bf16", len_lo=0),
-    Workload("c5", L=20, d=64, n_max=130, B=8, r=192, C=2, N=8, cache_dtype="bf16", len_lo=40),
-], ids=lambda w: w.name)
-def test_chains_over_groups_of_layers(w):
+# holds one layer, on a few rows (c4), a group that is not a power of two wide (c5), a first part of two groups and a last
+# group of one layer (c6).
+@pytest.mark.parametrize("w,plan", [
+    (Workload("c1", L=8, d=32, n_max=180, B=30, r=512, C=2, N=30, cache_dtype="bf16", len_lo=160), (4, 2, 1, 1, 256, 256)),
+    (Workload("c2", L=14, d=96, n_max=90, B=5, r=160, C=3, N=5, cache_dtype="bf16", len_lo=3), (3, 6, 1, 1, 128, 128)),
+    (Workload("c3", L=14, d=32, n_max=4200, B=2, r=160, C=2, N=2, cache_dtype="bf16", len_lo=3900), (3, 6, 0, 2, 128, 128)),
+    (Workload("c4", L=9, d=64, n_max=23, B=1, r=384, C=4, N=1, cache_dtype="bf16", len_lo=0), (5, 2, 1, 1, 128, 128)),
+    (Workload("c5", L=20, d=64, n_max=130, B=8, r=192, C=2, N=8, cache_dtype="bf16", len_lo=40), (4, 5, 1, 1, 128, 128)),
+    (Workload("c6", L=9, d=32, n_max=120, B=20, r=512, C=2, N=20, cache_dtype="bf16", len_lo=110), (5, 2, 1, 2, 128, 256)),
+], ids=lambda v: getattr(v, "name", None))
+def test_chains_over_groups_of_layers(w, plan):
     lens, ids = inputs.lengths(w), np.arange(w.B)
     acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
     sess = make_session(w, lens=lens)
+    assert tuple(pb.pac_chain_plan(sess.ctx, lens[:w.B], w.B).values()) == plan
     sess.cache_fill(ids, acts, lens)
     check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["bf16"], what=w.name)
 
