@@ -2520,11 +2520,18 @@ static bool pp_pays(int64_t n256, int64_t n128, double steps)
     return n256 > 0 && (n256 / 256. + 0.8) * (15 + 1.65 * steps) < (n128 / 256. + 0.8) * (8 + 1.08 * steps);
 }
 
-// The wide contractions of the chains.  Estimated time of one over M rows, N columns and K (us): rounds of tiles x (start,
-// epilogue and the fp32 sums' way through memory + a step of 64 in K, dearer the fuller the chip); fitted on all three
-// tiles at 22 launches, 512 to 8192 rows, K and N 768 to 8192 (4096 each: 176 us on 128 x 128 tiles, 141 on 128 x 256, 113
-// on 256 x 256; 1024 each at 2048 rows: 17.0, 21.0, 30.1; 5120 rows, 2048 each: 74, 73, 63).
-static const struct { int bm, bn; double start, step, fill; } kSeqTimes[3] = {{128, 128, 8, 0.37, 0.24}, {128, 256, 8, 0.65, 0.33}, {256, 256, 13, 0.82, 0.68}};
+// The wide contractions of the chains: estimated time of one over M rows, N columns and K (us).  With steps of 64 in K one tile
+// fills a compute unit's LDS: rounds of tiles x (start, epilogue and the fp32 sums' way through memory + a step, dearer the
+// fuller the chip).  Fitted on all three tiles at 22 launches of 512 to 8192 rows, K and N 768 to 8192 (4096 each: 176 us on
+// 128 x 128 tiles, 141 on 128 x 256, 113 on 256 x 256; 1024 each at 2048 rows: 17.0, 21.0, 30.1; 5120 rows, 2048 each: 74,
+// 73, 63); of 472 other launches, 11 to 8000 rows, it picks the fastest for all but one (0.7 us).  With steps of 32 several
+// tiles share a compute unit, so there are no rounds, and two steps of 32 cost more than one of 64: fitted on both tiles at 256
+// launches (2642 rows, K = 4480, N = 2016: 85 us and 96; 5017, 1792, 896: 33 and 40, which rounds got wrong; 5017, 2688,
+// 2464: 115 and 89); at five of them the tiles picked are more than 5 % slower than the other, 7 us at most.
+static const struct { int bm, bn; double start, step, fill; } kSeqTimes[2][3] = {
+    {{128, 128, 4.5, 0.65, 0.46}, {128, 256, 5, 0.88, 0.71}},                          // steps of 32 (pp_loop takes 64)
+    {{128, 128, 8, 0.37, 0.24}, {128, 256, 8, 0.65, 0.33}, {256, 256, 13, 0.82, 0.68}} // steps of 64
+};
 struct SeqPick {
     SeqForm form;
     double us;
@@ -2532,10 +2539,11 @@ struct SeqPick {
 static SeqPick seq_pick(int M, int K, int N, bool k64)
 {
     SeqPick best{kSeq128, 0};
-    for (int f = 0; f < (k64 ? 3 : 2); ++f) { // pp_loop takes 64 of K a step
-        const auto &t = kSeqTimes[f];
+    for (int f = 0; f < (k64 ? 3 : 2); ++f) {
+        const auto &t = kSeqTimes[k64][f];
         const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn);
-        const double us = cdiv(tiles, 256) * (t.start + K / 64. * (t.step + t.fill * (tiles < 256 ? tiles / 256. : 1)));
+        const double fill = k64 && tiles > 256 ? 1 : tiles / 256.;
+        const double us = (k64 ? cdiv(tiles, 256) : 1) * (t.start + K / 64. * (t.step + t.fill * fill));
         if (f == 0 || us < best.us) best = SeqPick{(SeqForm)f, us};
     }
     return best;
@@ -2569,8 +2577,8 @@ void gram_chain_plan(const Dims &D, const WsLayout &W, int M, int32_t out[6])
     if (W.chain_split) seq_plan(M, g * D.r, ngroups, k64, cut);
     out[3] = W.chain_split ? cut[ngroups] : ngroups - 1;
     const SeqForm form = seq_pick(M, out[3] * g * D.r, (D.L - out[3] * g) * D.r, k64).form;
-    out[4] = kSeqTimes[form].bm;
-    out[5] = kSeqTimes[form].bn;
+    out[4] = kSeqTimes[k64][form].bm;
+    out[5] = kSeqTimes[k64][form].bn;
 }
 
 // The tiles of a launch of the contractions over the tokens: the weights' nE (dispatched first) and those nG of the Gram

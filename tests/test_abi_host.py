@@ -161,6 +161,7 @@ def test_chain_plan_per_batch():
     assert plan(32, 4096, 256, 256, 16) == (8, 4, 1, 4, 256, 256)              # LLaMA-7B-shaped: halves
     assert plan(32, 4096, 1024, 512, 8, [640] * 8) == (16, 2, 1, 13, 256, 256)  # long sequences
     assert plan(14, 32, 4200, 160, 2) == (3, 6, 0, 2, 128, 128)                # many tokens on few weights: no room for ranges
+    assert plan(8, 576, 627, 224, 8) == (2, 4, 1, 1, 128, 128)                 # K steps of 32: no rounds (20.9 us / 23.8)
     assert plan(4, 512, 64, 224, 8) == (1, 4, 1, 0, 0, 0)                      # one group
     assert plan(12, 768, 128, 96, 32) == (0, 0, 0, 0, 0, 0)                    # single-launch chains
     assert plan(12, 768, 128, 96, 32, flags=pb.PAC_FLAG_LAYER_CHAIN)[:3] == (2, 8, 1)
