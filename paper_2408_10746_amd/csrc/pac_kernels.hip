@@ -80,13 +80,13 @@ void plan_workspace(const Dims &D, WsLayout &W)
     W.grads = take(D.P * 4);
     W.use_gram = 0;
     if (gram) plan_gram_workspace(D, W, o);
-    // Four steps of 64 token rows a split, and shorter splits where those are fewer than the compute units (512 rows,
-    // d = 256, r = 32: two splits of eight tiles, 12.4 us a layer, against 6.4 us with eight), unless only they would take the
-    // workspace past what pac_adapter_step_static has.
+    // 256 token rows a split, and single steps (256 bytes of rows: 64 in fp32, 128 in bf16) where those are fewer than the
+    // compute units (fp32, 512 rows, d = 256, r = 32: two splits of eight tiles, 12.4 us a layer, against 6.4 us with eight),
+    // unless only they would take the workspace past what pac_adapter_step_static has.
     W.splits = choose_splits(D, 1024, 256);
     W.part = 0;
     if (!gram) {
-        const int more = choose_splits(D, 256, 64);
+        const int more = choose_splits(D, 256, D.cache_dtype == 0 ? Stage<bf16_t, 4>::BK : Stage<float, 4>::BK);
         auto end = [&](int splits) { return align256(o + splits * D.PL * 4); };
         if (more > W.splits && (end(more) <= PAC_STATIC_WORKSPACE_BYTES || end(W.splits) > PAC_STATIC_WORKSPACE_BYTES)) W.splits = more;
         W.part = take((int64_t)W.splits * D.PL * 4);

@@ -150,6 +150,19 @@ def test_tiles_chosen_per_batch():
     assert pb.lib().pac_step_tiles(None, None, 1, (C.c_int32 * 6)()) == pb.PAC_ERR_NULL
 
 
+def test_per_layer_workspace_holds_the_splits_that_run():
+    """bf16 weight gradients walk 128 token rows a step: 128 rows are one split and reserve one set of partial sums."""
+    def ws(n):
+        ctx = pb.pac_create(1, 512, n, 512, 2, 1, 1, pb.PAC_BF16, flags=pb.PAC_FLAG_PER_LAYER)
+        try:
+            return pb.pac_workspace_bytes(ctx)
+        finally:
+            pb.pac_destroy(ctx)
+    partials = 4 * (2 * 512 * 512 + 512 + 512 + 1)
+    assert ws(128) - ws(64) < partials       # the 64 rows more need a quarter of that
+    assert ws(129) - ws(128) > partials
+
+
 def test_chain_plan_per_batch():
     """Host logic: how the layer-by-layer chains are cut, and the tiles of the widest contraction."""
     def plan(L, d, n, r, B, lens=None, **kw):
