@@ -1212,7 +1212,7 @@ template <bool FWD, int NT, int CMAX = kMaxClasses> __global__ __launch_bounds__
 // are cut the same way.  The running sums wait in fp32 in P.  Where to cut is planned per call (seq_plan) from the tiles'
 // measured times: grids that leave the last round of tiles nearly full, and long K for the large tiles.  (One contraction
 // per group over everything before it does the same operations on g r = 1024 columns at a time, 328 tiles of 128 x 128 for
-// 5120 token rows: 32 layers of r = 512, both directions, 4.23 ms against 2.7 ms.)  Inside the group each layer contracts over
+// 5120 token rows: 32 layers of r = 512, both directions, 4.23 ms against 2.45 ms.)  Inside the group each layer contracts over
 // the group's earlier layers and then adds P and applies the nonlinearity: up to r = 256 one launch walks all layers of the
 // group per 16-token tile (k_gseq_group), above that each layer is a short tiled contraction of its own (k_gseq_layer).
 // The per-tile column sums the later launches need are taken from the finished bf16 arrays in one pass per direction.

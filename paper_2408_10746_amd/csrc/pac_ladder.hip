@@ -2021,8 +2021,8 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
     const float scale = 1.f / sqrtf((float)a.dh);
     int nlong = 1; // longest sample of the batch
     for (int i = 0; i < B; ++i) nlong = meta.len[i] > nlong ? meta.len[i] : nlong;
-    int nchunk = cdivi(nlong, 64); // workgroups per sample and head: 64 rows each, one tile of 16 per wavefront
-    nchunk = nchunk > 8 ? 8 : nchunk;
+    int nchunk = cdivi(nlong, 64); // workgroups per sample and head: 64 rows each, one tile of 16 per wavefront,
+    nchunk = nchunk > 8 ? 8 : nchunk; // above 512 tokens several
     for (int l = 0; l < L; ++l) {
         const float *pl = params + (int64_t)l * a.PLb;
         if (w <= 128) { // gate, LayerNorm 1 and the q, k, v projection in one launch
