@@ -139,14 +139,16 @@ int64_t pac_cache_bytes(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int64_
 int64_t pac_workspace_bytes(const pac_ctx *ctx);
 
 /* Which formulation of the step (paper Sec. 4.1, 5.2: the same function of the same inputs in each)
- * this configuration runs on: 0 the per-layer kernels; 1 the Gram-matrix formulation with the chains
- * over the layers as one launch per direction; 2 the Gram-matrix formulation with the chains launched
- * layer by layer.  Decided by pac_create from the shape, cache dtype and flags.  -1 if ctx is NULL. */
+ * this configuration runs on: 0 the per-layer kernels or, on an fp32 cache where the adapters are at most half as wide
+ * as the hidden state and 16 rows of all layers fit a compute unit's LDS, the fp32 kernels of the Gram-matrix
+ * formulation; 1 the bf16 kernels of the Gram-matrix formulation with the chains over the layers as one launch per
+ * direction; 2 the same with the chains launched layer by layer.  Decided by pac_create from the shape, cache dtype and flags.  -1 if ctx is NULL. */
 int32_t pac_step_path(const pac_ctx *ctx);
 
 /* Which tiles the launches of a step on such a batch take (same results up to rounding in each; host logic, for
  * measurements and tests that have to know which form they ran):
- *   out[0]  token rows per tile of the projection launch (paths 1, 2), of the layers' down-projections (path 0)
+ *   out[0]  token rows per tile of the projection launch (paths 1, 2), of the layers' down-projections (path 0; 16, of the
+ *           chains over the layers, where an fp32 step takes the Gram-matrix formulation)
  *   out[1]  columns of d per tile of the contractions over the tokens      out[2]  side of the gradient launch's tiles
  *   out[3]  1: the gradients that are no contractions as whole rows        out[4], out[5]  token splits of the
  *           weights' contraction and of the Gram matrix                    (out[1..5] are 0 on path 0)

@@ -224,7 +224,7 @@ pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens, int32_t B, in
     const pac_status s = batch_rows(ctx, lens, B, M, ntiles);
     if (s != PAC_OK) return s;
     if (ctx->W.use_gram) gram_step_tiles(ctx->D, ctx->W, M, ntiles, out);
-    else layer_step_tiles(ctx->D, M, out);
+    else layer_step_tiles(ctx->D, ctx->W, M, out);
     return PAC_OK;
 }
 

@@ -55,6 +55,10 @@ struct WsLayout {
     int64_t g_dlam_part;            // f32 [L][slots]
     int64_t g_samp_tile0, g_loss_part, g_Gp, g_E, g_zero;
     int32_t g_dlam_slots;
+
+    // ---- fp32 steps in the Gram-matrix formulation (pac_gram32.hip; use_gram is 0) ----
+    int32_t f32_gram;   // the step runs there
+    int32_t f_splits;   // token splits of its contractions over the tokens at the largest batch
 };
 
 constexpr int kChainRows = 16; // token rows per chain workgroup (Gram-matrix path)
@@ -143,7 +147,10 @@ void plan_gram_workspace(const Dims &D, WsLayout &W, int64_t &offset);
 hipError_t launch_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io);
 // pac_step_tiles for a batch of M token rows in ntiles 16-row tiles
 void gram_step_tiles(const Dims &D, const WsLayout &W, int M, int ntiles, int32_t out[6]);
-void layer_step_tiles(const Dims &D, int M, int32_t out[6]);
+void layer_step_tiles(const Dims &D, const WsLayout &W, int M, int32_t out[6]);
+bool f32_gram_fits(const Dims &D); // whether pac_gram32.hip has kernels for the configuration
+void plan_f32_gram_workspace(const Dims &D, WsLayout &W, int64_t &offset);
+hipError_t launch_f32_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io);
 void gram_chain_plan(const Dims &D, const WsLayout &W, int M, int32_t out[6]); // pac_chain_plan for a batch of M token rows
 // mixed-precision linear layer on block-wise quantised weights (pac_quant.hip)
 // (returns a pac_status value)

@@ -48,8 +48,11 @@ static int choose_splits(const Dims &D, int workgroups, int min_rows)
     return s;
 }
 
+static bool rows16_pays(int M, int ncols, bool long_steps);
+
 void plan_workspace(const Dims &D, WsLayout &W)
 {
+    W.f32_gram = W.f_splits = 0;
     const int64_t tc = D.cache_dtype == 0 ? 2 : 4;
     int64_t o = 0;
     auto take = [&](int64_t bytes) { int64_t at = o; o = align256(o + bytes); return at; };
@@ -92,6 +95,18 @@ void plan_workspace(const Dims &D, WsLayout &W)
         W.part = take((int64_t)W.splits * D.PL * 4);
     }
     W.total = o;
+    // fp32 in the Gram-matrix formulation, where 16-row tiles pay (there its launches have been measured against these), and
+    // where it takes no more workspace than pac_adapter_step_static has or, above that, than twice the per-layer kernels'
+    if (f32_gram_fits(D) && rows16_pays((int)D.Mmax, D.r, D.d % Stage<float, 4>::BK == 0)) {
+        WsLayout G = W;
+        int64_t at = 0;
+        plan_f32_gram_workspace(D, G, at);
+        if (at <= PAC_STATIC_WORKSPACE_BYTES || (W.total > PAC_STATIC_WORKSPACE_BYTES && at <= 2 * W.total)) {
+            W = G;
+            W.f32_gram = 1;
+            W.total = at;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1203,15 +1218,17 @@ static hipError_t run_loss_grad(const Dims &D, const WsLayout &W, const BatchMet
     return hipGetLastError();
 }
 
-void layer_step_tiles(const Dims &D, int M, int32_t out[6])
+void layer_step_tiles(const Dims &D, const WsLayout &W, int M, int32_t out[6])
 {
     for (int i = 0; i < 6; ++i) out[i] = 0;
-    out[0] = D.cache_dtype != 0 && rows16_pays(M, D.r, D.d % Stage<float, 4>::BK == 0) ? 16 : 64;
+    if (W.f32_gram) out[0] = kChainRows;
+    else out[0] = D.cache_dtype != 0 && rows16_pays(M, D.r, D.d % Stage<float, 4>::BK == 0) ? 16 : 64;
 }
 
 hipError_t launch_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io)
 {
     if (W.use_gram) return launch_gram_loss_grad(D, W, meta, io);
+    if (W.f32_gram) return launch_f32_gram_loss_grad(D, W, meta, io);
     if (D.cache_dtype == 0) return run_loss_grad<bf16_t>(D, W, meta, io);
     return run_loss_grad<float>(D, W, meta, io);
 }

@@ -106,6 +106,45 @@ def test_fp32_contractions(w, rows):
     check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
 
 
+# fp32 in the Gram-matrix formulation: adapter widths of each instantiation, d of a last tile and a last chunk half empty (96,
+# 288, 352), samples of less than one and of several 16-row tiles, fewer than 16 rows in all (t1), 32-row projection tiles (t4),
+# a partial last chunk of the vector parts' classes (16), layers whose chains need two wavefronts a unit (t5, and r > 96), token
+# splits (t7).
+@pytest.mark.parametrize("w", [
+    Workload("t1", L=2, d=64, n_max=5, B=2, r=32, C=2, N=2, cache_dtype="f32", len_lo=1),
+    Workload("t2", L=4, d=96, n_max=37, B=3, r=32, C=3, N=3, cache_dtype="f32", len_lo=9),
+    Workload("t3", L=5, d=288, n_max=33, B=5, r=96, C=16, N=5, cache_dtype="f32", len_lo=15),
+    Workload("t4", L=16, d=128, n_max=130, B=12, r=64, C=4, N=12, cache_dtype="f32", len_lo=126),
+    Workload("t5", L=31, d=128, n_max=40, B=3, r=64, C=3, N=3, cache_dtype="f32", len_lo=17),
+    Workload("t6", L=3, d=352, n_max=50, B=3, r=128, C=1, N=3, cache_dtype="f32", len_lo=3),
+    Workload("t7", L=2, d=64, n_max=400, B=8, r=32, C=3, N=8, cache_dtype="f32", len_lo=250),
+    Workload("t8", L=3, d=416, n_max=40, B=3, r=192, C=5, N=3, cache_dtype="f32", len_lo=30),
+    Workload("t9", L=2, d=512, n_max=20, B=2, r=256, C=3, N=2, cache_dtype="f32"),
+], ids=lambda w: w.name)
+def test_fp32_gram(w):
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+    params = inputs.random_params(w, up_scale=0.3)
+    got = []
+    for flags in (0, pb.PAC_FLAG_SPLIT_LAUNCH):
+        sess = make_session(w, lens=lens, flags=flags)
+        sess.cache_fill(ids, acts, lens)
+        pb.pac_profile_begin(sess.ctx)
+        check_against_oracle(w, sess, ids, acts, lens, labels, params, TOL["f32"], what=w.name)
+        assert any(k.startswith("g_tokred") and n for k, (_, n) in pb.pac_profile_end(sess.ctx).items())
+        got.append((sess.loss.clone(), sess.logits.clone(), sess.grads.clone()))
+        sess.loss_grad(ids, torch.from_numpy(labels).to(sess.dev), want_grads=False)
+        assert torch.equal(sess.loss, got[0][0]) and torch.equal(sess.logits, got[0][1])
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a, b)
+    # a smaller batch on the same workspace, and a training step with the last two sums left to the optimizer
+    sel = ids[:max(1, w.B - 1)]
+    check_against_oracle(w, sess, sel, acts[sel], None if lens is None else lens[sel], labels[sel], params, TOL["f32"], what=w.name)
+    loss, grads = sess.loss.clone(), sess.grads.clone()
+    sess.step(sel, torch.from_numpy(labels[sel]).to(sess.dev))
+    assert torch.equal(sess.loss, loss) and torch.equal(sess.grads, grads)
+
+
 # Every sum behind a gradient has a fixed order, and a launch rule or a faster load is no reason for other results: SHA-1 of
 # the gradients' bits.  The rows of the vector gradients: two threads each with 2, 6 and 8 chunks of 16 bytes, four with 5,
 # eight with 5.
