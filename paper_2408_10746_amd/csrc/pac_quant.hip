@@ -269,6 +269,188 @@ template <int BITS, int BK, int WT> __global__ __launch_bounds__(256, 2) void k_
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same product (bit for bit) for blocks of 32 and 64: a block's products of one 32 x 32 piece are two or four matrix
+// instructions, so a partial sum lives from one piece to the next and only the running sums take registers throughout.
+// While a piece's matrix instructions run, the vector units scale the piece before it and turn this thread's next codes
+// into the next step's tile: in k_dq_linear a step is matrix instructions, then scaling, then conversions, one behind the
+// other (1670 cycles a wavefront and step of 64 x 64, 512 of them matrix instructions).  Bound by what a compute unit reads: 40
+// KB a step of 256 x 128 from L2 or behind it (128 x 128 tiles read 48 KB for as much), 128 KB of fragments from LDS, and
+// the matrix units wait while either returns.  4096 x 4096 x 4096 with operands from memory, against k_dq_linear on 128 x
+// 128 tiles: blocks of 64, 209 -> 182 us, of 32, 291 -> 221; 128 x 128 tiles 201 and 234, eight wavefronts of 128 x 256
+// 200 and 235, four wavefronts of 256 x 128 with a wider piece each 212.  The order of tiles below: 216 -> 201.
+// ---------------------------------------------------------------------------
+template <int BITS, int BLK, int WTM, int WTN, int WM, int OCC> __global__ __launch_bounds__(128 * WM, OCC) void k_dq_short(DqArgs a)
+{
+    constexpr int BK = 64, WN = 2, TM = 32 * WM * WTM, TN = 32 * WN * WTN, PITCH = kDqPitch<BK>;
+    constexpr int RP = 8 * WM * WN, PA = TM / RP, PB = TN / RP, KS = BLK / 16, NBLK = BK / BLK; // rows a pass, passes
+    constexpr int NT = WTM * WTN * NBLK; // blocks of 32 x 32 x BLK a step
+    __shared__ __attribute__((aligned(16))) char lds[2 * (TM + TN) * PITCH];
+    auto As = [&](int s) { return lds + (s & 1) * TM * PITCH; };
+    auto Bs = [&](int s) { return lds + 2 * TM * PITCH + (s & 1) * TN * PITCH; };
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int i = lane & 31, g = lane >> 5;
+    // A die (blocks go round the eight of them) takes a run of tiles eight high: what its workgroups read at a time, 8 + 8
+    // tiles of rows for 64 of the output, stays in its L2
+    int m0, n0;
+    {
+        const int nt = (a.N + TN - 1) / TN, mt = (a.M + TM - 1) / TM, all = nt * mt, die = blockIdx.x & 7;
+        const int v = die * (all >> 3) + min(die, all & 7) + (blockIdx.x >> 3), mg = v / (8 * nt) * 8, high = min(8, mt - mg);
+        m0 = (mg + v % (8 * nt) % high) * TM;
+        n0 = v % (8 * nt) / high * TN;
+    }
+    const int K = a.K, nsteps = (K + BK - 1) / BK, bpr = K / BLK;
+    const int lrow = t >> 3, lch = t & 7;
+    const bf16_t *xp[PA];
+    const int8_t *wp[PB];
+#pragma unroll
+    for (int h = 0; h < PA; ++h) xp[h] = a.x + (int64_t)min(m0 + lrow + RP * h, a.M - 1) * K + lch * 8;
+#pragma unroll
+    for (int h = 0; h < PB; ++h) {
+        const int wr = min(n0 + lrow + RP * h, a.N - 1);
+        wp[h] = a.codes + (BITS == 8 ? (int64_t)wr * K + lch * 8 : ((int64_t)wr * K + lch * 8) / 2);
+    }
+    u32x4 av[PA];
+    uint64_t bv[PB];
+    // blocks of 32: a last step of one block reads its pieces twice, and the second half counts as zero
+    auto kof = [&](int s) { s = min(s, nsteps - 1); return BLK == 32 && s * BK + lch * 8 >= K ? s * BK - 32 : s * BK; };
+    auto load_a = [&](int h, int k) { av[h] = *reinterpret_cast<const u32x4 *>(xp[h] + k); };
+    auto load_b = [&](int h, int k) {
+        if (BITS == 8) bv[h] = *reinterpret_cast<const uint64_t *>(wp[h] + k);
+        else bv[h] = *reinterpret_cast<const uint32_t *>(wp[h] + k / 2);
+    };
+    auto store_a = [&](int h, int s) {
+        const bool dead = BLK == 32 && s * BK + lch * 8 >= K;
+        *reinterpret_cast<u32x4 *>(As(s) + (lrow + RP * h) * PITCH + lch * 16) = dead ? u32x4{0, 0, 0, 0} : av[h];
+    };
+    auto store_b = [&](int h, int s) {
+        u32x4 w;
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+            int q0, q1;
+            if (BITS == 8) {
+                const uint32_t word = (uint32_t)(bv[h] >> (32 * (e2 >> 1)));
+                q0 = (int)(word << (24 - 16 * (e2 & 1))) >> 24;
+                q1 = (int)(word << (16 - 16 * (e2 & 1))) >> 24;
+            } else {
+                const uint32_t word = (uint32_t)bv[h];
+                q0 = (int)(word << (28 - 8 * e2)) >> 28;
+                q1 = (int)(word << (24 - 8 * e2)) >> 28;
+            }
+            // bytes 2, 3 of both images
+            w[e2] = __builtin_amdgcn_perm(__float_as_uint((float)q1), __float_as_uint((float)q0), 0x07060302u);
+        }
+        *reinterpret_cast<u32x4 *>(Bs(s) + (lrow + RP * h) * PITCH + lch * 16) = w;
+    };
+    f32x16 tot[WTM][WTN];
+#pragma unroll
+    for (int x = 0; x < WTM; ++x)
+#pragma unroll
+        for (int y = 0; y < WTN; ++y)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) tot[x][y][v] = 0.f;
+    const float *crow[WTN];
+    float cnext[WTN][NBLK];
+    auto consts = [&](int s) {
+#pragma unroll
+        for (int y = 0; y < WTN; ++y)
+#pragma unroll
+            for (int q = 0; q < NBLK; ++q) cnext[y][q] = crow[y][min(s * NBLK + q, bpr - 1)];
+    };
+#pragma unroll
+    for (int y = 0; y < WTN; ++y) crow[y] = a.consts + (int64_t)min(n0 + wn * (32 * WTN) + y * 32 + i, a.N - 1) * bpr;
+#pragma unroll
+    for (int h = 0; h < PA; ++h) load_a(h, kof(0));
+#pragma unroll
+    for (int h = 0; h < PB; ++h) load_b(h, kof(0));
+    consts(0);
+#pragma unroll
+    for (int h = 0; h < PA; ++h) { store_a(h, 0); load_a(h, kof(1)); }
+#pragma unroll
+    for (int h = 0; h < PB; ++h) { store_b(h, 0); load_b(h, kof(1)); }
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 part[2];
+    part[1] = zero;
+    float pinv = 0.f; // of the block whose sums wait in part[(NT - 1) & 1]
+    __syncthreads();
+    for (int s = 0; s < nsteps; ++s) {
+        float inv[WTN][NBLK];
+#pragma unroll
+        for (int y = 0; y < WTN; ++y)
+#pragma unroll
+            for (int q = 0; q < NBLK; ++q) inv[y][q] = s * NBLK + q < bpr ? __fdiv_rn(1.f, cnext[y][q]) : 0.f;
+        consts(s + 1);
+        const char *A = As(s) + (wm * (32 * WTM) + i) * PITCH + g * 16, *B = Bs(s) + (wn * (32 * WTN) + i) * PITCH + g * 16;
+        const int k2 = kof(s + 2);
+        bf16x8 fa[WTM][KS], fb[2][KS];
+        auto read_a = [&](int q) {
+#pragma unroll
+            for (int x = 0; x < WTM; ++x)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) fa[x][ks] = *reinterpret_cast<const bf16x8 *>(A + x * 32 * PITCH + (q * KS + ks) * 32);
+        };
+        auto read_b = [&](int n) { // the n-th column block of the step
+            const int q = n / WTN, y = n % WTN;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) fb[n & 1][ks] = *reinterpret_cast<const bf16x8 *>(B + y * 32 * PITCH + (q * KS + ks) * 32);
+        };
+        read_a(0);
+        read_b(0);
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int n = b / WTM, x = b % WTM, y = n % WTN, q = n / WTN;
+            if (x == 0 && y == 0 && q > 0) read_a(q);
+            if (x == 0 && n + 1 < WTN * NBLK) read_b(n + 1);
+            part[b & 1] = zero;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) part[b & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[x][ks], fb[n & 1][ks], part[b & 1], 0, 0, 0);
+            // the block before it, and this block's share of the next step's tiles
+            const int bp = (b + NT - 1) % NT, np = bp / WTM, xp_ = bp % WTM, yp = np % WTN, qp = np / WTN;
+            const float pi = b == 0 ? pinv : inv[yp][qp];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) tot[xp_][yp][v] += part[(b + 1) & 1][v] * pi;
+            if (b == NT - 1) pinv = inv[y][q];
+#pragma unroll
+            for (int h = PA * b / NT; h < PA * (b + 1) / NT; ++h) { store_a(h, s + 1); load_a(h, k2); }
+#pragma unroll
+            for (int h = PB * b / NT; h < PB * (b + 1) / NT; ++h) { store_b(h, s + 1); load_b(h, k2); }
+#pragma unroll
+            for (int j = 0; j < KS; ++j) { // one matrix instruction, eight vector instructions
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0); // no piece's sums wait longer than to the next one
+        }
+        static_assert(NT % 2 == 0, "the last block's sums wait in part[1]");
+        __syncthreads();
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) tot[WTM - 1][WTN - 1][v] += part[1][v] * pinv;
+#pragma unroll
+    for (int y = 0; y < WTN; ++y) {
+        const int n = n0 + wn * (32 * WTN) + y * 32 + i;
+        if (n >= a.N) continue;
+#pragma unroll
+        for (int x = 0; x < WTM; ++x)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int m = m0 + wm * (32 * WTM) + x * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                if (m >= a.M) continue;
+                if (a.y) {
+                    a.y[(int64_t)m * a.N + n] = tot[x][y][v];
+                } else {
+                    const int smp = m / a.n_max, tok = m - smp * a.n_max;
+                    const int len = a.meta.len[smp];
+                    if (tok >= len) continue;
+                    const int64_t o = a.meta.off[smp] + ((int64_t)a.layer * len + tok) * a.N + n;
+                    if (a.cache_f32) reinterpret_cast<float *>(a.cache)[o] = tot[x][y][v];
+                    else reinterpret_cast<uint16_t *>(a.cache)[o] = dq_bf16_rne(tot[x][y][v]);
+                }
+            }
+    }
+}
+
 static pac_status check_quant_args(const void *a, const void *b, const void *c, int64_t n, int32_t block, int32_t bits)
 {
     if (!a || !b || !c) return PAC_ERR_NULL;
@@ -277,13 +459,56 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
     return PAC_OK;
 }
 
-// More tiles of 128 x 128 than compute units: two share a unit and hide each other's waits.  Up to one per unit, tiles of
-// 64 x 64 (four times as many) are as fast or faster: K = 4096, blocks of 64, 256 tiles 72.5 against 74.5 us, 192 tiles
-// 57.4 / 73.4, 64 tiles 49 / 72, one tile row 37 / 73; beyond, 320 tiles 110.6 against 89.8 us, 1024 tiles 287 / 211.
-// Blocks that are an odd multiple of 32 keep K steps of 32, where a wide tile has less to hide its barriers behind: K = 1920,
-// blocks of 32, 288 tiles 54.4 against 67.7 us, 320 tiles 57.6 / 69.5, 352 tiles 69.6 / 70.0, 448 tiles 84.5 / 70.8.
-// Up to 64 rows leave half of a wide tile and more empty: 16 x 33000, K = 1920, blocks of 64, 29.9 against 44.6 us.
-static bool dq_wide(int64_t tiles128, int M, int block) { return M > 64 && tiles128 > (block % 64 == 0 ? 256 : 320); }
+// Which kernel and tiles.  Blocks of 32 and 64, both kernels measured at 56 shapes: k_dq_short takes
+//  - 128 x 128 tiles, two workgroups a compute unit, where there are more than three quarters as many (blocks of 32: more)
+//    as compute units: blocks of 64, 160 tiles 54.9 us on 128 x 64 tiles and 55.4 on these, 256 tiles 60.5 / 58.3, 320 tiles
+//    100 / 84.8; blocks of 32, 256 tiles 78.2 / 87.4, 400 tiles 50.4 / 44.5;
+//  - 256 x 128 tiles, one workgroup of eight wavefronts a compute unit, in place of 128 x 128 ones where rounds of them
+//    end sooner: a round of 256 against 1.09 for 512 of the smaller, 0.65 where those are one a compute unit.  512 tiles
+//    of 256 rows 176 / 190 us (4096 x 4096 x 4096), 172 of them 79.7 / 94.9, 192 76.7 / 84.4, but 128 69.8 / 56.9, 288
+//    193 / 167, 384 154 / 146 and 41.1 / 39.4.
+//  - 128 x 64 tiles, three a compute unit, below, where K is long enough to hide the first step's wait: blocks of 64,
+//    K = 4096, 128 x 4096 out 45.3 against 49.3 us on k_dq_linear's 64 x 64, K = 1536, 284 x 1181 16.9 / 21.4, but K = 832,
+//    137 x 3061 10.8 / 10.5; not for fewer than eight tiles (K = 1664, 129 x 96 17.8 / 16.9) nor up to 128 rows of 4-bit
+//    codes (K = 2304, 68 x 90 22.1 / 20.9).  Blocks of 32: K = 1152, 18 x 213 15.3 / 16.9, K = 640, 1732 x 321 11.7 / 13.6,
+//    but K = 1056, 21 x 644 17.2 / 16.7, K = 512, 129 x 164 10.5 / 10.2.
+// k_dq_linear otherwise, on 64 x 64 tiles up to as many 128 x 128 ones as compute units: longer blocks, K = 4096, 256 tiles
+// 72.5 against 74.5 us, 64 tiles 49 / 72, 320 tiles 110.6 / 89.8; odd multiples of 32 keep K steps of 32, where a wide tile
+// has less to hide its barriers behind (up to 320); up to 64 rows leave half of a wide tile and more empty.
+enum DqForm { DQ_STEP_64, DQ_STEP_128, DQ_SHORT_64, DQ_SHORT_128, DQ_SHORT_256 };
+static DqForm dq_short_tiles(int64_t tiles128, int M, int N)
+{
+    const int64_t tiles256 = (int64_t)((M + 255) / 256) * ((N + 127) / 128), rest = tiles128 % 512;
+    const int64_t rounds128 = 109 * (tiles128 / 512) + (rest > 256 ? 109 : rest > 0 ? 65 : 0); // hundredths
+    return 100 * ((tiles256 + 255) / 256) <= rounds128 ? DQ_SHORT_256 : DQ_SHORT_128;
+}
+
+static DqForm dq_form(int64_t tiles128, int M, int K, int N, int block, int bits)
+{
+    if (block == 64) {
+        if (tiles128 > 192 && M > 64) return dq_short_tiles(tiles128, M, N);
+        if (K >= 1536 && (bits == 8 || M > 128) && (int64_t)((M + 127) / 128) * ((N + 63) / 64) >= 8) return DQ_SHORT_64;
+        return DQ_STEP_64;
+    }
+    if (block == 32) {
+        if (tiles128 > 256 && M > 64) return dq_short_tiles(tiles128, M, N);
+        return K >= 1152 || (K >= 512 && M > 256) ? DQ_SHORT_64 : DQ_STEP_64;
+    }
+    return M > 64 && tiles128 > (block % 64 == 0 ? 256 : 320) ? DQ_STEP_128 : DQ_STEP_64;
+}
+
+template <int WTN, int WM, int OCC> static void dq_launch_short(const DqArgs &a, int bits, hipStream_t st)
+{
+    constexpr int TM = 64 * WM, TN = 64 * WTN;
+    const dim3 grid((unsigned)((a.N + TN - 1) / TN) * (unsigned)((a.M + TM - 1) / TM));
+    if (a.block == 64) {
+        if (bits == 8) hipLaunchKernelGGL((k_dq_short<8, 64, 2, WTN, WM, OCC>), grid, dim3(128 * WM), 0, st, a);
+        else hipLaunchKernelGGL((k_dq_short<4, 64, 2, WTN, WM, OCC>), grid, dim3(128 * WM), 0, st, a);
+    } else {
+        if (bits == 8) hipLaunchKernelGGL((k_dq_short<8, 32, 2, WTN, WM, OCC>), grid, dim3(128 * WM), 0, st, a);
+        else hipLaunchKernelGGL((k_dq_short<4, 32, 2, WTN, WM, OCC>), grid, dim3(128 * WM), 0, st, a);
+    }
+}
 
 template <int BITS, int BK, int WT> static void dq_launch_as(const DqArgs &a, hipStream_t st)
 {
@@ -312,7 +537,11 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     a.y = y; a.cache = cache; a.cache_f32 = cache_f32; a.n_max = n_max; a.layer = layer;
     if (meta) a.meta = *meta;
     const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
-    if (dq_wide(tiles128, M, block)) dq_launch<2>(a, bits, st);
+    const DqForm form = dq_form(tiles128, M, K, N, block, bits);
+    if (form == DQ_SHORT_256) dq_launch_short<2, 4, 1>(a, bits, st);
+    else if (form == DQ_SHORT_128) dq_launch_short<2, 2, 2>(a, bits, st);
+    else if (form == DQ_SHORT_64) dq_launch_short<1, 2, 3>(a, bits, st);
+    else if (form == DQ_STEP_128) dq_launch<2>(a, bits, st);
     else dq_launch<1>(a, bits, st);
     return hipGetLastError();
 }

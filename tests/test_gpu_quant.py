@@ -75,6 +75,16 @@ def test_linear_layer_tiles_by_block_and_rows(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
+# blocks of 32 and 64 on 128 x 128 tiles (258 and 210 tiles, ragged at both edges), 256 x 128 ones (289 and 386 tiles of 128 rows,
+# the last of 256 half or more empty; two and three K steps of 64, a last one of a single block of 32) and 128 x 64 ones (long K,
+# fewer tiles; a tile of a few rows and columns)
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block", [(2100, 160, 2100, 32), (2050, 128, 2111, 32), (1700, 192, 1799, 64), (129, 64, 24650, 64),
+                                         (70, 96, 33000, 32), (300, 1536, 200, 64), (131, 1568, 70, 32), (5, 1184, 3, 32), (300, 512, 129, 32)])
+def test_linear_layer_short_blocks(M, K, N, block, bits):
+    check_linear_layer(M, K, N, block, bits)
+
+
 def check_linear_layer(M, K, N, block, bits):
     rng = np.random.default_rng(M + K + bits)
     W = weights(rng, N, K)
