@@ -15,7 +15,7 @@
 //   per layer, backward: FFN out^T (x GELU'), FFN in^T, LN2^T (+da), output projection^T, attention^T, qkv^T,
 //                        LN1^T + gate^T (+dt, gate gradient partials, da_{l-1})
 //   all token contractions of all layers in ONE launch (second pass over the cache slice for dW_down; the bias
-//   gradients are the column sums its right-hand loaders keep), then one ordered reduction into the gradient.
+//   gradients are the column sums its first tiles keep), then one ordered reduction into the gradient.
 // Every intermediate the reverse pass needs is kept in the workspace; every reduction runs in a fixed order.
 #include "../../include/pac_ladder.h"
 #include "pac_mma.h"
@@ -48,6 +48,10 @@ constexpr int kTileLds = tile_lds_bytes<float, TL>();
 constexpr int kLnRows = 16;    // token rows per workgroup of the LayerNorm reverse kernels (four per wavefront)
 constexpr int kFields = 15;    // tensors of one layer block
 
+// Tiles of one token contraction, 16 va x 32 vb outputs each (k_lwgrad), and the first of its work items in a layer's
+struct WgTensor {
+    int va, vb, tiles_j, item0;
+};
 // Shapes, parameter offsets (elements) and workspace offsets (bytes).
 struct Lad {
     int L, d, w, f, nh, dh, C, Bmax, cache_f32;
@@ -67,7 +71,8 @@ struct Lad {
     int64_t grads;
     int64_t total;
     int nblk, splits, rows_per_split;
-    int items_per_layer, tiles[5][2], item0[6];
+    int items_per_layer;
+    WgTensor ten[5];
 };
 enum Field { F_WD = 0, F_CD, F_G1, F_H1, F_WQKV, F_BQKV, F_WO, F_BO, F_G2, F_H2, F_W1, F_B1, F_W2, F_B2, F_LAM };
 
@@ -120,16 +125,24 @@ bool lad_plan(const Dims &D, int heads, Lad &a)
     a.pooled = take((int64_t)a.Bmax * d * 4); a.logits = take((int64_t)a.Bmax * a.C * 4);
     a.dz = take((int64_t)a.Bmax * a.C * 4); a.dp = take((int64_t)a.Bmax * d * 4);
     a.daL = take((int64_t)a.Bmax * w * 4); a.lossp = take((int64_t)a.Bmax * 4);
-    // tiles of the five token contractions of one layer: W_down [d][w], W_qkv [w][3w], W_o [w][w], W_1 [w][f], W_2 [f][w]
+    // tiles of the five token contractions of one layer: W_down [d][w], W_qkv [w][3w], W_o [w][w], W_1 [w][f], W_2 [f][w].
+    // Widths by the least matrix work, a third of a unit for each of a step's loads (32 cycles an instruction, 35 a load).
     const int rows[5] = {a.d, a.w, a.w, a.w, a.f}, cols[5] = {a.w, 3 * a.w, a.w, a.f, a.w};
-    a.item0[0] = 0;
+    a.items_per_layer = 0;
     for (int t = 0; t < 5; ++t) {
-        a.tiles[t][0] = cdivi(rows[t], 64);
-        a.tiles[t][1] = cdivi(cols[t], 64);
-        a.item0[t + 1] = a.item0[t] + a.tiles[t][0] * a.tiles[t][1];
+        int64_t best = 0;
+        for (int va = t ? 3 : 4; va <= 4; ++va)
+            for (int vb = 2; vb <= 4; ++vb) {
+                const int64_t cost = (int64_t)cdivi(rows[t], 16 * va) * cdivi(cols[t], 32 * vb) * (2 * va * vb + 3);
+                if (best && cost >= best) continue;
+                best = cost;
+                a.ten[t] = {va, vb, cdivi(cols[t], 32 * vb), a.items_per_layer};
+            }
+        a.items_per_layer += cdivi(rows[t], 16 * a.ten[t].va) * a.ten[t].tiles_j;
     }
-    a.items_per_layer = a.item0[5];
-    int s = cdivi(1024, (int64_t)a.items_per_layer * a.L);
+    // Six workgroups a compute unit, two at a time (12 layers of 768 x 96, 4096 tokens, contractions and the sum over splits:
+    // two splits 225 us, three 227, four 209, eight 219)
+    int s = cdivi(1536, (int64_t)a.items_per_layer * a.L);
     const int by_rows = cdivi(M, 256);
     if (s > by_rows) s = by_rows;
     if (s > 16) s = 16;
@@ -229,56 +242,6 @@ template <typename SRC, int ROWS, int KU> struct LoadRowsCache {
             Raw4<SRC>::widen(reg[SLOT][u], f);
             const f32x4 v = {keep ? f[0] : 0.f, keep ? f[1] : 0.f, keep ? f[2] : 0.f, keep ? f[3] : 0.f};
             if (c < G::TOTAL) *reinterpret_cast<f32x4 *>(lds + (c / S::CPK) * S::LDP + (c % S::CPK) * 4) = v;
-        }
-    }
-};
-
-// operand[i][k] = b_layer[k][i]   (K = token row: the contraction over the tokens)
-template <typename SRC, int ROWS, int KU> struct LoadColsCache {
-    static constexpr bool kSwizzled = ColsSwizzle<float, KU>::value;
-    using S = Stage<float, KU>;
-    using G = ColsGeom<float, ROWS, KU>;
-    using R = typename Raw4<SRC>::type;
-    const SRC *cache;
-    RowMap map;
-    int layer, ncols, kend, i0;
-    int kpos[2];
-    R reg[2][G::NCH][4];
-    __device__ void init(int i0_) { i0 = i0_; }
-    template <int SLOT> __device__ void fetch(int k0)
-    {
-        kpos[SLOT] = k0;
-        const int t = threadIdx.x;
-#pragma unroll
-        for (int u = 0; u < G::NCH; ++u) {
-            const int c = (t + kThreads * u) % G::TOTAL;
-            const int i = min(i0 + (c % G::IB) * 4, ncols - 4);
-            const int kb = k0 + (c / G::IB) * 4;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const int k = min(kb + kk, kend - 1);
-                reg[SLOT][u][kk] = *reinterpret_cast<const R *>(cache + map.rowoff[k] + (int64_t)layer * map.rowstride[k] + i);
-            }
-        }
-    }
-    template <int SLOT> __device__ void store(float *lds, bool)
-    {
-        const int t = threadIdx.x;
-#pragma unroll
-        for (int u = 0; u < G::NCH; ++u) {
-            const int c = t + kThreads * u;
-            const bool icol = i0 + (c % G::IB) * 4 < ncols;
-            const int kb = kpos[SLOT] + (c / G::IB) * 4;
-            Chunk<float> blk[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const bool keep = icol && kb + kk < kend && c < G::TOTAL;
-                float f[4];
-                Raw4<SRC>::widen(reg[SLOT][u][kk], f);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) blk[kk].e[e] = keep ? f[e] : 0.f;
-            }
-            if (c < G::TOTAL) cols_store_block<float, ROWS, KU>(lds, c, blk);
         }
     }
 };
@@ -1779,8 +1742,16 @@ __global__ __launch_bounds__(256) void k_lhead_c(HeadArgs a)
 // ---------------------------------------------------------------------------
 // All contractions over the tokens, one launch: work item = (split, layer, tensor, tile).
 //   W_down: b_l^T dx_l    W_qkv: xn_l^T dqkv_l    W_o: o_l^T dt_l    W_1: tn_l^T df1_l    W_2: g_l^T da_l
-// The right-hand loader of the first row of tiles keeps the column sums: the bias gradients.
+// The tiles of the first row keep the column sums of their right-hand operand: the bias gradients.
 // Results go to part[split] at the tensors' offsets in the parameter vector.
+//
+// Bound by the fp32 matrix instructions.  Both operands have the token index outermost, as the 16x16x4 instruction wants
+// it: lane (q, c) holds VA or VB neighbouring columns of token 4 s + q, sixteen lanes side by side in memory, and value e
+// of every lane makes the operand of the columns = e modulo VA, so nothing passes through LDS on the way.  A wavefront
+// multiplies 16 VA x 32 VB outputs over every fourth eight of the workgroup's tokens, requested eight ahead; the four sums
+// meet in LDS at the end.  A die takes neighbouring items (one layer's tiles over the same tokens), whose operands its L2
+// then holds.  12 layers of 768 x 96, 4096 tokens, bf16 cache: 296 -> 188 us
+// against 64 x 64 tiles through LDS, 62 % of it matrix instructions (64 x 96 at most 227: more operand bytes a product).
 // ---------------------------------------------------------------------------
 struct WgArgs {
     const void *cache;
@@ -1789,41 +1760,156 @@ struct WgArgs {
     float *part;
     int64_t Mmax, PLb, LP; // LP = L * PLb
     int64_t fo[kFields + 1];
-    int L, d, w, f, rows_per_split, items_per_layer;
-    int tiles_j[5], item0[6];
+    int L, d, w, f, rows_per_split, items_per_layer, splits;
+    WgTensor ten[5];
 };
-struct EpiSt {
-    float *out;
-    int ld;
-    __device__ void operator()(int row, int col, float v) const { out[(int64_t)row * ld + col] = v; }
-};
-template <class BL> __device__ __forceinline__ void lad_colsums(BL &bl, float *red, float *dst, int ncols, int j0)
+// V neighbouring columns of one token row, widened exactly
+template <int V> __device__ __forceinline__ void wg_load(const float *p, float (&x)[V]) { __builtin_memcpy(x, p, V * 4); }
+template <int V> __device__ __forceinline__ void wg_load(const bf16_t *p, uint32_t (&x)[V / 2]) { __builtin_memcpy(x, p, V * 2); }
+template <int V> __device__ __forceinline__ float wg_value(const float (&x)[V], int e) { return x[e]; }
+template <int V> __device__ __forceinline__ float wg_value(const uint32_t (&x)[V], int e)
 {
-    using G = ColsGeom<float, 64, 4>;
+    return __uint_as_float(e & 1 ? x[e >> 1] & 0xffff0000u : x[e >> 1] << 16);
+}
+template <typename T, int V> struct WgRaw { typedef float type[V]; };
+template <int V> struct WgRaw<bf16_t, V> { typedef uint32_t type[V / 2]; };
+
+// rows(m): where token m's row starts in the left-hand operand A, in elements, this lane's columns counted in
+template <int VA, int VB, typename SRC, class ROWS>
+__device__ __forceinline__ void wg_tile(float *lds, const SRC *A, ROWS rows, const float *Bsrc, int nA, int nB, int i0, int j0,
+                                        int kbegin, int kend, float *out, float *bias)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int k0 = kbegin + 8 * wave;
+    constexpr int NX = 32; // four wavefronts, eight tokens each
+    // columns past the end: the last ones once more, multiplied and stored with the same values
+    const int cb0 = min(j0 + VB * c, nB - VB), cb1 = min(j0 + VB * (16 + c), nB - VB);
+    struct Slot {
+        typename WgRaw<SRC, VA>::type A[2];
+        float B0[2][VB], B1[2][VB];
+    } X, Y;
+    f32x4 acc[VA][2 * VB];
+    float sum[2 * VB];
+#pragma unroll
+    for (int f = 0; f < 2 * VB; ++f) {
+        sum[f] = 0.f;
+#pragma unroll
+        for (int e = 0; e < VA; ++e) acc[e][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    int64_t at[2]; // rows of the next eight tokens: looked up a turn early, the cache's lie in a table
+    auto look = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) at[h] = rows(min(k + 4 * h + q, kend - 1));
+    };
+    auto load = [&](Slot &s, int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float *b = Bsrc + (int64_t)min(k + 4 * h + q, kend - 1) * nB;
+            wg_load<VA>(A + at[h], s.A[h]);
+            wg_load<VB>(b + cb0, s.B0[h]);
+            wg_load<VB>(b + cb1, s.B1[h]);
+        }
+        look(k + NX);
+    };
+    auto mma = [&](const Slot &s, int k) __attribute__((always_inline)) {
+        const bool whole = k + 8 <= kend;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float av[VA], bv[2 * VB];
+#pragma unroll
+            for (int e = 0; e < VA; ++e) av[e] = wg_value(s.A[h], e);
+#pragma unroll
+            for (int f = 0; f < VB; ++f) { bv[f] = s.B0[h][f]; bv[VB + f] = s.B1[h][f]; }
+            if (!whole) {
+                const bool ok = k + 4 * h + q < kend;
+#pragma unroll
+                for (int e = 0; e < VA; ++e) av[e] = ok ? av[e] : 0.f;
+#pragma unroll
+                for (int f = 0; f < 2 * VB; ++f) bv[f] = ok ? bv[f] : 0.f;
+            }
+#pragma unroll
+            for (int f = 0; f < 2 * VB; ++f) {
+                sum[f] += bv[f];
+#pragma unroll
+                for (int e = 0; e < VA; ++e) acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[f], acc[e][f], 0, 0, 0);
+            }
+        }
+    };
+    if (k0 < kend) {
+        look(k0);
+        load(X, k0);
+        for (int k = k0; k < kend; k += 2 * NX) {
+            load(Y, k + NX);
+            __builtin_amdgcn_sched_barrier(0); // the requests stay ahead of the products
+            mma(X, k);
+            if (k + NX >= kend) break;
+            load(X, k + 2 * NX);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(Y, k + NX);
+        }
+    }
+    // the four sums: 2 onto 0 and 3 onto 1, then 1 onto 0
+    f32x4 *own = reinterpret_cast<f32x4 *>(lds) + (wave & 1) * VA * 2 * VB * 64;
+#pragma unroll
+    for (int step = 2; step >= 1; --step) {
+        if (wave >= step && wave < 2 * step) {
+            f32x4 *to = step == 2 ? own : reinterpret_cast<f32x4 *>(lds);
+#pragma unroll
+            for (int e = 0; e < VA; ++e)
+#pragma unroll
+                for (int f = 0; f < 2 * VB; ++f) to[(e * 2 * VB + f) * 64 + lane] = acc[e][f];
+        }
+        __syncthreads();
+        if (wave < step) {
+#pragma unroll
+            for (int e = 0; e < VA; ++e)
+#pragma unroll
+                for (int f = 0; f < 2 * VB; ++f) acc[e][f] += own[(e * 2 * VB + f) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int e = 0; e < VA; ++e)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float lo[VB], hi[VB];
+#pragma unroll
+                for (int f = 0; f < VB; ++f) { lo[f] = acc[e][f][v]; hi[f] = acc[e][VB + f][v]; }
+                float *o = out + (int64_t)(min(i0 + VA * (4 * q + v), nA - VA) + e) * nB;
+                __builtin_memcpy(o + cb0, lo, VB * 4);
+                __builtin_memcpy(o + cb1, hi, VB * 4);
+            }
+    }
+    if (!bias) return;
+#pragma unroll
+    for (int f = 0; f < 2 * VB; ++f) lds[(wave * 2 * VB + f) * 64 + lane] = sum[f];
     __syncthreads();
-    for (int e = 0; e < G::CE; ++e) red[threadIdx.x * G::CE + e] = bl.sums[e];
-    __syncthreads();
-    if ((int)threadIdx.x < 64) {
-        const int col = threadIdx.x, blk = col / G::CE, e = col % G::CE;
-        float acc = 0.f;
-        for (int t = blk; t < kThreads; t += G::IB) acc += red[t * G::CE + e];
-        if (j0 + col < ncols) dst[j0 + col] = acc;
+    if (wave == 0 && q == 0) {
+#pragma unroll
+        for (int f = 0; f < 2 * VB; ++f) {
+            float t = 0.f;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t += lds[((u >> 2) * 2 * VB + f) * 64 + 16 * (u & 3) + c];
+            bias[f < VB ? cb0 + f : cb1 + f - VB] = t;
+        }
     }
 }
-template <typename SRC> __global__ __launch_bounds__(256) void k_lwgrad(WgArgs a)
+template <typename SRC> __global__ __launch_bounds__(256, 2) void k_lwgrad(WgArgs a)
 {
-    __shared__ __attribute__((aligned(16))) char smem[kTileLds];
-    static_assert(kTileLds >= 256 * 4 * 4, "column-sum scratch must fit");
-    int b = blockIdx.x;
-    const int per_split = a.items_per_layer * a.L;
+    __shared__ __attribute__((aligned(16))) float lds[2 * 4 * 2 * 4 * 64 * 4]; // two wavefronts' largest tiles
+    const int per_split = a.items_per_layer * a.L, all = a.splits * per_split, die = blockIdx.x & 7;
+    int b = die * (all >> 3) + min(die, all & 7) + ((int)blockIdx.x >> 3);
     const int split = b / per_split;
     b -= split * per_split;
     const int l = b / a.items_per_layer, it = b % a.items_per_layer;
     int t = 0;
-    while (t < 4 && it >= a.item0[t + 1]) ++t;
-    const int ti = (it - a.item0[t]) / a.tiles_j[t], tj = (it - a.item0[t]) % a.tiles_j[t];
-    const int M = a.map.M;
-    const int kbegin = split * a.rows_per_split, kend = min(M, kbegin + a.rows_per_split);
+    while (t < 4 && it >= a.ten[t + 1].item0) ++t;
+    const int va = a.ten[t].va, vb = a.ten[t].vb;
+    const int i0 = (it - a.ten[t].item0) / a.ten[t].tiles_j * 16 * va, j0 = (it - a.ten[t].item0) % a.ten[t].tiles_j * 32 * vb;
+    const int kbegin = split * a.rows_per_split, kend = min(a.map.M, kbegin + a.rows_per_split);
+    if (kbegin >= kend) return; // (no such item: splits are planned from the batch's own row count)
     float *part = a.part + (int64_t)split * a.LP + (int64_t)l * a.PLb;
     const int64_t lm = (int64_t)l * a.Mmax;
     const int w = a.w, f = a.f;
@@ -1836,20 +1922,29 @@ template <typename SRC> __global__ __launch_bounds__(256) void k_lwgrad(WgArgs a
     case 3: Bsrc = a.DF1 + lm * f; ncolsB = f; fieldW = F_W1; fieldB = F_B1; Asrc = a.TN + lm * w; nrowsA = w; break;
     default: Bsrc = a.DA + lm * w; ncolsB = w; fieldW = F_W2; fieldB = F_B2; Asrc = a.G + lm * f; nrowsA = f; break;
     }
-    LoadCols<float, 64, 4, float, true> bl;
-    bl.src = Bsrc; bl.ld = ncolsB; bl.ncols = ncolsB; bl.kend = kend;
-    EpiSt epi{part + a.fo[fieldW], ncolsB};
-    if (kbegin >= kend) return; // (no such item: splits are planned from the batch's own row count)
+    float *out = part + a.fo[fieldW], *bias = i0 == 0 ? part + a.fo[fieldB] : nullptr;
+    const int c = threadIdx.x & 15;
+    const int c0 = min(i0 + 4 * c, nrowsA - 4), ca = min(i0 + va * c, nrowsA - va);
+    auto cache_rows = [&](int m) __attribute__((always_inline)) {
+        return a.map.rowoff[m] + (int64_t)l * a.map.rowstride[m] + c0;
+    };
+    auto rows = [&](int m) __attribute__((always_inline)) { return (int64_t)m * nrowsA + ca; };
+    const SRC *cache = static_cast<const SRC *>(a.cache);
+#define WG_TILE(VA, VB, A, R) wg_tile<VA, VB>(lds, A, R, Bsrc, nrowsA, ncolsB, i0, j0, kbegin, kend, out, bias)
     if (t == 0) {
-        LoadColsCache<SRC, 64, 4> al;
-        al.cache = static_cast<const SRC *>(a.cache); al.map = a.map; al.layer = l; al.ncols = a.d; al.kend = kend;
-        gemm_tile<float, TL>(smem, al, bl, epi, kbegin, kend, ti * 64, tj * 64, nrowsA, ncolsB);
+        if (vb == 2) WG_TILE(4, 2, cache, cache_rows);
+        else if (vb == 3) WG_TILE(4, 3, cache, cache_rows);
+        else WG_TILE(4, 4, cache, cache_rows);
+    } else if (va == 3) {
+        if (vb == 2) WG_TILE(3, 2, Asrc, rows);
+        else if (vb == 3) WG_TILE(3, 3, Asrc, rows);
+        else WG_TILE(3, 4, Asrc, rows);
     } else {
-        LoadCols<float, 64, 4, float, false> al;
-        al.src = Asrc; al.ld = nrowsA; al.ncols = nrowsA; al.kend = kend;
-        gemm_tile<float, TL>(smem, al, bl, epi, kbegin, kend, ti * 64, tj * 64, nrowsA, ncolsB);
+        if (vb == 2) WG_TILE(4, 2, Asrc, rows);
+        else if (vb == 3) WG_TILE(4, 3, Asrc, rows);
+        else WG_TILE(4, 4, Asrc, rows);
     }
-    if (ti == 0) lad_colsums(bl, reinterpret_cast<float *>(smem), part + a.fo[fieldB], ncolsB, tj * 64);
+#undef WG_TILE
 }
 
 // ordered sums into the gradient vector: thread per element of the layer blocks
@@ -2149,9 +2244,8 @@ hipError_t run_ladder(const Lad &a, const BatchMeta &meta, const void *cache, co
     wg.G = F(a.G); wg.DA = F(a.DA); wg.DX = F(a.DX);
     wg.part = F(a.part); wg.Mmax = Mm; wg.PLb = a.PLb; wg.LP = (int64_t)L * a.PLb;
     for (int i = 0; i <= kFields; ++i) wg.fo[i] = a.fo[i];
-    wg.L = L; wg.d = d; wg.w = w; wg.f = f; wg.rows_per_split = rps; wg.items_per_layer = a.items_per_layer;
-    for (int t = 0; t < 5; ++t) wg.tiles_j[t] = a.tiles[t][1];
-    for (int t = 0; t < 6; ++t) wg.item0[t] = a.item0[t];
+    wg.L = L; wg.d = d; wg.w = w; wg.f = f; wg.rows_per_split = rps; wg.items_per_layer = a.items_per_layer; wg.splits = splits;
+    for (int t = 0; t < 5; ++t) wg.ten[t] = a.ten[t];
     LAD_LAUNCH(prof, st, KC_L_WGRAD, (k_lwgrad<SRC>), dim3(splits * L * a.items_per_layer), dim3(256), 0, st, wg);
     RedArgs rd;
     rd.part = F(a.part); rd.ln1p = F(a.ln1p); rd.ln2p = F(a.ln2p); rd.dlamp = F(a.dlamp); rd.params = params;

@@ -194,3 +194,14 @@ def test_attention_blocks(r, heads, n_max):
     w = Workload("attn", L=2, d=64, n_max=n_max, B=5, r=r, C=6, N=5, cache_dtype="f32", len_lo=1)
     lens = np.array([1, 16, 65, n_max - 1, n_max], dtype=np.int32)
     run_case(w, heads, lens, seed=5, what=f"w {r}, {heads} heads, {n_max} tokens")
+
+
+# token contractions: tiles of 48 and 64 columns by 64, 96 and 128 with and without a remainder on either side (d = 96 and 160
+# against 64; w = 32 against 48 and 64; w = 160 on 96; w = 224 on 128), batches of fewer rows than one wavefront's eight, of
+# one row, of a remainder of the last four, and of several splits with a ragged end
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,r,lens", [(96, 32, [1]), (160, 64, [3, 2]), (64, 96, [31, 2]), (128, 160, [40, 33, 7]), (160, 224, [24, 9]),
+                                      (96, 64, [128, 127, 128, 128, 99])])
+def test_token_contraction_tiles(dtype, d, r, lens):
+    w = Workload("lad_t", L=2, d=d, n_max=max(lens), B=len(lens), r=r, C=3, N=len(lens), cache_dtype=dtype)
+    run_case(w, r // 8, np.array(lens, dtype=np.int32), seed=17 + d + r, what=f"lad_t d={d} r={r} {dtype}")
