@@ -126,7 +126,7 @@ bool lad_plan(const Dims &D, int heads, Lad &a)
     a.dz = take((int64_t)a.Bmax * a.C * 4); a.dp = take((int64_t)a.Bmax * d * 4);
     a.daL = take((int64_t)a.Bmax * w * 4); a.lossp = take((int64_t)a.Bmax * 4);
     // tiles of the five token contractions of one layer: W_down [d][w], W_qkv [w][3w], W_o [w][w], W_1 [w][f], W_2 [f][w].
-    // Widths by the least matrix work, a third of a unit for each of a step's loads (32 cycles an instruction, 35 a load).
+    // Widths by the least matrix work and loads: 2 va vb instructions of 32 cycles a step, three loads of about 35.
     const int rows[5] = {a.d, a.w, a.w, a.w, a.f}, cols[5] = {a.w, 3 * a.w, a.w, a.f, a.w};
     a.items_per_layer = 0;
     for (int t = 0; t < 5; ++t) {
