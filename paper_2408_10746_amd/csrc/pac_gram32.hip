@@ -61,6 +61,33 @@ __device__ __forceinline__ float gelu_grad_f(float u)
     const float phi = 0.3989422804014327f * expf(-0.5f * u * u);
     return Phi + u * phi;
 }
+// Classes c0 .. c0 + 3 of one row of a [.][C] array: a row's classes lie together, so a load for each would touch the same
+// lines again and again.  Past the last class its value once more.
+__device__ __forceinline__ f32x4 load_classes(const float *row, int c0, int C)
+{
+    if (c0 + 4 <= C) return load4(row + c0);
+    f32x4 v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = row[min(c0 + c, C - 1)];
+    return v;
+}
+// Sums of N values over the lanes, added as a tree of offsets 32, 16, .. 1: with every offset a lane keeps half of the values
+// and hands the other half over, so N = 16 takes 17 exchanges, not 96.  Lane i ends with the sum of value i * N / 64.
+template <int N> __device__ __forceinline__ float lane_sums(float (&v)[N], int o = 32)
+{
+    if constexpr (N > 1) {
+        const bool hi = threadIdx.x & o;
+        float keep[N / 2];
+#pragma unroll
+        for (int k = 0; k < N / 2; ++k)
+            keep[k] = (hi ? v[k + N / 2] : v[k]) + __shfl_xor(hi ? v[k] : v[k + N / 2], o, 64);
+        return lane_sums<N / 2>(keep, o / 2);
+    } else {
+        float s = v[0];
+        for (; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        return s;
+    }
+}
 __device__ __forceinline__ int pair_index(int k, int l) { return l * (l - 1) / 2 + k; } // k < l
 
 constexpr int kT = kChainRows;   // 16
@@ -401,6 +428,42 @@ template <int RT, int NB> __device__ __forceinline__ void proj_tile(const FProjA
     __syncthreads();
 }
 
+// Rows row0 .. + R - 1 of V (one layer's), by a wavefront, four classes at a time.  Bound by how often a wavefront touches the
+// lines of W_cls, 64 rows of it at once: a load for each class and row of V took 80 us with 16 classes at 5 layers of 1248 x
+// 256 (the step 358 us, 120 of it forward with three classes and 187 with 16), four classes a load and four rows 22 (283; 132).
+constexpr int kVRows = 4;
+template <int R> __device__ __forceinline__ void v_rows(const FProjArgs &a, int row0, int r)
+{
+    const int lane = threadIdx.x & 63, L = a.L, d = a.d, C = a.C;
+    if (row0 >= L * r) return;
+    const float *Wc = a.params + (int64_t)L * a.PL;
+    const float *wu = a.params + (int64_t)(row0 / r) * a.PL + (int64_t)d * r + r + (int64_t)(row0 % r) * d;
+    for (int c0 = 0; c0 < C; c0 += 4) {
+        float acc[R * 4];
+#pragma unroll
+        for (int x = 0; x < R * 4; ++x) acc[x] = 0.f;
+        for (int j0 = 0; j0 < d; j0 += 64 * 4) {
+            float w[R][4];
+            f32x4 wc[4];
+#pragma unroll
+            for (int x = 0; x < R; ++x)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) w[x][u] = j0 + 64 * u + lane < d ? wu[(int64_t)x * d + j0 + 64 * u + lane] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) wc[u] = load_classes(Wc + (int64_t)min(j0 + 64 * u + lane, d - 1) * C, c0, C);
+#pragma unroll
+            for (int x = 0; x < R; ++x)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) acc[4 * x + c] += w[x][u] * wc[u][c];
+        }
+        const float v = lane_sums<R * 4>(acc);
+        const int at = lane * (R * 4) / 64, c = c0 + at % 4;
+        if (lane % (64 / (R * 4)) == 0 && c < C) a.V[(int64_t)(row0 + at / 4) * C + c] = v;
+    }
+}
+
 template <int RT, int NB> __global__ __launch_bounds__(256) void k_f_proj(FProjArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -470,7 +533,7 @@ template <int RT, int NB> __global__ __launch_bounds__(256) void k_f_proj(FProjA
         }
         const float y = j < d ? mean + cu : 0.f;
         const float *Wc = a.params + (int64_t)L * a.PL + (int64_t)jc * C;
-        float *wred = sh + 4 * kChunk; // [8][kMaxClasses]
+        float *wred = sh + 4 * kChunk; // [4][kMaxClasses]
 #pragma unroll
         for (int c = 0; c < kMaxClasses; ++c) {
             if (c >= C) continue;
@@ -486,35 +549,10 @@ template <int RT, int NB> __global__ __launch_bounds__(256) void k_f_proj(FProjA
     }
     b -= a.nb_pb;
     if (b < a.nb_V) {
-        // V[(k,i)][c] = sum_j W_up^k[i][j] W_cls[j][c], a wavefront a row
-        const int row = b * 4 + wave;
-        if (row >= L * r) return;
-        const float *Wc = a.params + (int64_t)L * a.PL, *wu = a.params + (int64_t)(row / r) * a.PL + dr + r + (int64_t)(row % r) * d;
-        float acc[kMaxClasses];
-#pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c) acc[c] = 0.f;
-        for (int j0 = 0; j0 < d; j0 += 64 * 4) {
-            float w[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) w[u] = j0 + 64 * u + lane < d ? wu[j0 + 64 * u + lane] : 0.f;
-#pragma unroll
-            for (int c = 0; c < kMaxClasses; ++c) {
-                if (c >= C) continue;
-                float wc[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) wc[u] = Wc[(int64_t)min(j0 + 64 * u + lane, d - 1) * C + c];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[c] += w[u] * wc[u];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c) {
-            if (c >= C) continue;
-            float v = acc[c];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-            if (lane == 0) a.V[(int64_t)row * C + c] = v;
-        }
+        // V[(k,i)][c] = sum_j W_up^k[i][j] W_cls[j][c]: a wavefront a row; above four classes kVRows of them share what they
+        // read of W_cls
+        if (C <= 4) v_rows<1>(a, b * 4 + wave, r);
+        else v_rows<kVRows>(a, (b * 4 + wave) * kVRows, r);
         return;
     }
     b -= a.nb_V;
@@ -639,7 +677,7 @@ template <bool FWD, int NB, int WC> __global__ __launch_bounds__(kChainThreads) 
     float *red = Hs + (size_t)L * kT * RP;           // [WK][16][r]
     float *vec = red + WK * kT * r;                  // [L][r]  (1 - lambda) chat + c_down (forward), dz V^T / len (backward)
     float *lamS = vec + (size_t)L * r;               // [L]
-    float *zs = lamS + (L + 3) / 4 * 4, *dzs = zs + kMaxClasses, *zred = dzs + kMaxClasses; // [4][kMaxClasses]
+    float *zs = lamS + (L + 3) / 4 * 4, *dzs = zs + kMaxClasses, *zred = dzs + kMaxClasses; // [8][kMaxClasses]
     const int t = threadIdx.x, lane = t & 63, wave = wave_id(), i = lane & 15, g = lane >> 4;
     const int wc = wave % WC, wk = wave / WC;
     const int tile = blockIdx.x, s = sample_of(a.tile0, a.meta.B, tile);
@@ -807,25 +845,29 @@ template <bool FWD, int NB, int WC> __global__ __launch_bounds__(kChainThreads) 
             else sum[u] = 0.f;
         if (FWD) {
 #pragma unroll
-            for (int q = 0; q < kMaxClasses; ++q)
-                if (q < a.C) {
-                    float v[4];
+            for (int q0 = 0; q0 < kMaxClasses; q0 += 4) // the loads of four classes under way together
+                if (q0 < a.C) {
+                    f32x4 v[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) v[u] = a.V[(int64_t)min(c0 + u * kChainThreads, Lr - 1) * a.C + q];
+                    for (int u = 0; u < 4; ++u)
+                        v[u] = load_classes(a.V + (int64_t)min(c0 + u * kChainThreads, Lr - 1) * a.C, q0, a.C);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) zacc[q] += sum[u] * v[u];
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) zacc[q0 + q] += sum[u] * v[u][q];
                 }
         }
     }
     if (FWD) {
 #pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c) {
-            if (c >= a.C) continue;
-            float v = zacc[c];
+        for (int c0 = 0; c0 < kMaxClasses; c0 += 4)
+            if (c0 < a.C) {
+                float v[4];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-            if (lane == 0) zred[wave * kMaxClasses + c] = v;
-        }
+                for (int c = 0; c < 4; ++c) v[c] = zacc[c0 + c];
+                const float sum = lane_sums<4>(v);
+                if (lane % 16 == 0) zred[wave * kMaxClasses + c0 + lane / 16] = sum;
+            }
         __syncthreads();
         if (t < a.C) {
             float v = 0.f;
@@ -1199,22 +1241,30 @@ template <int NB> __global__ __launch_bounds__(kPostThreads) void k_f_post(FPost
                 for (int v = 0; v < 4; ++v) red[(wave * 32 + 16 * x + 4 * g + v) * 32 + 16 * y + i] = acc[x][y][v];
         __syncthreads();
         const int j = j0 + (t & 31);
-        float wc[kMaxClasses];
-#pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c) wc[c] = c < C ? Wc[(int64_t)j * C + c] : 0.f;
         float *gw = a.grads + (int64_t)l * a.PL + dr + r;
+        float v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int row = (t >> 5) + 8 * q;
-            float v = 0.f;
+            v[q] = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) v += red[(w * 32 + row) * 32 + (t & 31)];
-            const float *Z = a.Z + (int64_t)(l * r + i0 + row) * kZP;
-#pragma unroll
-            for (int c = 0; c < kMaxClasses; ++c)
-                if (c < C) v += Z[c] * wc[c];
-            gw[(int64_t)(i0 + row) * d + j] = v;
+            for (int w = 0; w < 4; ++w) v[q] += red[(w * 32 + (t >> 5) + 8 * q) * 32 + (t & 31)];
         }
+        const float *Z = a.Z + (int64_t)(l * r + i0 + (t >> 5)) * kZP;
+#pragma unroll
+        for (int c0 = 0; c0 < kMaxClasses; c0 += 4)
+            if (c0 < C) {
+                f32x4 z[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) z[q] = *reinterpret_cast<const f32x4 *>(Z + 8 * q * kZP + c0);
+                const f32x4 wc = load_classes(Wc + (int64_t)j * C, c0, C);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (c0 + c < C)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] += z[q][c] * wc[c];
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) gw[(int64_t)(i0 + (t >> 5) + 8 * q) * d + j] = v[q];
         return;
     }
     b -= L * (nF + nW);
@@ -1404,7 +1454,7 @@ template <int NB, int WC> static hipError_t run_f32_gram(const Dims &D, const Ws
         const int t16 = tiles_of(meta, 16, a.tile0), t32 = tiles_of(meta, 32, a.tile0);
         const int rt = r <= 128 && (int64_t)L * t32 >= 512 && 20 * t32 <= 11 * t16 ? 2 : 1;
         const int tiles = tiles_of(meta, 16 * rt, a.tile0);
-        a.nb_chat = (L + 1) * nch; a.nb_pb = B * nch; a.nb_V = cdiv(Lr, 4); a.nb_tab = cdiv(M, 256);
+        a.nb_chat = (L + 1) * nch; a.nb_pb = B * nch; a.nb_V = cdiv(Lr, C > 4 ? 4 * kVRows : 4); a.nb_tab = cdiv(M, 256);
         a.nb_Q = W.pairs * (r / (rt > 1 ? 32 : 16)); a.nb_U = L * tiles;
         const int counts[6] = {a.nb_chat, a.nb_pb, a.nb_V, a.nb_tab, a.nb_Q, a.nb_U};
         const int classes[6] = {KC_G_PREP_CHAT, KC_G_PROJ_PB, KC_G_PREP_V, KC_G_PREP_SETUP, KC_G_PROJ_Q, KC_G_PROJ_U};

@@ -145,6 +145,17 @@ def test_fp32_gram(w):
     assert torch.equal(sess.loss, loss) and torch.equal(sess.grads, grads)
 
 
+# What the fp32 launches do for each class: four at a time, a last group of one, two, three and four.
+@pytest.mark.parametrize("C", [2, 4, 5, 7, 16])
+def test_fp32_gram_class_counts(C):
+    w = Workload(f"tc{C}", L=3, d=320, n_max=37, B=3, r=64, C=C, N=3, cache_dtype="f32", len_lo=5)
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+    sess = make_session(w, lens=lens)
+    sess.cache_fill(ids, acts, lens)
+    check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
+
+
 # Every sum behind a gradient has a fixed order, and a launch rule or a faster load is no reason for other results: SHA-1 of
 # the gradients' bits.  The rows of the vector gradients: two threads each with 2, 6 and 8 chunks of 16 bytes, four with 5,
 # eight with 5.
