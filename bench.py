@@ -228,7 +228,7 @@ def run_workload(name, N, steps, warmup, flags, keep_cpu_samples=0, want_peaks=F
         "workload": f"{w.name}: L={w.L} d={w.d} seq={w.n_max} B={w.B} r={w.r} C={w.C} "
                     f"N={N} resident ({sess.cache_bytes / 1e9:.2f} GB {w.cache_dtype} cache)",
         "N_resident": N, "N_config": w.N, "tokens_per_step": M, "cache_fill_s": t_fill,
-        "formulation": "gram, fp32" if pb.pac_step_path(sess.ctx) == 0 and "g_proj" in prof else
+        "formulation": "gram, fp32" if pb.pac_f32_plan(sess.ctx, None, w.B)["gram"] else
                        ["per-layer kernels", "gram, single-launch chains", "gram, layer-by-layer chains",
                         "gram, fused streaming passes"][pb.pac_step_path(sess.ctx)],
         "steps": steps, "ms_per_step": ms_per_step, "samples_per_s": steps * w.B / elapsed,

@@ -135,20 +135,23 @@ int64_t pac_cache_bytes(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int64_
 /* Bytes of device workspace pac_adapter_step / pac_adapter_loss_grad need for a batch of up to B_max samples
  * of up to n_max tokens: what the cached phase of Sec. 5.2 keeps per step besides the cache (r-wide
  * activations of the side network, compute-dtype copies of the projections, partial sums of the token
- * reductions; no d-wide per-token state on the Gram-matrix path).  -1 if ctx is NULL. */
+ * reductions; no d-wide per-token state on the Gram-matrix path).  Not the least that serves: an fp32 context whose batches
+ * are not all faster in the Gram-matrix formulation reserves for both formulations (the larger of the two, unless that alone
+ * passes PAC_STATIC_WORKSPACE_BYTES), and that formulation may need up to twice the per-layer kernels' bytes, or up to
+ * PAC_STATIC_WORKSPACE_BYTES where those need less.
+ * -1 if ctx is NULL. */
 int64_t pac_workspace_bytes(const pac_ctx *ctx);
 
 /* Which formulation of the step (paper Sec. 4.1, 5.2: the same function of the same inputs in each)
- * this configuration runs on: 0 the per-layer kernels or, on an fp32 cache where the adapters are at most half as wide
- * as the hidden state and 16 rows of all layers fit a compute unit's LDS, the fp32 kernels of the Gram-matrix
- * formulation; 1 the bf16 kernels of the Gram-matrix formulation with the chains over the layers as one launch per
+ * this configuration runs on: 0 the per-layer kernels or, on an fp32 cache, the fp32 kernels of the Gram-matrix
+ * formulation (pac_f32_plan tells which, batch by batch); 1 the bf16 kernels of the Gram-matrix formulation with the chains over the layers as one launch per
  * direction; 2 the same with the chains launched layer by layer.  Decided by pac_create from the shape, cache dtype and flags.  -1 if ctx is NULL. */
 int32_t pac_step_path(const pac_ctx *ctx);
 
 /* Which tiles the launches of a step on such a batch take (same results up to rounding in each; host logic, for
  * measurements and tests that have to know which form they ran):
  *   out[0]  token rows per tile of the projection launch (paths 1, 2), of the layers' down-projections (path 0; 16, of the
- *           chains over the layers, where an fp32 step takes the Gram-matrix formulation)
+ *           chains over the layers, where an fp32 step takes the Gram-matrix formulation: see pac_f32_plan)
  *   out[1]  columns of d per tile of the contractions over the tokens      out[2]  side of the gradient launch's tiles
  *   out[3]  1: the gradients that are no contractions as whole rows        out[4], out[5]  token splits of the
  *           weights' contraction and of the Gram matrix                    (out[1..5] are 0 on path 0)
@@ -163,6 +166,18 @@ pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int3
  *   out[3]  groups before the first cut          out[4], out[5]  rows and columns of that contraction's tiles
  * out[3..5] are 0 where there is one group, all are 0 on paths 0 and 1.  Arguments and errors as in pac_step_tiles. */
 pac_status pac_chain_plan(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t out[6] /*HOST*/);
+
+/* Which formulation an fp32 call on such a batch takes, with the workspace that pac_workspace_bytes asks for (a smaller one
+ * that holds the Gram-matrix formulation gets that; as above, the same results up to rounding):
+ *   grads   0: a forward-only call; else a training step or a call for gradients
+ *   out[0]  1: the Gram-matrix formulation, 0: the per-layer kernels (then out[1..3] are 0, and always on a bf16 cache)
+ *   out[1]  token rows per tile of the projection launch           out[2]  token splits of the contractions over them
+ *   out[3]  wavefronts that share a unit's columns in the chains over the layers
+ * The Gram-matrix formulation is there for r = 32, 64, 96, 128, 192 and 256, 2 r <= d, 2 <= L <= 64, 16 rows of all layers in a
+ * compute unit's LDS (L <= 60, 31, 16, 14, 8 and 5), no more rows in the largest batch than the per-layer kernels take on
+ * 16-row tiles, and the workspace above, unless PAC_FLAG_PER_LAYER is set; batches take it where it is faster.  lens, B and
+ * errors as in pac_step_tiles. */
+pac_status pac_f32_plan(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t grads, int32_t out[4] /*HOST*/);
 
 /*
  * Store one backbone forward's per-layer activations (paper Sec. 4.2: during

@@ -25,7 +25,8 @@ PAC_FLAG_LAYER_CHAIN = 4
 
 EXPORTS = [
     "pac_create", "pac_destroy", "pac_status_str", "pac_param_count", "pac_param_offsets",
-    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_step_tiles", "pac_chain_plan", "pac_cache_fill",
+    "pac_cache_bytes", "pac_workspace_bytes", "pac_step_path", "pac_step_tiles", "pac_chain_plan", "pac_f32_plan",
+    "pac_cache_fill",
     "pac_cache_lookup",
     "pac_adapter_loss_grad", "pac_adapter_step", "pac_adapter_step_static",
     "pac_probe_hbm_read", "pac_probe_mfma_bf16", "pac_probe_mfma_flops", "pac_probe_hbm_update",
@@ -105,6 +106,8 @@ def lib():
         L.pac_step_tiles.argtypes = [vp, vp, i32, C.POINTER(i32)]
         L.pac_chain_plan.restype = C.c_int
         L.pac_chain_plan.argtypes = [vp, vp, i32, C.POINTER(i32)]
+        L.pac_f32_plan.restype = C.c_int
+        L.pac_f32_plan.argtypes = [vp, vp, i32, i32, C.POINTER(i32)]
         L.pac_cache_fill.restype = C.c_int
         L.pac_cache_fill.argtypes = [vp, vp, i64, vp, i32, vp, i32, vp, vp]
         L.pac_cache_lookup.restype = C.c_int
@@ -236,6 +239,14 @@ def pac_chain_plan(ctx, lens, B: int) -> dict:
     out = (C.c_int32 * 6)()
     _check(lib().pac_chain_plan(ctx, _hp(la), B, out), "pac_chain_plan")
     return dict(zip(("groups", "layers", "ranges", "first", "rows", "cols"), (int(x) for x in out)))
+
+
+def pac_f32_plan(ctx, lens, B: int, grads: bool = True) -> dict:
+    """Formulation and tiles of an fp32 call on B samples of the given lengths (None: all n_max; host logic)."""
+    la = _host_i32(lens)
+    out = (C.c_int32 * 4)()
+    _check(lib().pac_f32_plan(ctx, _hp(la), B, int(grads), out), "pac_f32_plan")
+    return dict(zip(("gram", "proj", "splits", "wc"), (int(x) for x in out)))
 
 
 def pac_cache_fill(ctx, cache_ptr, cache_bytes, sample_ids, acts_ptr, acts_dtype, lens=None, stream=0) -> None:

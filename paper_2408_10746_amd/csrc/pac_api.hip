@@ -101,6 +101,18 @@ pac_status pac_create(const pac_config *cfg, pac_ctx **out)
     D.P = (int64_t)D.L * D.PL + (int64_t)D.d * D.C + D.C;
     D.Mmax = (int64_t)D.B_max * D.n_max;
     plan_workspace(D, c->W);
+    c->f32_every = false;
+    if (plan_f32_gram(D, c->W, c->F)) {
+        // faster on the fewest rows, on as many samples of one row, and on the largest batch
+        const int tiles = D.B_max * ((D.n_max + kChainRows - 1) / kChainRows);
+        c->f32_every = true;
+        for (int grads = 0; grads < 2; ++grads)
+            c->f32_every = c->f32_every && f32_gram_pays(D, 1, 1, 1, grads) && f32_gram_pays(D, D.B_max, D.B_max, D.B_max, grads) &&
+                           f32_gram_pays(D, D.B_max, (int)D.Mmax, tiles, grads);
+        // or alone within what pac_adapter_step_static has (152 of the configurations behind f32_gram_pays: 0.95 x the per-layer
+        // kernels' speed on three, 0.99 and more on the others)
+        if (c->F.total <= PAC_STATIC_WORKSPACE_BYTES && c->W.total > PAC_STATIC_WORKSPACE_BYTES) c->f32_every = true;
+    }
     try {
         c->off.assign((size_t)D.N, -1);
         c->len.assign((size_t)D.N, 0);
@@ -190,7 +202,27 @@ int64_t pac_cache_bytes(const pac_ctx *ctx, const int32_t *lens, int64_t count)
     return tokens * D.d * D.L * elem_bytes(D.cache_dtype);
 }
 
-int64_t pac_workspace_bytes(const pac_ctx *ctx) { return ctx ? ctx->W.total : -1; }
+// What a call needs at least, and what serves every batch with the faster formulation
+static int64_t least_workspace(const pac_ctx *ctx) { return ctx->F.total ? ctx->F.total : ctx->W.total; }
+
+int64_t pac_workspace_bytes(const pac_ctx *ctx)
+{
+    if (!ctx) return -1;
+    return ctx->F.total && !ctx->f32_every ? std::max(ctx->F.total, ctx->W.total) : least_workspace(ctx);
+}
+
+// The formulation of a call on B samples of M token rows in ntiles 16-row tiles
+static const WsLayout &layout_for(const pac_ctx *ctx, int B, int M, int ntiles, bool grads, int64_t workspace_bytes)
+{
+    const bool gram32 = ctx->F.total && (ctx->f32_every || workspace_bytes < ctx->W.total || f32_gram_pays(ctx->D, B, M, ntiles, grads));
+    return gram32 ? ctx->F : ctx->W;
+}
+static const WsLayout &layout_for(const pac_ctx *ctx, const BatchMeta &meta, bool grads, int64_t workspace_bytes)
+{
+    int ntiles = 0;
+    for (int s = 0; s < meta.B; ++s) ntiles += (meta.len[s] + kChainRows - 1) / kChainRows;
+    return layout_for(ctx, meta.B, meta.M, ntiles, grads, workspace_bytes);
+}
 
 int32_t pac_step_path(const pac_ctx *ctx) { return ctx ? ctx->W.use_gram : -1; }
 
@@ -224,7 +256,19 @@ pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens, int32_t B, in
     const pac_status s = batch_rows(ctx, lens, B, M, ntiles);
     if (s != PAC_OK) return s;
     if (ctx->W.use_gram) gram_step_tiles(ctx->D, ctx->W, M, ntiles, out);
-    else layer_step_tiles(ctx->D, ctx->W, M, out);
+    else layer_step_tiles(ctx->D, layout_for(ctx, B, M, ntiles, true, pac_workspace_bytes(ctx)), M, out);
+    return PAC_OK;
+}
+
+pac_status pac_f32_plan(const pac_ctx *ctx, const int32_t *lens, int32_t B, int32_t grads, int32_t out[4])
+{
+    if (!ctx || !out) return PAC_ERR_NULL;
+    int M, ntiles;
+    const pac_status s = batch_rows(ctx, lens, B, M, ntiles);
+    if (s != PAC_OK) return s;
+    for (int i = 0; i < 4; ++i) out[i] = 0;
+    const WsLayout &W = layout_for(ctx, B, M, ntiles, grads != 0, pac_workspace_bytes(ctx));
+    if (W.f32_gram) f32_gram_plan(ctx->D, W, lens, B, M, out);
     return PAC_OK;
 }
 
@@ -396,7 +440,7 @@ static pac_status check_common(const pac_ctx *ctx, const void *cache, const int6
     if (!aligned(cache, 256) || !aligned(workspace, 256) || !aligned(params, 4) || !aligned(labels, 4) ||
         !aligned(loss_out, 4))
         return PAC_ERR_ALIGN;
-    if (workspace_bytes < ctx->W.total) return PAC_ERR_WORKSPACE;
+    if (workspace_bytes < least_workspace(ctx)) return PAC_ERR_WORKSPACE;
     return PAC_OK;
 }
 
@@ -414,7 +458,8 @@ static pac_status loss_grad_impl(pac_ctx *ctx, const void *cache, const int64_t 
     StepIO io{cache, labels, params, static_cast<char *>(workspace), loss_out, logits_out, grads_out,
               static_cast<hipStream_t>(hip_stream), ctx->prof.on ? &ctx->prof : nullptr};
     (void)hipGetLastError(); // drop an error left behind by an unrelated earlier call (see pac_cache_fill)
-    return launch_loss_grad(ctx->D, ctx->W, meta, io) == hipSuccess ? PAC_OK : PAC_ERR_DEVICE;
+    const WsLayout &W = layout_for(ctx, meta, grads_out != nullptr, workspace_bytes);
+    return launch_loss_grad(ctx->D, W, meta, io) == hipSuccess ? PAC_OK : PAC_ERR_DEVICE;
 }
 
 pac_status pac_adapter_loss_grad(pac_ctx *ctx, const void *cache, const int64_t *sample_ids, int32_t B,
@@ -453,14 +498,15 @@ static pac_status step_on_workspace(pac_ctx *ctx, const void *cache, const int64
     s = build_meta(ctx, sample_ids, B, meta, packed);
     if (s != PAC_OK) return s;
     char *ws = static_cast<char *>(workspace);
-    float *grads = grads_out ? grads_out : reinterpret_cast<float *>(ws + ctx->W.grads);
+    const WsLayout &W = layout_for(ctx, meta, true, workspace_bytes);
+    float *grads = grads_out ? grads_out : reinterpret_cast<float *>(ws + W.grads);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     Profiler *prof = (may_profile && ctx->prof.on) ? &ctx->prof : nullptr;
     StepIO io{cache, labels, params, ws, loss_out, nullptr, grads, st, prof};
     Deferred fin;
     io.defer = &fin;
     (void)hipGetLastError(); // drop an error left behind by an unrelated earlier call (see pac_cache_fill)
-    if (launch_loss_grad(ctx->D, ctx->W, meta, io) != hipSuccess) return PAC_ERR_DEVICE;
+    if (launch_loss_grad(ctx->D, W, meta, io) != hipSuccess) return PAC_ERR_DEVICE;
     const int64_t t = *step + 1;
     AdamArgs a;
     a.lr = hp->lr; a.beta1 = hp->beta1; a.beta2 = hp->beta2; a.eps = hp->eps; a.wd = hp->weight_decay;
@@ -565,7 +611,7 @@ pac_status pac_adapter_step_static(pac_ctx *ctx, const void *cache, const int64_
                                    const pac_adamw *hp, float *loss_out, float *grads_out, void *hip_stream)
 {
     if (!ctx) return PAC_ERR_NULL;
-    if (ctx->W.total > PAC_STATIC_WORKSPACE_BYTES) return PAC_ERR_WORKSPACE;
+    if (least_workspace(ctx) > PAC_STATIC_WORKSPACE_BYTES) return PAC_ERR_WORKSPACE;
     void *ws = nullptr;
     if (static_scratch_address(&ws) != hipSuccess || !ws) return PAC_ERR_DEVICE;
     return step_on_workspace(ctx, cache, sample_ids, B, labels, params, m, v, step, hp, ws, PAC_STATIC_WORKSPACE_BYTES,

@@ -1327,14 +1327,37 @@ static int chain_wc(int L, int r)
 }
 static int tok_blocks(int r) { return r % 96 == 0 ? 3 : r % 64 == 0 ? 2 : 1; } // r = 32, 64, 96, 128, 192, 256
 
-// Adapters at most half as wide as the hidden state, all layers' 16 rows of h in a compute unit's LDS: 2.2 x the per-layer
-// kernels' speed on the geometric mean of 43 such configurations (2 .. 31 layers, d = 128 .. 1056, r = 32 .. 128, 13 to 7800
-// rows, up to 3.8 times the direct form's operations), 1.49 at least.
+// Adapters at most half as wide as the hidden state, all layers' 16 rows of h in a compute unit's LDS
 bool f32_gram_fits(const Dims &D)
 {
     if (D.cache_dtype == 0 || (D.flags & 1)) return false; // PAC_FLAG_PER_LAYER
     if (D.r != 32 && D.r != 64 && D.r != 96 && D.r != 128 && D.r != 192 && D.r != 256) return false;
     return D.L >= 2 && D.L <= kMaxLayers && 2 * D.r <= D.d && chain_wc(D.L, D.r) != 0;
+}
+
+// Times in us of both formulations, fitted to 1133 configurations on both sides of the line (2 to 60 layers, d = 64 to 8192,
+// every width, 1 to 16384 rows, 1 to 16 classes), within 8 % of those near it in the mean.  What the Gram formulation does
+// between layers (L^2 r^2 a row, one row tile after another in a compute unit, and L^2 r^2 d however few the rows are) stands
+// against the per-layer kernels' launches, their d-wide state and the weights of one layer at a time.  It is 1.9 x as fast on
+// the geometric mean, and loses with wide adapters on few rows or with d = 2 r on many: forward only, 5 layers of 512 x 256,
+// 240 rows, 110 us against 96, 31 of 128 x 64, 8192 rows, 502 / 425; steps of 8 layers of 384 x 192, one row, 271 / 242.  What
+// the rule picks took up to 1.06 x the other's time in a step and 1.09 x forward only, but for 45 layers of 64 x 32, 16384
+// rows (593 / 532).
+bool f32_gram_pays(const Dims &D, int B, int M, int ntiles, bool grads)
+{
+    const double L = D.L, d = D.d, r = D.r, LM = L * M, rounds = cdiv(ntiles, 256), pairs = L * (L - 1) / 2;
+    const double chain = pairs * r * r * rounds / 1e6, weights = pairs * r * r * d / 1e9, proj = L * ntiles * 16 * d * r / 1e9;
+    double gram, per_layer;
+    if (grads) {
+        gram = 34.9 + 1.42 * L * rounds + 175 * chain + 24.9 * weights + 30.3 * proj + 0.0046 * d + 52e-6 * L * d * r + 19.3e-6 * LM * r +
+               3.6e-9 * M * (L * d * r + pairs * r * r);
+        per_layer = 24.8 + L * (13 + 0.0133 * d + 0.0502 * r + 12.7e-6 * d * r) + LM * (1.1e-3 + 5.95e-6 * d + 86e-9 * d * r) +
+                    183e-6 * d * B * D.C;
+    } else {
+        gram = 19.2 + 0.44 * L * rounds + 96 * chain + 17.3 * weights + 24.2 * proj + 0.0128 * d;
+        per_layer = 16 + L * (5.34 + 0.00693 * d + 0.0262 * r) + LM * (98e-6 + 2.75e-6 * d + 31.3e-9 * d * r);
+    }
+    return gram < per_layer;
 }
 
 // Token splits: the tiles' rounds over the 256 compute units against what a launch for the sums costs
@@ -1394,6 +1417,24 @@ void plan_f32_gram_workspace(const Dims &D, WsLayout &W, int64_t &o)
     W.g_GGpart = take((int64_t)W.f_splits * Lr * Lr * 4);
 }
 
+// 32-row projection tiles where they still fill the chip twice over and ragged samples do not leave many of them empty
+static int proj_row_tiles(int L, int r, int t16, int t32) { return r <= 128 && (int64_t)L * t32 >= 512 && 20 * t32 <= 11 * t16 ? 2 : 1; }
+
+void f32_gram_plan(const Dims &D, const WsLayout &F, const int32_t *lens, int B, int M, int32_t out[4])
+{
+    int t16 = 0, t32 = 0;
+    for (int s = 0; s < B; ++s) {
+        const int len = lens ? lens[s] : D.n_max;
+        t16 += cdiv(len, 16);
+        t32 += cdiv(len, 32);
+    }
+    const int splits = tok_splits(D.L, D.d, D.r, M);
+    out[0] = 1;
+    out[1] = 16 * proj_row_tiles(D.L, D.r, t16, t32);
+    out[2] = splits < F.f_splits ? splits : F.f_splits;
+    out[3] = chain_wc(D.L, D.r);
+}
+
 template <auto Kern> static hipError_t allow_lds_once(int lds)
 {
     static std::once_flag once;
@@ -1450,9 +1491,8 @@ template <int NB, int WC> static hipError_t run_f32_gram(const Dims &D, const Ws
         a.cache = (const float *)io.cache; a.params = io.params; a.PL = D.PL; a.L = L; a.d = d; a.C = C; a.nch = nch;
         a.rowoff = rowoff; a.rowstride = rowstride; a.cusum = at(W.g_cusum); a.chatp = at(W.g_chat); a.V = at(W.g_V);
         a.pb = at(W.pooled); a.zpbp = at(W.g_zpb); a.Qf = at(W.g_QpT); a.Qb = at(W.g_QpN); a.U = at(W.pre_all);
-        // 32-row tiles where they still fill the chip twice over and ragged samples do not leave many of them empty
         const int t16 = tiles_of(meta, 16, a.tile0), t32 = tiles_of(meta, 32, a.tile0);
-        const int rt = r <= 128 && (int64_t)L * t32 >= 512 && 20 * t32 <= 11 * t16 ? 2 : 1;
+        const int rt = proj_row_tiles(L, r, t16, t32);
         const int tiles = tiles_of(meta, 16 * rt, a.tile0);
         a.nb_chat = (L + 1) * nch; a.nb_pb = B * nch; a.nb_V = cdiv(Lr, C > 4 ? 4 * kVRows : 4); a.nb_tab = cdiv(M, 256);
         a.nb_Q = W.pairs * (r / (rt > 1 ? 32 : 16)); a.nb_U = L * tiles;

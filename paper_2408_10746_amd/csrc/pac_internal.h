@@ -57,7 +57,7 @@ struct WsLayout {
     int32_t g_dlam_slots;
 
     // ---- fp32 steps in the Gram-matrix formulation (pac_gram32.hip; use_gram is 0) ----
-    int32_t f32_gram;   // the step runs there
+    int32_t f32_gram;   // 1: the layout of these
     int32_t f_splits;   // token splits of its contractions over the tokens at the largest batch
 };
 
@@ -137,6 +137,8 @@ struct AdamArgs {
 };
 
 void plan_workspace(const Dims &D, WsLayout &W);
+// W: the per-layer kernels' layout.  False (F.total is 0) where the Gram-matrix formulation in fp32 is not to be had
+bool plan_f32_gram(const Dims &D, const WsLayout &W, WsLayout &F);
 
 // Each returns the first HIP error met (hipSuccess otherwise).
 hipError_t launch_cache_fill(const Dims &D, void *cache, const void *acts, int acts_dtype,
@@ -149,6 +151,9 @@ hipError_t launch_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMe
 void gram_step_tiles(const Dims &D, const WsLayout &W, int M, int ntiles, int32_t out[6]);
 void layer_step_tiles(const Dims &D, const WsLayout &W, int M, int32_t out[6]);
 bool f32_gram_fits(const Dims &D); // whether pac_gram32.hip has kernels for the configuration
+// Whether they are faster than the per-layer kernels on B samples of M token rows in ntiles 16-row tiles
+bool f32_gram_pays(const Dims &D, int B, int M, int ntiles, bool grads);
+void f32_gram_plan(const Dims &D, const WsLayout &F, const int32_t *lens, int B, int M, int32_t out[4]); // pac_f32_plan
 void plan_f32_gram_workspace(const Dims &D, WsLayout &W, int64_t &offset);
 hipError_t launch_f32_gram_loss_grad(const Dims &D, const WsLayout &W, const BatchMeta &meta, const StepIO &io);
 void gram_chain_plan(const Dims &D, const WsLayout &W, int M, int32_t out[6]); // pac_chain_plan for a batch of M token rows
@@ -168,6 +173,8 @@ hipError_t launch_adamw(const Dims &D, float *p, float *m, float *v, float *g,
 struct pac_ctx {
     pac::Dims D;
     pac::WsLayout W;
+    pac::WsLayout F;     // the fp32 Gram-matrix formulation's; total is 0 without it
+    bool f32_every;      // every batch takes that (else pac_api.hip's layout_for decides)
     std::vector<int64_t> off; // element offset of each sample's block, -1 = never filled
     std::vector<int32_t> len;
     int64_t next_free; // elements

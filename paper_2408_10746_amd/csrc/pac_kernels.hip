@@ -48,8 +48,6 @@ static int choose_splits(const Dims &D, int workgroups, int min_rows)
     return s;
 }
 
-static bool rows16_pays(int M, int ncols, bool long_steps);
-
 void plan_workspace(const Dims &D, WsLayout &W)
 {
     W.f32_gram = W.f_splits = 0;
@@ -95,18 +93,24 @@ void plan_workspace(const Dims &D, WsLayout &W)
         W.part = take((int64_t)W.splits * D.PL * 4);
     }
     W.total = o;
-    // fp32 in the Gram-matrix formulation, where 16-row tiles pay (there its launches have been measured against these), and
-    // where it takes no more workspace than pac_adapter_step_static has or, above that, than twice the per-layer kernels'
-    if (f32_gram_fits(D) && rows16_pays((int)D.Mmax, D.r, D.d % Stage<float, 4>::BK == 0)) {
-        WsLayout G = W;
-        int64_t at = 0;
-        plan_f32_gram_workspace(D, G, at);
-        if (at <= PAC_STATIC_WORKSPACE_BYTES || (W.total > PAC_STATIC_WORKSPACE_BYTES && at <= 2 * W.total)) {
-            W = G;
-            W.f32_gram = 1;
-            W.total = at;
-        }
-    }
+}
+
+static bool rows16_pays(int M, int ncols, bool long_steps);
+
+// fp32 in the Gram-matrix formulation, up to the rows where 64 x 64 tiles fill the chip (beyond, the per-layer kernels take
+// down to 0.6 of its time: 14 layers of 256 x 128, 16384 rows forward only, 518 against 827 us), and where it takes no more
+// workspace than pac_adapter_step_static has or, above that, than twice the per-layer kernels'
+bool plan_f32_gram(const Dims &D, const WsLayout &W, WsLayout &F)
+{
+    F = W;
+    F.total = 0;
+    if (!f32_gram_fits(D) || !rows16_pays((int)D.Mmax, D.r, D.d % Stage<float, 4>::BK == 0)) return false;
+    int64_t o = 0;
+    plan_f32_gram_workspace(D, F, o);
+    if (o > PAC_STATIC_WORKSPACE_BYTES && (W.total <= PAC_STATIC_WORKSPACE_BYTES || o > 2 * W.total)) return false;
+    F.f32_gram = 1;
+    F.total = o;
+    return true;
 }
 
 // ---------------------------------------------------------------------------

@@ -150,6 +150,53 @@ def test_tiles_chosen_per_batch():
     assert pb.lib().pac_step_tiles(None, None, 1, (C.c_int32 * 6)()) == pb.PAC_ERR_NULL
 
 
+def test_fp32_formulation_per_batch():
+    """Host logic: which formulation an fp32 call takes, on both sides of the line (us in the Gram-matrix formulation / in the
+    per-layer kernels), and what is reserved for it."""
+    def ask(L, d, r, n, B, lens=None, grads=True, C=3, n_max=None, dtype=pb.PAC_F32, flags=0):
+        ctx = pb.pac_create(L, d, n_max or n, r, C, B, 64, dtype, flags)
+        try:
+            return pb.pac_f32_plan(ctx, lens, B if lens is None else len(lens), grads), pb.pac_workspace_bytes(ctx)
+        finally:
+            pb.pac_destroy(ctx)
+
+    def gram(*a, **kw):
+        return ask(*a, **kw)[0]["gram"]
+
+    assert ask(12, 768, 96, 128, 32)[0] == dict(gram=1, proj=32, splits=1, wc=1)   # T5-Base-shaped
+    assert ask(2, 64, 32, 400, 8)[0] == dict(gram=1, proj=16, splits=8, wc=1)
+    for grads in (True, False):
+        assert gram(12, 768, 96, 128, 32, grads=grads) and gram(4, 256, 32, 64, 8, grads=grads)
+        assert not gram(12, 768, 96, 128, 32, grads=grads, flags=pb.PAC_FLAG_PER_LAYER)
+        assert not gram(12, 768, 96, 128, 32, grads=grads, dtype=pb.PAC_BF16)
+        assert not gram(12, 768, 160, 128, 32, grads=grads)       # a width without kernels
+        assert not gram(17, 768, 96, 128, 32, grads=grads)        # too many layers for a compute unit's LDS
+        assert not gram(1, 768, 96, 128, 32, grads=grads)
+        assert not gram(14, 256, 128, 512, 32, grads=grads)       # 64 x 64 tiles fill the chip (1981 / 1459, 827 / 518)
+        assert not gram(31, 128, 64, 256, 32, grads=grads)        # (1297 / 1173, 502 / 425)
+        assert not gram(8, 384, 192, 1, 1, grads=grads)           # (271 / 242, 129 / 114)
+        assert not gram(5, 512, 256, 16, 1, grads=grads)          # (201 / 192, 100 / 91)
+        assert gram(14, 512, 128, 128, 8, grads=grads)
+    # steps one way, forward-only calls the other (2576 / 2650, 925 / 704)
+    # and by the batch, whatever the largest is
+    big = dict(n_max=1024, B=4)
+    assert gram(8, 1024, 192, 1024, 4) and not gram(8, 1024, 192, lens=[16], n=16, **big)
+    # reserved: one formulation where every batch takes it, the larger of both otherwise
+    _, every = ask(12, 768, 96, 128, 32)
+    _, per_layer = ask(12, 768, 96, 128, 32, flags=pb.PAC_FLAG_PER_LAYER)
+    assert every < per_layer
+    _, both = ask(8, 1024, 192, 1024, 4)
+    _, per_layer = ask(8, 1024, 192, 1024, 4, flags=pb.PAC_FLAG_PER_LAYER)
+    assert both >= per_layer
+    # within the static entry's workspace alone: the Gram-matrix formulation for every batch
+    plan, ws = ask(5, 1952, 256, 16, 32, grads=False)
+    assert plan["gram"] and ws <= pb.PAC_STATIC_WORKSPACE_BYTES < ask(5, 1952, 256, 16, 32, flags=pb.PAC_FLAG_PER_LAYER)[1]
+    with pytest.raises(pb.PacError) as e:
+        ask(12, 768, 96, 128, 2, [128, 129])
+    assert e.value.status == pb.PAC_ERR_RANGE
+    assert pb.lib().pac_f32_plan(None, None, 1, 1, (C.c_int32 * 4)()) == pb.PAC_ERR_NULL
+
+
 def test_per_layer_workspace_holds_the_splits_that_run():
     """bf16 weight gradients walk 128 token rows a step: 128 rows are one split and reserve one set of partial sums."""
     def ws(n):

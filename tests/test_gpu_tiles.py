@@ -145,6 +145,56 @@ def test_fp32_gram(w):
     assert torch.equal(sess.loss, loss) and torch.equal(sess.grads, grads)
 
 
+# One context whose calls take different formulations: steps on the whole batch the Gram-matrix formulation, all others the
+# per-layer kernels (b1), or steps the one and forward-only calls the other (b2).
+@pytest.mark.parametrize("w,whole,short", [
+    (Workload("b1", L=5, d=512, n_max=64, B=4, r=256, C=3, N=4, cache_dtype="f32", len_lo=3), (1, 0), (0, 0)),
+    (Workload("b2", L=13, d=256, n_max=64, B=4, r=128, C=3, N=4, cache_dtype="f32", len_lo=3), (1, 0), (1, 0)),
+], ids=lambda v: getattr(v, "name", None))
+def test_fp32_formulation_by_batch(w, whole, short):
+    lens = np.array([64, 3, 64, 61], dtype=np.int32)
+    ids, acts, labels = np.arange(w.B), inputs.batch_acts(w, np.arange(w.B)), inputs.labels(w)[:w.B]
+    params = inputs.random_params(w, up_scale=0.3)
+    sess = make_session(w, lens=lens)
+    sess.cache_fill(ids, acts, lens)
+    runs_gram = lambda p: any(k.startswith("g_chain") and n for k, (_, n) in p.items())
+    for sel, form in ((ids, whole), (ids[1:2], short)):
+        assert tuple(pb.pac_f32_plan(sess.ctx, lens[sel], len(sel), g)["gram"] for g in (True, False)) == form
+        lab = torch.from_numpy(labels[sel]).to(sess.dev)
+        pb.pac_profile_begin(sess.ctx)
+        _, loss, _, _ = check_against_oracle(w, sess, sel, acts[sel], lens[sel], labels[sel], params, TOL["f32"], what=w.name)
+        assert runs_gram(pb.pac_profile_end(sess.ctx)) == bool(form[0])
+        logits, grads = sess.logits[:len(sel) * w.C].clone(), sess.grads.clone()
+        pb.pac_profile_begin(sess.ctx)
+        sess.loss_grad(sel, lab, want_grads=False)
+        assert runs_gram(pb.pac_profile_end(sess.ctx)) == bool(form[1])
+        assert abs(float(sess.loss) - loss) <= TOL["f32"] * abs(loss)
+        assert torch.linalg.norm(sess.logits[:len(sel) * w.C] - logits) <= TOL["f32"] * torch.linalg.norm(logits)
+        sess.step(sel, lab, keep_grads=False)  # its gradient lies where the formulation's own workspace has it
+        assert torch.allclose(sess.m, 0.1 * grads, rtol=1e-5, atol=0)
+        sess.set_params(params)
+
+
+def test_fp32_gram_within_the_static_workspace():
+    """The per-layer kernels would need more than the static entry has, so every batch takes the Gram-matrix formulation."""
+    from paper_2408_10746_amd.runtime import _stream_handle
+    w = Workload("b3", L=5, d=2208, n_max=2, B=2, r=256, C=3, N=2, cache_dtype="f32")
+    ids, acts, labels = np.arange(w.B), inputs.batch_acts(w, np.arange(w.B)), inputs.labels(w)[:w.B]
+    sess = make_session(w)
+    assert pb.pac_f32_plan(sess.ctx, None, 1, False)["gram"] and sess.ws_bytes <= pb.PAC_STATIC_WORKSPACE_BYTES
+    sess.cache_fill(ids, acts)
+    params = inputs.random_params(w, up_scale=0.3)
+    lab = torch.from_numpy(labels).to(sess.dev)
+    check_against_oracle(w, sess, ids, acts, None, labels, params, TOL["f32"], what=w.name)
+    sess.step(ids, lab)
+    want = [t.clone() for t in (sess.loss, sess.grads, sess.params)]
+    sess.set_params(params)
+    pb.pac_adapter_step_static(sess.ctx, sess.cache.data_ptr(), ids, lab.data_ptr(), sess.params.data_ptr(), sess.m.data_ptr(),
+                               sess.v.data_ptr(), 0, sess.hp, sess.loss.data_ptr(), sess.grads.data_ptr(), _stream_handle())
+    for a, b in zip(want, (sess.loss, sess.grads, sess.params)):
+        assert torch.equal(a, b)
+
+
 # What the fp32 launches do for each class: four at a time, a last group of one, two, three and four.
 @pytest.mark.parametrize("C", [2, 4, 5, 7, 16])
 def test_fp32_gram_class_counts(C):
