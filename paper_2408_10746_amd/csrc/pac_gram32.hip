@@ -1,5 +1,5 @@
 // Gram-matrix formulation of the cached Parallel-Adapter step for an fp32 cache (the equations at the head of
-// pac_gram.hip), fp32 throughout: matrix instructions, sums, and everything kept between the launches.
+// pac_gram.hip), in fp32: matrix instructions and everything kept between the launches.
 //
 // The layer-by-layer kernels read and write a d-wide side state and its gradient per layer, four dependent launches a layer,
 // each a contraction too small to fill the chip (12 layers of 768 x 96, 4096 token rows: 53 launches, 1000 us).  Here no
@@ -10,6 +10,13 @@
 //   k_f_tok     E_l = b_l^T dpre_l, G_kl = h_k^T dpre_l, column sums      (+ k_f_sum where the tokens are split)
 //   k_f_post    dW_down, dW_up, dW_cls and the vector gradients
 //   k_adamw
+//
+// Errors: what is computed once and used for every token (Q, V) or summed over many of them (column sums, gates, the head)
+// does not average out over the tokens as the per-layer kernels' errors do.  So no sum of those runs through one
+// accumulator from end to end: matrix accumulators are emptied into a second one every 32 to 96 of K, and the few sums that
+// every token or sample takes part in are kept in 64 bits.  Gradients against float64, geometric mean over 119 drawn
+// configurations and 242 deep or narrow ones: 1.30e-7 and 1.47e-7, gates 1.29e-7 and 1.69e-7 (per-layer kernels 1.43e-7,
+// 1.66e-7, 1.30e-7, 1.97e-7; with single accumulators 1.55e-7, 1.99e-7, 1.72e-7, 2.58e-7), at 2 us of a step of 400.
 //
 // All contractions are written on one pattern: an output tile's K range is dealt over the wavefronts of the workgroup, each
 // loads both operands straight from memory into 16x16x4 fp32 matrix operands one unit of 16 in K ahead, and the partial
@@ -73,17 +80,17 @@ __device__ __forceinline__ f32x4 load_classes(const float *row, int c0, int C)
 }
 // Sums of N values over the lanes, added as a tree of offsets 32, 16, .. 1: with every offset a lane keeps half of the values
 // and hands the other half over, so N = 16 takes 17 exchanges, not 96.  Lane i ends with the sum of value i * N / 64.
-template <int N> __device__ __forceinline__ float lane_sums(float (&v)[N], int o = 32)
+template <int N, class T> __device__ __forceinline__ T lane_sums(T (&v)[N], int o = 32)
 {
     if constexpr (N > 1) {
         const bool hi = threadIdx.x & o;
-        float keep[N / 2];
+        T keep[N / 2];
 #pragma unroll
         for (int k = 0; k < N / 2; ++k)
             keep[k] = (hi ? v[k + N / 2] : v[k]) + __shfl_xor(hi ? v[k] : v[k + N / 2], o, 64);
         return lane_sums<N / 2>(keep, o / 2);
     } else {
-        float s = v[0];
+        T s = v[0];
         for (; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         return s;
     }
@@ -180,8 +187,26 @@ template <int ROWS> struct RowStage {
     }
 };
 
+template <int RA, int NB> __device__ __forceinline__ void tt_zero(f32x4 (&acc)[RA][2 * NB])
+{
+#pragma unroll
+    for (int c = 0; c < RA; ++c)
+#pragma unroll
+        for (int q = 0; q < 2 * NB; ++q) acc[c][q] = zero4();
+}
+template <int RA, int NB> __device__ __forceinline__ void tt_move(f32x4 (&to)[RA][2 * NB], f32x4 (&from)[RA][2 * NB])
+{
+#pragma unroll
+    for (int c = 0; c < RA; ++c)
+#pragma unroll
+        for (int q = 0; q < 2 * NB; ++q) {
+            to[c][q] += from[c][q];
+            from[c][q] = zero4();
+        }
+}
+
 // A: 16 RT rows contiguous along K, staged in LDS; B: rows contiguous along the columns, bp its row 0.  Steps of 32 in K:
-// [s0, s1).
+// [s0, s1), the sums of each added to the total by themselves.
 template <int RT, int NB>
 __device__ __forceinline__ void nn_contract(f32x4 (&acc)[RT][2 * NB], RowStage<16 * RT> &A, float *lds, const float *bp, int ldb, int s0, int s1, int i, int g)
 {
@@ -203,6 +228,8 @@ __device__ __forceinline__ void nn_contract(f32x4 (&acc)[RT][2 * NB], RowStage<1
                 for (int q = 0; q < 2 * NB; ++q) acc[x][q] = mfma16(av[x][e], t.b[e].get(q), acc[x][q]);
     };
     if (s0 >= s1) return;
+    f32x4 total[RT][2 * NB];
+    tt_zero<RT, NB>(total);
     Unit s, t;
     A.fetch(s0 * kStageK);
     load(s, 2 * s0);
@@ -220,7 +247,9 @@ __device__ __forceinline__ void nn_contract(f32x4 (&acc)[RT][2 * NB], RowStage<1
         wave_sync();
         A.put(lds);
         wave_sync();
+        tt_move<RT, NB>(total, acc);
     }
+    tt_move<RT, NB>(acc, total);
 }
 
 // Both operands contiguous along the other index, K rows apart: 16 RA rows (lane i: RA i + c), 32 NB columns.  Src:
@@ -229,6 +258,7 @@ __device__ __forceinline__ void nn_contract(f32x4 (&acc)[RT][2 * NB], RowStage<1
 //   a(Idx, u, e)           this lane's rows at K index 16 u + 4 e + g
 //   b(u, e), b_off()       the other operand's row 16 u + 4 e at column 0 of the tile, and bytes from there to row + g
 //   live(u, e)             whether that K index counts (else both operands are zero); only asked of the last unit
+// FLUSH > 0 (a multiple of 3): the sums of so many units are added to the total by themselves.
 template <int RA> struct RowVec;
 template <> struct RowVec<2> { typedef f32x2 T; };
 template <> struct RowVec<4> { typedef f32x4 T; };
@@ -236,9 +266,15 @@ template <int RA, int NB> struct TtUnit {
     typename RowVec<RA>::T a[4];
     Cols<NB> b[4];
 };
-template <int RA, int NB, class Src>
+template <int RA, int NB, int FLUSH = 0, class Src>
 __device__ __forceinline__ void tt_contract(f32x4 (&acc)[RA][2 * NB], const Src &src, int u0, int u1, int i)
 {
+    static_assert(FLUSH % 3 == 0, "whole turns of the loop");
+    f32x4 total[FLUSH ? RA : 1][2 * NB];
+    if constexpr (FLUSH > 0) tt_zero<RA, NB>(total);
+    auto finish = [&]() {
+        if constexpr (FLUSH > 0) tt_move<RA, NB>(acc, total);
+    };
     typedef typename Src::Idx Idx;
     auto prep = [&](Idx &ix, int u) { src.prep(ix, min(u, u1 - 1)); };
     auto load = [&](TtUnit<RA, NB> &t, const Idx &ix, int u) {
@@ -291,23 +327,28 @@ __device__ __forceinline__ void tt_contract(f32x4 (&acc)[RA][2 * NB], const Src 
         prep(ix, u + 5);
         hold_loads();
         mma(r2);
+        if constexpr (FLUSH > 0)
+            if ((u - u0) % FLUSH == FLUSH - 3) tt_move<RA, NB>(total, acc);
     }
     if (u1 - u == 3) load(r2, ix, u + 2);
     hold_loads();
     if (u1 - u == 1) {
         mask(r0, u);
         mma(r0);
+        finish();
         return;
     }
     mma(r0);
     if (u1 - u == 2) {
         mask(r1, u + 1);
         mma(r1);
+        finish();
         return;
     }
     mma(r1);
     mask(r2, u + 2);
     mma(r2);
+    finish();
 }
 
 // Both operands contiguous along K, both staged: 16 RT rows, 16 CT columns; steps of 32 in K, at(st): K offset of both
@@ -430,7 +471,9 @@ template <int RT, int NB> __device__ __forceinline__ void proj_tile(const FProjA
 
 // Rows row0 .. + R - 1 of V (one layer's), by a wavefront, four classes at a time.  Bound by how often a wavefront touches the
 // lines of W_cls, 64 rows of it at once: a load for each class and row of V took 80 us with 16 classes at 5 layers of 1248 x
-// 256 (the step 358 us, 120 of it forward with three classes and 187 with 16), four classes a load and four rows 22 (283; 132).
+// 256 (the step 358 us, 120 of it forward with three classes and 187 with 16), four classes a load and four rows 24 (287; 135).
+// Sums of four products, then in 64 bits: V is used for every token, and in fp32 its error was the gates' and biases' largest
+// (3 us more with every product in 64 bits at three classes, 40 at 16).
 constexpr int kVRows = 4;
 template <int R> __device__ __forceinline__ void v_rows(const FProjArgs &a, int row0, int r)
 {
@@ -439,9 +482,9 @@ template <int R> __device__ __forceinline__ void v_rows(const FProjArgs &a, int 
     const float *Wc = a.params + (int64_t)L * a.PL;
     const float *wu = a.params + (int64_t)(row0 / r) * a.PL + (int64_t)d * r + r + (int64_t)(row0 % r) * d;
     for (int c0 = 0; c0 < C; c0 += 4) {
-        float acc[R * 4];
+        double acc[R * 4];
 #pragma unroll
-        for (int x = 0; x < R * 4; ++x) acc[x] = 0.f;
+        for (int x = 0; x < R * 4; ++x) acc[x] = 0.;
         for (int j0 = 0; j0 < d; j0 += 64 * 4) {
             float w[R][4];
             f32x4 wc[4];
@@ -454,11 +497,14 @@ template <int R> __device__ __forceinline__ void v_rows(const FProjArgs &a, int 
 #pragma unroll
             for (int x = 0; x < R; ++x)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
+                for (int c = 0; c < 4; ++c) {
+                    float part = w[x][0] * wc[0][c];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) acc[4 * x + c] += w[x][u] * wc[u][c];
+                    for (int u = 1; u < 4; ++u) part += w[x][u] * wc[u][c];
+                    acc[4 * x + c] += (double)part;
+                }
         }
-        const float v = lane_sums<R * 4>(acc);
+        const float v = (float)lane_sums<R * 4>(acc);
         const int at = lane * (R * 4) / 64, c = c0 + at % 4;
         if (lane % (64 / (R * 4)) == 0 && c < C) a.V[(int64_t)(row0 + at / 4) * C + c] = v;
     }
@@ -514,9 +560,15 @@ template <int RT, int NB> __global__ __launch_bounds__(256) void k_f_proj(FProjA
         // mean of b_L over the sample's tokens, a chunk of d; its and cusum_L's share of the logits
         const int s = b / a.nch, ch = b % a.nch, len = a.meta.len[s];
         const float *src = a.cache + a.meta.off[s] + (int64_t)(L - 1) * len * d + min(ch * kChunk + 4 * lane, d - 4);
-        f32x4 acc = zero4();
-#pragma unroll 8
-        for (int q = wave; q < len; q += 4) acc += *reinterpret_cast<const f32x4 *>(src + (int64_t)q * d);
+        f32x4 part[4] = {zero4(), zero4(), zero4(), zero4()};
+#pragma unroll 2
+        for (int q = wave; q < len; q += 16)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(src + (int64_t)min(q + 4 * e, len - 1) * d);
+                part[e] += q + 4 * e < len ? v : zero4();
+            }
+        const f32x4 acc = (part[0] + part[1]) + (part[2] + part[3]);
         *reinterpret_cast<f32x4 *>(sh + wave * kChunk + 4 * lane) = acc;
         __syncthreads();
         const int j = ch * kChunk + t, jc = min(j, d - 1);
@@ -739,9 +791,9 @@ template <bool FWD, int NB, int WC> __global__ __launch_bounds__(kChainThreads) 
             for (int q = 0; q < a.nch; ++q) chat += a.chatp[((int64_t)l * a.nch + q) * r + n];
             vec[c] = (1.f - pl[a.PL - 1]) * chat + pl[(int64_t)a.d * r + n];
         } else {
-            float v = 0.f;
-            for (int q = 0; q < a.C; ++q) v += dzs[q] * a.V[(int64_t)c * a.C + q];
-            vec[c] = v / (float)len;
+            double v = 0.;
+            for (int q = 0; q < a.C; ++q) v += (double)dzs[q] * (double)a.V[(int64_t)c * a.C + q];
+            vec[c] = (float)v / (float)len;
         }
     }
     f32x4 acc[2 * NB];
@@ -837,7 +889,10 @@ template <bool FWD, int NB, int WC> __global__ __launch_bounds__(kChainThreads) 
             const int c = min(c0 + u * kChainThreads, Lr - 1), l = c / r, n = c % r;
             sum[u] = 0.f;
 #pragma unroll
-            for (int q = 0; q < kT; ++q) sum[u] += Hs[((size_t)l * kT + q) * RP + n];
+            for (int q = 0; q < kT; q += 4) {
+                const float *h = Hs + ((size_t)l * kT + q) * RP + n;
+                sum[u] += (h[0] + h[RP]) + (h[2 * RP] + h[3 * RP]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -918,13 +973,6 @@ template <int RA, int NB> __device__ __forceinline__ void tt_meet(const f32x4 (&
         out[q] = s;
     }
 }
-template <int RA, int NB> __device__ __forceinline__ void tt_zero(f32x4 (&acc)[RA][2 * NB])
-{
-#pragma unroll
-    for (int c = 0; c < RA; ++c)
-#pragma unroll
-        for (int q = 0; q < 2 * NB; ++q) acc[c][q] = zero4();
-}
 
 // token rows of the cache (FROM_CACHE) or of H against those of DP.  The last unit ends with the range and repeats tokens of
 // the one before it, which do not count again (fewer than 16 tokens in all: it starts at row 0, and the arrays have 16).
@@ -964,7 +1012,7 @@ template <bool FROM_CACHE> struct TokSrc {
 // at most, so it fetches about 16 bytes a clock where they come from behind L2 and 50 from L2, and a tile of 64 x 96 wants
 // 13: a die takes neighbouring tiles of the list below, which share their columns of DP.  Eight wavefronts a workgroup drift
 // apart until their rows fall out of L2 (193 us).  Bound by the matrix instructions, 12.2 GFLOP at 12 layers of 768 x 96
-// and 4096 rows in 249 tiles, 83 us without a stall; 120 us.
+// and 4096 rows in 246 tiles, 83 us without a stall; 120 us.
 constexpr int kTokThreads = 256, kPostThreads = 256;
 // Work items numbered so that a die (blocks go round the eight of them) takes neighbours
 __device__ __forceinline__ int die_order(int b, int n)
@@ -984,20 +1032,25 @@ template <int NB> __global__ __launch_bounds__(kTokThreads) void k_f_tok(FTokArg
         // wavefronts.  (Dispatched last: in front of the tiles, one of which fills a compute unit, they delayed some of those.)
         b -= a.nb_tiles;
         const int col = b * 64 + lane, cc = min(col, Lr - 1);
-        float cs = 0.f, z[kMaxClasses];
+        double cs = 0., z[kMaxClasses];
 #pragma unroll
-        for (int c = 0; c < kMaxClasses; ++c) z[c] = 0.f;
+        for (int c = 0; c < kMaxClasses; ++c) z[c] = 0.;
         for (int s = wave; s < a.meta.B; s += 4) {
-            float hs = 0.f;
-#pragma unroll 8
-            for (int q = a.tile0[s]; q < a.tile0[s + 1]; ++q) {
-                hs += a.HSpart[(int64_t)q * Lr + cc];
-                cs += a.cspart[(int64_t)q * Lr + cc];
-            }
-            hs /= (float)a.meta.len[s];
+            float hp[4] = {0.f, 0.f, 0.f, 0.f}, cp[4] = {0.f, 0.f, 0.f, 0.f};
+            const int q1 = a.tile0[s + 1];
+#pragma unroll 2
+            for (int q = a.tile0[s]; q < q1; q += 4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t at = (int64_t)min(q + e, q1 - 1) * Lr + cc;
+                    hp[e] += q + e < q1 ? a.HSpart[at] : 0.f;
+                    cp[e] += q + e < q1 ? a.cspart[at] : 0.f;
+                }
+            const float hs = ((hp[0] + hp[1]) + (hp[2] + hp[3])) / (float)a.meta.len[s];
+            cs += (double)((cp[0] + cp[1]) + (cp[2] + cp[3]));
 #pragma unroll
             for (int c = 0; c < kMaxClasses; ++c)
-                if (c < C) z[c] += hs * a.dz[s * C + c];
+                if (c < C) z[c] += (double)hs * (double)a.dz[s * C + c];
         }
         red[wave * 64 + lane] = cs;
         float *zr = red + kTokThreads; // [4][kMaxClasses][64]
@@ -1019,9 +1072,9 @@ template <int NB> __global__ __launch_bounds__(kTokThreads) void k_f_tok(FTokArg
             if (b * 64 + q < Lr) a.Z[(int64_t)(b * 64 + q) * kZP + c] = v; // zero from class C on
         }
         if (b == 0 && t < C) {
-            float v = 0.f;
-            for (int s = 0; s < a.meta.B; ++s) v += a.dz[s * C + t];
-            a.dzsum[t] = v;
+            double v = 0.;
+            for (int s = 0; s < a.meta.B; ++s) v += (double)a.dz[s * C + t];
+            a.dzsum[t] = (float)v;
         }
         return;
     }
@@ -1151,22 +1204,25 @@ template <int NB> __global__ __launch_bounds__(kPostThreads) void k_f_post(FPost
         StackSrc src;
         src.A = a.params + dr + r + j0; src.at = 2 * i; src.B = a.Z; src.PL = a.PL; src.KB = KB; src.d = d; src.ldb = kZP; src.g = g;
         const int units = L * KB;
-        tt_contract<2, 1>(acc, src, units * wave / 4, units * (wave + 1) / 4, i);
+        tt_contract<2, 1, 3>(acc, src, units * wave / 4, units * (wave + 1) / 4, i);
         f32x4 out[1];
         tt_meet<2, 1>(acc, red, out);
         const int j = j0 + t / 8, c0 = t % 8 * 4;
         if (c0 < C) {
             const float cl = a.cusum[(int64_t)L * d + j];
+            double sum[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[c] = (double)out[0][c];
 #pragma unroll 8
             for (int s = 0; s < a.B; ++s) {
                 const float p = a.pb[(int64_t)s * d + j] + cl;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) out[0][c] += p * a.dz[s * C + min(c0 + c, C - 1)];
+                for (int c = 0; c < 4; ++c) sum[c] += (double)p * (double)a.dz[s * C + min(c0 + c, C - 1)];
             }
             float *gc = a.grads + (int64_t)L * a.PL + (int64_t)j * C + c0;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (c0 + c < C) gc[c] = out[0][c];
+                if (c0 + c < C) gc[c] = (float)sum[c];
         }
         return;
     }
@@ -1196,10 +1252,10 @@ template <int NB> __global__ __launch_bounds__(kPostThreads) void k_f_post(FPost
             cu[q] = a.cusum[(int64_t)l * d + row];
         }
         const int units = l * KB;
-        tt_contract<2, NB>(acc, src, units * wave / 4, units * (wave + 1) / 4, i);
+        tt_contract<2, NB, 6>(acc, src, units * wave / 4, units * (wave + 1) / 4, i);
         f32x4 out[NP];
         tt_meet<2, NB>(acc, red, out);
-        float dlam = 0.f;
+        double dlam = 0.;
         float *gw = a.grads + (int64_t)l * a.PL;
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
@@ -1207,13 +1263,13 @@ template <int NB> __global__ __launch_bounds__(kPostThreads) void k_f_post(FPost
             f32x4 gv;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const float F = out[q][c] + cu[q] * csv[q][c];
-                gv[c] = lam * Ev[q][c] + (1.f - lam) * F;
-                dlam += (Ev[q][c] - F) * Wv[q][c];
+                const double F = (double)out[q][c] + (double)cu[q] * (double)csv[q][c];
+                gv[c] = lam * Ev[q][c] + (1.f - lam) * (float)F;
+                dlam += ((double)Ev[q][c] - F) * (double)Wv[q][c];
             }
             *reinterpret_cast<f32x4u *>(gw + (int64_t)row * r + col) = gv;
         }
-        const float tot = block_sum(dlam, scratch);
+        const float tot = block_sum((float)dlam, scratch);
         if (t == 0) a.dlam_part[(int64_t)l * a.slots + slot] = tot; // summed in slot order by the last launch
         return;
     }
@@ -1308,10 +1364,10 @@ __global__ __launch_bounds__(64) void k_f_finish(const float *loss_part, int B, 
     }
     if (grads)
         for (int l = t; l < L; l += 64) {
-            float acc = 0.f;
+            double acc = 0.;
 #pragma unroll 8
-            for (int s = 0; s < slots; ++s) acc += dlam_part[(int64_t)l * slots + s];
-            grads[(int64_t)l * PL + PL - 1] = acc;
+            for (int s = 0; s < slots; ++s) acc += (double)dlam_part[(int64_t)l * slots + s];
+            grads[(int64_t)l * PL + PL - 1] = (float)acc;
         }
 }
 
@@ -1565,7 +1621,7 @@ template <int NB, int WC> static hipError_t run_f32_gram(const Dims &D, const Ws
     if (io.defer) { // the optimizer launch that follows does the last two sums
         io.defer->used = true;
         io.defer->loss_part = ca.loss_part; io.defer->B = B; io.defer->loss_out = io.loss_out;
-        io.defer->dlam_part = pa.dlam_part; io.defer->slots = pa.slots; io.defer->grads = io.grads;
+        io.defer->dlam_part = pa.dlam_part; io.defer->slots = pa.slots; io.defer->wide = true; io.defer->grads = io.grads;
     } else {
         PAC_LAUNCH(prof, st, KC_G_FINISH, k_f_finish, dim3(1), dim3(64), 0, st, ca.loss_part, B, io.loss_out, (const float *)pa.dlam_part, pa.slots, L, D.PL, io.grads);
     }

@@ -127,6 +127,7 @@ struct Deferred {
     float *loss_out = nullptr;
     const float *dlam_part = nullptr; // [L][slots]
     int slots = 0;
+    bool wide = false;      // the gate gradients are summed in 64 bits
     float *grads = nullptr; // where the gate gradients go as well
 };
 

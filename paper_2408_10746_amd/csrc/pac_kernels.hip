@@ -980,7 +980,14 @@ __device__ __forceinline__ void adamw_elem(int layer, int64_t o, int L, float &p
         if (fin.used && o == PL - 1) {
             const float *part = fin.dlam_part + (int64_t)layer * fin.slots;
             float acc = 0.f;
-            for (int s = 0; s < fin.slots; ++s) acc += part[s];
+            if (fin.wide) {
+                double sum = 0.;
+#pragma unroll 8
+                for (int s = 0; s < fin.slots; ++s) sum += (double)part[s];
+                acc = (float)sum;
+            } else {
+                for (int s = 0; s < fin.slots; ++s) acc += part[s];
+            }
             gi = acc;
         }
     } else {

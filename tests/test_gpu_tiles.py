@@ -11,7 +11,7 @@ from paper_2408_10746_amd.inputs import Workload
 
 pytestmark = pytest.mark.gpu
 
-from tests.test_gpu_parity import TOL, check_against_oracle, make_session  # noqa: E402
+from tests.test_gpu_parity import TOL, check_against_oracle, make_session, oracle_batch  # noqa: E402
 
 
 def tiles_of(w, lens):
@@ -193,6 +193,42 @@ def test_fp32_gram_within_the_static_workspace():
                                sess.v.data_ptr(), 0, sess.hp, sess.loss.data_ptr(), sess.grads.data_ptr(), _stream_handle())
     for a, b in zip(want, (sess.loss, sess.grads, sess.params)):
         assert torch.equal(a, b)
+
+
+def test_fp32_gram_error_is_no_larger_than_per_layer():
+    """Gradients against float64 in both fp32 formulations: deep narrow adapters, few rows and many, where the Gram-matrix
+    formulation has the longest sums and uses the same rounded products (Q, V) for every token.  Geometric means over the
+    configurations, of the whole gradient and of the gates' and head's parts; every sum's order is fixed, and so are they."""
+    rng = np.random.default_rng(7)
+    shapes = []
+    while len(shapes) < 48:
+        r = int(rng.choice([32, 64, 96, 128]))
+        L, d = int(rng.integers(5, {32: 48, 64: 30, 96: 16, 128: 14}[r])), 32 * int(rng.integers(r // 16, 20))
+        n, B = int(rng.integers(2, 80)), int(rng.integers(1, 6))
+        if L * d * r * n * B < 2e8:
+            shapes.append((L, d, r, n, B))
+    logs = np.zeros((len(shapes), 3))
+    for i, (L, d, r, n, B) in enumerate(shapes):
+        w = Workload(f"e{i}", L=L, d=d, n_max=n, B=B, r=r, C=2 + i % 3, N=B, cache_dtype="f32", len_lo=max(1, n // 2))
+        lens, ids = inputs.lengths(w), np.arange(B)
+        acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+        params = inputs.random_params(w, up_scale=0.3)
+        _, ref = oracle_batch(w, acts, lens, labels, params)
+        ref = np.asarray(ref["grads"], dtype=np.float64)
+        gates = np.arange(1, L + 1) * w.layer_block - 1
+        parts = [slice(None), gates, slice(L * w.layer_block, None)]
+        err = []
+        for flags in (0, pb.PAC_FLAG_PER_LAYER):
+            sess = make_session(w, lens=lens, flags=flags)
+            sess.cache_fill(ids, acts, lens)
+            sess.set_params(params)
+            sess.loss_grad(ids, torch.from_numpy(labels).to(sess.dev))
+            g = sess.grads.cpu().numpy().astype(np.float64)
+            err.append([np.linalg.norm(g[q] - ref[q]) / np.linalg.norm(ref[q]) for q in parts])
+        logs[i] = np.log(err[0]) - np.log(err[1])
+    ratio = np.exp(logs.mean(0))
+    print("error, Gram-matrix formulation / per-layer kernels: all %.3f, gates %.3f, head %.3f" % tuple(ratio))
+    assert (ratio <= 1.0).all(), ratio
 
 
 # What the fp32 launches do for each class: four at a time, a last group of one, two, three and four.
