@@ -138,7 +138,8 @@ int64_t pac_cache_bytes(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int64_
  * reductions; no d-wide per-token state on the Gram-matrix path).  Not the least that serves: an fp32 context whose batches
  * are not all faster in the Gram-matrix formulation reserves for both formulations (the larger of the two, unless that alone
  * passes PAC_STATIC_WORKSPACE_BYTES), and that formulation may need up to twice the per-layer kernels' bytes, or up to
- * PAC_STATIC_WORKSPACE_BYTES where those need less.
+ * PAC_STATIC_WORKSPACE_BYTES where those need less.  A call takes a smaller workspace that holds either formulation, and then
+ * that one; what the per-layer kernels need is what this returns for the same context with PAC_FLAG_PER_LAYER.
  * -1 if ctx is NULL. */
 int64_t pac_workspace_bytes(const pac_ctx *ctx);
 
@@ -168,7 +169,7 @@ pac_status pac_step_tiles(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int3
 pac_status pac_chain_plan(const pac_ctx *ctx, const int32_t *lens /*HOST*/, int32_t B, int32_t out[6] /*HOST*/);
 
 /* Which formulation an fp32 call on such a batch takes, with the workspace that pac_workspace_bytes asks for (a smaller one
- * that holds the Gram-matrix formulation gets that; as above, the same results up to rounding):
+ * that holds only one of them gets that; as above, the same results up to rounding):
  *   grads   0: a forward-only call; else a training step or a call for gradients
  *   out[0]  1: the Gram-matrix formulation, 0: the per-layer kernels (then out[1..3] are 0, and always on a bf16 cache)
  *   out[1]  token rows per tile of the projection launch           out[2]  token splits of the contractions over them

@@ -203,18 +203,20 @@ int64_t pac_cache_bytes(const pac_ctx *ctx, const int32_t *lens, int64_t count)
 }
 
 // What a call needs at least, and what serves every batch with the faster formulation
-static int64_t least_workspace(const pac_ctx *ctx) { return ctx->F.total ? ctx->F.total : ctx->W.total; }
+static int64_t least_workspace(const pac_ctx *ctx) { return ctx->F.total ? std::min(ctx->F.total, ctx->W.total) : ctx->W.total; }
 
 int64_t pac_workspace_bytes(const pac_ctx *ctx)
 {
     if (!ctx) return -1;
-    return ctx->F.total && !ctx->f32_every ? std::max(ctx->F.total, ctx->W.total) : least_workspace(ctx);
+    if (!ctx->F.total) return ctx->W.total;
+    return ctx->f32_every ? ctx->F.total : std::max(ctx->F.total, ctx->W.total);
 }
 
-// The formulation of a call on B samples of M token rows in ntiles 16-row tiles
+// The formulation of a call on B samples of M token rows in ntiles 16-row tiles: the faster one that the workspace holds
 static const WsLayout &layout_for(const pac_ctx *ctx, int B, int M, int ntiles, bool grads, int64_t workspace_bytes)
 {
-    const bool gram32 = ctx->F.total && (ctx->f32_every || workspace_bytes < ctx->W.total || f32_gram_pays(ctx->D, B, M, ntiles, grads));
+    const bool gram32 = ctx->F.total && workspace_bytes >= ctx->F.total &&
+                        (ctx->f32_every || workspace_bytes < ctx->W.total || f32_gram_pays(ctx->D, B, M, ntiles, grads));
     return gram32 ? ctx->F : ctx->W;
 }
 static const WsLayout &layout_for(const pac_ctx *ctx, const BatchMeta &meta, bool grads, int64_t workspace_bytes)

@@ -197,6 +197,25 @@ def test_fp32_formulation_per_batch():
     assert pb.lib().pac_f32_plan(None, None, 1, 1, (C.c_int32 * 4)()) == pb.PAC_ERR_NULL
 
 
+@pytest.mark.parametrize("shape", [(31, 128, 32, 26, 1), (13, 256, 128, 64, 4), (12, 768, 96, 16, 2)])
+def test_fp32_calls_take_the_workspace_of_either_formulation(shape):
+    """A workspace that holds the per-layer kernels alone, or the Gram-matrix formulation alone, is no error; a byte less is."""
+    L, d, r, n, B = shape
+    need = []
+    for flags in (0, pb.PAC_FLAG_PER_LAYER):
+        ctx = pb.pac_create(L, d, n, r, 3, B, 8, pb.PAC_F32, flags)
+        need.append(pb.pac_workspace_bytes(ctx))
+        pb.pac_destroy(ctx)
+    ctx = pb.pac_create(L, d, n, r, 3, B, 8, pb.PAC_F32)
+    dev, idp = 0x7000_0000_0000, np.zeros(1, dtype=np.int64).ctypes.data_as(C.c_void_p)
+    call = lambda ws_bytes: pb.lib().pac_adapter_loss_grad(ctx, dev, idp, 1, dev, dev, dev, ws_bytes, dev, None, None, None)
+    try:  # (sample 0 was never filled: where the workspace is accepted, the state is the next thing found wrong)
+        assert call(need[0]) == call(min(need)) == pb.PAC_ERR_STATE
+        assert call(min(need) - 1) == pb.PAC_ERR_WORKSPACE
+    finally:
+        pb.pac_destroy(ctx)
+
+
 def test_per_layer_workspace_holds_the_splits_that_run():
     """bf16 weight gradients walk 128 token rows a step: 128 rows are one split and reserve one set of partial sums."""
     def ws(n):

@@ -175,6 +175,31 @@ def test_fp32_formulation_by_batch(w, whole, short):
         sess.set_params(params)
 
 
+@pytest.mark.parametrize("w", [Workload("b4", L=31, d=128, n_max=26, B=1, r=32, C=3, N=1, cache_dtype="f32"),
+                               Workload("b5", L=13, d=256, n_max=64, B=4, r=128, C=3, N=4, cache_dtype="f32", len_lo=3)],
+                         ids=lambda w: w.name)
+def test_fp32_on_the_per_layer_kernels_workspace(w):
+    """A workspace too small for the Gram-matrix formulation gets the per-layer kernels, and their bits."""
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, lab = inputs.batch_acts(w, ids), torch.from_numpy(inputs.labels(w)[ids]).cuda()
+    params = inputs.random_params(w, up_scale=0.3)
+    per_layer, sess = make_session(w, lens=lens, flags=pb.PAC_FLAG_PER_LAYER), make_session(w, lens=lens)
+    assert pb.pac_f32_plan(sess.ctx, lens, w.B)["gram"] and per_layer.ws_bytes < sess.ws_bytes
+    sess.ws_bytes = per_layer.ws_bytes
+    sess.ws = torch.empty(sess.ws_bytes, dtype=torch.uint8, device=sess.dev)
+    got = []
+    for s in (per_layer, sess):
+        s.cache_fill(ids, acts, lens)
+        s.set_params(params)
+        s.step(ids, lab)
+        step = [t.clone() for t in (s.loss, s.grads, s.params)]
+        s.set_params(params)
+        s.loss_grad(ids, lab)
+        got.append(step + [s.loss.clone(), s.logits.clone(), s.grads.clone()])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_fp32_gram_within_the_static_workspace():
     """The per-layer kernels would need more than the static entry has, so every batch takes the Gram-matrix formulation."""
     from paper_2408_10746_amd.runtime import _stream_handle
