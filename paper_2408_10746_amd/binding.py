@@ -32,7 +32,8 @@ EXPORTS = [
     "pac_probe_hbm_read", "pac_probe_mfma_bf16", "pac_probe_mfma_flops", "pac_probe_hbm_update",
     "pac_profile_begin", "pac_profile_end", "pac_profile_class_name",
     "pac_plan_hybrid", "pac_plan_stage_time",
-    "pac_quant_blockwise", "pac_dequant_blockwise", "pac_dequant_linear", "pac_dequant_linear_to_cache",
+    "pac_quant_blockwise", "pac_dequant_blockwise", "pac_dequant_linear", "pac_dequant_linear_tiles",
+    "pac_dequant_linear_to_cache",
     "pac_tier_window_bytes", "pac_tier_fill", "pac_tier_stage", "pac_adapter_loss_grad_staged", "pac_adapter_step_staged",
     "pac_ladder_param_count", "pac_ladder_workspace_bytes", "pac_ladder_loss_grad", "pac_ladder_step",
 ]
@@ -144,6 +145,8 @@ def lib():
         L.pac_dequant_blockwise.argtypes = [vp, vp, i64, i32, i32, vp, vp]
         L.pac_dequant_linear.restype = C.c_int
         L.pac_dequant_linear.argtypes = [vp, i32, i32, vp, vp, i32, i32, i32, vp, vp]
+        L.pac_dequant_linear_tiles.restype = C.c_int
+        L.pac_dequant_linear_tiles.argtypes = [i32, i32, i32, i32, i32, C.POINTER(i32)]
         L.pac_dequant_linear_to_cache.restype = C.c_int
         L.pac_dequant_linear_to_cache.argtypes = [vp, vp, i64, vp, i32, vp, i32, vp, i32, vp, vp, i32, i32, vp]
         L.pac_plan_hybrid.restype = C.c_int
@@ -390,6 +393,13 @@ def pac_dequant_blockwise(codes_ptr, consts_ptr, n: int, block: int, bits: int, 
 
 def pac_dequant_linear(x_ptr, M: int, K: int, codes_ptr, consts_ptr, N: int, block: int, bits: int, y_ptr, stream=0) -> None:
     _check(lib().pac_dequant_linear(x_ptr, M, K, codes_ptr, consts_ptr, N, block, bits, y_ptr, stream), "pac_dequant_linear")
+
+
+def pac_dequant_linear_tiles(M: int, K: int, N: int, block: int, bits: int) -> dict:
+    """Kernel and output tiles of that layer (host logic)."""
+    out = (C.c_int32 * 3)()
+    _check(lib().pac_dequant_linear_tiles(M, K, N, block, bits, out), "pac_dequant_linear_tiles")
+    return dict(zip(("short", "rows", "cols"), (int(x) for x in out)))
 
 
 def pac_dequant_linear_to_cache(ctx, cache_ptr, cache_bytes, sample_ids, lens, layer: int, x_ptr, K: int, codes_ptr,

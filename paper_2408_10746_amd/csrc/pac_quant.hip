@@ -483,8 +483,9 @@ static DqForm dq_short_tiles(int64_t tiles128, int M, int N)
     return 100 * ((tiles256 + 255) / 256) <= rounds128 ? DQ_SHORT_256 : DQ_SHORT_128;
 }
 
-static DqForm dq_form(int64_t tiles128, int M, int K, int N, int block, int bits)
+static DqForm dq_form(int M, int K, int N, int block, int bits)
 {
+    const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
     if (block == 64) {
         if (tiles128 > 192 && M > 64) return dq_short_tiles(tiles128, M, N);
         if (K >= 1536 && (bits == 8 || M > 128) && (int64_t)((M + 127) / 128) * ((N + 63) / 64) >= 8) return DQ_SHORT_64;
@@ -536,8 +537,7 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     a.x = static_cast<const bf16_t *>(x); a.M = M; a.K = K; a.N = N; a.block = block; a.codes = codes; a.consts = consts;
     a.y = y; a.cache = cache; a.cache_f32 = cache_f32; a.n_max = n_max; a.layer = layer;
     if (meta) a.meta = *meta;
-    const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
-    const DqForm form = dq_form(tiles128, M, K, N, block, bits);
+    const DqForm form = dq_form(M, K, N, block, bits);
     if (form == DQ_SHORT_256) dq_launch_short<2, 4, 1>(a, bits, st);
     else if (form == DQ_SHORT_128) dq_launch_short<2, 2, 2>(a, bits, st);
     else if (form == DQ_SHORT_64) dq_launch_short<1, 2, 3>(a, bits, st);
@@ -546,13 +546,20 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     return hipGetLastError();
 }
 
+static int check_dq_linear_shape(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits)
+{
+    if (bits != 8 && bits != 4) return PAC_ERR_SHAPE;
+    if (M < 1 || N < 1 || K < 32 || K % 32) return PAC_ERR_SHAPE;
+    if (block < 32 || block % 32 || K % block) return PAC_ERR_RANGE;
+    return PAC_OK;
+}
+
 int check_dq_linear_args(const void *x, int32_t M, int32_t K, const int8_t *codes, const float *consts, int32_t N,
                                 int32_t block, int32_t bits)
 {
     if (!x || !codes || !consts) return PAC_ERR_NULL;
-    if (bits != 8 && bits != 4) return PAC_ERR_SHAPE;
-    if (M < 1 || N < 1 || K < 32 || K % 32) return PAC_ERR_SHAPE;
-    if (block < 32 || block % 32 || K % block) return PAC_ERR_RANGE;
+    const int s = check_dq_linear_shape(M, K, N, block, bits);
+    if (s != PAC_OK) return s;
     if (!q_aligned(x, 16) || !q_aligned(codes, 8) || !q_aligned(consts, 4)) return PAC_ERR_ALIGN;
     return PAC_OK;
 }
@@ -617,6 +624,18 @@ pac_status pac_dequant_linear(const void *x, int32_t M, int32_t K, const int8_t 
     (void)hipGetLastError();
     return launch_dq_linear(x, M, K, codes, consts, N, block, bits, y, nullptr, 0, 0, 0, nullptr,
                             static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PAC_OK : PAC_ERR_DEVICE;
+}
+
+pac_status pac_dequant_linear_tiles(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits, int32_t out[3])
+{
+    if (!out) return PAC_ERR_NULL;
+    const int s = check_dq_linear_shape(M, K, N, block, bits);
+    if (s != PAC_OK) return (pac_status)s;
+    const DqForm form = dq_form(M, K, N, block, bits);
+    out[0] = form == DQ_SHORT_64 || form == DQ_SHORT_128 || form == DQ_SHORT_256;
+    out[1] = form == DQ_STEP_64 ? 64 : form == DQ_SHORT_256 ? 256 : 128;
+    out[2] = form == DQ_STEP_64 || form == DQ_SHORT_64 ? 64 : 128;
+    return PAC_OK;
 }
 
 } // extern "C"

@@ -59,16 +59,16 @@ def test_linear_layer_against_oracle(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# outputs of 272 tiles of 128 x 128, ragged at both edges: blocks of one and three K steps of 32 (on the small tiles) and of
-# one of 64 (on the large ones); the last has 256 and takes the small tiles, blocks of two K steps of 64
+# outputs of 272 and 289 tiles of 128 x 128, ragged at both edges: blocks of 32 and 64 (both on tiles of 256 x 128), blocks of
+# three K steps of 32 (on the small tiles); the last has 256 and takes the small tiles, blocks of two K steps of 64
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2049, 64, 2001, 32), (2100, 192, 2033, 96), (2047, 192, 2100, 64), (2048, 256, 2048, 128)])
 def test_linear_layer_on_wide_and_narrow_tiles(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# where the line lies elsewhere: K steps of 32 take the large tiles from 321 on (342 and 361 here, then 304), up to 64 rows
-# never do
+# where the line lies elsewhere: blocks that are an odd multiple of 32 above it take the large tiles from 321 on (361 here), up
+# to 64 rows never do; blocks of 32 on 256 x 128 (342 and 304 tiles of 128 x 128)
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2401, 64, 2200, 32), (2310, 192, 2311, 96), (2400, 96, 2001, 32), (40, 128, 33000, 64)])
 def test_linear_layer_tiles_by_block_and_rows(M, K, N, block, bits):
@@ -82,6 +82,14 @@ def test_linear_layer_tiles_by_block_and_rows(M, K, N, block, bits):
 @pytest.mark.parametrize("M,K,N,block", [(2100, 160, 2100, 32), (2050, 128, 2111, 32), (1700, 192, 1799, 64), (129, 64, 24650, 64),
                                          (70, 96, 33000, 32), (300, 1536, 200, 64), (131, 1568, 70, 32), (5, 1184, 3, 32), (300, 512, 129, 32)])
 def test_linear_layer_short_blocks(M, K, N, block, bits):
+    check_linear_layer(M, K, N, block, bits)
+
+
+# blocks longer than 64 with K steps of 64 on 128 x 128 tiles, ragged at both edges: one and two steps a block more than two
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block", [(2100, 384, 2111, 128), (2100, 512, 2111, 256)])
+def test_linear_layer_long_blocks_on_wide_tiles(M, K, N, block, bits):
+    assert pb.pac_dequant_linear_tiles(M, K, N, block, bits) == dict(short=0, rows=128, cols=128)
     check_linear_layer(M, K, N, block, bits)
 
 
