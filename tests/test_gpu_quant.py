@@ -93,6 +93,74 @@ def test_linear_layer_long_blocks_on_wide_tiles(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
+def stored_layer(rng, N, K, block, bits):
+    W = torch.from_numpy(weights(rng, N, K)).cuda()
+    codes = torch.zeros((N, K * bits // 8), dtype=torch.int8, device="cuda")
+    consts = torch.zeros((N, K // block), dtype=torch.float32, device="cuda")
+    pb.pac_quant_blockwise(W.data_ptr(), N * K, block, bits, codes.data_ptr(), consts.data_ptr())
+    return codes, consts
+
+
+def linear(x, codes, consts, block, bits):
+    M, K, N = *x.shape, codes.shape[0]
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    pb.pac_dequant_linear(x.data_ptr(), M, K, codes.data_ptr(), consts.data_ptr(), N, block, bits, y.data_ptr())
+    return y
+
+
+# tiles of 128 x 64, 128 x 128 and 256 x 128 of the kernel for short blocks, 128 x 128 of the other one; ragged samples whose
+# rows lie across the tiles' edges
+FORMS = [(5, 37, 1536, 224, 64, (1, 128, 64)), (5, 37, 1184, 224, 32, (1, 128, 64)), (20, 85, 192, 1824, 64, (1, 128, 128)),
+         (20, 103, 96, 3712, 32, (1, 128, 128)), (20, 103, 192, 2144, 64, (1, 256, 128)), (20, 103, 96, 2144, 32, (1, 256, 128)),
+         (20, 103, 256, 2144, 128, (0, 128, 128))]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,n_max,K,N,block,form", FORMS)
+def test_linear_layer_to_cache_has_the_dense_call_s_bits(B, n_max, K, N, block, form, bits):
+    """Every epilogue that writes the cache, in both cache dtypes, against the dense output (rounded to nearest even)."""
+    from paper_2408_10746_amd.runtime import Session
+    assert tuple(pb.pac_dequant_linear_tiles(B * n_max, K, N, block, bits).values()) == form
+    rng = np.random.default_rng(B + K + bits)
+    codes, consts = stored_layer(rng, N, K, block, bits)
+    x = torch.from_numpy(rng.standard_normal((B * n_max, K)).astype(np.float32)).to(torch.bfloat16).cuda()
+    y = linear(x, codes, consts, block, bits).view(B, n_max, N)
+    assert torch.isfinite(y).all()
+    ids, lens = rng.permutation(B), rng.integers(1, n_max + 1, size=B).astype(np.int32)
+    lens[:2] = 1, n_max
+    for dtype in ("bf16", "f32"):
+        w = Workload("qf", L=2, d=N, n_max=n_max, B=B, r=32, C=2, N=B, cache_dtype=dtype)
+        by_id = np.empty_like(lens)
+        by_id[ids] = lens
+        sess = Session(w, lens=by_id)
+        sess.cache.fill_(0x55)
+        pb.pac_dequant_linear_to_cache(sess.ctx, sess.cache.data_ptr(), sess.cache_bytes, ids, lens, 1, x.data_ptr(), K,
+                                       codes.data_ptr(), consts.data_ptr(), block, bits)
+        torch.cuda.synchronize()
+        for b, sid in enumerate(ids):
+            got, want = sess.cache_block(int(sid)), y[b, :lens[b]]
+            want = want.cpu().numpy() if dtype == "f32" else want.to(torch.bfloat16).view(torch.int16).cpu().numpy().view(np.uint16)
+            assert np.array_equal(got[1], want)
+            assert (np.ascontiguousarray(got[0]).view(np.uint8) == 0x55).all()  # the other layer's rows stay as they were
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block,form", [(300, 1536, 200, 64, (1, 128, 64)), (300, 512, 129, 32, (1, 128, 64)),
+                                              (1700, 192, 1824, 64, (1, 128, 128)), (70, 96, 33000, 32, (1, 128, 128)),
+                                              (2060, 192, 2144, 64, (1, 256, 128)), (2060, 96, 2144, 32, (1, 256, 128))])
+def test_linear_layer_forms_give_the_same_bits(M, K, N, block, form, bits):
+    """Rows and columns of a large call alone, where the kernel for short blocks is not taken."""
+    assert tuple(pb.pac_dequant_linear_tiles(M, K, N, block, bits).values()) == form
+    assert tuple(pb.pac_dequant_linear_tiles(60, K, 90, block, bits).values()) == (0, 64, 64)
+    rng = np.random.default_rng(M + K + bits)
+    codes, consts = stored_layer(rng, N, K, block, bits)
+    x = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).to(torch.bfloat16).cuda()
+    y = linear(x, codes, consts, block, bits)
+    for m, n in ((0, 0), (M - 60, N - 90), (M // 3, N // 2)):
+        part = linear(x[m:m + 60].clone(), codes[n:n + 90].clone(), consts[n:n + 90].clone(), block, bits)
+        assert torch.equal(part, y[m:m + 60, n:n + 90])
+
+
 def check_linear_layer(M, K, N, block, bits):
     rng = np.random.default_rng(M + K + bits)
     W = weights(rng, N, K)
