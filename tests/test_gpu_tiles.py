@@ -145,6 +145,32 @@ def test_fp32_gram(w):
     assert torch.equal(sess.loss, loss) and torch.equal(sess.grads, grads)
 
 
+# What the cases above leave out of the fp32 Gram-matrix formulation: 32-row projection tiles at each width that has them
+# (i1-i3: last tiles of 18 to 32 rows), token splits and their sum at each width (i4-i8: ragged last splits), the most layers
+# that fit (i9-i12: 60, 16, 14 and 8).
+@pytest.mark.parametrize("w,plan", [
+    (Workload("i1", L=16, d=64, n_max=96, B=11, r=32, C=3, N=11, cache_dtype="f32", len_lo=82), (1, 32, 1, 1)),
+    (Workload("i2", L=16, d=192, n_max=96, B=11, r=96, C=3, N=11, cache_dtype="f32", len_lo=82), (1, 32, 1, 1)),
+    (Workload("i3", L=14, d=512, n_max=96, B=13, r=128, C=3, N=13, cache_dtype="f32", len_lo=82), (1, 32, 1, 2)),
+    (Workload("i4", L=2, d=128, n_max=400, B=8, r=64, C=3, N=8, cache_dtype="f32", len_lo=300), (1, 16, 8, 1)),
+    (Workload("i5", L=2, d=192, n_max=400, B=8, r=96, C=3, N=8, cache_dtype="f32", len_lo=300), (1, 16, 8, 1)),
+    (Workload("i6", L=2, d=256, n_max=400, B=8, r=128, C=3, N=8, cache_dtype="f32", len_lo=300), (1, 16, 8, 2)),
+    (Workload("i7", L=2, d=384, n_max=300, B=4, r=192, C=3, N=4, cache_dtype="f32", len_lo=201), (1, 16, 7, 2)),
+    (Workload("i8", L=2, d=512, n_max=300, B=4, r=256, C=3, N=4, cache_dtype="f32", len_lo=201), (1, 16, 3, 2)),
+    (Workload("i9", L=60, d=64, n_max=20, B=2, r=32, C=3, N=2, cache_dtype="f32", len_lo=3), (1, 16, 1, 1)),
+    (Workload("i10", L=16, d=192, n_max=9, B=1, r=96, C=3, N=1, cache_dtype="f32"), (1, 16, 1, 1)),
+    (Workload("i11", L=14, d=256, n_max=9, B=1, r=128, C=3, N=1, cache_dtype="f32"), (1, 16, 1, 2)),
+    (Workload("i12", L=8, d=768, n_max=64, B=4, r=192, C=3, N=4, cache_dtype="f32", len_lo=30), (1, 16, 1, 2)),
+], ids=lambda v: getattr(v, "name", None))
+def test_fp32_gram_widths_and_depths(w, plan):
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+    sess = make_session(w, lens=lens)
+    assert tuple(pb.pac_f32_plan(sess.ctx, lens, w.B).values()) == plan
+    sess.cache_fill(ids, acts, lens)
+    check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
+
+
 # One context whose calls take different formulations: steps on the whole batch the Gram-matrix formulation, all others the
 # per-layer kernels (b1), or steps the one and forward-only calls the other (b2).
 @pytest.mark.parametrize("w,whole,short", [
