@@ -171,6 +171,24 @@ def test_fp32_gram_widths_and_depths(w, plan):
     check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
 
 
+# The per-layer 16-row tiles at the longest K, by flag where the Gram-matrix formulation would be taken (q1: two wavefronts of
+# eight with a unit more than the others; q2) and at a width without it (q3).
+@pytest.mark.parametrize("w,flags", [
+    (Workload("q1", L=2, d=288, n_max=9, B=3, r=64, C=2, N=3, cache_dtype="f32", len_lo=1), pb.PAC_FLAG_PER_LAYER),
+    (Workload("q2", L=3, d=768, n_max=33, B=3, r=96, C=3, N=3, cache_dtype="f32", len_lo=9), pb.PAC_FLAG_PER_LAYER),
+    (Workload("q3", L=2, d=768, n_max=40, B=3, r=160, C=3, N=3, cache_dtype="f32", len_lo=9), 0),
+], ids=lambda v: getattr(v, "name", None))
+def test_fp32_per_layer_tiles_at_long_k(w, flags):
+    lens, ids = inputs.lengths(w), np.arange(w.B)
+    acts, labels = inputs.batch_acts(w, ids), inputs.labels(w)[ids]
+    sess = make_session(w, lens=lens, flags=flags)
+    assert not pb.pac_f32_plan(sess.ctx, lens, w.B)["gram"] and pb.pac_step_tiles(sess.ctx, lens, w.B)["proj"] == 16
+    sess.cache_fill(ids, acts, lens)
+    pb.pac_profile_begin(sess.ctx)
+    check_against_oracle(w, sess, ids, acts, lens, labels, inputs.random_params(w, up_scale=0.3), TOL["f32"], what=w.name)
+    assert not any(k.startswith("g_") and n for k, (_, n) in pb.pac_profile_end(sess.ctx).items())
+
+
 # One context whose calls take different formulations: steps on the whole batch the Gram-matrix formulation, all others the
 # per-layer kernels (b1), or steps the one and forward-only calls the other (b2).
 @pytest.mark.parametrize("w,whole,short", [
