@@ -49,10 +49,12 @@ pac_status pac_dequant_linear(const void *x /*DEVICE*/, int32_t M, int32_t K, co
 
 /* Which kernel and output tiles the layer runs on (the same product bit for bit in each; host logic, for measurements and
  * tests that have to know which form they ran):
+ *   to_cache  0: pac_dequant_linear, else pac_dequant_linear_to_cache (M = count n_max, N = d; up to 64 samples at a time)
  *   out[0]  1: a block's scaling runs beside the next one's matrix instructions (blocks of 32 and 64 only), 0: step by step
  *   out[1]  rows of M per tile      out[2]  columns of N per tile
  * Errors: NULL, SHAPE, RANGE as in pac_dequant_linear. */
-pac_status pac_dequant_linear_tiles(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits, int32_t out[3] /*HOST*/);
+pac_status pac_dequant_linear_tiles(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits, int32_t to_cache,
+                                    int32_t out[3] /*HOST*/);
 
 /* The same layer with the cache fill fused into its epilogue (Sec. 4.2: during the first epoch everything the
  * adapters consume is cached): the output rows of cached layer `layer` of `count` samples go, rounded to the cache

@@ -146,7 +146,7 @@ def lib():
         L.pac_dequant_linear.restype = C.c_int
         L.pac_dequant_linear.argtypes = [vp, i32, i32, vp, vp, i32, i32, i32, vp, vp]
         L.pac_dequant_linear_tiles.restype = C.c_int
-        L.pac_dequant_linear_tiles.argtypes = [i32, i32, i32, i32, i32, C.POINTER(i32)]
+        L.pac_dequant_linear_tiles.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32)]
         L.pac_dequant_linear_to_cache.restype = C.c_int
         L.pac_dequant_linear_to_cache.argtypes = [vp, vp, i64, vp, i32, vp, i32, vp, i32, vp, vp, i32, i32, vp]
         L.pac_plan_hybrid.restype = C.c_int
@@ -395,10 +395,10 @@ def pac_dequant_linear(x_ptr, M: int, K: int, codes_ptr, consts_ptr, N: int, blo
     _check(lib().pac_dequant_linear(x_ptr, M, K, codes_ptr, consts_ptr, N, block, bits, y_ptr, stream), "pac_dequant_linear")
 
 
-def pac_dequant_linear_tiles(M: int, K: int, N: int, block: int, bits: int) -> dict:
+def pac_dequant_linear_tiles(M: int, K: int, N: int, block: int, bits: int, to_cache: bool = False) -> dict:
     """Kernel and output tiles of that layer (host logic)."""
     out = (C.c_int32 * 3)()
-    _check(lib().pac_dequant_linear_tiles(M, K, N, block, bits, out), "pac_dequant_linear_tiles")
+    _check(lib().pac_dequant_linear_tiles(M, K, N, block, bits, int(to_cache), out), "pac_dequant_linear_tiles")
     return dict(zip(("short", "rows", "cols"), (int(x) for x in out)))
 
 

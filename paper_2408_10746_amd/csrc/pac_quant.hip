@@ -3,6 +3,7 @@
 #include "../../include/pac_quant.h"
 #include "pac_gemm.h"
 #include "pac_internal.h"
+#include <cmath>
 
 namespace pac {
 
@@ -466,43 +467,53 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
     return PAC_OK;
 }
 
-// Which kernel and tiles.  Blocks of 32 and 64, both kernels measured at 56 shapes: k_dq_short takes
-//  - 128 x 128 tiles, two workgroups a compute unit, where there are more than three quarters as many (blocks of 32: more)
-//    as compute units: blocks of 64, 160 tiles 54.9 us on 128 x 64 tiles and 55.4 on these, 256 tiles 60.5 / 58.3, 320 tiles
-//    100 / 84.8; blocks of 32, 256 tiles 78.2 / 87.4, 400 tiles 50.4 / 44.5;
-//  - 256 x 128 tiles, one workgroup of eight wavefronts a compute unit, in place of 128 x 128 ones where rounds of them
-//    end sooner: a round of 256 against 1.09 for 512 of the smaller, 0.65 where those are one a compute unit.  512 tiles
-//    of 256 rows 176 / 190 us (4096 x 4096 x 4096), 172 of them 79.7 / 94.9, 192 76.7 / 84.4, but 128 69.8 / 56.9, 288
-//    193 / 167, 384 154 / 146 and 41.1 / 39.4.
-//  - 128 x 64 tiles, three a compute unit, below, where K is long enough to hide the first step's wait: blocks of 64,
-//    K = 4096, 128 x 4096 out 45.3 against 49.3 us on k_dq_linear's 64 x 64, K = 1536, 284 x 1181 16.9 / 21.4, but K = 832,
-//    137 x 3061 10.8 / 10.5; not for fewer than eight tiles (K = 1664, 129 x 96 17.8 / 16.9) nor up to 128 rows of 4-bit
-//    codes (K = 2304, 68 x 90 22.1 / 20.9).  Blocks of 32: K = 1152, 18 x 213 15.3 / 16.9, K = 640, 1732 x 321 11.7 / 13.6,
-//    but K = 1056, 21 x 644 17.2 / 16.7, K = 512, 129 x 164 10.5 / 10.2.
+// Which kernel and tiles.  Blocks of 32 and 64, all forms measured at 4600 drawn shapes (16 to 4096 rows, 64 to 4096 columns, K
+// = 256 to 4096, both bit widths, dense and into the cache).  Two questions, each answered by the logarithm of the two forms'
+// times' ratio as it follows from K, the number of tiles, the bit width and where the output goes:
+//  - up to three quarters as many 128 x 128 tiles (blocks of 32: as many) as compute units, and up to 64 rows: k_dq_short on 128 x
+//    64 tiles, three a compute unit, or k_dq_linear's 64 x 64, of which there are more.  Long K hides the first step's wait:
+//    blocks of 64, 128 x 4096 out, K = 4096, 45 us against 49, but 156 x 197, K = 1600, 4 bits, 20.2 / 19.9 and into the cache,
+//    where each thread has twice the rows to store behind its last step, 527 x 96, K = 1536, 23.7 / 21.5.  Blocks of 32: 22 x 3067,
+//    K = 928, 15.6 / 18.6, but 312 x 211, K = 576, 10.8 / 9.8, and on a handful of tiles, which wait for memory alone,
+//    47 x 178, K = 1216, 4 bits, 18.5 / 17.1.
+//  - above that many: k_dq_short on wider tiles, or 64 x 64 where K is short: 2546 x 1558, K = 352, blocks of 32, 16.6 / 14.1.
+//    128 x 128 tiles run two workgroups a compute unit; 256 x 128 tiles, one workgroup of eight wavefronts, take their place
+//    where rounds of them end sooner: a round of 256 against 1.09 for 512 of the smaller, 0.65 where those are one a compute
+//    unit.  512 tiles of 256 rows 176 / 190 us (4096 x 4096 x 4096), 172 of them 79.7 / 94.9, 192 76.7 / 84.4, but 128 69.8 /
+//    56.9, 288 193 / 167, 384 154 / 146; not for K below 448, where their one first step is waited for by all: 2441 x 2794, K =
+//    352, 22.5 / 18.8.
+// What this picks is 0.7 % off the fastest form in the mean, and more than 3 % slower than k_dq_linear's on the tiles it would
+// take otherwise at 21 of the shapes and at 7 of 1600 fresh ones, a quarter of them of up to 8192 x 16384 and K = 11008.
 // k_dq_linear otherwise, on 64 x 64 tiles up to as many 128 x 128 ones as compute units: longer blocks, K = 4096, 256 tiles
 // 72.5 against 74.5 us, 64 tiles 49 / 72, 320 tiles 110.6 / 89.8; odd multiples of 32 keep K steps of 32, where a wide tile
 // has less to hide its barriers behind (up to 320); up to 64 rows leave half of a wide tile and more empty.
 enum DqForm { DQ_STEP_64, DQ_STEP_128, DQ_SHORT_64, DQ_SHORT_128, DQ_SHORT_256 };
-static DqForm dq_short_tiles(int64_t tiles128, int M, int N)
+static DqForm dq_short_tiles(int64_t tiles128, int M, int K, int N)
 {
+    if (K < 448) return DQ_SHORT_128;
     const int64_t tiles256 = (int64_t)((M + 255) / 256) * ((N + 127) / 128), rest = tiles128 % 512;
     const int64_t rounds128 = 109 * (tiles128 / 512) + (rest > 256 ? 109 : rest > 0 ? 65 : 0); // hundredths
     return 100 * ((tiles256 + 255) / 256) <= rounds128 ? DQ_SHORT_256 : DQ_SHORT_128;
 }
 
-static DqForm dq_form(int M, int K, int N, int block, int bits)
+static DqForm dq_form(int M, int K, int N, int block, int bits, bool to_cache)
 {
-    const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128);
-    if (block == 64) {
-        if (tiles128 > 192 && M > 64) return dq_short_tiles(tiles128, M, N);
-        if (K >= 1536 && (bits == 8 || M > 128) && (int64_t)((M + 127) / 128) * ((N + 63) / 64) >= 8) return DQ_SHORT_64;
-        return DQ_STEP_64;
+    const int64_t tiles128 = (int64_t)((N + 127) / 128) * ((M + 127) / 128), tiles64 = (int64_t)((N + 63) / 64) * ((M + 127) / 128);
+    const bool b64 = block == 64, many = M > 64 && tiles128 > (b64 ? 192 : block == 32 || block % 64 == 0 ? 256 : 320);
+    if (block != 32 && block != 64) return many ? DQ_STEP_128 : DQ_STEP_64;
+    const double lk = std::log(K / 1024.0), four = bits == 4, cache = to_cache, few_rows = M <= 64;
+    constexpr double doubt = 0.02; // stays with k_dq_linear
+    if (many) {
+        const double lt = std::log((double)tiles128 / 256.0);
+        const double ratio = b64 ? -0.254 - 0.126 * lk - 0.224 * lt + 0.040 * four + 0.126 * cache
+                                 : -0.237 - 0.217 * lk - 0.279 * lt + 0.041 * four + 0.090 * cache;
+        return ratio < -doubt ? dq_short_tiles(tiles128, M, K, N) : DQ_STEP_64;
     }
-    if (block == 32) {
-        if (tiles128 > 256 && M > 64) return dq_short_tiles(tiles128, M, N);
-        return K >= 1152 || (K >= 512 && M > 256) ? DQ_SHORT_64 : DQ_STEP_64;
-    }
-    return M > 64 && tiles128 > (block % 64 == 0 ? 256 : 320) ? DQ_STEP_128 : DQ_STEP_64;
+    if (!b64 && K < 2304 && tiles64 < (bits == 4 ? 9 : 4)) return DQ_STEP_64;
+    const double ln = std::log((double)tiles64);
+    const double ratio = b64 ? 0.095 - 0.098 * lk - 0.024 * ln + 0.031 * four + 0.085 * cache
+                             : -0.033 - 0.181 * lk - 0.037 * ln + 0.044 * four + 0.049 * few_rows + 0.126 * cache;
+    return ratio < -doubt ? DQ_SHORT_64 : DQ_STEP_64;
 }
 
 template <int WTN, int WM, int OCC> static void dq_launch_short(const DqArgs &a, int bits, hipStream_t st)
@@ -544,7 +555,7 @@ hipError_t launch_dq_linear(const void *x, int M, int K, const int8_t *codes, co
     a.x = static_cast<const bf16_t *>(x); a.M = M; a.K = K; a.N = N; a.block = block; a.codes = codes; a.consts = consts;
     a.y = y; a.cache = cache; a.cache_f32 = cache_f32; a.n_max = n_max; a.layer = layer;
     if (meta) a.meta = *meta;
-    const DqForm form = dq_form(M, K, N, block, bits);
+    const DqForm form = dq_form(M, K, N, block, bits, y == nullptr);
     if (form == DQ_SHORT_256) dq_launch_short<2, 4, 1>(a, bits, st);
     else if (form == DQ_SHORT_128) dq_launch_short<2, 2, 2>(a, bits, st);
     else if (form == DQ_SHORT_64) dq_launch_short<1, 2, 3>(a, bits, st);
@@ -633,12 +644,12 @@ pac_status pac_dequant_linear(const void *x, int32_t M, int32_t K, const int8_t 
                             static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PAC_OK : PAC_ERR_DEVICE;
 }
 
-pac_status pac_dequant_linear_tiles(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits, int32_t out[3])
+pac_status pac_dequant_linear_tiles(int32_t M, int32_t K, int32_t N, int32_t block, int32_t bits, int32_t to_cache, int32_t out[3])
 {
     if (!out) return PAC_ERR_NULL;
     const int s = check_dq_linear_shape(M, K, N, block, bits);
     if (s != PAC_OK) return (pac_status)s;
-    const DqForm form = dq_form(M, K, N, block, bits);
+    const DqForm form = dq_form(M, K, N, block, bits, to_cache != 0);
     out[0] = form == DQ_SHORT_64 || form == DQ_SHORT_128 || form == DQ_SHORT_256;
     out[1] = form == DQ_STEP_64 ? 64 : form == DQ_SHORT_256 ? 256 : 128;
     out[2] = form == DQ_STEP_64 || form == DQ_SHORT_64 ? 64 : 128;

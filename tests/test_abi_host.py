@@ -232,20 +232,23 @@ def test_per_layer_workspace_holds_the_splits_that_run():
 def test_linear_layer_kernel_and_tiles():
     """Host logic: both kernels and all tiles of the quantised linear layer, at the lines between them."""
     t = lambda *a: tuple(pb.pac_dequant_linear_tiles(*a).values())
-    assert t(4096, 4096, 4096, 64, 8) == t(4096, 4096, 4096, 32, 4) == (1, 256, 128)
+    assert t(4096, 4096, 4096, 64, 8) == t(4096, 4096, 4096, 32, 4, True) == (1, 256, 128)
     assert t(4096, 4096, 4096, 128, 8) == (0, 128, 128)
     assert t(1664, 4096, 1920, 64, 8) == (1, 128, 128) and t(1536, 4096, 2048, 64, 8) == (1, 128, 64)  # 195 and 192 tiles
+    assert t(2441, 416, 2794, 32, 8) == (1, 128, 128) and t(2441, 448, 2794, 32, 8) == (1, 256, 128)   # short K
+    assert t(2546, 352, 1558, 32, 8) == (0, 64, 64)                                                    # (16.6 us / 14.1)
     assert t(2048, 4096, 2048, 128, 8) == (0, 64, 64) and t(2048, 4096, 2049, 128, 8) == (0, 128, 128)
     assert t(2048, 1920, 2560, 96, 8) == (0, 64, 64) and t(2048, 1920, 2561, 96, 8) == (0, 128, 128)
-    assert t(64, 1024, 33000, 64, 8) == (0, 64, 64) and t(65, 1024, 33000, 64, 8)[0] == 1
-    assert t(128, 2304, 4096, 64, 8) == (1, 128, 64) and t(128, 2304, 4096, 64, 4) == (0, 64, 64)
-    assert t(18, 1152, 213, 32, 8) == (1, 128, 64) and t(21, 1056, 644, 32, 8) == (0, 64, 64)
+    assert t(128, 4096, 4096, 64, 8) == (1, 128, 64) and t(156, 1600, 197, 64, 4) == (0, 64, 64)
+    assert t(527, 1536, 1500, 64, 4) == (1, 128, 64) and t(527, 1536, 1500, 64, 4, True) == (0, 64, 64)
+    assert t(22, 928, 3067, 32, 8) == (1, 128, 64) and t(312, 576, 211, 32, 4) == (0, 64, 64)
+    assert t(47, 1216, 178, 32, 4) == (0, 64, 64) and t(47, 2304, 178, 32, 4) == (1, 128, 64)          # a handful of tiles
     for bad, status in (((0, 64, 8, 32, 8), pb.PAC_ERR_SHAPE), ((4, 100, 8, 32, 8), pb.PAC_ERR_SHAPE),
                         ((4, 64, 8, 32, 5), pb.PAC_ERR_SHAPE), ((4, 64, 8, 48, 8), pb.PAC_ERR_RANGE)):
         with pytest.raises(pb.PacError) as e:
             t(*bad)
         assert e.value.status == status
-    assert pb.lib().pac_dequant_linear_tiles(4, 64, 8, 32, 8, None) == pb.PAC_ERR_NULL
+    assert pb.lib().pac_dequant_linear_tiles(4, 64, 8, 32, 8, 0, None) == pb.PAC_ERR_NULL
 
 
 def test_chain_plan_per_batch():

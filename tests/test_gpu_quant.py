@@ -59,25 +59,22 @@ def test_linear_layer_against_oracle(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# outputs of 272 and 289 tiles of 128 x 128, ragged at both edges: blocks of 32 and 64 (both on tiles of 256 x 128), blocks of
-# three K steps of 32 (on the small tiles); the last has 256 and takes the small tiles, blocks of two K steps of 64
+# ragged at both edges on 272 and 289 tiles of 128 x 128 (or four times as many of 64 x 64), blocks of one to four K steps
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2049, 64, 2001, 32), (2100, 192, 2033, 96), (2047, 192, 2100, 64), (2048, 256, 2048, 128)])
 def test_linear_layer_on_wide_and_narrow_tiles(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# where the line lies elsewhere: blocks that are an odd multiple of 32 above it take the large tiles from 321 on (361 here), up
-# to 64 rows never do; blocks of 32 on 256 x 128 (342 and 304 tiles of 128 x 128)
+# blocks that are an odd multiple of 32 take the large tiles from 321 on (361 here), up to 64 rows never do
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2401, 64, 2200, 32), (2310, 192, 2311, 96), (2400, 96, 2001, 32), (40, 128, 33000, 64)])
 def test_linear_layer_tiles_by_block_and_rows(M, K, N, block, bits):
     check_linear_layer(M, K, N, block, bits)
 
 
-# blocks of 32 and 64 on 128 x 128 tiles (258 and 210 tiles, ragged at both edges), 256 x 128 ones (289 and 386 tiles of 128 rows,
-# the last of 256 half or more empty; two and three K steps of 64, a last one of a single block of 32) and 128 x 64 ones (long K,
-# fewer tiles; a tile of a few rows and columns)
+# blocks of 32 and 64, ragged at both edges: two and three K steps of 64, a last one of a single block of 32, long K on few
+# tiles, a tile of a few rows and columns (the forms of k_dq_short by name: below)
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,block", [(2100, 160, 2100, 32), (2050, 128, 2111, 32), (1700, 192, 1799, 64), (129, 64, 24650, 64),
                                          (70, 96, 33000, 32), (300, 1536, 200, 64), (131, 1568, 70, 32), (5, 1184, 3, 32), (300, 512, 129, 32)])
@@ -108,11 +105,25 @@ def linear(x, codes, consts, block, bits):
     return y
 
 
-# tiles of 128 x 64, 128 x 128 and 256 x 128 of the kernel for short blocks, 128 x 128 of the other one; ragged samples whose
-# rows lie across the tiles' edges
-FORMS = [(5, 37, 1536, 224, 64, (1, 128, 64)), (5, 37, 1184, 224, 32, (1, 128, 64)), (20, 85, 192, 1824, 64, (1, 128, 128)),
-         (20, 103, 96, 3712, 32, (1, 128, 128)), (20, 103, 192, 2144, 64, (1, 256, 128)), (20, 103, 96, 2144, 32, (1, 256, 128)),
-         (20, 103, 256, 2144, 128, (0, 128, 128))]
+# The kernel for short blocks on each of its tiles, ragged at both edges: last tiles of 12 and 20 rows, last steps of one block
+# of 32.
+DENSE = [(300, 2048, 2000, 64, (1, 128, 64)), (300, 1184, 200, 32, (1, 128, 64)), (20, 1184, 700, 32, (1, 128, 64)),
+         (1700, 320, 1799, 64, (1, 128, 128)), (1700, 512, 1799, 64, (1, 128, 128)), (2100, 416, 2111, 32, (1, 128, 128)),
+         (2060, 448, 2111, 64, (1, 256, 128)), (2060, 480, 2111, 32, (1, 256, 128))]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,block,form", DENSE)
+def test_linear_layer_short_blocks_on_each_tile(M, K, N, block, form, bits):
+    assert tuple(pb.pac_dequant_linear_tiles(M, K, N, block, bits).values()) == form
+    check_linear_layer(M, K, N, block, bits)
+
+
+# tiles of 128 x 64, 128 x 128 and 256 x 128 of the kernel for short blocks, 128 x 128 and 64 x 64 of the other one; ragged
+# samples whose rows lie across the tiles' edges
+FORMS = [(5, 37, 4096, 1760, 64, (1, 128, 64)), (5, 37, 1504, 448, 32, (1, 128, 64)), (20, 85, 960, 1824, 64, (1, 128, 128)),
+         (20, 103, 480, 3712, 32, (1, 128, 128)), (20, 103, 768, 2144, 64, (1, 256, 128)), (20, 103, 672, 2144, 32, (1, 256, 128)),
+         (20, 103, 256, 2144, 128, (0, 128, 128)), (20, 103, 96, 2144, 32, (0, 64, 64))]
 
 
 @pytest.mark.parametrize("bits", [8, 4])
@@ -120,7 +131,7 @@ FORMS = [(5, 37, 1536, 224, 64, (1, 128, 64)), (5, 37, 1184, 224, 32, (1, 128, 6
 def test_linear_layer_to_cache_has_the_dense_call_s_bits(B, n_max, K, N, block, form, bits):
     """Every epilogue that writes the cache, in both cache dtypes, against the dense output (rounded to nearest even)."""
     from paper_2408_10746_amd.runtime import Session
-    assert tuple(pb.pac_dequant_linear_tiles(B * n_max, K, N, block, bits).values()) == form
+    assert tuple(pb.pac_dequant_linear_tiles(B * n_max, K, N, block, bits, to_cache=True).values()) == form
     rng = np.random.default_rng(B + K + bits)
     codes, consts = stored_layer(rng, N, K, block, bits)
     x = torch.from_numpy(rng.standard_normal((B * n_max, K)).astype(np.float32)).to(torch.bfloat16).cuda()
@@ -145,9 +156,7 @@ def test_linear_layer_to_cache_has_the_dense_call_s_bits(B, n_max, K, N, block, 
 
 
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("M,K,N,block,form", [(300, 1536, 200, 64, (1, 128, 64)), (300, 512, 129, 32, (1, 128, 64)),
-                                              (1700, 192, 1824, 64, (1, 128, 128)), (70, 96, 33000, 32, (1, 128, 128)),
-                                              (2060, 192, 2144, 64, (1, 256, 128)), (2060, 96, 2144, 32, (1, 256, 128))])
+@pytest.mark.parametrize("M,K,N,block,form", [c for c in DENSE if c[0] > 60])
 def test_linear_layer_forms_give_the_same_bits(M, K, N, block, form, bits):
     """Rows and columns of a large call alone, where the kernel for short blocks is not taken."""
     assert tuple(pb.pac_dequant_linear_tiles(M, K, N, block, bits).values()) == form
