@@ -483,7 +483,7 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
 //    56.9, 288 193 / 167, 384 154 / 146; not for K below 448, where their one first step is waited for by all: 2441 x 2794, K =
 //    352, 22.5 / 18.8.
 // What this picks is 0.7 % off the fastest form in the mean, and more than 3 % slower than k_dq_linear's on the tiles it would
-// take otherwise at 21 of the shapes and at 7 of 1600 fresh ones, a quarter of them of up to 8192 x 16384 and K = 11008.
+// take otherwise at 21 of the shapes and at 10 of 2000 fresh ones, a fifth of them of up to 8192 x 16384 and K = 11008.
 // k_dq_linear otherwise, on 64 x 64 tiles up to as many 128 x 128 ones as compute units: longer blocks, K = 4096, 256 tiles
 // 72.5 against 74.5 us, 64 tiles 49 / 72, 320 tiles 110.6 / 89.8; odd multiples of 32 keep K steps of 32, where a wide tile
 // has less to hide its barriers behind (up to 320); up to 64 rows leave half of a wide tile and more empty.
