@@ -37,8 +37,14 @@ extern "C" {
 int64_t pac_ladder_param_count(const pac_ctx *ctx);
 
 /* Bytes of device workspace the two calls below need (the r-wide activations of every layer kept for the reverse
- * pass, one layer's cache rows widened to fp32, split sums of the token reductions); -1 on bad arguments. */
+ * pass, one layer's cache rows widened to fp32, the sums of up to sixteen splits of the token reductions, each as long as
+ * the layers' parameters); -1 on bad arguments. */
 int64_t pac_ladder_workspace_bytes(const pac_ctx *ctx, int32_t heads);
+
+/* Tiles of the contractions over the tokens (host logic, for measurements and tests that have to know which they ran):
+ * out[2 t], out[2 t + 1] rows and columns of a tile of the gradient of W_down, W_qkv, W_o, W_1, W_2 (t = 0 .. 4), out[10] token
+ * splits at the largest batch.  Errors: NULL, UNSUPPORTED as below. */
+pac_status pac_ladder_tiles(const pac_ctx *ctx, int32_t heads, int32_t out[11] /*HOST*/);
 
 /* Loss, logits and gradients of one batch read from the cache (Sec. 4.2: the cached activations are all the ladder
  * consumes; no gradient enters the backbone).  Arguments as pac_adapter_loss_grad, plus `heads`.

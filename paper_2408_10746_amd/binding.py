@@ -35,7 +35,7 @@ EXPORTS = [
     "pac_quant_blockwise", "pac_dequant_blockwise", "pac_dequant_linear", "pac_dequant_linear_tiles",
     "pac_dequant_linear_to_cache",
     "pac_tier_window_bytes", "pac_tier_fill", "pac_tier_stage", "pac_adapter_loss_grad_staged", "pac_adapter_step_staged",
-    "pac_ladder_param_count", "pac_ladder_workspace_bytes", "pac_ladder_loss_grad", "pac_ladder_step",
+    "pac_ladder_param_count", "pac_ladder_workspace_bytes", "pac_ladder_tiles", "pac_ladder_loss_grad", "pac_ladder_step",
 ]
 PAC_STATIC_WORKSPACE_BYTES = 64 << 20
 
@@ -155,6 +155,8 @@ def lib():
         L.pac_plan_stage_time.argtypes = [C.POINTER(pac_plan_problem), i32, i32, i32, i32, vp]
         L.pac_ladder_param_count.restype = i64
         L.pac_ladder_param_count.argtypes = [vp]
+        L.pac_ladder_tiles.restype = C.c_int
+        L.pac_ladder_tiles.argtypes = [vp, i32, C.POINTER(i32)]
         L.pac_ladder_workspace_bytes.restype = i64
         L.pac_ladder_workspace_bytes.argtypes = [vp, i32]
         L.pac_ladder_loss_grad.restype = C.c_int
@@ -430,6 +432,13 @@ def pac_profile_end(ctx):
 
 def pac_ladder_param_count(ctx) -> int:
     return int(lib().pac_ladder_param_count(ctx))
+
+
+def pac_ladder_tiles(ctx, heads: int):
+    """Tiles (rows, columns) of the five contractions over the tokens, and their splits (host logic)."""
+    out = (C.c_int32 * 11)()
+    _check(lib().pac_ladder_tiles(ctx, heads, out), "pac_ladder_tiles")
+    return [(int(out[2 * t]), int(out[2 * t + 1])) for t in range(5)], int(out[10])
 
 
 def pac_ladder_workspace_bytes(ctx, heads: int) -> int:

@@ -125,25 +125,32 @@ bool lad_plan(const Dims &D, int heads, Lad &a)
     a.pooled = take((int64_t)a.Bmax * d * 4); a.logits = take((int64_t)a.Bmax * a.C * 4);
     a.dz = take((int64_t)a.Bmax * a.C * 4); a.dp = take((int64_t)a.Bmax * d * 4);
     a.daL = take((int64_t)a.Bmax * w * 4); a.lossp = take((int64_t)a.Bmax * 4);
-    // tiles of the five token contractions of one layer: W_down [d][w], W_qkv [w][3w], W_o [w][w], W_1 [w][f], W_2 [f][w].
-    // Widths by the least matrix work and loads: 2 va vb instructions of 32 cycles a step, three loads of about 35.
+    // Tiles of the five token contractions of one layer: W_down [d][w], W_qkv [w][3w], W_o [w][w], W_1 [w][f], W_2 [f][w].
+    // Widths by the least matrix work and loads: 2 va vb instructions of 32 cycles a step, three loads of about 35.  But where
+    // splits of 256 tokens leave fewer workgroups than run at twice (1024), a wide tile only makes each of them longer: 64
+    // columns at most (6 layers of 448 x 64, 972 tokens, 384 workgroups of up to 128 columns 26.8 us, 456 of 64 in a step of
+    // 320 us 7 us less; 120 drawn ladders against tiles of 64 x 64 through LDS: six above 1.01, up to 1.019, now none; with the
+    // line at 512 one of 17 x 256 tokens stays at 1.010)
     const int rows[5] = {a.d, a.w, a.w, a.w, a.f}, cols[5] = {a.w, 3 * a.w, a.w, a.f, a.w};
-    a.items_per_layer = 0;
-    for (int t = 0; t < 5; ++t) {
-        int64_t best = 0;
-        for (int va = t ? 3 : 4; va <= 4; ++va)
-            for (int vb = 2; vb <= 4; ++vb) {
-                const int64_t cost = (int64_t)cdivi(rows[t], 16 * va) * cdivi(cols[t], 32 * vb) * (2 * va * vb + 3);
-                if (best && cost >= best) continue;
-                best = cost;
-                a.ten[t] = {va, vb, cdivi(cols[t], 32 * vb), a.items_per_layer};
-            }
-        a.items_per_layer += cdivi(rows[t], 16 * a.ten[t].va) * a.ten[t].tiles_j;
+    const int by_rows = cdivi(M, 256);
+    for (int most = 4;; most = 2) {
+        a.items_per_layer = 0;
+        for (int t = 0; t < 5; ++t) {
+            int64_t best = 0;
+            for (int va = t ? 3 : 4; va <= 4; ++va)
+                for (int vb = 2; vb <= most; ++vb) {
+                    const int64_t cost = (int64_t)cdivi(rows[t], 16 * va) * cdivi(cols[t], 32 * vb) * (2 * va * vb + 3);
+                    if (best && cost >= best) continue;
+                    best = cost;
+                    a.ten[t] = {va, vb, cdivi(cols[t], 32 * vb), a.items_per_layer};
+                }
+            a.items_per_layer += cdivi(rows[t], 16 * a.ten[t].va) * a.ten[t].tiles_j;
+        }
+        if (most == 2 || (int64_t)by_rows * a.items_per_layer * a.L >= 1024) break;
     }
     // Six workgroups a compute unit, two at a time (12 layers of 768 x 96, 4096 tokens, contractions and the sum over splits:
     // two splits 225 us, three 227, four 209, eight 219 us)
     int s = cdivi(1536, (int64_t)a.items_per_layer * a.L);
-    const int by_rows = cdivi(M, 256);
     if (s > by_rows) s = by_rows;
     if (s > 16) s = 16;
     if (s < 1) s = 1;
@@ -2291,6 +2298,19 @@ int64_t pac_ladder_param_count(const pac_ctx *ctx)
     if (!ctx) return -1;
     Lad a;
     return lad_shapes(ctx->D, a) ? a.P : -1;
+}
+
+pac_status pac_ladder_tiles(const pac_ctx *ctx, int32_t heads, int32_t out[11])
+{
+    if (!ctx || !out) return PAC_ERR_NULL;
+    Lad a;
+    if (!lad_plan(ctx->D, heads, a)) return PAC_ERR_UNSUPPORTED;
+    for (int t = 0; t < 5; ++t) {
+        out[2 * t] = 16 * a.ten[t].va;
+        out[2 * t + 1] = 32 * a.ten[t].vb;
+    }
+    out[10] = a.splits;
+    return PAC_OK;
 }
 
 int64_t pac_ladder_workspace_bytes(const pac_ctx *ctx, int32_t heads)

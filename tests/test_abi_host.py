@@ -229,6 +229,23 @@ def test_per_layer_workspace_holds_the_splits_that_run():
     assert ws(129) - ws(128) > partials
 
 
+def test_ladder_tiles_by_the_work_there_is():
+    """Host logic: tiles of the ladder's contractions over the tokens, at most 64 columns where the chip is not filled twice."""
+    def ask(L, d, w, n, B, heads):
+        ctx = pb.pac_create(L, d, n, w, 3, B, 64, pb.PAC_BF16)
+        try:
+            return pb.pac_ladder_tiles(ctx, heads)
+        finally:
+            pb.pac_destroy(ctx)
+    assert ask(12, 768, 96, 128, 32, 12) == ([(64, 96), (48, 96), (48, 96), (48, 128), (64, 96)], 4)   # T5-Base-shaped
+    assert ask(6, 448, 64, 36, 27, 8) == ([(64, 64)] * 5, 4)                                           # 384 workgroups
+    assert ask(3, 416, 64, 256, 17, 4)[0] == [(64, 64)] * 5
+    with pytest.raises(pb.PacError) as e:
+        ask(2, 64, 32, 16, 4, 3)
+    assert e.value.status == pb.PAC_ERR_UNSUPPORTED
+    assert pb.lib().pac_ladder_tiles(None, 4, (C.c_int32 * 11)()) == pb.PAC_ERR_NULL
+
+
 def test_linear_layer_kernel_and_tiles():
     """Host logic: both kernels and all tiles of the quantised linear layer, at the lines between them."""
     t = lambda *a: tuple(pb.pac_dequant_linear_tiles(*a).values())

@@ -205,3 +205,23 @@ def test_attention_blocks(r, heads, n_max):
 def test_token_contraction_tiles(dtype, d, r, lens):
     w = Workload("lad_t", L=2, d=d, n_max=max(lens), B=len(lens), r=r, C=3, N=len(lens), cache_dtype=dtype)
     run_case(w, r // 8, np.array(lens, dtype=np.int32), seed=17 + d + r, what=f"lad_t d={d} r={r} {dtype}")
+
+
+# the wider tiles, which only batches with work for the whole chip take: every instantiation with 96 and 128 columns and, at
+# w = 32, 48 x 64; ragged last splits, w = 32 and 64 with last tiles part empty
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("L,d,r,lens,tiles", [
+    (24, 64, 64, [256, 255, 129, 256, 140], [(64, 64), (64, 96), (64, 64), (64, 128), (64, 64)]),
+    (24, 96, 32, [256, 255, 129, 256, 140], [(64, 64), (48, 64), (48, 64), (48, 64), (64, 64)]),
+    (24, 128, 96, [256, 131, 256, 7], [(64, 96), (48, 96), (48, 96), (48, 128), (64, 96)]),
+    (24, 96, 128, [256, 131, 256, 7], [(64, 128), (64, 128), (64, 128), (64, 128), (64, 128)]),
+])
+def test_token_contraction_tiles_of_large_batches(L, d, r, lens, tiles, dtype):
+    from paper_2408_10746_amd import binding as pb
+    w = Workload("lad_w", L=L, d=d, n_max=max(lens), B=len(lens), r=r, C=3, N=len(lens), cache_dtype=dtype)
+    ctx = pb.pac_create(w.L, w.d, w.n_max, w.r, w.C, w.B, w.N, pb.PAC_BF16 if dtype == "bf16" else pb.PAC_F32)
+    try:
+        assert pb.pac_ladder_tiles(ctx, r // 8)[0] == tiles
+    finally:
+        pb.pac_destroy(ctx)
+    run_case(w, r // 8, np.array(lens, dtype=np.int32), seed=29 + d + r, what=f"lad_w d={d} r={r} {dtype}")
