@@ -19,7 +19,7 @@
  *               ln2_b w | W_1 w x 4w | b_1 4w | W_2 4w x w | b_2 w | lambda, 3 unused zeros ]
  *   then      [ W_up w x d | c_up d | W_cls d x C | c_cls C ]
  *
- * Supported: w a multiple of 32 up to 256, w / heads in {4, 8, 16, 32, 64}, n_max * (w / heads) <= 4096
+ * Supported: w a multiple of 32 up to 256, w / heads in {4, 8, 16, 32, 64}, n_max * (w / heads) <= 8192
  * (one head of one sample is kept on chip).  Otherwise PAC_ERR_UNSUPPORTED.
  */
 #ifndef PAC_LADDER_H

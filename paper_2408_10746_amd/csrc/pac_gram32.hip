@@ -1012,7 +1012,7 @@ template <bool FROM_CACHE> struct TokSrc {
 // at most, so it fetches about 16 bytes a clock where they come from behind L2 and 50 from L2, and a tile of 64 x 96 wants
 // 13: a die takes neighbouring tiles of the list below, which share their columns of DP.  Eight wavefronts a workgroup drift
 // apart until their rows fall out of L2 (193 us).  Bound by the matrix instructions, 12.2 GFLOP at 12 layers of 768 x 96
-// and 4096 rows in 246 tiles, 83 us without a stall; 120 us.
+// and 4096 rows in 246 tiles, 83 us without a stall; 119 to 124 us, matrix units busy 67 % of it.
 constexpr int kTokThreads = 256, kPostThreads = 256;
 // Work items numbered so that a die (blocks go round the eight of them) takes neighbours
 __device__ __forceinline__ int die_order(int b, int n)

@@ -303,11 +303,12 @@ template <int BITS, int BK, int WT> __global__ __launch_bounds__(256, 2) void k_
 // instructions, so a partial sum lives from one piece to the next and only the running sums take registers throughout.
 // While a piece's matrix instructions run, the vector units scale the piece before it and turn this thread's next codes
 // into the next step's tile: in k_dq_linear a step is matrix instructions, then scaling, then conversions, one behind the
-// other (1670 cycles a wavefront and step of 64 x 64, 512 of them matrix instructions).  Bound by what a compute unit reads: 40
-// KB a step of 256 x 128 from L2 or behind it (128 x 128 tiles read 48 KB for as much), 128 KB of fragments from LDS, and
-// the matrix units wait while either returns.  4096 x 4096 x 4096 with operands from memory, against k_dq_linear on 128 x
-// 128 tiles: blocks of 64, 209 -> 182 us, of 32, 291 -> 221; 128 x 128 tiles 201 and 234, eight wavefronts of 128 x 256
-// 200 and 235, four wavefronts of 256 x 128 with a wider piece each 212.  The order of tiles below: 216 -> 201.
+// other (1670 cycles a wavefront and step of 64 x 64, 512 of them matrix instructions).  A step of 256 x 128 reads 40 KB from L2
+// or behind it (128 x 128 tiles 48 KB for as much) and 128 KB of fragments from LDS.  No unit is near its limit: matrix units
+// busy 38 % of the time, LDS 33 %, L2 hits 84 %; a wavefront waits 32 % of its time for memory or a barrier and 28 % to issue,
+// with one workgroup a compute unit.  4096 x 4096 x 4096 with operands from memory, against k_dq_linear on 128 x 128 tiles:
+// blocks of 64, 209 -> 182 us, of 32, 291 -> 221; 128 x 128 tiles 201 and 234, eight wavefronts of 128 x 256 200 and 235, four
+// wavefronts of 256 x 128 with a wider piece each 212.  The order of tiles below: 216 -> 201.
 // ---------------------------------------------------------------------------
 template <int BITS, int BLK, int WTM, int WTN, int WM, int OCC> __global__ __launch_bounds__(128 * WM, OCC) void k_dq_short(DqArgs a)
 {
