@@ -468,23 +468,24 @@ static pac_status check_quant_args(const void *a, const void *b, const void *c, 
     return PAC_OK;
 }
 
-// Which kernel and tiles.  Blocks of 32 and 64, all forms measured at 4600 drawn shapes (16 to 4096 rows, 64 to 4096 columns, K
-// = 256 to 4096, both bit widths, dense and into the cache).  Two questions, each answered by the logarithm of the two forms'
-// times' ratio as it follows from K, the number of tiles, the bit width and where the output goes:
+// Which kernel and tiles.  Blocks of 32 and 64, all forms measured at 6200 drawn shapes with operands from memory and 3200 with
+// operands in the last-level cache (16 to 4096 rows, 64 to 4096 columns, K = 256 to 4096, both bit widths, dense and into the
+// activation cache).  Two questions, each answered by the logarithm of the two forms' times' ratio as it follows from K, the
+// number of tiles, the bit width and where the output goes:
 //  - up to three quarters as many 128 x 128 tiles (blocks of 32: as many) as compute units, and up to 64 rows: k_dq_short on 128 x
-//    64 tiles, three a compute unit, or k_dq_linear's 64 x 64, of which there are more.  Long K hides the first step's wait:
-//    blocks of 64, 128 x 4096 out, K = 4096, 45 us against 49, but 156 x 197, K = 1600, 4 bits, 20.2 / 19.9 and into the cache,
-//    where each thread has twice the rows to store behind its last step, 527 x 96, K = 1536, 23.7 / 21.5.  Blocks of 32: 22 x 3067,
-//    K = 928, 15.6 / 18.6, but 312 x 211, K = 576, 10.8 / 9.8, and on a handful of tiles, which wait for memory alone,
-//    47 x 178, K = 1216, 4 bits, 18.5 / 17.1.
+//    64 tiles, three a compute unit, or k_dq_linear's 64 x 64, of which there are more.  Long K hides the first step's wait; the
+//    mean of both kinds' fits, as it is waited for longer with operands from memory: blocks of 32, 135 x 1229, K = 576, 4 bits,
+//    10.9 us against 10.8 from memory and 10.8 / 9.5 from the cache, 22 x 3067, K = 928, 15.6 / 18.6 from memory; blocks of 64,
+//    128 x 4096 out, K = 4096, 45 / 49 from memory.  Into the activation cache each thread has twice the rows to store behind
+//    its last step: 527 x 96, K = 1536, 23.7 / 21.5.
 //  - above that many: k_dq_short on wider tiles, or 64 x 64 where K is short: 2546 x 1558, K = 352, blocks of 32, 16.6 / 14.1.
 //    128 x 128 tiles run two workgroups a compute unit; 256 x 128 tiles, one workgroup of eight wavefronts, take their place
 //    where rounds of them end sooner: a round of 256 against 1.09 for 512 of the smaller, 0.65 where those are one a compute
 //    unit.  512 tiles of 256 rows 176 / 190 us (4096 x 4096 x 4096), 172 of them 79.7 / 94.9, 192 76.7 / 84.4, but 128 69.8 /
 //    56.9, 288 193 / 167, 384 154 / 146; not for K below 448, where their one first step is waited for by all: 2441 x 2794, K =
 //    352, 22.5 / 18.8.
-// What this picks is 0.7 % off the fastest form in the mean, and more than 3 % slower than k_dq_linear's on the tiles it would
-// take otherwise at 21 of the shapes and at 10 of 2000 fresh ones, a fifth of them of up to 8192 x 16384 and K = 11008.
+// What this picks is 0.9 % off the fastest form in the mean from memory and 1.0 % from the cache (the sums of both: a rule for
+// one kind loses twice that at the other).
 // k_dq_linear otherwise, on 64 x 64 tiles up to as many 128 x 128 ones as compute units: longer blocks, K = 4096, 256 tiles
 // 72.5 against 74.5 us, 64 tiles 49 / 72, 320 tiles 110.6 / 89.8; odd multiples of 32 keep K steps of 32, where a wide tile
 // has less to hide its barriers behind (up to 320); up to 64 rows leave half of a wide tile and more empty.
@@ -503,18 +504,17 @@ static DqForm dq_form(int M, int K, int N, int block, int bits, bool to_cache)
     const bool b64 = block == 64, many = M > 64 && tiles128 > (b64 ? 192 : block == 32 || block % 64 == 0 ? 256 : 320);
     if (block != 32 && block != 64) return many ? DQ_STEP_128 : DQ_STEP_64;
     const double lk = std::log(K / 1024.0), four = bits == 4, cache = to_cache, few_rows = M <= 64;
-    constexpr double doubt = 0.02; // stays with k_dq_linear
     if (many) {
         const double lt = std::log((double)tiles128 / 256.0);
         const double ratio = b64 ? -0.254 - 0.126 * lk - 0.224 * lt + 0.040 * four + 0.126 * cache
                                  : -0.237 - 0.217 * lk - 0.279 * lt + 0.041 * four + 0.090 * cache;
-        return ratio < -doubt ? dq_short_tiles(tiles128, M, K, N) : DQ_STEP_64;
+        return ratio < -0.02 ? dq_short_tiles(tiles128, M, K, N) : DQ_STEP_64;
     }
-    if (!b64 && K < 2304 && tiles64 < (bits == 4 ? 9 : 4)) return DQ_STEP_64;
     const double ln = std::log((double)tiles64);
-    const double ratio = b64 ? 0.095 - 0.098 * lk - 0.024 * ln + 0.031 * four + 0.085 * cache
-                             : -0.033 - 0.181 * lk - 0.037 * ln + 0.044 * four + 0.049 * few_rows + 0.126 * cache;
-    return ratio < -doubt ? DQ_SHORT_64 : DQ_STEP_64;
+    const double ratio = b64 ? (bits == 8 ? 0.129 - 0.096 * lk - 0.026 * ln + 0.072 * cache : 0.163 - 0.088 * lk - 0.027 * ln + 0.079 * cache)
+                             : (bits == 8 ? 0.036 - 0.167 * lk - 0.040 * ln + 0.019 * few_rows + 0.110 * cache
+                                          : 0.071 - 0.152 * lk - 0.038 * ln + 0.038 * few_rows + 0.101 * cache);
+    return ratio < 0 ? DQ_SHORT_64 : DQ_STEP_64;
 }
 
 template <int WTN, int WM, int OCC> static void dq_launch_short(const DqArgs &a, int bits, hipStream_t st)

@@ -121,7 +121,7 @@ def test_linear_layer_short_blocks_on_each_tile(M, K, N, block, form, bits):
 
 # tiles of 128 x 64, 128 x 128 and 256 x 128 of the kernel for short blocks, 128 x 128 and 64 x 64 of the other one; ragged
 # samples whose rows lie across the tiles' edges
-FORMS = [(5, 37, 4096, 1760, 64, (1, 128, 64)), (5, 37, 1504, 448, 32, (1, 128, 64)), (20, 85, 960, 1824, 64, (1, 128, 128)),
+FORMS = [(5, 37, 8192, 1760, 64, (1, 128, 64)), (5, 37, 3040, 448, 32, (1, 128, 64)), (20, 85, 960, 1824, 64, (1, 128, 128)),
          (20, 103, 480, 3712, 32, (1, 128, 128)), (20, 103, 768, 2144, 64, (1, 256, 128)), (20, 103, 672, 2144, 32, (1, 256, 128)),
          (20, 103, 256, 2144, 128, (0, 128, 128)), (20, 103, 96, 2144, 32, (0, 64, 64))]
 
